@@ -10,12 +10,9 @@
 
 #include "fq_internal.h"
 #include "fq_layout.h"
+#include "fq_panel.h"
 
 namespace {
-
-__device__ inline float half_bits_to_float(uint16_t b) {
-    return __half2float(__ushort_as_half(b));
-}
 
 // stored scale (16 bits, binary16 or bfloat16) -> binary32
 __device__ inline float scale_bits_to_float(uint16_t b, int sfmt) {
@@ -42,50 +39,6 @@ __device__ inline uint32_t scale_bits_from_absmax_bits(uint32_t m, float L, int 
 // 16-byte load per row, so a row of the block is 256 contiguous bytes) of the rows ty, ty + 16,
 // ... of the group; the sixteen row slices are combined through LDS.
 // ---------------------------------------------------------------------------------
-typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
-
-// abs-max bit patterns of 8 columns (four packed pairs) over rows ty, ty + 16, ... < rows
-__device__ inline uint4 absmax8_slice(const uint16_t* __restrict__ base, int64_t N, int rows, int ty) {
-    u16x2_t m[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
-    auto fold = [&](const uint4& v) {
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t a = w[i] & 0x7fff7fffu;
-            m[i] = __builtin_elementwise_max(m[i], __builtin_bit_cast(u16x2_t, a));
-        }
-    };
-    int r = ty;
-    for (; r + 48 < rows; r += 64) {      // four loads in flight
-        const uint4 v0 = *reinterpret_cast<const uint4*>(base + (int64_t)r * N);
-        const uint4 v1 = *reinterpret_cast<const uint4*>(base + (int64_t)(r + 16) * N);
-        const uint4 v2 = *reinterpret_cast<const uint4*>(base + (int64_t)(r + 32) * N);
-        const uint4 v3 = *reinterpret_cast<const uint4*>(base + (int64_t)(r + 48) * N);
-        fold(v0); fold(v1); fold(v2); fold(v3);
-    }
-    for (; r < rows; r += 16) fold(*reinterpret_cast<const uint4*>(base + (int64_t)r * N));
-    return make_uint4(__builtin_bit_cast(uint32_t, m[0]), __builtin_bit_cast(uint32_t, m[1]),
-                      __builtin_bit_cast(uint32_t, m[2]), __builtin_bit_cast(uint32_t, m[3]));
-}
-// the sixteen slices of a block combined: valid in the threads with ty == 0
-__device__ inline uint4 absmax8_block(uint4 mine, uint4 (&red)[16][16], int tx, int ty) {
-    red[ty][tx] = mine;
-    __syncthreads();
-    if (ty != 0) return mine;
-    u16x2_t m[4];
-    m[0] = __builtin_bit_cast(u16x2_t, mine.x); m[1] = __builtin_bit_cast(u16x2_t, mine.y);
-    m[2] = __builtin_bit_cast(u16x2_t, mine.z); m[3] = __builtin_bit_cast(u16x2_t, mine.w);
-    for (int y = 1; y < 16; ++y) {
-        const uint4 o = red[y][tx];
-        m[0] = __builtin_elementwise_max(m[0], __builtin_bit_cast(u16x2_t, o.x));
-        m[1] = __builtin_elementwise_max(m[1], __builtin_bit_cast(u16x2_t, o.y));
-        m[2] = __builtin_elementwise_max(m[2], __builtin_bit_cast(u16x2_t, o.z));
-        m[3] = __builtin_elementwise_max(m[3], __builtin_bit_cast(u16x2_t, o.w));
-    }
-    return make_uint4(__builtin_bit_cast(uint32_t, m[0]), __builtin_bit_cast(uint32_t, m[1]),
-                      __builtin_bit_cast(uint32_t, m[2]), __builtin_bit_cast(uint32_t, m[3]));
-}
-
 __global__ __launch_bounds__(256) void fq_scales_kernel(const uint16_t* __restrict__ W, int64_t K,
                                                         int64_t N, int g, float L, int sfmt,
                                                         uint16_t* __restrict__ scales) {
@@ -134,37 +87,35 @@ __global__ __launch_bounds__(256) void fq_scales_fold_kernel(const uint16_t* __r
 }
 
 // ---------------------------------------------------------------------------------
-// Encode: divide (IEEE binary32), round half to even, clamp (Appendix A's q = int(w / s)).
-// ---------------------------------------------------------------------------------
-// The quotient is formed without the division instruction sequence: with rs = 1 / s rounded to nearest
-// (once per group; 0 for s = 0), x0 = w * rs is within two units in the last place of w / s, its residual
-// e = w - x0 * s comes exactly out of one fused multiply-add, and x = x0 + e * rs (fused again) is the
-// quotient rounded to nearest wherever that matters here: an exact tie k + 1/2 is representable and is
-// returned exactly, and any other quotient of a binary16 weight by a binary16 or bfloat16 scale lies at
-// least 2^-12 away from a tie (numerator and denominator are integers of at most 11 bits times powers of
-// two), far beyond the error of x.  Checked on the host for every finite scale and every weight within
-// the code range (tests/encode_identity_check.c: 2 x 10^9 pairs, no difference).  What the general
-// division adds (scaling against overflow and subnormal quotients, the fix-ups for zero, infinity and
-// NaN operands) cannot occur: |w / s| <= (2^bits - 1) / 2.
-__device__ inline int encode_one(uint16_t wbits, float s, float rs, int qmax) {
-    const float w = half_bits_to_float(wbits);
-    const float x0 = w * rs;
-    const float e = __builtin_fmaf(-x0, s, w);
-    const float x = __builtin_fmaf(e, rs, x0);
-    const float c = fminf(fmaxf(rintf(x), (float)-qmax), (float)qmax);
-    return (int)c;
-}
-
-// ---------------------------------------------------------------------------------
 // One-pass quantiser for group sizes that divide 128 (32, 64, 128): a block stages a panel of
 // 128 rows x 128 columns of W in LDS with coalesced 16-byte loads, takes the abs-max of every
 // 32-row sub-block, derives the scales of the panel's groups, and encodes and packs the panel
-// from LDS.  W is read from HBM once (the two-pass path reads it twice, the second time with
-// 2-byte loads).  Same arithmetic as the two-pass kernels, hence the same bits.
+// from LDS.  W is read from HBM once.
+// A thread works on pairs of neighbouring columns: one 4-byte LDS read per row serves two weights (one 2-byte
+// read per weight made the LDS reads a third of the kernel's instructions), and its two lane records are
+// adjacent in memory.  Bound by HBM next to its own instructions (about 10 per weight; 20 with per-weight reads
+// and roundings): 8192 x 28672 to int4, g = 128: 152 -> 108 us (5.4 TB/s;
+// a device copy reaches 4.9).
 // ---------------------------------------------------------------------------------
-#define FQ_QP_ROWS 128
-#define FQ_QP_COLS 128
-#define FQ_QP_PITCH (FQ_QP_COLS + 8)   // binary16 elements per LDS row
+// Packs the eight biased codes of one 32-row step (rows 32 t + 8 j .. + 7) into the record dwords.
+template <int BITS>
+__device__ inline void pack_step(uint32_t (&rec)[4], int t, const uint32_t (&b)[8]) {
+    if constexpr (BITS == 8) {
+        rec[2 * t] = fq_gather_bytes(b[0], b[1], b[2], b[3]);
+        rec[2 * t + 1] = fq_gather_bytes(b[4], b[5], b[6], b[7]);
+    } else {
+        // nibble slots 0..7 hold elements 0, 2, 4, 6, 1, 3, 5, 7: low nibbles of the bytes 0, 4, 1, 5, high 2, 6, 3, 7
+        const uint32_t v = fq_gather_bytes(b[0], b[4], b[1], b[5]) | (fq_gather_bytes(b[2], b[6], b[3], b[7]) << 4);
+        if (BITS == 4 || t < 3) {
+            rec[t] |= v;
+        } else {
+            // 3-bit codes, step 3: bit i of the value goes to the fourth bit of the same nibble of dword i
+#pragma unroll
+            for (int i = 0; i < 3; ++i) rec[i] |= (v << (3 - i)) & 0x88888888u;
+        }
+    }
+}
+
 // OWN_SCALES = false: the scales were computed before (groups larger than the panel) and are only read.
 template <int BITS, bool OWN_SCALES>
 __global__ __launch_bounds__(256) void fq_quantize_panel_kernel(const uint16_t* __restrict__ W, int64_t K,
@@ -173,55 +124,49 @@ __global__ __launch_bounds__(256) void fq_quantize_panel_kernel(const uint16_t* 
                                                                 uint32_t* __restrict__ codes) {
     constexpr int KBLK = fq_kblk(BITS);
     constexpr int STEPS = KBLK / FQ_KSTEP;
-    constexpr int QMAX = (1 << (BITS - 1)) - 1;
-    __shared__ uint16_t panel[FQ_QP_ROWS * FQ_QP_PITCH];
-    __shared__ uint16_t submax[4][FQ_QP_COLS];      // abs-max bits of the 32-row sub-blocks
-    __shared__ float sub_scale[4][FQ_QP_COLS];      // scale of the group each sub-block belongs to
-    __shared__ float sub_rscale[4][FQ_QP_COLS];     // its reciprocal (0 for an all-zero group)
+    constexpr int RW = fq_rec_bytes(BITS) / 4;           // dwords per lane record
+    constexpr float QMAX = (float)((1 << (BITS - 1)) - 1);
+    constexpr float MAGIC = FQ_ENCODE_MAGIC + (float)(1 << (BITS - 1));
+    __shared__ __align__(16) uint16_t panel[FQ_QP_ROWS * FQ_QP_PITCH];
+    __shared__ __align__(16) uint16_t submax[8][FQ_QP_COLS];      // abs-max bits of 16-row slices
+    __shared__ __align__(16) float sub_scale[4][FQ_QP_COLS];      // scale of the group each 32-row sub-block belongs to
+    __shared__ __align__(16) float sub_rscale[4][FQ_QP_COLS];     // its reciprocal (0 for an all-zero group)
     const int tid = threadIdx.x;
     const int64_t n0 = (int64_t)blockIdx.x * FQ_QP_COLS;
     const int64_t k0 = (int64_t)blockIdx.y * FQ_QP_ROWS;
     const int cols = (int)((N - n0) < FQ_QP_COLS ? (N - n0) : FQ_QP_COLS);   // multiple of 16
     const int rows = (int)((K - k0) < FQ_QP_ROWS ? (K - k0) : FQ_QP_ROWS);   // 128, or 64 at the end (8-bit)
 
-    // stage: thread -> (row = tid / 16 + 16 i, 8 columns starting at 8 (tid % 16))
-    {
-        const int c8 = (tid & 15) * 8;
-#pragma unroll
-        for (int i = 0; i < FQ_QP_ROWS / 16; ++i) {
-            const int r = (tid >> 4) + 16 * i;
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (r < rows && c8 < cols) v = *reinterpret_cast<const uint4*>(W + (k0 + r) * N + n0 + c8);
-            *reinterpret_cast<uint4*>(&panel[r * FQ_QP_PITCH + c8]) = v;
-        }
-    }
+    fq_stage_panel(W, N, k0, n0, rows, cols, panel);
     __syncthreads();
     if constexpr (OWN_SCALES) {
-        // abs-max of the 32-row sub-blocks: thread -> column pair tid % 64, sub-block tid / 64; one 4-byte
-        // LDS read per row and a packed 16-bit maximum
+        // abs-max of 16-row slices: thread -> four columns 4 (tid % 32), slice tid / 32; 8-byte LDS reads and
+        // packed 16-bit maxima
         {
-            const int cp = (tid & 63) * 2;
-            const int sb = tid >> 6;
-            u16x2_t m = {0, 0};
+            const int c4 = (tid & 31) * 4;
+            const int sl = tid >> 5;
+            u16x2_t m0 = {0, 0}, m1 = {0, 0};
 #pragma unroll
-            for (int r = 0; r < 32; ++r) {
-                const uint32_t v = *reinterpret_cast<const uint32_t*>(&panel[(sb * 32 + r) * FQ_QP_PITCH + cp]);
-                m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2_t, v & 0x7fff7fffu));
+            for (int r = 0; r < 16; ++r) {
+                const uint2 v = *reinterpret_cast<const uint2*>(&panel[(sl * 16 + r) * FQ_QP_PITCH + c4]);
+                m0 = __builtin_elementwise_max(m0, __builtin_bit_cast(u16x2_t, v.x & 0x7fff7fffu));
+                m1 = __builtin_elementwise_max(m1, __builtin_bit_cast(u16x2_t, v.y & 0x7fff7fffu));
             }
-            *reinterpret_cast<uint32_t*>(&submax[sb][cp]) = __builtin_bit_cast(uint32_t, m);
+            *reinterpret_cast<uint2*>(&submax[sl][c4]) =
+                make_uint2(__builtin_bit_cast(uint32_t, m0), __builtin_bit_cast(uint32_t, m1));
         }
         __syncthreads();
-        // scales: one per (group, column); a group is g / 32 consecutive sub-blocks
+        // scales: one per (group, column); a group is g / 16 consecutive slices
         {
-            const int per = g / 32;                 // 1, 2 or 4
+            const int per = g / 32;                 // 1, 2 or 4 sub-blocks of 32 rows
             const int c = tid & 127;
-    #pragma unroll
+#pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int sb = (tid >> 7) + 2 * h;
                 const int first = (sb / per) * per;
                 uint32_t m = 0;
-                for (int i = 0; i < per; ++i) {
-                    const uint32_t a = submax[first + i][c];
+                for (int i = 0; i < 2 * per; ++i) {
+                    const uint32_t a = submax[2 * first + i][c];
                     m = a > m ? a : m;
                 }
                 const uint32_t sbits = scale_bits_from_absmax_bits(m, L, sfmt);
@@ -244,51 +189,33 @@ __global__ __launch_bounds__(256) void fq_quantize_panel_kernel(const uint16_t* 
         }
         __syncthreads();
     }
-    // encode + pack: wave w takes column tiles w, w + 4 of the panel
-    const int lane = tid & 63, wave = tid >> 6;
-    const int nl = lane & 15, j = lane >> 4;
+    // encode + pack: thread -> columns c, c + 1 and lane group j; its records of every k-block of the panel
+    const int c = (tid & 63) * 2, j = tid >> 6;
+    if (c >= cols) return;                               // (no barrier below)
     const int64_t ntiles = N / FQ_NTILE;
-    for (int tl = wave; tl * FQ_NTILE < cols; tl += 4) {
-        const int c = tl * FQ_NTILE + nl;
-        for (int kb = 0; kb * KBLK < rows; ++kb) {
-            uint32_t rec[4] = {0u, 0u, 0u, 0u};
+    for (int kb = 0; kb * KBLK < rows; ++kb) {
+        uint32_t rec0[4] = {0u, 0u, 0u, 0u}, rec1[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-            for (int t = 0; t < STEPS; ++t) {
-                const int r0 = kb * KBLK + t * FQ_KSTEP + j * 8;
-                const float sc = sub_scale[r0 / 32][c];
-                const float rsc = sub_rscale[r0 / 32][c];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int q = encode_one(panel[(r0 + e) * FQ_QP_PITCH + c], sc, rsc, QMAX);
-                    if (BITS == 4) {
-                        rec[t] |= (uint32_t)(q + 8) << (4 * fq_nibble_slot(e));
-                    } else if (BITS == 3) {
-                        // steps 0..2: low three bits of the nibble; step 3: bit b of the value goes to
-                        // the fourth bit of the same nibble of dword b
-                        const uint32_t u = (uint32_t)(q + 4);
-                        const int p = 4 * fq_nibble_slot(e);
-                        if (t < 3) {
-                            rec[t] |= u << p;
-                        } else {
-                            rec[0] |= (u & 1u) << (p + 3);
-                            rec[1] |= ((u >> 1) & 1u) << (p + 3);
-                            rec[2] |= ((u >> 2) & 1u) << (p + 3);
-                        }
-                    } else {
-                        rec[2 * t + (e >> 2)] |= (uint32_t)(q + 128) << (8 * (e & 3));
-                    }
-                }
-            }
-            const int64_t kblock = (k0 / KBLK) + kb;
-            const int64_t at = fq_rec(n0 / FQ_NTILE + tl, kblock, ntiles, lane);
-            if (BITS == 3) {
-                uint32_t* dst = codes + at * 3;
-                dst[0] = rec[0];
-                dst[1] = rec[1];
-                dst[2] = rec[2];
-            } else {
-                *reinterpret_cast<uint4*>(codes + at * 4) = make_uint4(rec[0], rec[1], rec[2], rec[3]);
-            }
+        for (int t = 0; t < STEPS; ++t) {
+            const int r0 = kb * KBLK + t * FQ_KSTEP + j * 8;
+            const float2 s = *reinterpret_cast<const float2*>(&sub_scale[r0 / 32][c]);
+            const float2 rs = *reinterpret_cast<const float2*>(&sub_rscale[r0 / 32][c]);
+            uint32_t b0[8], b1[8];
+            fq_encode8_pair(panel, r0, c, s, rs, QMAX, MAGIC, b0, b1);
+            pack_step<BITS>(rec0, t, b0);
+            pack_step<BITS>(rec1, t, b1);
+        }
+        const int64_t kblock = (k0 / KBLK) + kb;
+        const int64_t at = fq_rec(n0 / FQ_NTILE + c / FQ_NTILE, kblock, ntiles, j * 16 + c % FQ_NTILE);
+        uint32_t* dst = codes + at * RW;                 // record of column c; the next one follows it
+        if constexpr (BITS == 3) {
+            // 24 bytes, 8-byte aligned (c is even)
+            *reinterpret_cast<uint2*>(dst) = make_uint2(rec0[0], rec0[1]);
+            *reinterpret_cast<uint2*>(dst + 2) = make_uint2(rec0[2], rec1[0]);
+            *reinterpret_cast<uint2*>(dst + 4) = make_uint2(rec1[1], rec1[2]);
+        } else {
+            *reinterpret_cast<uint4*>(dst) = make_uint4(rec0[0], rec0[1], rec0[2], rec0[3]);
+            *reinterpret_cast<uint4*>(dst + 4) = make_uint4(rec1[0], rec1[1], rec1[2], rec1[3]);
         }
     }
 }
@@ -323,19 +250,6 @@ __global__ __launch_bounds__(256) void fq_unpack_kernel(const uint32_t* __restri
 // fine values pairwise, level by level, and sets flag[level] when the smaller child is
 // below thr * parent.  The host then walks the flags from the coarsest level down.
 // ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void fq_fine_absmax_kernel(const uint16_t* __restrict__ W, int64_t N,
-                                                             int f, uint16_t* __restrict__ fine) {
-    // thread layout as in fq_scales_kernel: 16 x 16, eight columns per thread
-    __shared__ uint4 red[16][16];
-    const int tx = threadIdx.x, ty = threadIdx.y;
-    const int64_t n = ((int64_t)blockIdx.x * 16 + tx) * 8;
-    const int64_t blk = blockIdx.y;
-    uint4 m = make_uint4(0u, 0u, 0u, 0u);
-    if (n < N) m = absmax8_slice(W + (blk * f) * N + n, N, f, ty);
-    m = absmax8_block(m, red, tx, ty);
-    if (ty == 0 && n < N) *reinterpret_cast<uint4*>(fine + blk * N + n) = m;
-}
-
 // levels = number of halvings covered; a top group spans 2^levels fine blocks.
 // flag[l] (l = 0 is the coarsest transition g_start -> g_start/2) is set to 1 when any
 // parent at that level has min(child) < thr * parent.
@@ -637,7 +551,7 @@ int fq_launch_quantize(const void* W, int64_t K, int64_t N, int bits, int g, int
         uint16_t* fine = (uint16_t*)codes;
         dim3 block(16, 16);
         dim3 grid((unsigned)((N + 127) / 128), (unsigned)(K / 128));
-        hipLaunchKernelGGL(fq_fine_absmax_kernel, grid, block, 0, stream, (const uint16_t*)W, N, 128, fine);
+        hipLaunchKernelGGL(fq_fine_absmax_kernel<256>, grid, block, 0, stream, (const uint16_t*)W, N, 128, fine);
         dim3 grid2((unsigned)((N + 255) / 256), (unsigned)(K / g));
         hipLaunchKernelGGL(fq_scales_fold_kernel, grid2, dim3(256), 0, stream, (const uint16_t*)fine, N, g / 128, L,
                            sfmt, (uint16_t*)scales);
@@ -677,7 +591,7 @@ int fq_launch_choose_group(const void* W, int64_t K, int64_t N, int g_top, int l
     {
         dim3 block(16, 16);
         dim3 grid((unsigned)((N + 127) / 128), (unsigned)(K / f));
-        hipLaunchKernelGGL(fq_fine_absmax_kernel, grid, block, 0, stream, (const uint16_t*)W, N, f, fine);
+        hipLaunchKernelGGL(fq_fine_absmax_kernel<256>, grid, block, 0, stream, (const uint16_t*)W, N, f, fine);
     }
     {
         const float thr = 1.0f - alpha;

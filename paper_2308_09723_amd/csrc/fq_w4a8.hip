@@ -29,6 +29,7 @@
 #include "fq_gemm_kernels.h"
 #include "fq_internal.h"
 #include "fq_layout.h"
+#include "fq_panel.h"
 
 using namespace fqk;
 
@@ -40,57 +41,70 @@ constexpr float ALEVELS = 255.0f;  // 2^8 - 1
 constexpr int W8_NT = 3;           // column tiles per wave
 constexpr int W8_WAVES = 8;
 
-__device__ inline float f16_bits_to_float(uint16_t b) { return __half2float(__ushort_as_half(b)); }
+__device__ inline float f16_bits_to_float(uint16_t b) { return half_bits_to_float(b); }
 
 // ------------------------------------------------------------------------------------------------------
-// Weight quantiser, three small kernels (offline path):
-//   1. abs-max of every group, as binary16 bit patterns, parked in the not-yet-written code buffer;
+// Weight quantiser (offline path):
+//   1. abs-max of every group, as binary16 bit patterns, parked in the not-yet-written code buffer
+//      (fq_fine_absmax_kernel; groups of more than 1024 rows as blocks of 128 rows, folded by a second kernel);
 //   2. per column: t = smallest binary16 with 16 * 15 * t >= 2 * (largest group abs-max), then for every
 //      group the smallest z in 1..16 with 15 * z * t >= 2 * (its abs-max)  (all products exact in binary32);
 //   3. codes q = clamp(round_half_even(w / (z t)), -7, 7), IEEE binary32 quotient, packed.
+// W has to be read twice (a column's step needs all of it).  Both passes are bound by HBM: 16-byte loads, the second
+// from panels staged in LDS.  On 12288 x 12288, g = 128 (us): abs-max with 2-byte loads 96 -> 64, steps and
+// multipliers 60 -> 9, encoding with a strided 2-byte load and a division per weight 201 -> 72 (5.2 TB/s).
 // ------------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void w8_group_absmax_kernel(const uint16_t* __restrict__ W, int64_t N, int g,
-                                                               uint16_t* __restrict__ amax) {
-    // thread (x, y): column x of the block's 64 columns, rows y, y + 4, ... of group blockIdx.y
-    __shared__ uint16_t red[4][64];
-    const int x = threadIdx.x & 63, y = threadIdx.x >> 6;
-    const int64_t n = (int64_t)blockIdx.x * 64 + x;
-    const int64_t grp = blockIdx.y;
-    uint16_t m = 0;
-    if (n < N) {
-        const uint16_t* base = W + grp * g * N + n;
-        for (int r = y; r < g; r += 4) {
-            const uint16_t v = base[(int64_t)r * N] & 0x7fffu;
-            m = v > m ? v : m;
-        }
-    }
-    red[y][x] = m;
-    __syncthreads();
-    if (y == 0 && n < N) {
-        for (int i = 1; i < 4; ++i) m = red[i][x] > m ? red[i][x] : m;
-        amax[grp * N + n] = m;
-    }
-}
-
-__global__ __launch_bounds__(256) void w8_scales_kernel(const uint16_t* __restrict__ amax, int64_t N, int groups,
-                                                         uint8_t* __restrict__ z, uint16_t* __restrict__ tstep) {
+// abs-max of every group from the maxima of its `per_group` blocks
+__global__ __launch_bounds__(256) void w8_fold_kernel(const uint16_t* __restrict__ fine, int64_t N, int per_group,
+                                                       uint16_t* __restrict__ amax) {
     const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (n >= N) return;
-    uint16_t mcol = 0;
-    for (int i = 0; i < groups; ++i) {
-        const uint16_t v = amax[(int64_t)i * N + n];
-        mcol = v > mcol ? v : mcol;
+    const uint16_t* src = fine + (int64_t)blockIdx.y * per_group * N + n;
+    uint16_t m = 0;
+#pragma unroll 8
+    for (int i = 0; i < per_group; ++i) {
+        const uint16_t v = src[(int64_t)i * N];
+        m = v > m ? v : m;
     }
+    amax[(int64_t)blockIdx.y * N + n] = m;
+}
+
+// Block = 32 columns x 8 slices of the groups (a column per thread left 48 blocks for a 12288-column matrix, each
+// thread walking every group twice: 60 us, now 9).
+__global__ __launch_bounds__(256) void w8_scales_kernel(const uint16_t* __restrict__ amax, int64_t N, int groups,
+                                                         uint8_t* __restrict__ z, uint16_t* __restrict__ tstep) {
+    __shared__ uint16_t red[8][32];
+    const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
+    const int64_t n = (int64_t)blockIdx.x * 32 + x;
+    const bool ok = n < N;
+    uint16_t mcol = 0;
+    if (ok) {
+#pragma unroll 4
+        for (int i = y; i < groups; i += 8) {
+            const uint16_t v = amax[(int64_t)i * N + n];
+            mcol = v > mcol ? v : mcol;
+        }
+    }
+    red[y][x] = mcol;
+    __syncthreads();
+    if (!ok) return;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) mcol = red[i][x] > mcol ? red[i][x] : mcol;
     const float L = WLEVELS * (float)ZMAX;                                  // 240
     const float two_m = 2.0f * f16_bits_to_float(mcol);
     uint16_t tb = __half_as_ushort(__float2half_rn(__fdiv_rn(two_m, L)));   // nearest, then up if too small
     if (__fmul_rn(L, f16_bits_to_float(tb)) < two_m) tb += 1;
-    tstep[n] = tb;
+    if (y == 0) tstep[n] = tb;
     const float t = f16_bits_to_float(tb);
-    for (int i = 0; i < groups; ++i) {
+    const float r15t = t == 0.0f ? 0.0f : __fdiv_rn(1.0f, WLEVELS * t);
+#pragma unroll 4
+    for (int i = y; i < groups; i += 8) {
         const float two_mi = 2.0f * f16_bits_to_float(amax[(int64_t)i * N + n]);
-        int zi = 1;
-        while (zi < ZMAX && __fmul_rn(WLEVELS * (float)zi, t) < two_mi) ++zi;   // (15 z) * t: exact
+        // an estimate of the quotient, then the exact tests on either side of it ((15 z) * t: exact)
+        int zi = (int)(two_mi * r15t);
+        zi = zi < 1 ? 1 : (zi > ZMAX ? ZMAX : zi);
+        while (zi > 1 && __fmul_rn(WLEVELS * (float)(zi - 1), t) >= two_mi) --zi;
+        while (zi < ZMAX && __fmul_rn(WLEVELS * (float)zi, t) < two_mi) ++zi;
         z[(int64_t)i * N + n] = (uint8_t)zi;
     }
 }
@@ -98,35 +112,50 @@ __global__ __launch_bounds__(256) void w8_scales_kernel(const uint16_t* __restri
 // row of the k-block that element e of dword d of lane group j holds
 __host__ __device__ inline int w8_row(int d, int j, int e) { return 64 * (d >> 1) + 16 * j + 8 * (d & 1) + e; }
 
-// one thread per lane record (16 bytes: 32 codes of one column in one k-block)
-__global__ __launch_bounds__(256) void w8_encode_kernel(const uint16_t* __restrict__ W, int64_t K, int64_t N,
-                                                         int g, const uint8_t* __restrict__ z,
+// A block encodes a 128 x 128 panel staged in LDS: thread -> two neighbouring columns and lane group j, i.e. two
+// adjacent lane records (16 bytes each: 32 codes of one column in one k-block).
+__global__ __launch_bounds__(256) void w8_encode_kernel(const uint16_t* __restrict__ W, int64_t N, int g,
+                                                         const uint8_t* __restrict__ z,
                                                          const uint16_t* __restrict__ tstep,
                                                          uint32_t* __restrict__ codes) {
-    const int64_t rec = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t ntiles = N / FQ_NTILE;
-    if (rec >= (K / 128) * ntiles * 64) return;
-    const int lane = (int)(rec & 63);
-    const int64_t tile = (rec >> 6) % ntiles, kb = (rec >> 6) / ntiles;
-    const int64_t n = tile * FQ_NTILE + (lane & 15);
-    const int j = lane >> 4;
-    const float t = f16_bits_to_float(tstep[n]);
-    uint32_t out[4];
+    __shared__ __align__(16) uint16_t panel[FQ_QP_ROWS * FQ_QP_PITCH];
+    __shared__ __align__(16) float sub_scale[4][FQ_QP_COLS];      // z t of the group each 32-row sub-block belongs to
+    __shared__ __align__(16) float sub_rscale[4][FQ_QP_COLS];     // its reciprocal (0 for an all-zero column)
+    const int tid = threadIdx.x;
+    const int64_t n0 = (int64_t)blockIdx.x * FQ_QP_COLS;
+    const int64_t k0 = (int64_t)blockIdx.y * FQ_QP_ROWS;          // K is a multiple of 128
+    const int cols = (int)((N - n0) < FQ_QP_COLS ? (N - n0) : FQ_QP_COLS);   // multiple of 16
+    fq_stage_panel(W, N, k0, n0, FQ_QP_ROWS, cols, panel);
+    {
+        const int c = tid & 127;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int sb = (tid >> 7) + 2 * h;
+            float v = 0.0f;
+            if (c < cols) v = (float)z[((k0 + sb * 32) / g) * N + n0 + c] * f16_bits_to_float(tstep[n0 + c]);   // exact
+            sub_scale[sb][c] = v;
+            sub_rscale[sb][c] = v == 0.0f ? 0.0f : __fdiv_rn(1.0f, v);
+        }
+    }
+    __syncthreads();
+    const int c = (tid & 63) * 2, j = tid >> 6;
+    if (c >= cols) return;
+    uint32_t out0[4], out1[4];
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-        const int64_t k0 = kb * 128 + w8_row(d, j, 0);
-        const float s = (float)z[(k0 / g) * N + n] * t;                      // exact; 8 rows inside one group
-        uint32_t w = 0;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float x = f16_bits_to_float(W[(k0 + e) * N + n]);
-            int q = 0;
-            if (s != 0.0f) q = (int)fminf(fmaxf(rintf(__fdiv_rn(x, s)), -7.0f), 7.0f);
-            w |= (uint32_t)(q + 8) << (8 * (e & 3) + 4 * (e >> 2));
-        }
-        out[d] = w;
+        const int r0 = w8_row(d, j, 0);                            // 8 rows inside one group
+        const float2 s = *reinterpret_cast<const float2*>(&sub_scale[r0 / 32][c]);
+        const float2 rs = *reinterpret_cast<const float2*>(&sub_rscale[r0 / 32][c]);
+        uint32_t b0[8], b1[8];
+        fq_encode8_pair(panel, r0, c, s, rs, 7.0f, FQ_ENCODE_MAGIC + 8.0f, b0, b1);
+        // byte b: element b in the low, element b + 4 in the high nibble
+        out0[d] = fq_gather_bytes(b0[0], b0[1], b0[2], b0[3]) | (fq_gather_bytes(b0[4], b0[5], b0[6], b0[7]) << 4);
+        out1[d] = fq_gather_bytes(b1[0], b1[1], b1[2], b1[3]) | (fq_gather_bytes(b1[4], b1[5], b1[6], b1[7]) << 4);
     }
-    *reinterpret_cast<uint4*>(codes + rec * 4) = make_uint4(out[0], out[1], out[2], out[3]);
+    const int64_t at = fq_rec(n0 / FQ_NTILE + c / FQ_NTILE, blockIdx.y, N / FQ_NTILE, j * 16 + c % FQ_NTILE);
+    uint32_t* dst = codes + at * 4;                                // record of column c; the next one follows it
+    *reinterpret_cast<uint4*>(dst) = make_uint4(out0[0], out0[1], out0[2], out0[3]);
+    *reinterpret_cast<uint4*>(dst + 4) = make_uint4(out1[0], out1[1], out1[2], out1[3]);
 }
 
 // the logical codes q[K, N] (int8) of a packed buffer: one thread per lane record
@@ -901,14 +930,25 @@ int fq_quantize_w4a8(const void* W_f16, int64_t K, int64_t N, int group_size, vo
     hipStream_t s = (hipStream_t)stream;
     const int groups = (int)(K / g);
     if (groups > 65535) return FQ_ERR_UNSUPPORTED;
-    uint16_t* amax = (uint16_t*)codes;      // K N / 2 bytes hold the K / g x N abs-max values (g >= 32)
-    hipLaunchKernelGGL(w8_group_absmax_kernel, dim3((unsigned)((N + 63) / 64), (unsigned)groups), dim3(256), 0, s,
-                       (const uint16_t*)W_f16, N, g, amax);
-    hipLaunchKernelGGL(w8_scales_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, (const uint16_t*)amax, N,
+    // The code buffer (K N / 2 bytes) holds the K / g x N abs-max values (g >= 32: at most K N / 16 bytes) on the way.
+    // Groups of up to 1024 rows take one block of threads per (group, 128 columns); longer ones are cut into blocks
+    // of 128 rows, which keeps the chip full when there are few groups, and folded afterwards (where 128 does not
+    // divide the group its blocks stay whole).
+    uint16_t* amax = (uint16_t*)codes;
+    const bool cut = g > 1024 && g % 128 == 0;
+    const int f = cut ? 128 : g;
+    hipLaunchKernelGGL(fq_fine_absmax_kernel<256>, dim3((unsigned)((N + 127) / 128), (unsigned)(K / f)), dim3(16, 16), 0, s,
+                       (const uint16_t*)W_f16, N, f, amax);
+    if (cut) {
+        uint16_t* fine = amax;
+        amax = fine + (K / f) * N;
+        hipLaunchKernelGGL(w8_fold_kernel, dim3((unsigned)((N + 255) / 256), (unsigned)groups), dim3(256), 0, s,
+                           (const uint16_t*)fine, N, g / f, amax);
+    }
+    hipLaunchKernelGGL(w8_scales_kernel, dim3((unsigned)((N + 31) / 32)), dim3(256), 0, s, (const uint16_t*)amax, N,
                        groups, zscale, (uint16_t*)tstep_f16);
-    const int64_t recs = (K / 128) * (N / FQ_NTILE) * 64;
-    hipLaunchKernelGGL(w8_encode_kernel, dim3((unsigned)((recs + 255) / 256)), dim3(256), 0, s, (const uint16_t*)W_f16, K,
-                       N, g, (const uint8_t*)zscale, (const uint16_t*)tstep_f16, (uint32_t*)codes);
+    hipLaunchKernelGGL(w8_encode_kernel, dim3((unsigned)((N + 127) / 128), (unsigned)(K / 128)), dim3(256), 0, s,
+                       (const uint16_t*)W_f16, N, g, (const uint8_t*)zscale, (const uint16_t*)tstep_f16, (uint32_t*)codes);
     return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_HIP;
 }
 

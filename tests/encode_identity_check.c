@@ -3,7 +3,8 @@
  * |w| <= s * (2^bits - 1) / 2,
  *     clamp(rint(fl32(w / s)))  ==  clamp(rint(fma(fma(-x0, s, w), rs, x0))),  x0 = fl32(w * rs), rs = fl32(1 / s),
  * i.e. Appendix A's q = int(w / s) with the quotient in IEEE binary32 can be formed from one reciprocal per
- * group and two fused multiply-adds per weight.  Walks every `stride`-th finite scale (argv[1], default 1 =
+ * group and two fused multiply-adds per weight; and, with a second argument,
+ * the same for the integer path's scales z * t.  Walks every `stride`-th finite scale (argv[1], default 1 =
  * all of them) and every non-negative binary16 numerator in range; prints one line per (format, bits) and
  * returns the number of formats with a mismatch.  Build: gcc -O2 -ffp-contract=off encode_identity_check.c -lm */
 #include <math.h>
@@ -30,7 +31,7 @@ int main(int argc, char** argv) {
     int failed = 0;
     if (stride < 1) return 99;
     for (int i = 0; i < 0x7c00; ++i) W[i] = half_to_float((uint16_t)i);
-    for (int fmt = 0; fmt < 2; ++fmt) {
+    for (int fmt = 0; argc <= 2 && fmt < 2; ++fmt) {
         const int bit_widths[3] = {3, 4, 8};
         for (int b = 0; b < 3; ++b) {
             const int bits = bit_widths[b];
@@ -66,6 +67,38 @@ int main(int argc, char** argv) {
                    fmt == 0 ? "binary16" : "bfloat16", bits, pairs, ties, bad);
             if (bad) ++failed;
         }
+    }
+    /* the integer path: s = z * t, z in 1..16, t binary16 (15 significant bits), codes within +-7 */
+    if (argc > 2) {
+        unsigned long long pairs = 0, ties = 0, bad = 0;
+        for (int ti = 1; ti < 0x7c00; ti += stride) {
+            for (int z = 1; z <= 16; ++z) {
+                const float s = (float)z * W[ti], top = s * 7.5f;
+                if (W[ti] > 546.0f) continue;          /* 16 * 15 * t / 2 stays within binary16 */
+                volatile float rs_v = 1.0f / s;
+                const float rs = rs_v;
+                for (int wi = 0; wi < 0x7c00 && W[wi] <= top; wi += stride > 1 ? 3 : 1) {
+                    const float w = W[wi];
+                    volatile float quotient = w / s;
+                    float ref = rintf(quotient);
+                    volatile float x0_v = w * rs;
+                    const float x0 = x0_v;
+                    const float x = fmaf(fmaf(-x0, s, w), rs, x0);
+                    ref = ref > 7.0f ? 7.0f : ref;
+                    /* the kernel's rounding: clamp, then add 1.5 * 2^23 + bias */
+                    volatile float sum = (x > 7.0f ? 7.0f : x) + 12582920.0f;
+                    const float got = sum - 12582920.0f;
+                    ++pairs;
+                    if (quotient - floorf(quotient) == 0.5f) ++ties;
+                    if (got != ref) {
+                        if (bad < 5) printf("  mismatch: z %d t %a w %a: %g vs %g\n", z, W[ti], w, ref, got);
+                        ++bad;
+                    }
+                }
+            }
+        }
+        printf("integer path: %llu pairs, %llu exact ties, %llu mismatches\n", pairs, ties, bad);
+        if (bad) ++failed;
     }
     return failed;
 }

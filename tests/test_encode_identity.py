@@ -26,3 +26,17 @@ def test_quotient_from_reciprocal_and_two_fused_corrections(tmp_path):
         words = line.split()
         pairs, ties, bad = (int(words[words.index(k) - 1]) for k in ("pairs,", "exact", "mismatches"))
         assert pairs > 5_000_000 and ties > 1000 and bad == 0, line
+
+
+@pytest.mark.skipif(shutil.which("gcc") is None, reason="needs gcc")
+def test_quotient_by_the_integer_path_scales_and_rounding_by_addition(tmp_path):
+    """The same for the integer path's scales z * t (15 significant bits), with the kernel's rounding: clamp, then add
+    1.5 * 2^23 plus the storage bias."""
+    exe = str(tmp_path / "encode_identity_check")
+    subprocess.run(["gcc", "-O2", "-ffp-contract=off", "-o", exe, os.path.join(HERE, "encode_identity_check.c"), "-lm"],
+                   check=True)
+    out = subprocess.run([exe, "11", "integer"], capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0, out.stdout + out.stderr
+    words = out.stdout.split()
+    pairs, ties, bad = (int(words[words.index(k) - 1]) for k in ("pairs,", "exact", "mismatches"))
+    assert pairs > 50_000_000 and ties > 1000 and bad == 0, out.stdout

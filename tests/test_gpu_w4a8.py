@@ -212,3 +212,14 @@ def test_rejects_bad_arguments():
     need = fq.gemm_w4a8_workspace_bytes(4, 1024, 4096, 128)
     assert need > 0 and need % (4 * 1024 * 4) == 0           # whole slabs of int32 partial sums
     assert fq.gemm_w4a8_raw(p, p, 4, 1024, 4096, p, p, p, 128, p, 0, None, 0, 0) == fq.FQ_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("K,N,g", [(128, 16, 32), (256, 144, 64), (2304, 272, 1152), (4224, 48, 1056), (2048, 400, 0)])
+def test_weight_quantiser_panels_and_long_groups(K, N, g):
+    """Panels of fewer than 128 columns, the last panel of a ragged matrix, and groups longer than one block of rows
+    (cut into blocks of 128 rows where 128 divides them, whole where it does not)."""
+    rng = np.random.default_rng(K + N + g)
+    W = (rng.standard_normal((K, N)) * 0.02 * rng.choice([1.0, 20.0], (K, N), p=[0.99, 0.01])).astype(np.float16)
+    W[:, 3] = 0
+    W[K // 2, 5] = 65504.0
+    _quantize_weights(W, g)
