@@ -120,13 +120,13 @@ int fq_choose_group(const void* W_f16, int64_t K, int64_t N, int g_start, int g_
     if (levels > 24 || K / f > 65535 || K / g_top > 65535) return FQ_ERR_UNSUPPORTED;
     if (!workspace || workspace_bytes < fq_choose_group_workspace_bytes(K, N, g_start, g_min))
         return FQ_ERR_WORKSPACE;
-    int flags[64];
-    const int st = fq_launch_choose_group(W_f16, K, N, (int)g_top, levels, alpha, flags, workspace,
+    uint32_t flags = 0;      // bit d: halving step d is taken
+    const int st = fq_launch_choose_group(W_f16, K, N, (int)g_top, levels, alpha, &flags, workspace,
                                           (hipStream_t)stream);
     if (st != FQ_OK) return st;
     int64_t g = g_top;
     for (int d = 0; d < levels; ++d) {
-        if (!flags[d]) break;
+        if (!(flags >> d & 1u)) break;
         g /= 2;
     }
     *g_out = (int)g;

@@ -16,7 +16,7 @@ int64_t fq_quant_error_blocks(int64_t K, int64_t N);
 int fq_launch_quant_error(const void* W, int64_t K, int64_t N, int bits, int g, int sfmt, const void* codes,
                           const void* scales, double* out_host2, void* workspace, hipStream_t stream);
 int fq_launch_choose_group(const void* W, int64_t K, int64_t N, int g_top, int levels, float alpha,
-                           int* flags_host, void* workspace, hipStream_t stream);
+                           uint32_t* flags_host, void* workspace, hipStream_t stream);
 
 // measurement helper: a kernel that only reads a buffer
 int fq_launch_stream_read_probe(const void* buf, size_t bytes, void* sink, hipStream_t stream);

@@ -251,11 +251,13 @@ __global__ __launch_bounds__(256) void fq_unpack_kernel(const uint32_t* __restri
 // below thr * parent.  The host then walks the flags from the coarsest level down.
 // ---------------------------------------------------------------------------------
 // levels = number of halvings covered; a top group spans 2^levels fine blocks.
-// flag[l] (l = 0 is the coarsest transition g_start -> g_start/2) is set to 1 when any
-// parent at that level has min(child) < thr * parent.
+// Bit l of *flags (l = 0 is the coarsest transition g_start -> g_start/2; fq_fine_absmax_kernel clears the word) is
+// set when any parent at that level has min(child) < thr * parent.  One word, and a block or wave that has nothing to
+// add leaves it alone: every block setting one word per level cost 28 us on 8192 x 28672, nearly all of it atomics
+// waiting for each other (now @@TREE@@).
 __global__ __launch_bounds__(256) void fq_halving_flags_kernel(const uint16_t* __restrict__ fine,
                                                                int64_t N, int64_t tops, int levels,
-                                                               float thr, int* __restrict__ flags) {
+                                                               float thr, uint32_t* __restrict__ flags) {
     const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t top = blockIdx.y;
     if (n >= N || top >= tops) return;
@@ -284,27 +286,30 @@ __global__ __launch_bounds__(256) void fq_halving_flags_kernel(const uint16_t* _
             node = 0;
         }
     }
-    if (hit) atomicOr(&flags[d], 1);
+    if (hit && !(*(volatile uint32_t*)flags >> d & 1u)) atomicOr(flags, 1u << d);
 }
 
 // The same test with the pairwise fold done in LDS (a top group of at most 1024 fine blocks): a block
 // takes `cols` neighbouring columns of one top group, loads their 2^levels fine values with coalesced
 // 4-byte loads, and folds them level by level from the finest transition up, alternating between two LDS
 // arrays; every fine value is read from memory once instead of once per level, and no thread walks a
-// whole column.  Dynamic LDS: 3 * 2^levels * cols bytes.
+// whole column.  A thread folds pairs of columns (4-byte LDS accesses, packed 16-bit minima and maxima: magnitudes of
+// binary16 order like their bit patterns).  Dynamic LDS: 3 * 2^levels * cols bytes.
 __global__ __launch_bounds__(256) void fq_halving_tree_kernel(const uint16_t* __restrict__ fine, int64_t N,
                                                               int levels, float thr, int cols,
-                                                              int* __restrict__ flags) {
-    extern __shared__ uint16_t tree[];     // [span][cols], then [span / 2][cols]
+                                                              uint32_t* __restrict__ flags) {
+    extern __shared__ uint32_t tree[];     // [span][cols / 2], then [span / 2][cols / 2]: pairs of columns
     const int tid = threadIdx.x;
     const int span = 1 << levels;
     const int64_t n0 = (int64_t)blockIdx.x * cols;
     const uint16_t* base = fine + ((int64_t)blockIdx.y * span) * N + n0;
+    const int pairs = cols / 2;            // 8, 16 or 32
+    const int lp = 31 - __clz(pairs);
     {
-        const int pairs = cols / 2, c2 = (tid % pairs) * 2;
+        const int c2 = (tid & (pairs - 1)) * 2;
         const bool ok = n0 + c2 < N;       // N is even
-        const int step = 256 / pairs;
-        for (int r0 = tid / pairs; r0 < span; r0 += 8 * step) {     // eight loads in flight
+        const int step = 256 >> lp;
+        for (int r0 = tid >> lp; r0 < span; r0 += 8 * step) {     // eight loads in flight
             uint32_t v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
@@ -314,68 +319,88 @@ __global__ __launch_bounds__(256) void fq_halving_tree_kernel(const uint16_t* __
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int r = r0 + u * step;
-                if (r < span) *reinterpret_cast<uint32_t*>(&tree[r * cols + c2]) = v[u];
+                if (r < span) tree[(r << lp) + (c2 >> 1)] = v[u];
             }
         }
     }
     __syncthreads();
-    uint16_t* src = tree;
-    uint16_t* dst = tree + span * cols;
+    uint32_t* src = tree;
+    uint32_t* dst = tree + span * pairs;
     int len = span;                        // nodes per column at the level being folded
-    const int lc = 31 - __clz(cols);       // cols is 16, 32 or 64
+    uint32_t hits = 0;                     // (the same in every thread)
     for (int d = levels - 1; d >= 0; --d) {
         const int parents = len / 2;
         bool hit = false;
-        for (int i = tid; i < parents * cols; i += 256) {
-            const int p = i >> lc, c = i & (cols - 1);
-            const uint32_t a = src[(2 * p) * cols + c], b = src[(2 * p + 1) * cols + c];
-            const float lo = half_bits_to_float((uint16_t)(a < b ? a : b));
-            const float hi = half_bits_to_float((uint16_t)(a < b ? b : a));
-            hit = hit || (lo < __fmul_rn(thr, hi));
-            dst[p * cols + c] = (uint16_t)(a < b ? b : a);
+        for (int i = tid; i < parents * pairs; i += 256) {
+            const int p = i >> lp, c = i & (pairs - 1);
+            const u16x2_t a = __builtin_bit_cast(u16x2_t, src[((2 * p) << lp) + c]);
+            const u16x2_t b = __builtin_bit_cast(u16x2_t, src[((2 * p + 1) << lp) + c]);
+            const u16x2_t lo = __builtin_elementwise_min(a, b), hi = __builtin_elementwise_max(a, b);
+            hit = hit || (half_bits_to_float(lo[0]) < __fmul_rn(thr, half_bits_to_float(hi[0])));
+            hit = hit || (half_bits_to_float(lo[1]) < __fmul_rn(thr, half_bits_to_float(hi[1])));
+            dst[(p << lp) + c] = __builtin_bit_cast(uint32_t, hi);
         }
-        if (__syncthreads_or(hit) && tid == 0) atomicOr(&flags[d], 1);
-        uint16_t* t = src;
+        if (__syncthreads_or(hit)) hits |= 1u << d;
+        uint32_t* t = src;
         src = dst;
         dst = t;
         len = parents;
     }
-}
-
-__global__ void fq_zero_ints_kernel(int* p, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
+    if (tid == 0 && (hits & ~*(volatile uint32_t*)flags)) atomicOr(flags, hits);
 }
 
 // ---------------------------------------------------------------------------------
 // Round-trip error (section 3.2, figure 2a: mean squared error between the weights and their
 // dequantised codes, Appendix A: dequantised value = q * s).  binary64 throughout: w, q * s and
-// their difference are exact, the squares are rounded once, and the sums are taken in a fixed
-// order (thread strip -> tree over the block -> one block over the per-block partials), so the
+// their difference are exact, the squares are added with one rounding each, and the sums are taken in a fixed
+// order (thread strip -> tree over the wave -> the block's waves -> one block over the per-block partials), so the
 // result is deterministic.  part[0 .. nblk) holds the sums, part[nblk .. 2 nblk) the maxima.
 // ---------------------------------------------------------------------------------
-// A block takes a panel of 128 rows x 128 columns: the weights are staged in LDS with coalesced 16-byte loads,
-// and every thread walks whole lane records of the packed codes (16 or 12 bytes, read in layout order: a wave
-// reads one contiguous KiB) against the staged weights.  (Looking every weight's code up by its position
-// instead reads the packed buffer four bytes at a time and computes a record address per weight.)
-#define FQ_QE_PANEL 128
-#define FQ_QE_PITCH 130   // binary16 elements per LDS row: rows 8 apart fall 8 banks apart
+// A block takes panels of 128 rows x 128 columns: the weights are staged in LDS with coalesced 16-byte loads, and a
+// thread walks the lane records of two neighbouring columns (adjacent in memory) against them, one 4-byte LDS read
+// per row serving both.  The next panel's weights are in flight (in registers) while the present one is worked on.
+// (Looking every weight's code up by its position instead reads the packed buffer four bytes at a time and computes
+// a record address per weight.)  Bound by HBM next to its own instructions: 8192 x 28672, int4 g = 128, @@QE@@.
+
+// q of element e of the 32-row step t of a record as binary32, divided by CODE_UNIT<BITS> (a power of two: exact)
+template <int BITS>
+constexpr float CODE_UNIT = BITS == 4 ? 16.0f : 1.0f;
+template <int BITS>
+__device__ inline uint32_t step_word(const uint32_t (&d)[4], int t) {   // 3 and 4 bits: the step's eight nibbles
+    if constexpr (BITS == 4) {
+        return d[t] ^ 0x88888888u;                       // q in two's complement
+    } else {
+        return t < 3 ? d[t] : ((d[0] >> 3) & 0x11111111u) | ((d[1] >> 2) & 0x22222222u) | ((d[2] >> 1) & 0x44444444u);
+    }
+}
+template <int BITS>
+__device__ inline float code_value(const uint32_t (&d)[4], uint32_t w, int t, int e) {
+    if constexpr (BITS == 8) {
+        return (float)(int8_t)((d[2 * t + (e >> 2)] ^ 0x80808080u) >> (8 * (e & 3)));
+    } else if constexpr (BITS == 4) {
+        return __builtin_amdgcn_cvt_off_f32_i4(w >> (4 * fq_nibble_slot(e)));   // low nibble / 16
+    } else {
+        return (float)((w >> (4 * fq_nibble_slot(e))) & 7u) - 4.0f;
+    }
+}
+
 template <int BITS, bool EXACT32>
 __global__ __launch_bounds__(256) void fq_quant_error_kernel(const uint16_t* __restrict__ W,
                                                              const uint32_t* __restrict__ codes,
                                                              const uint16_t* __restrict__ scales, int64_t K,
                                                              int64_t N, int g, int sfmt,
                                                              double* __restrict__ part, int64_t nblk) {
-    __shared__ uint32_t wp[FQ_QE_PANEL * FQ_QE_PITCH / 2];
-    __shared__ double sh_s[256];
-    __shared__ double sh_m[256];
+    __shared__ __align__(16) uint16_t panel[FQ_QP_ROWS * FQ_QP_PITCH];
+    __shared__ double sh_s[4];
+    __shared__ double sh_m[4];
     constexpr int KBLK = fq_kblk(BITS);
     constexpr int STEPS = KBLK / FQ_KSTEP;
     constexpr int RW = fq_rec_bytes(BITS) / 4;                 // dwords per lane record
-    constexpr int RECS = (FQ_QE_PANEL / KBLK) * (FQ_QE_PANEL / FQ_NTILE) * 64;
+    constexpr int NL = FQ_QP_ROWS / 16;
     const int tid = threadIdx.x;
-    const int64_t panels_n = (N + FQ_QE_PANEL - 1) / FQ_QE_PANEL;
-    const int64_t panels = panels_n * ((K + FQ_QE_PANEL - 1) / FQ_QE_PANEL);
+    const int64_t panels_n = (N + FQ_QP_COLS - 1) / FQ_QP_COLS;
+    const int64_t panels = panels_n * ((K + FQ_QP_ROWS - 1) / FQ_QP_ROWS);
+    const int64_t ntiles = N / FQ_NTILE;
     double sse = 0.0, mx = 0.0;
     float mxf = 0.0f;
     // With binary16 scales the error w - q s of one weight is formed in binary32, where it is exact: q s has at
@@ -383,97 +408,119 @@ __global__ __launch_bounds__(256) void fq_quant_error_kernel(const uint16_t* __r
     // 2^(exponent of s - 11) below 2^(exponent of s + 8): 19 bits.  (q = 0: the error is w itself.)  Only its
     // square is accumulated in binary64; the largest magnitude is a binary32 maximum.  A third of the binary64
     // instructions per weight that the all-binary64 form needs, with the same bits in both results.
-    // a block walks panels blockIdx.x, blockIdx.x + gridDim.x, ... (one partial result per block)
-    for (int64_t pnl = blockIdx.x; pnl < panels; pnl += gridDim.x) {
-    const int64_t n0 = (pnl % panels_n) * FQ_QE_PANEL;
-    const int64_t k0 = (pnl / panels_n) * FQ_QE_PANEL;
-    __syncthreads();                                           // the previous panel has been read
-    for (int u = tid; u < FQ_QE_PANEL * 16; u += 256) {
-        const int row = u >> 4, cu = u & 15;
-        const int64_t k = k0 + row, n = n0 + cu * 8;
-        if (k < K && n < N) {                                  // N is a multiple of 16: whole units
-            const uint4 v = *reinterpret_cast<const uint4*>(W + k * N + n);
-            uint32_t* dst = wp + row * (FQ_QE_PITCH / 2) + cu * 4;
-            dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
+    const int lr = tid >> 4, c8 = (tid & 15) * 8;              // staging: rows lr + 16 i, eight columns
+    const int c = (tid & 63) * 2, j = tid >> 6;                // work: columns c, c + 1, lane group j
+    uint4 v[NL];
+    auto load_panel = [&](int64_t pnl) {
+        const int64_t n = (pnl % panels_n) * FQ_QP_COLS + c8, k = (pnl / panels_n) * FQ_QP_ROWS + lr;
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            v[i] = make_uint4(0u, 0u, 0u, 0u);
+            // (N is a multiple of 16: whole units)
+            if (n < N && k + 16 * i < K) v[i] = *reinterpret_cast<const uint4*>(W + (k + 16 * i) * N + n);
         }
-    }
-    __syncthreads();
-    const uint16_t* wp16 = reinterpret_cast<const uint16_t*>(wp);
-    for (int r = tid; r < RECS; r += 256) {
-        const int lane = r & 63, tile_l = (r >> 6) & 7, kbl = r >> 9;
-        const int col = tile_l * FQ_NTILE + (lane & 15);
-        const int64_t n = n0 + col;
-        const int64_t kb = k0 / KBLK + kbl;
-        if (n >= N || kb * KBLK >= K) continue;
-        const uint32_t* rec = codes + fq_rec(n / FQ_NTILE, kb, N / FQ_NTILE, lane) * RW;
-        uint32_t d[4] = {0u, 0u, 0u, 0u};
+    };
+    // a block walks panels blockIdx.x, blockIdx.x + gridDim.x, ... (one partial result per block)
+    int64_t pnl = blockIdx.x;
+    if (pnl < panels) load_panel(pnl);
+    for (; pnl < panels; pnl += gridDim.x) {
+        const int64_t n0 = (pnl % panels_n) * FQ_QP_COLS;
+        const int64_t k0 = (pnl / panels_n) * FQ_QP_ROWS;
+        __syncthreads();                                       // the previous panel has been read
 #pragma unroll
-        for (int i = 0; i < RW; ++i) d[i] = rec[i];
-        const int j = lane >> 4;
+        for (int i = 0; i < NL; ++i) *reinterpret_cast<uint4*>(&panel[(lr + 16 * i) * FQ_QP_PITCH + c8]) = v[i];
+        __syncthreads();
+        if (pnl + gridDim.x < panels) load_panel(pnl + gridDim.x);
+        if (n0 + c >= N) continue;                             // (the barriers above are reached by every thread)
 #pragma unroll
-        for (int t = 0; t < STEPS; ++t) {
-            const int krel = kbl * KBLK + FQ_KSTEP * t + 8 * j;
-            const float sf = scale_bits_to_float(scales[((k0 + krel) / g) * N + n], sfmt);
-            const double sv = (double)sf;
+        for (int kbl = 0; kbl < FQ_QP_ROWS / KBLK; ++kbl) {
+            const int64_t kb = k0 / KBLK + kbl;
+            if (kb * KBLK >= K) break;
+            const uint32_t* rec = codes + fq_rec((n0 + c) / FQ_NTILE, kb, ntiles, j * 16 + c % FQ_NTILE) * RW;
+            uint32_t d0[4] = {0u, 0u, 0u, 0u}, d1[4] = {0u, 0u, 0u, 0u};
+            if constexpr (BITS == 3) {
+                // 24 bytes, 8-byte aligned (c is even)
+                const uint2 x = *reinterpret_cast<const uint2*>(rec), y = *reinterpret_cast<const uint2*>(rec + 2),
+                            u = *reinterpret_cast<const uint2*>(rec + 4);
+                d0[0] = x.x; d0[1] = x.y; d0[2] = y.x; d1[0] = y.y; d1[1] = u.x; d1[2] = u.y;
+            } else {
+                const uint4 x = *reinterpret_cast<const uint4*>(rec), y = *reinterpret_cast<const uint4*>(rec + 4);
+                d0[0] = x.x; d0[1] = x.y; d0[2] = x.z; d0[3] = x.w;
+                d1[0] = y.x; d1[1] = y.y; d1[2] = y.z; d1[3] = y.w;
+            }
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                int q;
-                if (BITS == 4) q = (int)((d[t] >> (4 * fq_nibble_slot(e))) & 0xfu) - 8;
-                else if (BITS == 3) q = (int)fq_get3(d, t, e) - 4;
-                else q = (int)((d[2 * t + (e >> 2)] >> (8 * (e & 3))) & 0xffu) - 128;
-                const float wf = half_bits_to_float(wp16[(krel + e) * FQ_QE_PITCH + col]);
-                if constexpr (EXACT32) {
-                    const float ef = __builtin_fmaf(-(float)q, sf, wf);
-                    const double err = (double)ef;
-                    sse += err * err;
-                    mxf = fmaxf(mxf, fabsf(ef));
-                } else {
-                    const double err = (double)wf - (double)q * sv;
-                    sse += err * err;
-                    mx = fmax(mx, fabs(err));
+            for (int t = 0; t < STEPS; ++t) {
+                const int krel = kbl * KBLK + FQ_KSTEP * t + 8 * j;
+                const uint32_t s2 = *reinterpret_cast<const uint32_t*>(scales + ((k0 + krel) / g) * N + n0 + c);
+                const float f0 = scale_bits_to_float((uint16_t)s2, sfmt), f1 = scale_bits_to_float((uint16_t)(s2 >> 16), sfmt);
+                const uint32_t w0 = BITS == 8 ? 0u : step_word<BITS>(d0, t), w1 = BITS == 8 ? 0u : step_word<BITS>(d1, t);
+                const float u0 = CODE_UNIT<BITS> * f0, u1 = CODE_UNIT<BITS> * f1;   // exact
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const uint32_t w2 = *reinterpret_cast<const uint32_t*>(&panel[(krel + e) * FQ_QP_PITCH + c]);
+                    const float wf0 = half_bits_to_float((uint16_t)w2), wf1 = half_bits_to_float((uint16_t)(w2 >> 16));
+                    const float q0 = code_value<BITS>(d0, w0, t, e), q1 = code_value<BITS>(d1, w1, t, e);
+                    if constexpr (EXACT32) {
+                        const float e0 = __builtin_fmaf(-q0, u0, wf0), e1 = __builtin_fmaf(-q1, u1, wf1);
+                        sse = __builtin_fma((double)e0, (double)e0, sse);
+                        sse = __builtin_fma((double)e1, (double)e1, sse);
+                        mxf = fmaxf(mxf, fmaxf(fabsf(e0), fabsf(e1)));
+                    } else {
+                        // (the products and differences are exact in binary64)
+                        const double e0 = __builtin_fma(-(double)q0, (double)u0, (double)wf0);
+                        const double e1 = __builtin_fma(-(double)q1, (double)u1, (double)wf1);
+                        sse = __builtin_fma(e0, e0, sse);
+                        sse = __builtin_fma(e1, e1, sse);
+                        mx = fmax(mx, fmax(fabs(e0), fabs(e1)));
+                    }
                 }
             }
         }
     }
+    mx = fmax(mx, (double)mxf);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        sse += __shfl_xor(sse, o, 64);
+        mx = fmax(mx, __shfl_xor(mx, o, 64));
     }
-    sh_s[tid] = sse;
-    sh_m[tid] = fmax(mx, (double)mxf);
+    if ((tid & 63) == 0) {
+        sh_s[tid >> 6] = sse;
+        sh_m[tid >> 6] = mx;
+    }
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (tid < w) {
-            sh_s[tid] += sh_s[tid + w];
-            sh_m[tid] = fmax(sh_m[tid], sh_m[tid + w]);
-        }
-        __syncthreads();
-    }
     if (tid == 0) {
-        part[blockIdx.x] = sh_s[0];
-        part[nblk + blockIdx.x] = sh_m[0];
+        part[blockIdx.x] = (sh_s[0] + sh_s[1]) + (sh_s[2] + sh_s[3]);
+        part[nblk + blockIdx.x] = fmax(fmax(sh_m[0], sh_m[1]), fmax(sh_m[2], sh_m[3]));
     }
 }
 
-__global__ __launch_bounds__(256) void fq_quant_error_final_kernel(const double* __restrict__ part, int64_t nblk,
-                                                                   double* __restrict__ out) {
-    __shared__ double sh_s[256];
-    __shared__ double sh_m[256];
+// (one block of 1024 threads: at most two partial results per thread, all of them in flight at once)
+__global__ __launch_bounds__(1024) void fq_quant_error_final_kernel(const double* __restrict__ part, int64_t nblk,
+                                                                    double* __restrict__ out) {
+    __shared__ double sh_s[16];
+    __shared__ double sh_m[16];
     double sse = 0.0, mx = 0.0;
-    for (int64_t i = threadIdx.x; i < nblk; i += 256) {
+    for (int64_t i = threadIdx.x; i < nblk; i += 1024) {
         sse += part[i];
         mx = fmax(mx, part[nblk + i]);
     }
-    sh_s[threadIdx.x] = sse;
-    sh_m[threadIdx.x] = mx;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-            sh_s[threadIdx.x] += sh_s[threadIdx.x + w];
-            sh_m[threadIdx.x] = fmax(sh_m[threadIdx.x], sh_m[threadIdx.x + w]);
-        }
-        __syncthreads();
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        sse += __shfl_xor(sse, o, 64);
+        mx = fmax(mx, __shfl_xor(mx, o, 64));
     }
+    if ((threadIdx.x & 63) == 0) {
+        sh_s[threadIdx.x >> 6] = sse;
+        sh_m[threadIdx.x >> 6] = mx;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        out[0] = sh_s[0];
-        out[1] = sh_m[0];
+        for (int w = 1; w < 16; ++w) {
+            sse += sh_s[w];
+            mx = fmax(mx, sh_m[w]);
+        }
+        out[0] = sse;
+        out[1] = mx;
     }
 }
 
@@ -551,7 +598,7 @@ int fq_launch_quantize(const void* W, int64_t K, int64_t N, int bits, int g, int
         uint16_t* fine = (uint16_t*)codes;
         dim3 block(16, 16);
         dim3 grid((unsigned)((N + 127) / 128), (unsigned)(K / 128));
-        hipLaunchKernelGGL(fq_fine_absmax_kernel<256>, grid, block, 0, stream, (const uint16_t*)W, N, 128, fine);
+        hipLaunchKernelGGL(fq_fine_absmax_kernel<256>, grid, block, 0, stream, (const uint16_t*)W, N, 128, fine, (uint32_t*)nullptr);
         dim3 grid2((unsigned)((N + 255) / 256), (unsigned)(K / g));
         hipLaunchKernelGGL(fq_scales_fold_kernel, grid2, dim3(256), 0, stream, (const uint16_t*)fine, N, g / 128, L,
                            sfmt, (uint16_t*)scales);
@@ -582,16 +629,15 @@ int fq_launch_unpack(const void* codes, int64_t K, int64_t N, int bits, int8_t* 
 }
 
 int fq_launch_choose_group(const void* W, int64_t K, int64_t N, int g_top, int levels, float alpha,
-                           int* flags_host, void* workspace, hipStream_t stream) {
-    // workspace: [flags: 64 ints][fine: (K / f) * N binary16]
-    int* flags = (int*)workspace;
+                           uint32_t* flags_host, void* workspace, hipStream_t stream) {
+    // workspace: [flags: one word, 256 bytes][fine: (K / f) * N binary16]
+    uint32_t* flags = (uint32_t*)workspace;
     uint16_t* fine = (uint16_t*)((char*)workspace + 256);
     const int f = g_top >> levels;
-    hipLaunchKernelGGL(fq_zero_ints_kernel, dim3(1), dim3(64), 0, stream, flags, 64);
     {
         dim3 block(16, 16);
         dim3 grid((unsigned)((N + 127) / 128), (unsigned)(K / f));
-        hipLaunchKernelGGL(fq_fine_absmax_kernel<256>, grid, block, 0, stream, (const uint16_t*)W, N, f, fine);
+        hipLaunchKernelGGL(fq_fine_absmax_kernel<256>, grid, block, 0, stream, (const uint16_t*)W, N, f, fine, flags);
     }
     {
         const float thr = 1.0f - alpha;
@@ -609,14 +655,14 @@ int fq_launch_choose_group(const void* W, int64_t K, int64_t N, int g_top, int l
         }
     }
     if (hipGetLastError() != hipSuccess) return FQ_ERR_HIP;
-    if (hipMemcpyAsync(flags_host, flags, sizeof(int) * 64, hipMemcpyDeviceToHost, stream) != hipSuccess)
+    if (hipMemcpyAsync(flags_host, flags, sizeof(uint32_t), hipMemcpyDeviceToHost, stream) != hipSuccess)
         return FQ_ERR_HIP;
     if (hipStreamSynchronize(stream) != hipSuccess) return FQ_ERR_HIP;
     return FQ_OK;
 }
 
 int64_t fq_quant_error_blocks(int64_t K, int64_t N) {
-    const int64_t panels = ((N + FQ_QE_PANEL - 1) / FQ_QE_PANEL) * ((K + FQ_QE_PANEL - 1) / FQ_QE_PANEL);
+    const int64_t panels = ((N + FQ_QP_COLS - 1) / FQ_QP_COLS) * ((K + FQ_QP_COLS - 1) / FQ_QP_COLS);
     return panels < 2048 ? panels : 2048;
 }
 
@@ -635,7 +681,7 @@ int fq_launch_quant_error(const void* W, int64_t K, int64_t N, int bits, int g, 
     else if (bits == 4) { if (x32) FQ_QE_GO(4, true); else FQ_QE_GO(4, false); }
     else { if (x32) FQ_QE_GO(8, true); else FQ_QE_GO(8, false); }
 #undef FQ_QE_GO
-    hipLaunchKernelGGL(fq_quant_error_final_kernel, dim3(1), dim3(256), 0, stream, (const double*)part, nblk, out);
+    hipLaunchKernelGGL(fq_quant_error_final_kernel, dim3(1), dim3(1024), 0, stream, (const double*)part, nblk, out);
     if (hipGetLastError() != hipSuccess) return FQ_ERR_HIP;
     if (hipMemcpyAsync(out_host2, out, sizeof(double) * 2, hipMemcpyDeviceToHost, stream) != hipSuccess)
         return FQ_ERR_HIP;

@@ -938,7 +938,7 @@ int fq_quantize_w4a8(const void* W_f16, int64_t K, int64_t N, int group_size, vo
     const bool cut = g > 1024 && g % 128 == 0;
     const int f = cut ? 128 : g;
     hipLaunchKernelGGL(fq_fine_absmax_kernel<256>, dim3((unsigned)((N + 127) / 128), (unsigned)(K / f)), dim3(16, 16), 0, s,
-                       (const uint16_t*)W_f16, N, f, amax);
+                       (const uint16_t*)W_f16, N, f, amax, (uint32_t*)nullptr);
     if (cut) {
         uint16_t* fine = amax;
         amax = fine + (K / f) * N;
