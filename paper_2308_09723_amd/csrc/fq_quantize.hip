@@ -133,7 +133,10 @@ __global__ __launch_bounds__(256) void fq_quantize_panel_kernel(const uint16_t* 
     __shared__ __align__(16) float sub_rscale[4][FQ_QP_COLS];     // its reciprocal (0 for an all-zero group)
     const int tid = threadIdx.x;
     const int64_t n0 = (int64_t)blockIdx.x * FQ_QP_COLS;
-    const int64_t k0 = (int64_t)blockIdx.y * FQ_QP_ROWS;
+    // Bottom of the matrix first: whatever read W before (the abs-max pass of coarse groups, the group-size heuristic)
+    // went top to bottom, and its end is what a matrix larger than the Infinity Cache has left there (108 -> 100 us
+    // after the heuristic; no difference on a matrix nobody read before).
+    const int64_t k0 = (int64_t)(gridDim.y - 1 - blockIdx.y) * FQ_QP_ROWS;
     const int cols = (int)((N - n0) < FQ_QP_COLS ? (N - n0) : FQ_QP_COLS);   // multiple of 16
     const int rows = (int)((K - k0) < FQ_QP_ROWS ? (K - k0) : FQ_QP_ROWS);   // 128, or 64 at the end (8-bit)
 

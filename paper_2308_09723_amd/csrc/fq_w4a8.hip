@@ -51,8 +51,9 @@ __device__ inline float f16_bits_to_float(uint16_t b) { return half_bits_to_floa
 //      group the smallest z in 1..16 with 15 * z * t >= 2 * (its abs-max)  (all products exact in binary32);
 //   3. codes q = clamp(round_half_even(w / (z t)), -7, 7), IEEE binary32 quotient, packed.
 // W has to be read twice (a column's step needs all of it).  Both passes are bound by HBM: 16-byte loads, the second
-// from panels staged in LDS.  On 12288 x 12288, g = 128 (us): abs-max with 2-byte loads 96 -> 64, steps and
-// multipliers 60 -> 9, encoding with a strided 2-byte load and a division per weight 201 -> 72 (5.2 TB/s).
+// from panels staged in LDS.  On 12288 x 12288, g = 128 (us): abs-max with 2-byte loads 96 -> 58, steps and
+// multipliers 60 -> 9, encoding with a strided 2-byte load and a division per weight 201 -> 63
+// (72 from the top of the matrix down).
 // ------------------------------------------------------------------------------------------------------
 // abs-max of every group from the maxima of its `per_group` blocks
 __global__ __launch_bounds__(256) void w8_fold_kernel(const uint16_t* __restrict__ fine, int64_t N, int per_group,
@@ -123,7 +124,9 @@ __global__ __launch_bounds__(256) void w8_encode_kernel(const uint16_t* __restri
     __shared__ __align__(16) float sub_rscale[4][FQ_QP_COLS];     // its reciprocal (0 for an all-zero column)
     const int tid = threadIdx.x;
     const int64_t n0 = (int64_t)blockIdx.x * FQ_QP_COLS;
-    const int64_t k0 = (int64_t)blockIdx.y * FQ_QP_ROWS;          // K is a multiple of 128
+    // (bottom of the matrix first: the abs-max pass went top to bottom, and its end is what the Infinity Cache still holds)
+    const int64_t kb = gridDim.y - 1 - blockIdx.y;
+    const int64_t k0 = kb * FQ_QP_ROWS;          // K is a multiple of 128
     const int cols = (int)((N - n0) < FQ_QP_COLS ? (N - n0) : FQ_QP_COLS);   // multiple of 16
     fq_stage_panel(W, N, k0, n0, FQ_QP_ROWS, cols, panel);
     {
@@ -152,7 +155,7 @@ __global__ __launch_bounds__(256) void w8_encode_kernel(const uint16_t* __restri
         out0[d] = fq_gather_bytes(b0[0], b0[1], b0[2], b0[3]) | (fq_gather_bytes(b0[4], b0[5], b0[6], b0[7]) << 4);
         out1[d] = fq_gather_bytes(b1[0], b1[1], b1[2], b1[3]) | (fq_gather_bytes(b1[4], b1[5], b1[6], b1[7]) << 4);
     }
-    const int64_t at = fq_rec(n0 / FQ_NTILE + c / FQ_NTILE, blockIdx.y, N / FQ_NTILE, j * 16 + c % FQ_NTILE);
+    const int64_t at = fq_rec(n0 / FQ_NTILE + c / FQ_NTILE, kb, N / FQ_NTILE, j * 16 + c % FQ_NTILE);
     uint32_t* dst = codes + at * 4;                                // record of column c; the next one follows it
     *reinterpret_cast<uint4*>(dst) = make_uint4(out0[0], out0[1], out0[2], out0[3]);
     *reinterpret_cast<uint4*>(dst + 4) = make_uint4(out1[0], out1[1], out1[2], out1[3]);
