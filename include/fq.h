@@ -226,7 +226,7 @@ size_t fq_gemm_noalloc_scratch_bytes(void);
  *   scales_f16    in  E scale matrices back to back (fq_scales_bytes() apart)
  *   A, C              [offsets[E], K] and [offsets[E], N]
  * E <= 256.
- * Experts are cut into row tiles of up to three sizes and each size is one kernel; these
+ * Experts are cut into row tiles of up to four sizes and each size is one kernel; these
  * independent kernels run on `stream` and on two streams the library creates (once per
  * device, default priority, never destroyed), forked from and joined back to `stream` with
  * events, so the call still behaves as one asynchronous operation on `stream`.  Calls from several host

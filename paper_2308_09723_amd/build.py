@@ -50,8 +50,8 @@ HIPCC_FLAGS = [
 # scratch traffic into their inner loops and moves with the compiler version.  The build fails if one does.
 # (template arguments as in csrc/fq_gemm_kernels.h)
 NO_SPILL = [
-    "fq_gemm_skinny_kernel<0, 4, 3, 2, 1, 12, 1>",     # decode, fp16 int4 g >= 128: QKV / FC1 / FC2 / out-proj at M = 1
-    "fq_gemm_skinny_kernel<0, 4, 1, 4, 1, 12, 1>",     # out-proj at M = 8
+    "fq_gemm_skinny_kernel<0, 4, 3, 2, 1, 12, 1, fq_no_items>",     # decode, fp16 int4 g >= 128: QKV / FC1 / FC2 / out-proj at M = 1
+    "fq_gemm_skinny_kernel<0, 4, 1, 4, 1, 12, 1, fq_no_items>",     # out-proj at M = 8
     "fq_gemm_mma_kernel<0, 4, 8, 3, 8, 1, false, 2, false, 1>",   # prefill, fp16
     "fq_gemm_mma_kernel<3, 4, 8, 3, 8, 1, false, 2, false, 1>",   # prefill, bf16 on the fp16 matrix path
     "fq_gemm_mma_kernel<0, 4, 2, 3, 4, 1, false, 2, true, 1>",    # M = 32, fp16, post-scaled

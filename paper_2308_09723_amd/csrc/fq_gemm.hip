@@ -226,6 +226,43 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g) {
     return p;
 }
 
+// Block shape for the experts of the small-M kernel: the shape with the least
+//   (blocks / slots + 0.7) * (iterations * 1.5 us + ramp)
+// i.e. the rounds of blocks, with an average partly filled one, times the time of a block: 12 waves stream 36 KiB per
+// iteration, and a block's start and end cost 2.5 us (5 with the sum over k-workers).  Not rounded up to whole rounds:
+// the other row classes of the call hold an unknown part of the compute units.  Against sweeps of 64 experts of 16384 x
+// 4096 and 4096 x 16384 with 96 rows the model is within 10 %: e.g. 3 x 4 waves 224 us predicted / 239 measured, 12 x 1
+// 336 / 337 on the former, 12 x 1 224 / 222, 4 x 3 253 / 248 on the latter.  Blocks have 12 or 4 waves: two blocks of
+// six do not fit a compute unit's four SIMDs (310 us where 12 x 1 takes 222).
+bool fq_split_32_rows(const int32_t* offsets, int E) {
+    int n16 = 0, n32 = 0;
+    for (int e = 0; e < E; ++e) {
+        const int32_t rows = offsets[e + 1] - offsets[e];
+        if (rows > 32) return false;
+        n16 += rows > 0 && rows <= 16;
+        n32 += rows > 16;
+    }
+    return n32 > 0 && 8 * n32 <= n16;
+}
+
+fq_small_shape fq_plan_grouped_small(int count, int units, int ngroups, int KB) {
+    static const fq_small_shape shapes[7] = {{12, 1}, {6, 2}, {4, 3}, {3, 4}, {2, 6}, {4, 1}, {2, 2}};
+    fq_small_shape best = {12, 1};
+    double best_t = 1e30;
+    for (const fq_small_shape& s : shapes) {
+        if (units > 64 * s.gp || s.kw > KB) continue;
+        const double together = 12.0 / (s.gp * s.kw);
+        const double rounds = (double)((ngroups + s.gp - 1) / s.gp) * count / (fq_cu_count() * together);
+        const double filled = rounds + 0.7;
+        const double t = (filled < 1.0 ? 1.0 : filled) * (1.5 * ((KB + s.kw - 1) / s.kw) + (s.kw > 1 ? 5.0 : 2.5));
+        if (t < best_t) {
+            best_t = t;
+            best = s;
+        }
+    }
+    return best;
+}
+
 int fq_launch_gemm(const void* A, int act, int64_t M, int64_t N, int64_t K, const void* codes,
                    const void* scales, int bits, int g, void* C, void* workspace, hipStream_t stream) {
     const fq_gemm_plan plan = fq_plan_gemm(M, N, K, bits, g);
@@ -239,9 +276,9 @@ int fq_launch_gemm(const void* A, int act, int64_t M, int64_t N, int64_t K, cons
 #undef FQ_PICK
 }
 
-// The grouped product launches up to three kernels (row tiles of 128, 64 and 32 rows) that do not
+// The grouped product launches up to four kernels (row tiles of 128, 64, 32 and 16 rows) that do not
 // depend on each other.  Launched one after the other on the caller's stream, each would end with
-// a partly filled last round of blocks; on three streams the blocks of the next kernel fill the
+// a partly filled last round of blocks; on streams of their own the blocks of the next kernel fill the
 // compute units the previous one leaves idle.  The two extra streams (default priority) and the
 // events that fork them from and join them to the caller's stream are created once per device and
 // live until the process ends.
@@ -262,11 +299,10 @@ fq_side* side_streams() {
     fq_side& x = g_side[dev];
     if (!x.tried) {
         x.tried = true;
-        bool ok = hipStreamCreateWithFlags(&x.s[0], hipStreamNonBlocking) == hipSuccess &&
-                  hipStreamCreateWithFlags(&x.s[1], hipStreamNonBlocking) == hipSuccess &&
-                  hipEventCreateWithFlags(&x.fork, hipEventDisableTiming) == hipSuccess &&
-                  hipEventCreateWithFlags(&x.join[0], hipEventDisableTiming) == hipSuccess &&
-                  hipEventCreateWithFlags(&x.join[1], hipEventDisableTiming) == hipSuccess;
+        bool ok = hipEventCreateWithFlags(&x.fork, hipEventDisableTiming) == hipSuccess;
+        for (int i = 0; i < 2; ++i)
+            ok = ok && hipStreamCreateWithFlags(&x.s[i], hipStreamNonBlocking) == hipSuccess &&
+                 hipEventCreateWithFlags(&x.join[i], hipEventDisableTiming) == hipSuccess;
         x.ok = ok;
         if (!ok) (void)hipGetLastError();
     }
@@ -278,34 +314,43 @@ int fq_launch_gemm_grouped(const void* A, int act, const int32_t* offsets, int E
                            const void* codes, const void* scales, int bits, int g, void* C,
                            hipStream_t stream) {
     // which tile sizes occur (same cutting rule as the launcher)
-    bool has[3] = {false, false, false};
+    const bool split32 = fq_split_32_rows(offsets, E);
+    bool has[4] = {false, false, false, false};
     for (int e = 0; e < E; ++e) {
         const int32_t rows = offsets[e + 1] - offsets[e];
         if (rows <= 0) continue;
+        if (rows <= (split32 ? 32 : 16)) {
+            has[3] = true;
+            continue;
+        }
         if (rows > 64) has[0] = true;
         const int32_t rest = rows > 64 ? rows % 128 : rows;
         if (rest > 64) has[0] = true;
         else if (rest > 32) has[1] = true;
         else if (rest > 0) has[2] = true;
     }
-    hipStream_t streams[3] = {stream, stream, stream};
-    fq_side* side = (int)has[0] + (int)has[1] + (int)has[2] > 1 ? side_streams() : nullptr;
+    hipStream_t streams[4] = {stream, stream, stream, stream};
+    fq_side* side = (int)has[0] + (int)has[1] + (int)has[2] + (int)has[3] > 1 ? side_streams() : nullptr;
     // host threads that fork at the same time would record and wait on each other's events
     std::unique_lock<std::mutex> fork_lock(g_fork_mutex, std::defer_lock);
     if (side) fork_lock.lock();
     bool forked[2] = {false, false};
     if (side) {
-        // the first tile size present stays on the caller's stream, the others go to the side streams
-        int next = 0;
+        // the first tile size present stays on the caller's stream, the others go to the side streams; the fourth
+        // follows the third on its stream (a queue more to wake up costs a call on an idle GPU 20 - 60 us, and by then
+        // the compute units are filled anyway)
+        int next = -1;
         bool first = true;
         if (hipEventRecord(side->fork, stream) != hipSuccess) return FQ_ERR_HIP;
-        for (int c = 0; c < 3; ++c) {
+        for (int c = 0; c < 4; ++c) {
             if (!has[c]) continue;
             if (first) { first = false; continue; }
-            if (hipStreamWaitEvent(side->s[next], side->fork, 0) != hipSuccess) return FQ_ERR_HIP;
+            if (next < 1) {
+                ++next;
+                if (hipStreamWaitEvent(side->s[next], side->fork, 0) != hipSuccess) return FQ_ERR_HIP;
+                forked[next] = true;
+            }
             streams[c] = side->s[next];
-            forked[next] = true;
-            ++next;
         }
     }
     int st;

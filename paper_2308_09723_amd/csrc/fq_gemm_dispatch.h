@@ -55,7 +55,7 @@ int launch_skinny(const void* A, int64_t M, int64_t N, int64_t K, const void* co
     hipLaunchKernelGGL(kern, dim3((unsigned)(bgroups * plan.splits)), dim3((unsigned)(plan.gp * plan.kw * 64)),
                        lds, stream, (const uint16_t*)A, (const u32x4*)codes, (const uint16_t*)scales,
                        (uint16_t*)C, partial, (int)M, (int)N, (int)K, g32, g32_recip, plan.gp, plan.kw,
-                       plan.splits);
+                       plan.splits, fq_no_items{});
     return FQ_OK;
 }
 
@@ -202,16 +202,47 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
     return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_HIP;
 }
 
-// Grouped (per-expert) product.  Every expert's rows are cut into row tiles of 128, 64 or 32
-// rows (the smallest that holds what is left), and the tiles of each size go to the kernel
-// instantiated for that size: experts with few rows then stream their weights through small
-// tiles instead of multiplying mostly padding.  Experts without rows produce no tile.
+// The experts with few rows of a grouped product: the small-M kernel, items of 1 .. 16 rows.  Block shape: gp column
+// groups (of three tiles) x kw k-workers, gp * kw waves; gp is at least what lets one activation unit per lane hold a
+// super-block's slice of the tallest item (more units per lane spill registers).
+template <int ACT, int BITS>
+int launch_grouped_small(const void* A, const fq_small_items& items, int count, int rows_max, int64_t N, int64_t K,
+                         const void* codes, const void* scales, int g, void* C, hipStream_t stream) {
+    constexpr int NT = 3, DEPTH = 2, MAXW = 12;
+    constexpr int kblk = fq_kblk(BITS);
+    constexpr int STEPS = kblk / FQ_KSTEP;
+    const int sr = (g % kblk) == 0 ? 1 : ((kblk % g) == 0 ? kblk / g : STEPS);
+    const int KB = (int)(K / kblk);
+    const int ngroups = (int)((N / FQ_NTILE + NT - 1) / NT);
+    const fq_small_shape sh = fq_plan_grouped_small(count, rows_max * (kblk / 8), ngroups, KB);
+    const size_t lds_act = (size_t)2 * sh.kw * (kblk / 8) * FQ_SK_PITCH * 16;
+    const size_t lds_red = (size_t)sh.gp * sh.kw * NT * 64 * 16;
+    const size_t lds = lds_act > lds_red ? lds_act : lds_red;       // at most 52 KiB (gp >= 2)
+    const uint32_t g32 = (uint32_t)(g / 32);
+    const uint32_t g32_recip = (uint32_t)((((uint64_t)1 << 32) + g32 - 1) / g32);   // unused when g32 == 1
+    auto kern = sr == 1 ? fq_gemm_skinny_kernel<ACT, BITS, NT, DEPTH, 1, MAXW, 1, fq_small_items>
+                        : (sr == 2 ? fq_gemm_skinny_kernel<ACT, BITS, NT, DEPTH, 2, MAXW, 1, fq_small_items>
+                                   : fq_gemm_skinny_kernel<ACT, BITS, NT, DEPTH, STEPS, MAXW, 1, fq_small_items>);
+    const int64_t blocks = (int64_t)((ngroups + sh.gp - 1) / sh.gp) * count;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3((unsigned)(sh.gp * sh.kw * 64)), lds, stream, (const uint16_t*)A,
+                       (const u32x4*)codes, (const uint16_t*)scales, (uint16_t*)C, (float*)nullptr, 0, (int)N, (int)K, g32,
+                       g32_recip, sh.gp, sh.kw, 1, items);
+    return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_HIP;
+}
+
+// Grouped (per-expert) product.  Every expert's rows are cut into row tiles of 128, 64, 32 or 16
+// rows (the smallest that holds what is left; 16 only where the expert has no more than 16 rows in all, or 32: see
+// fq_split_32_rows), and the tiles
+// of each size go to the kernel instantiated for that size: experts with few rows then stream their weights through
+// small tiles instead of multiplying mostly padding, those with at most 16 through the small-M kernel.  Experts without
+// rows produce no tile.
 template <int ACT, int BITS>
 int launch_grouped_typed(const void* A, const int32_t* offsets, int E, int64_t N, int64_t K,
                          const void* codes, const void* scales, int g, void* C, const hipStream_t* streams) {
     const int ntiles = (int)(N / FQ_NTILE);
     const int64_t codes_stride16 = (int64_t)(K * N * BITS / 8) / 16;
     const int64_t scales_stride = (K / g) * N;
+    const int32_t small_most = fq_split_32_rows(offsets, E) ? 32 : 16;   // experts up to here take the small-M kernel
     fq_group_items items;
     for (int mt = 8; mt >= 2; mt /= 2) {
         const int bm = mt * 16;
@@ -270,6 +301,7 @@ int launch_grouped_typed(const void* A, const int32_t* offsets, int E, int64_t N
         };
         for (int e = 0; e < E; ++e) {
             int32_t r = offsets[e];
+            if (offsets[e + 1] - r <= small_most) continue;      // below
             while (r < offsets[e + 1]) {
                 const int32_t left = offsets[e + 1] - r;
                 const int tile_mt = left > 64 ? 8 : (left > 32 ? 4 : 2);
@@ -290,7 +322,31 @@ int launch_grouped_typed(const void* A, const int32_t* offsets, int E, int64_t N
         const int st = flush_items();
         if (st != FQ_OK) return st;
     }
-    return FQ_OK;
+    fq_small_items small;
+    small.codes_stride16 = codes_stride16;
+    small.scales_stride = scales_stride;
+    int count = 0, rows_max = 0;
+    auto flush_small = [&]() -> int {
+        const int n = count;
+        count = 0;
+        return n == 0 ? FQ_OK
+                      : launch_grouped_small<ACT, BITS>(A, small, n, rows_max, N, K, codes, scales, g, C, streams[3]);
+    };
+    for (int e = 0; e < E; ++e) {
+        if (offsets[e + 1] - offsets[e] > small_most) continue;
+        for (int32_t r = offsets[e]; r < offsets[e + 1]; r += 16) {
+            const int rows = offsets[e + 1] - r < 16 ? offsets[e + 1] - r : 16;
+            small.row0[count] = r;
+            small.rows[count] = (uint8_t)rows;
+            small.expert[count] = (uint8_t)e;
+            rows_max = rows > rows_max ? rows : rows_max;
+            if (++count == 256) {
+                const int st = flush_small();
+                if (st != FQ_OK) return st;
+            }
+        }
+    }
+    return flush_small();
 }
 
 

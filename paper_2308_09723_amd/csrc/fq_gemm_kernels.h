@@ -395,11 +395,26 @@ __device__ inline void skinny_block(const SkinnyStage<BITS, NT, SR, AU>& sl,
 // lanes = consecutive unit columns of one row) spread over the banks.
 #define FQ_SK_PITCH 17
 
-template <int ACT, int BITS, int NT, int DEPTH, int SR, int MAXW, int AU>
+// Grouped (per-expert) form: items of 1 .. 16 rows; block b works for item b / (column blocks).  Rows
+// row0 .. row0 + rows - 1 of the stacked activations belong to expert `expert`, whose weights start
+// expert * codes_stride16 records / expert * scales_stride scales into the buffers.  Passed by value in the kernel
+// arguments.
+struct fq_small_items {
+    static constexpr bool grouped = true;
+    int64_t codes_stride16, scales_stride;
+    int32_t row0[256];
+    uint8_t rows[256];
+    uint8_t expert[256];
+};
+struct fq_no_items {
+    static constexpr bool grouped = false;
+};
+
+template <int ACT, int BITS, int NT, int DEPTH, int SR, int MAXW, int AU, typename ITEMS = fq_no_items>
 __global__ __launch_bounds__(MAXW * 64) void fq_gemm_skinny_kernel(
     const uint16_t* __restrict__ A, const u32x4* __restrict__ codes, const uint16_t* __restrict__ scales,
     uint16_t* __restrict__ C, float* __restrict__ partial, int M, int N, int K, uint32_t g32,
-    uint32_t g32_recip, int gp, int kw_n, int grid_splits) {
+    uint32_t g32_recip, int gp, int kw_n, int grid_splits, ITEMS items) {
     constexpr int KBLK = fq_kblk(BITS);
     constexpr int STEPS = KBLK / FQ_KSTEP;
     constexpr int KC = KBLK / 8;                    // 16-byte activation units per row and k-block
@@ -416,7 +431,18 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_skinny_kernel(
     const int ngroups = (ntiles + NT - 1) / NT;
     const int bgroups = (ngroups + gp - 1) / gp;      // blocks per grid split
     const int bx = blockIdx.x % bgroups;
-    const int gsplit = blockIdx.x / bgroups;          // < grid_splits
+    int gsplit = blockIdx.x / bgroups;                // < grid_splits
+    if constexpr (ITEMS::grouped) {
+        const int item = gsplit;
+        gsplit = 0;                                   // (no split of K over the grid: grid_splits is 1)
+        const int64_t row0 = items.row0[item];
+        const int e = items.expert[item];
+        M = items.rows[item];
+        A += row0 * K;
+        C += row0 * N;
+        codes += e * items.codes_stride16;
+        scales += e * items.scales_stride;
+    }
     const int ng = bx * gp + gi;
     const bool gvalid = ng < ngroups;
     const int KB = K / KBLK;

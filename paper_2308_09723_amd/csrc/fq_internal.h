@@ -41,6 +41,15 @@ struct fq_gemm_plan {
     int tail_tiles, tail_splits, tail_kbs;
 };
 fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g);
+// Grouped products in which no expert has more than 32 rows and at most one in nine has more than 16 give those few to
+// the small-M kernel as two items of 16 rows (their weights are read twice, mostly from a cache the second time):
+// a kernel of their own beside it costs the fork to another stream and more compute units than the second reading
+// (64 experts, 96 rows: 237 -> 216 us).
+bool fq_split_32_rows(const int32_t* offsets, int E);
+// Block shape of the small-M kernel for `count` items of a grouped product (at most 16 rows each);
+// units = activation units (16 bytes) of a k-block in the tallest of them, ngroups = groups of three column tiles.
+struct fq_small_shape { int gp, kw; };
+fq_small_shape fq_plan_grouped_small(int count, int units, int ngroups, int KB);
 // compute units of the device (asked once per process; 256 without a device)
 int fq_cu_count();
 // Rows of K per k-block of the tiled kernel for a block shape (the unit of kb_per_split and tail_kbs):

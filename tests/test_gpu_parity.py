@@ -508,3 +508,27 @@ def test_grouped_gemm_int8_two_layout_blocks_per_k_block(dtype, g, K):
     are multiples of 128 (an odd number of them here), the smaller tiles and g = 64 keep the 64-row blocks."""
     _say(f"grouped int8 wide {dtype} g={g} K={K}")
     _grouped_case(dtype, 8, g, K, 784, [130, 31, 64, 0, 257, 1, 97], seed=35)
+
+
+@pytest.mark.parametrize("rows", [[16, 1, 0, 15, 4], [1], [17, 16, 1, 2, 3, 16, 4, 5, 16], [32, 16, 3], [130, 16, 0, 33, 9, 20]],
+                         ids=["at-most-16", "one-row", "one-of-nine-17", "32-and-16", "every-size"])
+@pytest.mark.parametrize("dtype,bits,g,K,N", [("f16", 4, 64, 640, 112), ("bf16", 4, 128, 1664, 1040), ("bf16", 8, 0, 192, 48),
+                                              ("f16", 8, 32, 256, 816), ("f16", 3, 96, 384, 16)])
+def test_grouped_gemm_few_rows_per_expert(dtype, bits, g, K, N, rows):
+    """Experts of at most 16 rows take the small-M kernel, those of 17 .. 32 too (as two items) where they are few and
+    nobody has more; neighbours with more rows take the tiled kernel.  Column counts that leave idle column groups, k
+    ranges shorter than the k-workers' turn, and every expert's rows next to another expert's."""
+    _say(f"grouped few rows {dtype} int{bits} g={g} {rows}")
+    fq = _fq()
+    torch = torch_mod()
+    offsets = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    A = workloads.activations(int(offsets[-1]), K, dtype, 60 + K)
+    qs, ss, codes, scales = [], [], [], []
+    for e in range(len(rows)):
+        c, s, q_ref, s_ref = assert_quantizer_parity(workloads.weights_gaussian(K, N, 700 + e, outlier_prob=1e-3), bits, g)
+        qs.append(q_ref); ss.append(s_ref); codes.append(c); scales.append(s.reshape(-1))
+    C = torch.full((int(offsets[-1]) + 2, N), 7.0, dtype=to_dev_act(A[:1], dtype).dtype, device="cuda")
+    fq.gemm_grouped(to_dev_act(A, dtype), offsets.tolist(), torch.cat(codes), torch.cat(scales), bits, g, N,
+                    out=C[:int(offsets[-1])])
+    assert_gemm_close(from_dev_act(C[:int(offsets[-1])], dtype), oracle.gemm_ref_grouped(A, offsets, qs, ss), dtype)
+    assert bool((C[int(offsets[-1]):] == 7.0).all())
