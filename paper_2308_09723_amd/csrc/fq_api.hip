@@ -305,6 +305,8 @@ int fq_gemm_describe(int64_t M, int64_t N, int64_t K, int bits, int group_size, 
     if (p.kind == 0)
         snprintf(buf, buf_bytes, "small-m variant=%d gp=%d kw=%d au=%d waves=%d splits=%d", p.variant, p.gp,
                  p.kw, p.au, p.waves, p.splits);
+    else if (p.kind == 2)
+        snprintf(buf, buf_bytes, "mid-m mt=%d gp=%d kw=%d waves=%d splits=%d", p.mt, p.gp, p.kw, p.waves, p.splits);
     else
         snprintf(buf, buf_bytes, "tiled mt=%d waves=%d splits=%d kb_per_split=%d tail=%dx%d", p.mt, p.waves, p.splits,
                  p.kb_per_split, p.tail_tiles, p.tail_tiles > 0 ? p.tail_splits : 1);

@@ -44,6 +44,61 @@ int fq_cu_count() {
     return n;
 }
 
+// Mid-M streaming kernel (17 <= M <= 48): the block shape (gp column groups x kw k-workers, at most 12 waves, three
+// (M <= 32) or two activation tiles of kw k-blocks in the 160 KiB of LDS) and split of K over the grid with the least
+//   sum over rounds of blocks (iterations * t_it + 5 us)  +  partial sums (their traffic at 5 TB/s + 4 us, if split)
+// where an iteration takes the longest of the time the vector and matrix units need for the block's waves, the time
+// HBM needs for what the resident blocks ask of it (5.4 TB/s), and a latency of 1.4 us.  Against sweeps of (gp, kw, splits) on forty
+// shapes at M = 17 .. 48 the choice is the sweep's best or within 3 % of it on most and 8 % slower at worst (49152 x
+// 12288: 72 where 67 us is possible).  The kernel against the tiled one with 32- and 64-row blocks on the same shapes:
+// 1.15x faster on average (0.94 - 2.0x; 33 of the 40 faster), so there is no rule between the two below 49 rows; with
+// four row tiles (M = 64) it took 88 - 101 us where the tiled kernel takes 91 - 98, so 49 rows and more stay there.
+static void fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int ncu, fq_gemm_plan* p) {
+    const int mt = M <= 32 ? 2 : 3;
+    const int kblk = fq_kblk(bits);
+    const int KB = (int)(K / kblk);
+    const int64_t ngroups = (N / FQ_NTILE + MMA_NT - 1) / MMA_NT;
+    const int sr = g % kblk == 0 ? 1 : (kblk % g == 0 ? kblk / g : kblk / 32);
+    // microseconds of vector / matrix work per iteration of a full block (12 waves, one k-block of 48 columns each)
+    double work = mt == 2 ? (bits == 8 ? 0.85 : (bits == 3 ? 1.75 : 1.5)) : (bits == 8 ? 1.3 : (bits == 3 ? 2.6 : 2.4));
+    work += (sr - 1) * (mt == 2 ? 0.27 : 0.4);
+    const double rec_bytes = MMA_NT * 64.0 * fq_rec_bytes(bits) + MMA_NT * 32.0 * sr;   // per wave and iteration
+    const int tile_bytes = mt * 16 * kblk * 2;
+    double best = 1e30;
+    for (int gp = 1; gp <= 12; ++gp) {
+        int kw = 12 / gp;
+        const int fit = 160 * 1024 / ((mt == 2 ? 3 : 2) * tile_bytes);
+        if (kw > fit) kw = fit;
+        if (kw > KB) kw = KB;
+        const int waves = gp * kw;
+        const int64_t blocks = (ngroups + gp - 1) / gp;
+        const int SB = (KB + kw - 1) / kw;
+        const double t_work = work * (double)((waves + 3) / 4) / 3.0;
+        for (int gs = 1; gs <= 8 && gs <= SB; ++gs) {
+            const int64_t grid = blocks * gs;
+            if (gs > 1 && grid > 2 * (int64_t)ncu) break;
+            const int n_it = (SB + gs - 1) / gs;
+            const int64_t full = grid / ncu, rest = grid % ncu;
+            auto round_us = [&](double active) {
+                const double t_mem = active * waves * rec_bytes / 5.4e6;
+                const double t_it = t_mem > t_work ? t_mem : t_work;
+                return n_it * (t_it > 1.4 ? t_it : 1.4) + 5.0;
+            };
+            double t = (double)full * round_us((double)ncu) + (rest ? round_us((double)rest) : 0.0);
+            if (gs > 1) t += 2.0 * gs * (double)M * (double)N * 4.0 / 5e6 + 4.0;
+            if (t < best - 1e-9) {
+                best = t;
+                p->kind = 2;
+                p->mt = mt;
+                p->gp = gp;
+                p->kw = kw;
+                p->waves = waves;
+                p->splits = gs;
+            }
+        }
+    }
+}
+
 fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g) {
     fq_gemm_plan p = {};
     const int ncu = fq_cu_count();
@@ -110,6 +165,8 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g) {
             }
         }
         p.kb_per_split = 0;
+    } else if (M <= 48) {
+        fq_plan_mid(M, N, K, bits, g, ncu, &p);
     } else {
         // Tiled MFMA kernel: BM = 16 * mt rows per block (mt = 2, 4 or 8), 48 columns per wave, 4 or 8
         // waves, and optionally a split of K over `splits` blocks whose binary32 partial tiles a second

@@ -35,7 +35,6 @@ constexpr bool use_post(int act, int bits, int mt, int sr, int pipe) {
 struct SkinnyVariant { int nt, depth, maxw; };
 constexpr SkinnyVariant SKINNY_VARIANTS[4] = {{3, 2, 12}, {3, 3, 8}, {1, 4, 12}, {2, 3, 12}};
 
-
 }  // namespace fqd
 
 #endif  // FQ_GEMM_CONFIG_H_

@@ -69,6 +69,34 @@ int launch_skinny_au(const void* A, int64_t M, int64_t N, int64_t K, const void*
     }
 }
 
+// Mid-M streaming kernel (plan.kind == 2)
+template <int ACT, int BITS, int NT, int MT, int DEPTH, int NBUF, int MAXW>
+int launch_mid(const void* A, int64_t M, int64_t N, int64_t K, const void* codes, const void* scales, int g, void* C,
+               float* partial, const fq_gemm_plan& plan, hipStream_t stream) {
+    constexpr int kblk = fq_kblk(BITS);
+    constexpr int STEPS = kblk / FQ_KSTEP;
+    const int sr = (g % kblk) == 0 ? 1 : ((kblk % g) == 0 ? kblk / g : STEPS);
+    const int ngroups = (int)((N / FQ_NTILE + NT - 1) / NT);
+    const int bgroups = (ngroups + plan.gp - 1) / plan.gp;
+    const size_t lds_act = (size_t)NBUF * plan.kw * MT * 16 * (kblk / 8) * 16;
+    const size_t lds_red = (size_t)plan.gp * plan.kw * NT * MT * 64 * 16;
+    const size_t lds = lds_act > lds_red ? lds_act : lds_red;
+    if (lds > 160 * 1024) return FQ_ERR_UNSUPPORTED;
+    const uint32_t g32 = (uint32_t)(g / 32);
+    const uint32_t g32_recip = (uint32_t)((((uint64_t)1 << 32) + g32 - 1) / g32);   // unused when g32 == 1
+    auto kern = sr == 1 ? fq_gemm_mid_kernel<ACT, BITS, NT, MT, DEPTH, NBUF, 1, MAXW>
+                        : (sr == 2 ? fq_gemm_mid_kernel<ACT, BITS, NT, MT, DEPTH, NBUF, 2, MAXW>
+                                   : fq_gemm_mid_kernel<ACT, BITS, NT, MT, DEPTH, NBUF, STEPS, MAXW>);
+    if (lds > 65536) {
+        static std::atomic<uint64_t> raised[3];   // per instantiation: [scale rows per k-block]
+        if (raise_lds_limit((const void*)kern, raised[sr == 1 ? 0 : (sr == 2 ? 1 : 2)]) != FQ_OK) return FQ_ERR_HIP;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)(bgroups * plan.splits)), dim3((unsigned)(plan.gp * plan.kw * 64)), lds, stream,
+                       (const uint16_t*)A, (const u32x4*)codes, (const uint16_t*)scales, (uint16_t*)C, partial, (int)M,
+                       (int)N, (int)K, g32, g32_recip, plan.gp, plan.kw, plan.splits);
+    return FQ_OK;
+}
+
 template <int ACT, int BITS>
 int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* codes, const void* scales,
                  int g, void* C, void* workspace, const fq_gemm_plan& plan, hipStream_t stream) {
@@ -82,6 +110,12 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
             case 2: st = launch_skinny_au<ACT, BITS, 1, 4, 12>(A, M, N, K, codes, scales, g, C, partial, plan, stream); break;
             default: st = launch_skinny_au<ACT, BITS, 2, 3, 12>(A, M, N, K, codes, scales, g, C, partial, plan, stream); break;
         }
+        if (st != FQ_OK) return st;
+    } else if (plan.kind == 2) {
+        // two row tiles: three stages of weights in flight and three activation tiles; three: two (registers) and two (LDS)
+        const int st = plan.mt == 2
+                           ? launch_mid<ACT, BITS, MMA_NT, 2, 3, 3, 12>(A, M, N, K, codes, scales, g, C, partial, plan, stream)
+                           : launch_mid<ACT, BITS, MMA_NT, 3, 2, 2, 12>(A, M, N, K, codes, scales, g, C, partial, plan, stream);
         if (st != FQ_OK) return st;
     } else {
         // rows of K per k-block of this block shape (two layout blocks at a time for 8-bit codes in the

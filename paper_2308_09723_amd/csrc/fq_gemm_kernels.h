@@ -280,6 +280,13 @@ __device__ inline void flush(f32x4& acc, const f32x4& p, const f32x4& s, float r
     }
 }
 
+// s_waitcnt vmcnt(N) only (the other counters left alone); gfx9 encoding: vmcnt in bits 3:0 and 15:14
+template <int N>
+__device__ inline void wait_vmcnt() {
+    static_assert(N >= 0 && N < 64, "");
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
 // ==========================================================================================
 // Small-M kernel (M <= 16): the decode case, bound by the HBM read of the weights
 // (section 2.1, "Large weights with small activations").
@@ -314,7 +321,7 @@ struct SkinnyStage {
     // quad broadcast hands every lane the row of the step at hand: one load per tile and k-block
     // instead of one per step.
     u32x2 sc[NT];
-    u32x4 areg[AU];
+    u32x4 areg[AU > 0 ? AU : 1];   // (none used for AU = 0)
 };
 
 // four stored scales -> binary32
@@ -339,6 +346,19 @@ __device__ inline u32x2 quad_bcast(const u32x2& v) {
     r[0] = (uint32_t)__builtin_amdgcn_mov_dpp((int)v[0], T * 0x55, 0xf, 0xf, true);
     r[1] = (uint32_t)__builtin_amdgcn_mov_dpp((int)v[1], T * 0x55, 0xf, 0xf, true);
     return r;
+}
+
+// true (in every lane) when some lane of the wave holds an infinity or a NaN among its sums
+template <int MT, int NT>
+__device__ inline bool any_not_finite(const f32x4 (&acc)[MT][NT]) {
+    float t = 0.0f;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) t = __builtin_fmaf(acc[mt][nt][i], 0.0f, t);   // NaN from then on
+    return __builtin_amdgcn_ballot_w64(t != t) != 0;
 }
 
 // acc[nt] += (this wave's k-block of the stage) x (activation fragments af[0..STEPS)).
@@ -390,6 +410,115 @@ __device__ inline void skinny_block(const SkinnyStage<BITS, NT, SR, AU>& sl,
     }
 }
 
+// Biased operands remove their bias with the activations' row sums.  In a row with an infinity, or with values so near
+// the top of binary32's range that the biased sums overflow, that leaves a NaN where the product itself is an infinity
+// or finite.  A wave that ends with a sum that is not finite therefore computes its share once more here, with operands
+// that hold q itself.  Not a fast path: no ring, activations from global memory.
+template <int ACT, int BITS, int T>
+__device__ inline u32x4 unbiased_operand(const u32x4& rec) {
+    if constexpr (ACT == FQ_F16) {
+        return Dequant<FQ_F16, BITS>::template run<T>(rec, Dequant<FQ_F16, BITS>::init());
+    } else {
+        constexpr float BIAS = BITS == 8 ? 128.0f : (BITS == 4 ? 8.0f : 4.0f);
+        constexpr uint32_t MASK = BITS == 8 ? 0xffu : (BITS == 4 ? 0xfu : 0x7u);
+        u32x4 r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {                    // elements 2 i, 2 i + 1
+            uint32_t lo, hi;
+            if constexpr (BITS == 8) {
+                const uint32_t w = rec[2 * T + (i >> 1)] >> (16 * (i & 1));
+                lo = w;
+                hi = w >> 8;
+            } else {
+                const uint32_t w = code_word<BITS, T>(rec) >> (4 * i);
+                lo = w;
+                hi = w >> 16;
+            }
+            const float f0 = (float)(lo & MASK) - BIAS, f1 = (float)(hi & MASK) - BIAS;
+            // upper halves of the two binary32 values (exact: at most 8 significant bits)
+            r[i] = __builtin_amdgcn_perm(bitcast<uint32_t>(f1), bitcast<uint32_t>(f0), 0x07060302u);
+        }
+        return r;
+    }
+}
+
+// acc = this wave's tiles over the k-blocks kb, kb + kb_step, ... < KB (one 32-row step after the other)
+template <int ACT, int BITS, int NT, int MT>
+__device__ inline void multiply_unbiased(f32x4 (&acc)[MT][NT], const uint16_t* A, int M, int N, int K,
+                                         const char* const (&wbase)[NT], const uint16_t* const (&sbase)[NT], uint32_t g32,
+                                         uint32_t g32_recip, int kb, int kb_step, int KB, int lane) {
+    constexpr int STEPS = fq_kblk(BITS) / FQ_KSTEP;
+    constexpr int RB = fq_rec_bytes(BITS);
+    const int64_t kb_stride = (int64_t)(N / FQ_NTILE) * 64;
+    const int ml = lane & 15, j = lane >> 4;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = zero;
+#pragma unroll 1
+    for (; kb < KB; kb += kb_step) {
+        u32x4 q[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) q[nt] = load_rec<BITS, false>(wbase[nt] + ((int64_t)kb * kb_stride + lane) * RB);
+#pragma unroll
+        for (int t = 0; t < STEPS; ++t) {
+            const uint32_t step = (uint32_t)kb * STEPS + t;
+            const int64_t srow = (int64_t)(g32 == 1 ? step : __umulhi(step, g32_recip)) * N;
+            u32x4 a[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                const int row = mt * 16 + ml < M ? mt * 16 + ml : M - 1;
+                a[mt] = *reinterpret_cast<const u32x4*>(A + (int64_t)row * K + ((int64_t)step * FQ_KSTEP + 8 * j));
+            }
+            // bfloat16 rows near the top of the range are brought down by 2^-16 for this step, so that the sums of
+            // a q stay in range before their scale (a lane's fragments and its results belong to the same row)
+            float back[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                back[mt] = 1.0f;
+                if constexpr (ACT != FQ_F16) {
+                    uint32_t m = 0;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uint32_t lo = a[mt][i] & 0x7fffu, hi = (a[mt][i] >> 16) & 0x7fffu;
+                        m = m > lo ? m : lo;
+                        m = m > hi ? m : hi;
+                    }
+                    const uint32_t m1 = (uint32_t)__shfl_xor((int)m, 16, 64);
+                    m = m > m1 ? m : m1;
+                    const uint32_t m2 = (uint32_t)__shfl_xor((int)m, 32, 64);
+                    m = m > m2 ? m : m2;
+                    if (m >= 0x7180u) {                  // 2^100
+                        back[mt] = 65536.0f;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const float lo = bitcast<float>(a[mt][i] << 16) * 0x1p-16f;
+                            const float hi = bitcast<float>(a[mt][i] & 0xffff0000u) * 0x1p-16f;
+                            a[mt][i] = __builtin_amdgcn_perm(bitcast<uint32_t>(hi), bitcast<uint32_t>(lo), 0x07060302u);
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                u32x4 w;
+                if (t == 0) w = unbiased_operand<ACT, BITS, 0>(q[nt]);
+                if (t == 1) w = unbiased_operand<ACT, BITS, 1>(q[nt]);
+                if (STEPS > 2 && t == 2) w = unbiased_operand<ACT, BITS, 2 % STEPS>(q[nt]);
+                if (STEPS > 2 && t == 3) w = unbiased_operand<ACT, BITS, 3 % STEPS>(q[nt]);
+                __builtin_amdgcn_sched_barrier(0);       // (one tile after the other: few registers, not speed)
+                const f32x4 s = scales4<ACT>(*reinterpret_cast<const u32x2*>(sbase[nt] + srow + 4 * j));
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    const f32x4 p = mfma16x16x32<ACT>(w, a[mt], zero);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[mt][nt][i] = __builtin_fmaf(s[i] * back[mt], p[i], acc[mt][nt][i]);
+                }
+            }
+        }
+    }
+}
 // LDS row pitch of the activation buffer in 16-byte units: 16 rows + 1 pad, so that both the
 // fragment reads (16 lanes = 16 rows of one unit column) and the staging writes (consecutive
 // lanes = consecutive unit columns of one row) spread over the banks.
@@ -567,6 +696,17 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_skinny_kernel(
         }
     }
 
+    if constexpr (ITEMS::grouped && Dequant<ACT, BITS>::OFFSET != 0.0f) {
+        f32x4 again[1][NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) again[0][nt] = acc[nt];
+        if (any_not_finite<1, NT>(again)) {
+            multiply_unbiased<ACT, BITS, NT, 1>(again, A, M, N, K, wbase, sbase, g32, g32_recip, kw, kw_n, KB, lane);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[nt] = again[0][nt];
+        }
+    }
+
     // Combine the k-workers of each column group in fixed order (worker 0 + worker 1 + worker 2 ...).  Every
     // wave parks its sums in LDS and the block's threads share the NT * 64 result quads of every group, so that
     // each thread adds kw_n independent values (one wave adding all of them one after the other spent a
@@ -603,6 +743,327 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_skinny_kernel(
             v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3];
         }
         store_quad(v, bx * gp + gq, r >> 6, r & 63);
+    }
+}
+
+// ==========================================================================================
+// Mid-M streaming kernel (17 <= M <= 16 MT): still bound by the HBM read of the weights.
+//
+// The small-M kernel's structure with MT row tiles: block = GP column groups x KW k-workers, one block per compute
+// unit, weights and scales through a DEPTH-deep register ring, the KW partial results added through LDS.  Differences:
+//  - The activations of a super-block (16 MT rows x KW k-blocks) go global -> LDS directly (no registers: with MT = 2
+//    staging them through the ring spilled), NBUF - 1 iterations ahead into one of NBUF LDS tiles.  Their waits are
+//    explicit; the counter retires in order, and every wave leaves at most the loads of the last NBUF - 1 iterations'
+//    weights in flight at the barrier, whatever its own share of the activation loads was.
+//  - The weights keep their storage bias (MidOperand): the first MFMA of a scale group starts from -BIAS * rowsum,
+//    which MFMAs of the activations against a constant operand provide (one per row tile and k-step for all column tiles),
+//    instead of from zero with the bias removed by vector instructions afterwards: the fold is one fused
+//    multiply-add per element.
+// Against the tiled kernel with 32 rows per block: no split of K over the grid (no partial sums through memory, no
+// second kernel), and a barrier per KW k-blocks instead of one per k-block.  12288 x 36864, int4 g = 128, M = 32
+// (us): bf16 60 -> 49.5 (4.8 TB/s of weights), fp16 56 -> 49; M = 48: 94 -> 64.
+// LDS tile of k-worker kw, in 16-byte units: unit(row, kc) = row * KC + (kc ^ swz(row)): a wave-level direct load
+// fills whole rows, a fragment read (16 rows of one kc) touches 16 different bank groups.
+// ==========================================================================================
+// Operand of this kernel: (u - BIAS) * UNIT with the stored value u in place and -BIAS * UNIT as the start of the
+// accumulation (NEG, the constant 16-bit operand of the row-sum MFMAs).
+//   bf16: Dequant's biased operand (128 + u, or u), UNIT = 1
+//   fp16: the stored value alone in the low bits of the 16-bit lane, i.e. the subnormal u * 2^-24 (the matrix cores
+//         honour fp16 subnormals); the results are multiplied by 2^24 once at the end.  Products and sums are those of
+//         the integers, scaled by a power of two: exact as before, and with 7 (4 for bytes) vector instructions per
+//         eight weights instead of the 9 (8) that normal numbers without a bias take.
+template <int ACT, int BITS>
+struct MidOperand {
+    static constexpr float OFF = Dequant<ACT, BITS>::OFFSET;      // 128, 132 or 136: exact in bfloat16
+    static constexpr uint32_t NEG = OFF == 136.0f ? 0xc308u : (OFF == 132.0f ? 0xc304u : 0xc300u);
+    static constexpr float BACK = 1.0f;
+    static __device__ inline uint32_t init() { return Dequant<ACT, BITS>::init(); }
+    template <int T>
+    static __device__ inline u32x4 run(const u32x4& rec, uint32_t magic) {
+        return Dequant<ACT, BITS>::template run<T>(rec, magic);
+    }
+};
+template <int BITS>
+struct MidOperand<FQ_F16, BITS> {
+    static constexpr uint32_t NEG = BITS == 8 ? 0x8080u : (BITS == 4 ? 0x8008u : 0x8004u);
+    static constexpr float BACK = 16777216.0f;
+    static __device__ inline uint32_t init() { return 0u; }
+    template <int T>
+    static __device__ inline u32x4 run(const u32x4& rec, uint32_t) {
+        u32x4 r;
+        if constexpr (BITS == 8) {
+            const uint32_t w0 = rec[2 * T], w1 = rec[2 * T + 1];
+            r[0] = __builtin_amdgcn_perm(0u, w0, 0x0c010c00u);
+            r[1] = __builtin_amdgcn_perm(0u, w0, 0x0c030c02u);
+            r[2] = __builtin_amdgcn_perm(0u, w1, 0x0c010c00u);
+            r[3] = __builtin_amdgcn_perm(0u, w1, 0x0c030c02u);
+        } else {
+            constexpr uint32_t M = BITS == 4 ? 0x000f000fu : 0x00070007u;
+            const uint32_t w = code_word<BITS, T>(rec);
+            r[0] = w & M;
+            r[1] = (w >> 4) & M;
+            r[2] = (w >> 8) & M;
+            r[3] = (w >> 12) & M;
+        }
+        return r;
+    }
+};
+
+template <int ACT, int BITS, int NT, int MT, int DEPTH, int NBUF, int SR, int MAXW>
+__global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_kernel(
+    const uint16_t* __restrict__ A, const u32x4* __restrict__ codes, const uint16_t* __restrict__ scales,
+    uint16_t* __restrict__ C, float* __restrict__ partial, int M, int N, int K, uint32_t g32,
+    uint32_t g32_recip, int gp, int kw_n, int grid_splits) {
+    constexpr int KBLK = fq_kblk(BITS);
+    constexpr int STEPS = KBLK / FQ_KSTEP;
+    constexpr int GSTEPS = STEPS / SR;              // k-steps per scale row
+    constexpr int KC = KBLK / 8;                    // 16-byte activation units per row and k-block
+    constexpr int TILE = 16 * MT * KC;              // units of one k-worker's activation tile
+    constexpr int NI = TILE / 64;                   // wave-level direct loads of such a tile
+    constexpr int RB = fq_rec_bytes(BITS);
+    constexpr int NW = 2 * NT;                      // vector loads of one stage
+    typedef MidOperand<ACT, BITS> OP;
+    static_assert(STEPS % SR == 0 && (NBUF == 2 || NBUF == 3) && DEPTH >= 2 && (DEPTH - 1) * NW < 64, "");
+    constexpr int AHEAD = NBUF - 1;                 // iterations the activations are loaded ahead
+    typedef SkinnyStage<BITS, NT, SR, 0> Stage;
+    extern __shared__ u32x4 lds[];   // NBUF activation buffers [kw_n][TILE]; later the reduction
+
+    const int tid = threadIdx.x;
+    const int nthreads = blockDim.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int gi = wave / kw_n;
+    const int kw = wave - gi * kw_n;
+    const int ntiles = N / FQ_NTILE;
+    const int ngroups = (ntiles + NT - 1) / NT;
+    const int bgroups = (ngroups + gp - 1) / gp;      // blocks per grid split
+    const int bx = blockIdx.x % bgroups;
+    const int gsplit = blockIdx.x / bgroups;          // < grid_splits
+    const int ng = bx * gp + gi;
+    const bool gvalid = ng < ngroups;
+    const int KB = K / KBLK;
+    const int SB = (KB + kw_n - 1) / kw_n;            // super-blocks of kw_n k-blocks
+    const int n_it = gsplit < SB ? (SB - gsplit + grid_splits - 1) / grid_splits : 0;   // block-uniform
+    const int64_t kb_stride = (int64_t)ntiles * 64;   // records between consecutive k-blocks of a tile
+    const int ml = lane & 15, j = lane >> 4;
+    const uint32_t magic = OP::init();
+    const int abuf_units = kw_n * TILE;
+
+    // Wave-uniform bases (scalar registers) plus one 32-bit offset per lane.
+    const char* wbase[NT];
+    const uint16_t* sbase[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        const int tile = ng * NT + nt;
+        const int tc = gvalid && tile < ntiles ? tile : 0;
+        wbase[nt] = reinterpret_cast<const char*>(codes) + fq_rec(tc, 0, ntiles, 0) * RB;
+        sbase[nt] = scales + tc * FQ_NTILE;
+    }
+    const uint32_t lane_rec = (uint32_t)lane * RB;
+
+    // activations of iteration `it`: this wave's share (every gp-th load) of its k-worker's tile
+    auto swz = [](int row) { return KC == 16 ? (row & 15) : ((row >> 1) & 7); };
+    auto load_act = [&](int it) {
+        const int kb = (gsplit + it * grid_splits) * kw_n + kw;
+        const uint16_t* base = A + (int64_t)(kb < KB ? kb : KB - 1) * KBLK;   // past the end: never multiplied
+        const uint32_t lds_tile = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)(
+            lds + (it % NBUF) * abuf_units + kw * TILE);
+        for (int i = gi; i < NI; i += gp) {
+            const int row = i * (64 / KC) + lane / KC, pos = lane % KC;
+            const int rowc = row < M ? row : M - 1;                            // (their results are never stored)
+            const uint16_t* src = base + (uint32_t)rowc * (uint32_t)K + (uint32_t)((pos ^ swz(row)) * 8);
+            // (assembly on purpose: issued through the compiler's builtin these loads make its wait-count pass drain
+            // the whole memory queue at every later wait)
+            const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_tile + i * 1024);
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
+                         :
+                         : "s"(m0), "v"(src)
+                         : "memory", "m0");
+        }
+    };
+    auto load_stage = [&](Stage& sl, int it) {
+        int kb = (gsplit + it * grid_splits) * kw_n + kw;
+        kb = kb < KB ? kb : KB - 1;                      // tail super-block: idle workers re-read the last block
+        const int64_t kb_bytes = (int64_t)kb * kb_stride * RB;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            sl.wq[nt] = load_rec<BITS, true>(scalar_ptr(wbase[nt] + kb_bytes) + lane_rec);
+        if constexpr (SR == 1) {
+            const uint32_t step = (uint32_t)kb * STEPS;
+            const uint32_t row = g32 == 1 ? step : __umulhi(step, g32_recip);
+            const int64_t srow = (int64_t)row * N;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+                sl.sc[nt] = *reinterpret_cast<const FQ_GLOBAL u32x2*>(scalar_ptr(sbase[nt] + srow) + (uint32_t)j * 4u);
+        } else {
+            // the lane fetches the row of step (lane % STEPS) of the k-block
+            const uint32_t step = (uint32_t)kb * STEPS + (uint32_t)(lane & (STEPS - 1));
+            const uint32_t row = g32 == 1 ? step : __umulhi(step, g32_recip);
+            const int64_t srow = (int64_t)row * N;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) sl.sc[nt] = *reinterpret_cast<const u32x2*>(sbase[nt] + srow + (uint32_t)j * 4u);
+        }
+    };
+
+    // unit of this lane's fragment row for k-step t (row tile 0): this one with 4 t folded in by an exclusive or (the
+    // position inside the row is (4 t + j) ^ swz, and a row starts at a multiple of KC units)
+    const int a_rd0 = kw * TILE + ml * KC + (j ^ swz(ml));
+
+    f32x4 acc[MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    auto multiply = [&](const Stage& sl, int it) {
+        const int a_now = (it % NBUF) * abuf_units + a_rd0;
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < SR; ++r) {
+            u32x4 af[GSTEPS][MT];
+#pragma unroll
+            for (int u = 0; u < GSTEPS; ++u)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) af[u][mt] = lds[(a_now ^ (4 * (r * GSTEPS + u))) + mt * 16 * KC];
+            f32x4 start[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) start[mt] = zero;
+            const u32x4 neg = {OP::NEG * 0x10001u, OP::NEG * 0x10001u, OP::NEG * 0x10001u, OP::NEG * 0x10001u};
+#pragma unroll
+            for (int u = 0; u < GSTEPS; ++u)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) start[mt] = mfma16x16x32<ACT>(neg, af[u][mt], start[mt]);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                f32x4 p[MT];
+#pragma unroll
+                for (int u = 0; u < GSTEPS; ++u) {
+                    const int t = r * GSTEPS + u;
+                    u32x4 w;
+                    if (t == 0) w = OP::template run<0>(sl.wq[nt], magic);
+                    if (t == 1) w = OP::template run<1>(sl.wq[nt], magic);
+                    if (STEPS > 2 && t == 2) w = OP::template run<2 % STEPS>(sl.wq[nt], magic);
+                    if (STEPS > 2 && t == 3) w = OP::template run<3 % STEPS>(sl.wq[nt], magic);
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) p[mt] = mfma16x16x32<ACT>(w, af[u][mt], u == 0 ? start[mt] : p[mt]);
+                }
+                u32x2 sq = sl.sc[nt];
+                if constexpr (SR > 1) {
+                    // the lane of the quad that fetched the row of this scale row's first k-step
+                    const int t0 = r * GSTEPS;
+                    if (t0 == 0) sq = quad_bcast<0>(sl.sc[nt]);
+                    if (t0 == 1) sq = quad_bcast<1>(sl.sc[nt]);
+                    if (STEPS > 2 && t0 == 2) sq = quad_bcast<2 % STEPS>(sl.sc[nt]);
+                    if (STEPS > 2 && t0 == 3) sq = quad_bcast<3 % STEPS>(sl.sc[nt]);
+                }
+                const f32x4 s = scales4<ACT>(sq);
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[mt][nt][i] = __builtin_fmaf(s[i], p[mt][i], acc[mt][nt][i]);
+            }
+        }
+    };
+    // Iteration `it`.  On entry its activations and weights have landed; in flight: weights of it + 1 .. it + DEPTH - 1,
+    // activations up to it + AHEAD - 1.
+    auto iterate = [&](Stage& sl, int it, bool more) {
+        // (every register of the stage is named here, so that the compiler places its waits for them in front of the
+        // loads issued below: in its count, which does not know of the direct loads, a later wait would reach into them)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            asm volatile("" : "+v"(sl.wq[nt][0]), "+v"(sl.wq[nt][1]), "+v"(sl.wq[nt][2]), "+v"(sl.wq[nt][3]));
+            asm volatile("" : "+v"(sl.sc[nt][0]), "+v"(sl.sc[nt][1]));
+        }
+        if (it + AHEAD < n_it) load_act(it + AHEAD);     // into the tile read during it - 1
+        __builtin_amdgcn_sched_barrier(0);
+        if (gvalid && (gsplit + it * grid_splits) * kw_n + kw < KB) multiply(sl, it);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) {
+            load_stage(sl, it + DEPTH);
+            __builtin_amdgcn_sched_barrier(0);
+            // activations of it + 1 have landed: younger than they are AHEAD stages of weights (issued at the end of the
+            // iterations since) and this wave's share of the activations of it + 2 .. it + AHEAD, whose number differs
+            // between the waves and is left out of the count
+            wait_vmcnt<AHEAD * NW>();
+        } else {
+            wait_vmcnt<0>();
+        }
+        __syncthreads();
+    };
+
+    if (n_it > 0) {
+        Stage ring[DEPTH];
+        load_act(0);
+        load_stage(ring[0], 0);
+        if (AHEAD > 1 && 1 < n_it) load_act(1);
+#pragma unroll
+        for (int d = 1; d < DEPTH; ++d)
+            if (d < n_it) load_stage(ring[d], d);
+        __builtin_amdgcn_sched_barrier(0);
+        if (DEPTH <= n_it) wait_vmcnt<(DEPTH - 1) * NW>();     // (the loads younger than the activations of 0, at least)
+        else wait_vmcnt<0>();
+        __syncthreads();
+        int it = 0;
+        for (; it + 2 * DEPTH <= n_it; it += DEPTH) {
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) iterate(ring[d], it + d, true);
+        }
+        // drain: at most 2 * DEPTH - 1 iterations are left, the first min(DEPTH, left) already loaded
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d)
+            if (it + d < n_it) iterate(ring[d], it + d, it + d + DEPTH < n_it);
+#pragma unroll
+        for (int d = 0; d < DEPTH - 1; ++d)
+            if (it + d + DEPTH < n_it) iterate(ring[d], it + d + DEPTH, false);
+    }
+
+    if constexpr (OP::BACK != 1.0f) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = acc[mt][nt] * OP::BACK;
+    }
+    if (any_not_finite<MT, NT>(acc))
+        multiply_unbiased<ACT, BITS, NT, MT>(acc, A, M, N, K, wbase, sbase, g32, g32_recip, gsplit * kw_n + kw,
+                                             grid_splits * kw_n, KB, lane);
+    // the k-workers' sums of each column group, added by all threads of the block (as in the small-M kernel)
+    auto store_quad = [&](const f32x4& v, int group, int mt, int nt, int ln) {
+        const int mq = mt * 16 + (ln & 15), jq = ln >> 4;
+        const int tile = group * NT + nt;
+        if (mq >= M || group >= ngroups || tile >= ntiles) return;
+        const int64_t n = (int64_t)tile * FQ_NTILE + jq * 4;
+        if (grid_splits == 1) {
+            *reinterpret_cast<u32x2*>(C + (int64_t)mq * N + n) = pack4<ACT>(v);
+        } else {
+            *reinterpret_cast<f32x4*>(partial + ((int64_t)gsplit * M + mq) * N + n) = v;
+        }
+    };
+    if (kw_n == 1) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) store_quad(acc[mt][nt], ng, mt, nt, lane);
+        return;
+    }
+    constexpr int Q = MT * NT * 64;                // result quads of a column group
+    f32x4* red = reinterpret_cast<f32x4*>(lds);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) red[wave * Q + (mt * NT + nt) * 64 + lane] = acc[mt][nt];
+    __syncthreads();
+    for (int q = tid; q < gp * Q; q += nthreads) {
+        const int gq = q / Q;                      // column group of the block
+        const int r = q - gq * Q;
+        const f32x4* src = red + gq * kw_n * Q + r;
+        f32x4 v = src[0];
+#pragma unroll 4
+        for (int w = 1; w < kw_n; ++w) {
+            const f32x4 o = src[w * Q];
+            v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3];
+        }
+        const int tl = r >> 6;
+        store_quad(v, bx * gp + gq, tl / NT, tl % NT, r & 63);
     }
 }
 
@@ -885,13 +1346,6 @@ __global__ __launch_bounds__(THREADS) void fq_scale_exp_kernel(const uint32_t* _
     e = e < -120 ? -120 : (e > 120 ? 120 : e);
     out2[0] = ldexpf(1.0f, -e);
     out2[1] = ldexpf(1.0f, e);
-}
-
-// s_waitcnt vmcnt(N) only (the other counters left alone); gfx9 encoding: vmcnt in bits 3:0 and 15:14
-template <int N>
-__device__ inline void wait_vmcnt() {
-    static_assert(N >= 0 && N < 64, "");
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
 // KREC = k-blocks of the packed layout that make one k-block of this kernel (lane records per column tile

@@ -28,11 +28,11 @@ int fq_launch_mfma_rate_probe(const void* operands, void* sink, int iterations, 
 
 // product side
 struct fq_gemm_plan {
-    int kind;      // 0 = skinny (M <= 16), 1 = tiled
-    int mt;        // row tiles of 16 per block (tiled kernel)
+    int kind;      // 0 = skinny (M <= 16), 1 = tiled, 2 = mid-M streaming (17 <= M <= 48)
+    int mt;        // row tiles of 16 per block (tiled and mid-M kernel)
     int waves;     // waves per block
     int variant;   // small-M kernel: which compiled variant (NT, ring depth, register class)
-    int gp, kw;    // small-M kernel: column groups x k-workers per block
+    int gp, kw;    // small-M and mid-M kernel: column groups x k-workers per block
     int au;        // small-M kernel: activation units a lane stages per super-block (1, 2 or 4)
     int splits;    // split-K factor (>= 1)
     int kb_per_split;   // k-blocks per grid split (tiled) or per wave (small-M)

@@ -532,3 +532,55 @@ def test_grouped_gemm_few_rows_per_expert(dtype, bits, g, K, N, rows):
                     out=C[:int(offsets[-1])])
     assert_gemm_close(from_dev_act(C[:int(offsets[-1])], dtype), oracle.gemm_ref_grouped(A, offsets, qs, ss), dtype)
     assert bool((C[int(offsets[-1]):] == 7.0).all())
+
+
+@pytest.mark.parametrize("M", [17, 31, 32, 33, 48])
+@pytest.mark.parametrize("dtype,bits,g,K,N", [("f16", 4, 128, 128, 16), ("bf16", 4, 128, 640, 144), ("f16", 4, 64, 1664, 1040),
+                                              ("bf16", 4, 32, 3200, 208), ("bf16", 8, 0, 64, 80), ("f16", 8, 128, 2048, 656),
+                                              ("f16", 3, 0, 1152, 336), ("bf16", 3, 96, 768, 96), ("f16", 8, 32, 448, 48)])
+def test_gemm_mid_rows(dtype, bits, g, K, N, M):
+    """17 .. 48 rows: both row-tile counts at their edges, fewer k-blocks than k-workers, last super-blocks that are not
+    full, idle column groups, K split over the grid, and every number of scale rows per k-block."""
+    _say(f"gemm mid {dtype} int{bits} g={g} K={K} N={N} M={M}")
+    assert "mid-m" in _fq().gemm_describe(M, N, K, bits, g)
+    _gemm_case(M, K, N, dtype, bits, g, seed=8000 + M + K + N)
+
+
+@pytest.mark.parametrize("form", ["M=20", "M=40", "grouped"])
+@pytest.mark.parametrize("dtype,bits", [("f16", 4), ("f16", 8), ("f16", 3), ("bf16", 4), ("bf16", 8), ("bf16", 3)])
+def test_rows_with_infinities_nans_and_the_largest_magnitudes(dtype, bits, form):
+    """The kernels whose operands carry the storage bias remove it with row sums; a row whose sums are not finite must
+    still give what the product gives: infinities and NaNs in its own row only, and (bf16) finite results for
+    magnitudes at which the biased sums overflow."""
+    _say(f"non-finite rows {dtype} int{bits} {form}")
+    fq = _fq()
+    K, N, g = 768, 112, 128
+    rows = [16, 9] if form == "grouped" else [int(form[2:])]
+    M = sum(rows)
+    A = workloads.activations(M, K, dtype, 5).astype(np.float32)
+    A[1, 3] = np.inf
+    A[4, 700] = -np.inf
+    A[6, 100] = np.nan
+    A[M - 1, 0], A[M - 1, 767] = np.inf, -np.inf
+    if dtype == "bf16":
+        A[2] = workloads.round_to_bf16(A[2] * np.float32(1e36))
+    W = workloads.weights_gaussian(K, N, 6, outlier_prob=1e-3)
+    codes, scales, q_ref, s_ref = assert_quantizer_parity(W, bits, g)
+    Ad = to_dev_act(A.astype(np.float16) if dtype == "f16" else A, dtype)
+    if form == "grouped":
+        torch = torch_mod()
+        offsets = [0, rows[0], M]
+        C = from_dev_act(fq.gemm_grouped(Ad, offsets, torch.cat([codes] * 2), torch.cat([scales.reshape(-1)] * 2), bits, g, N),
+                         dtype)
+    else:
+        C = from_dev_act(fq.gemm(Ad, codes, scales, bits, g), dtype)
+    Wd = q_ref.astype(np.float64) * np.repeat(s_ref.astype(np.float64), g, axis=0)
+    with np.errstate(invalid="ignore"):
+        ref = A.astype(np.float64) @ Wd
+    for r in range(M):
+        want = ref[r]
+        assert np.array_equal(np.isnan(C[r]), np.isnan(want)), (r, C[r], want)
+        assert np.array_equal(C[r][np.isinf(want)], want[np.isinf(want)]), r
+        ok = np.isfinite(want)
+        if ok.any():
+            assert_gemm_close(C[r][ok], want[ok], dtype, f"row {r}")
