@@ -97,6 +97,16 @@ int launch_mid(const void* A, int64_t M, int64_t N, int64_t K, const void* codes
     return FQ_OK;
 }
 
+// rows whose units of 8 values fit four waves' registers take those, longer ones sixteen waves
+inline void launch_rows_to_f16(const void* A, int64_t M, int64_t K, uint16_t* A16, float* rowscale, hipStream_t stream) {
+    if (K <= 256 * ROW_UNITS * 8)
+        hipLaunchKernelGGL(fq_rows_to_f16_kernel<256>, dim3((unsigned)M), dim3(256), 0, stream, (const uint16_t*)A, (int)K,
+                           A16, rowscale);
+    else
+        hipLaunchKernelGGL(fq_rows_to_f16_kernel<1024>, dim3((unsigned)M), dim3(1024), 0, stream, (const uint16_t*)A, (int)K,
+                           A16, rowscale);
+}
+
 template <int ACT, int BITS>
 int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* codes, const void* scales,
                  int g, void* C, void* workspace, const fq_gemm_plan& plan, hipStream_t stream) {
@@ -177,8 +187,7 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
                 char* extra = (char*)workspace + fq_partial_bytes(plan, M, N);
                 uint16_t* A16 = (uint16_t*)extra;
                 float* rs = (float*)(extra + fq_a16_bytes(M, K));
-                hipLaunchKernelGGL(fq_rows_to_f16_kernel<256>, dim3((unsigned)M), dim3(256), 0, stream,
-                                   (const uint16_t*)A, (int)K, A16, rs);
+                launch_rows_to_f16(A, M, K, A16, rs, stream);
                 if (plan.waves == 8) FQ_MMA_LAUNCH_BIG(FQ_BF16_VIA_F16, A16, rs);
                 else FQ_MMA_LAUNCH_ACT(FQ_BF16_VIA_F16, A16, rs, 8, 4, 0);
                 launched = true;
@@ -196,8 +205,7 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
                                    (const uint16_t*)scales, count, parts);
                 hipLaunchKernelGGL(fq_scale_exp_kernel<256>, dim3(1), dim3(256), 0, stream, (const uint32_t*)parts,
                                    FQ_SCALE_PARTS, rs + M);
-                hipLaunchKernelGGL(fq_rows_to_f16_kernel<256>, dim3((unsigned)M), dim3(256), 0, stream,
-                                   (const uint16_t*)A, (int)K, A16, rs);
+                launch_rows_to_f16(A, M, K, A16, rs, stream);
                 if (plan.waves == 8) FQ_MMA_LAUNCH_BIG(FQ_BF16S_VIA_F16, A16, rs);
                 else FQ_MMA_LAUNCH_ACT(FQ_BF16S_VIA_F16, A16, rs, 8, 4, 0);
                 launched = true;

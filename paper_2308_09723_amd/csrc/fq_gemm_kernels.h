@@ -1259,26 +1259,35 @@ __global__ __launch_bounds__(256) void fq_reduce_tail_kernel(const float* __rest
 // magnitude is brought to 2^14 .. 2^15, an exact scaling);
 // A16[r, :] = A[r, :] * 2^-e rounded to binary16, rowscale[r] = e as a float (2^e itself need not be a
 // normal binary32 number; the product kernel applies it in two halves).
+// Rows of up to THREADS * ROW_UNITS units of 8 values are read once and kept in registers across the search for the
+// largest element (2048 x 12288: 25.5 -> 18.8 us); what lies beyond is read a second time.
+constexpr int ROW_UNITS = 8;
 template <int THREADS>   // (a template so that every translation unit may hold a copy)
 __global__ __launch_bounds__(THREADS) void fq_rows_to_f16_kernel(const uint16_t* __restrict__ A, int K,
                                                              uint16_t* __restrict__ A16,
                                                              float* __restrict__ rowscale) {
-    __shared__ uint32_t red[4];
+    __shared__ uint32_t red[THREADS / 64];
+    typedef uint16_t u16x2r __attribute__((ext_vector_type(2)));
     const int64_t r = blockIdx.x;
     const u32x4* src = reinterpret_cast<const u32x4*>(A + r * K);
     u32x4* dst = reinterpret_cast<u32x4*>(A16 + r * K);
     const int units = K / 8;
-    uint32_t m = 0;
-    static_assert(THREADS == 256, "four waves are reduced below");
-    for (int u = threadIdx.x; u < units; u += 256) {
-        const u32x4 v = src[u];
+    u32x4 v[ROW_UNITS];
+    u16x2r m2 = {0, 0};
+    auto largest = [&](const u32x4& x) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t a0 = v[i] & 0x7fffu, a1 = (v[i] >> 16) & 0x7fffu;
-            m = a0 > m ? a0 : m;
-            m = a1 > m ? a1 : m;
-        }
+        for (int i = 0; i < 4; ++i) m2 = __builtin_elementwise_max(m2, bitcast<u16x2r>(x[i] & 0x7fff7fffu));
+    };
+#pragma unroll
+    for (int i = 0; i < ROW_UNITS; ++i) {
+        const int u = threadIdx.x + i * THREADS;
+        v[i] = src[u < units ? u : units - 1];           // (past the end: the last unit again, never stored)
     }
+#pragma unroll
+    for (int i = 0; i < ROW_UNITS; ++i) largest(v[i]);
+#pragma unroll 1
+    for (int u = threadIdx.x + ROW_UNITS * THREADS; u < units; u += THREADS) largest(src[u]);
+    uint32_t m = m2[0] > m2[1] ? m2[0] : m2[1];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const uint32_t t = (uint32_t)__shfl_xor((int)m, o, 64);
@@ -1286,23 +1295,30 @@ __global__ __launch_bounds__(THREADS) void fq_rows_to_f16_kernel(const uint16_t*
     }
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
-    m = red[0];
 #pragma unroll
-    for (int i = 1; i < 4; ++i) m = red[i] > m ? red[i] : m;
+    for (int i = 0; i < THREADS / 64; ++i) m = red[i] > m ? red[i] : m;
     const int e = (int)(m >> 7) - 127 - 14;
     if (threadIdx.x == 0) rowscale[r] = (float)e;
-    for (int u = threadIdx.x; u < units; u += 256) {
-        const u32x4 v = src[u];
+    auto rewrite = [&](const u32x4& x) -> u32x4 {
         u32x4 o;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float f0 = ldexpf(bitcast<float>(v[i] << 16), -e);
-            const float f1 = ldexpf(bitcast<float>(v[i] & 0xffff0000u), -e);
+            const float f0 = ldexpf(bitcast<float>(x[i] << 16), -e);
+            const float f1 = ldexpf(bitcast<float>(x[i] & 0xffff0000u), -e);
             const f16x2 h = {(_Float16)f0, (_Float16)f1};
             o[i] = bitcast<uint32_t>(h);
         }
-        dst[u] = o;
+        return o;
+    };
+#pragma unroll
+    for (int i = 0; i < ROW_UNITS; ++i) {
+        const int u = threadIdx.x + i * THREADS;
+        // (one unit after the other: all of them at once would take four times the registers)
+        asm volatile("" : "+v"(v[i][0]), "+v"(v[i][1]), "+v"(v[i][2]), "+v"(v[i][3]));
+        if (u < units) dst[u] = rewrite(v[i]);
     }
+#pragma unroll 1
+    for (int u = threadIdx.x + ROW_UNITS * THREADS; u < units; u += THREADS) dst[u] = rewrite(src[u]);
 }
 
 // Largest scale of a bfloat16 scale matrix (FQ_BF16S_VIA_F16), in two steps without atomics: every block

@@ -191,28 +191,30 @@ __device__ inline float act_to_float(uint16_t b) {
     else return __uint_as_float((uint32_t)b << 16);
 }
 
+// 2 max / 255 = max / 127.5 (the same real number; this form cannot overflow for bfloat16 inputs near 2^128)
+__device__ inline float w8_alpha(float amax) {
+    float al = __fdiv_rn(amax, 0.5f * ALEVELS);
+    if (__builtin_fmaf(0.5f * ALEVELS, al, -amax) < 0.0f) al = __uint_as_float(__float_as_uint(al) + 1u);   // next value up
+    return al;
+}
+
+// the code of one value by the division itself, as a byte
+__device__ inline uint32_t w8_act_code(float a, float al) {
+    int q = 0;
+    if (al != 0.0f) q = (int)fminf(fmaxf(rintf(__fdiv_rn(a, al)), -127.0f), 127.0f);
+    return (uint32_t)q & 0xffu;
+}
+
+// Rows of any length and alignment: one value per lane and memory instruction, the row read twice.
 template <int ACT>
 __global__ __launch_bounds__(256) void w8_act_quant_kernel(const uint16_t* __restrict__ A, int64_t K,
                                                             int8_t* __restrict__ Aq, float* __restrict__ alpha) {
     __shared__ uint32_t red[4];
     const int64_t r = blockIdx.x;
     const uint16_t* src = A + r * K;
-    // rows of whole 16-byte units at 16-byte aligned addresses are read eight values and written eight bytes per
-    // lane (with one value per lane the kernel is bound by the number of its memory instructions)
-    const bool wide = (K & 7) == 0 && ((uintptr_t)A & 15) == 0 && ((uintptr_t)Aq & 7) == 0;
-    const int64_t units = wide ? K >> 3 : 0;
     uint32_t m = 0;
-    for (int64_t u = threadIdx.x; u < units; u += 256) {
-        const u32x4 v = reinterpret_cast<const u32x4*>(src)[u];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t a0 = v[i] & 0x7fffu, a1 = (v[i] >> 16) & 0x7fffu;   // magnitudes of one format order
-            m = a0 > m ? a0 : m;                                                // like their bit patterns
-            m = a1 > m ? a1 : m;
-        }
-    }
-    for (int64_t k = units * 8 + threadIdx.x; k < K; k += 256) {
-        const uint32_t v = src[k] & 0x7fffu;
+    for (int64_t k = threadIdx.x; k < K; k += 256) {
+        const uint32_t v = src[k] & 0x7fffu;             // magnitudes of one format order like their bit patterns
         m = v > m ? v : m;
     }
 #pragma unroll
@@ -225,27 +227,106 @@ __global__ __launch_bounds__(256) void w8_act_quant_kernel(const uint16_t* __res
     m = red[0];
 #pragma unroll
     for (int i = 1; i < 4; ++i) m = red[i] > m ? red[i] : m;
-    // 2 max / 255 = max / 127.5 (the same real number; this form cannot overflow for bfloat16 inputs near 2^128)
-    const float amax = act_to_float<ACT>((uint16_t)m);
-    float al = __fdiv_rn(amax, 0.5f * ALEVELS);
-    if (__builtin_fmaf(0.5f * ALEVELS, al, -amax) < 0.0f) al = __uint_as_float(__float_as_uint(al) + 1u);   // next value up
+    const float al = w8_alpha(act_to_float<ACT>((uint16_t)m));
     if (threadIdx.x == 0) alpha[r] = al;
     int8_t* dst = Aq + r * K;
-    auto code = [&](uint16_t bits) -> uint32_t {
-        int q = 0;
-        if (al != 0.0f) q = (int)fminf(fmaxf(rintf(__fdiv_rn(act_to_float<ACT>(bits), al)), -127.0f), 127.0f);
-        return (uint32_t)q & 0xffu;
-    };
-    for (int64_t u = threadIdx.x; u < units; u += 256) {
-        const u32x4 v = reinterpret_cast<const u32x4*>(src)[u];
-        u32x2 o;
+    for (int64_t k = threadIdx.x; k < K; k += 256) dst[k] = (int8_t)w8_act_code(act_to_float<ACT>(src[k]), al);
+}
+
+// Rows of whole 16-byte units at aligned addresses, short enough for the block's registers (8 units of 8 values per
+// thread): read once, eight values per load, kept in registers across the search for the largest one.
+// The quotient A / alpha must be the correctly rounded binary32 one (it is rounded a second time, to an integer): with
+// rs = 1 / alpha rounded to nearest, two steps x + fma(-x, alpha, A) * rs from x0 = A * rs give it (Markstein's theorem:
+// the second one starts within one unit in the last place), wherever residuals do not underflow and rs is finite; rows
+// with alpha outside 2^-90 .. 2^100 take the division.  Checked on the host against the division
+// (tests/encode_identity_check.c).  Then clamp, round by adding 1.5 * 2^23, keep the low byte.  Bound by memory:
+// 2048 x 12288 26 -> 16 us; eight rows 6.4 -> 4.9 us (latency: 1024 threads per row).
+constexpr int W8_ROW_UNITS = 8;
+template <int ACT, int THREADS>
+__global__ __launch_bounds__(THREADS) void w8_act_quant_row_kernel(const uint16_t* __restrict__ A, int units,
+                                                                    int8_t* __restrict__ Aq, float* __restrict__ alpha) {
+    __shared__ uint32_t red[THREADS / 64];
+    const int64_t r = blockIdx.x;
+    const u32x4* src = reinterpret_cast<const u32x4*>(A) + r * units;
+    u32x4 v[W8_ROW_UNITS];
+    u16x2_t m2 = {0, 0};
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-            o[h] = code((uint16_t)v[2 * h]) | (code((uint16_t)(v[2 * h] >> 16)) << 8) |
-                   (code((uint16_t)v[2 * h + 1]) << 16) | (code((uint16_t)(v[2 * h + 1] >> 16)) << 24);
-        reinterpret_cast<u32x2*>(dst)[u] = o;
+    for (int i = 0; i < W8_ROW_UNITS; ++i) {
+        const int u = threadIdx.x + i * THREADS;
+        v[i] = src[u < units ? u : units - 1];           // (past the end: the last unit again, never stored)
     }
-    for (int64_t k = units * 8 + threadIdx.x; k < K; k += 256) dst[k] = (int8_t)code(src[k]);
+#pragma unroll
+    for (int i = 0; i < W8_ROW_UNITS; ++i)
+#pragma unroll
+        for (int d = 0; d < 4; ++d)                      // magnitudes of one format order like their bit patterns
+            m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2_t, v[i][d] & 0x7fff7fffu));
+    uint32_t m = m2[0] > m2[1] ? m2[0] : m2[1];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const uint32_t t = (uint32_t)__shfl_xor((int)m, o, 64);
+        m = t > m ? t : m;
+    }
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < THREADS / 64; ++i) m = red[i] > m ? red[i] : m;
+    const float al = w8_alpha(act_to_float<ACT>((uint16_t)m));
+    if (threadIdx.x == 0) alpha[r] = al;
+    u32x2* dst = reinterpret_cast<u32x2*>(Aq) + r * units;
+    if (al >= 0x1p-90f && al <= 0x1p100f) {
+        const float rs = __fdiv_rn(1.0f, al);
+        auto code = [&](uint16_t bits) -> uint32_t {
+            const float a = act_to_float<ACT>(bits);
+            float x = a * rs;
+            x = __builtin_fmaf(__builtin_fmaf(-x, al, a), rs, x);
+            x = __builtin_fmaf(__builtin_fmaf(-x, al, a), rs, x);
+            return __float_as_uint(__builtin_amdgcn_fmed3f(x, -127.0f, 127.0f) + FQ_ENCODE_MAGIC);
+        };
+#pragma unroll
+        for (int i = 0; i < W8_ROW_UNITS; ++i) {
+            const int u = threadIdx.x + i * THREADS;
+            // (one unit after the other: all of them at once would take four times the registers)
+            asm volatile("" : "+v"(v[i][0]), "+v"(v[i][1]), "+v"(v[i][2]), "+v"(v[i][3]));
+            if (u >= units) continue;
+            u32x2 o;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                o[h] = fq_gather_bytes(code((uint16_t)v[i][2 * h]), code((uint16_t)(v[i][2 * h] >> 16)),
+                                       code((uint16_t)v[i][2 * h + 1]), code((uint16_t)(v[i][2 * h + 1] >> 16)));
+            dst[u] = o;
+        }
+    } else {
+#pragma unroll 1
+        for (int u = threadIdx.x; u < units; u += THREADS) {
+            const u32x4 w = src[u];
+            u32x2 o;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                uint32_t c[4];
+#pragma unroll
+                for (int d = 0; d < 4; ++d)
+                    c[d] = w8_act_code(act_to_float<ACT>((uint16_t)(w[2 * h + (d >> 1)] >> (16 * (d & 1)))), al);
+                o[h] = c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24);
+            }
+            dst[u] = o;
+        }
+    }
+}
+
+template <int ACT>
+void w8_launch_act_quant(const uint16_t* A, int64_t M, int64_t K, int8_t* Aq, float* alpha, hipStream_t stream) {
+    const dim3 grid((unsigned)M);
+    const bool wide = (K & 7) == 0 && ((uintptr_t)A & 15) == 0 && ((uintptr_t)Aq & 7) == 0;
+    const int64_t units = K >> 3;
+    // few rows: as many threads per row as it has work for (one block per compute unit, latency counts); many rows:
+    // four waves per block, several blocks per compute unit
+    const bool narrow = units <= 256 * W8_ROW_UNITS && (M > 512 || units <= 256);
+    if (wide && narrow)
+        hipLaunchKernelGGL((w8_act_quant_row_kernel<ACT, 256>), grid, dim3(256), 0, stream, A, (int)units, Aq, alpha);
+    else if (wide && units <= 1024 * W8_ROW_UNITS)
+        hipLaunchKernelGGL((w8_act_quant_row_kernel<ACT, 1024>), grid, dim3(1024), 0, stream, A, (int)units, Aq, alpha);
+    else
+        hipLaunchKernelGGL(w8_act_quant_kernel<ACT>, grid, dim3(256), 0, stream, A, K, Aq, alpha);
 }
 
 // ------------------------------------------------------------------------------------------------------
@@ -972,12 +1053,8 @@ int fq_quantize_act_i8(const void* A, int act_dtype, int64_t M, int64_t K, int8_
     if (M == 0) return FQ_OK;
     if (!A || !Aq || !alpha) return FQ_ERR_INVALID_ARG;
     if (M > (int64_t)1 << 24 || K > (int64_t)1 << 24) return FQ_ERR_UNSUPPORTED;
-    if (act_dtype == FQ_F16)
-        hipLaunchKernelGGL(w8_act_quant_kernel<FQ_F16>, dim3((unsigned)M), dim3(256), 0, (hipStream_t)stream,
-                           (const uint16_t*)A, K, Aq, alpha);
-    else
-        hipLaunchKernelGGL(w8_act_quant_kernel<FQ_BF16>, dim3((unsigned)M), dim3(256), 0, (hipStream_t)stream,
-                           (const uint16_t*)A, K, Aq, alpha);
+    if (act_dtype == FQ_F16) w8_launch_act_quant<FQ_F16>((const uint16_t*)A, M, K, Aq, alpha, (hipStream_t)stream);
+    else w8_launch_act_quant<FQ_BF16>((const uint16_t*)A, M, K, Aq, alpha, (hipStream_t)stream);
     return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_HIP;
 }
 

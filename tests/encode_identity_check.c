@@ -100,5 +100,37 @@ int main(int argc, char** argv) {
         printf("integer path: %llu pairs, %llu exact ties, %llu mismatches\n", pairs, ties, bad);
         if (bad) ++failed;
     }
+    /* the integer path's activations: a / alpha, any binary32 alpha between 2^-90 and 2^100, two corrections: the
+     * correctly rounded binary32 quotient itself */
+    if (argc > 2) {
+        unsigned long long pairs = 0, bad = 0;
+        uint64_t x = 88172645463325252ull;
+        for (long i = 0; i < 60000000L; ++i) {
+            x ^= x << 13; x ^= x >> 7; x ^= x << 17;
+            const uint32_t mant = (uint32_t)x & 0x7fffffu;
+            /* alpha close to powers of two and to the next ones up more often than by chance */
+            const uint32_t am = (i & 7) == 0 ? (mant & 7u) : (i & 7) == 1 ? 0x7fffffu - (mant & 7u) : mant;
+            const uint32_t ae = 37u + (uint32_t)(x >> 24) % 190u;
+            uint32_t ab = (ae << 23) | am, wb;
+            /* numerators with 8 or 11 significant bits, |a| <= 127.5 alpha */
+            const uint32_t wm = (i & 8) ? ((uint32_t)(x >> 40) & 0x7fu) << 16 : ((uint32_t)(x >> 40) & 0x3ffu) << 13;
+            wb = ((ae + 6u - (uint32_t)(x >> 52) % 12u) << 23) | wm;
+            float al, w;
+            memcpy(&al, &ab, 4);
+            memcpy(&w, &wb, 4);
+            volatile float rs_v = 1.0f / al, q_v = w / al, x0_v = w * rs_v;
+            const float rs = rs_v;
+            float t = x0_v;
+            t = fmaf(fmaf(-t, al, w), rs, t);
+            t = fmaf(fmaf(-t, al, w), rs, t);
+            ++pairs;
+            if (t != q_v) {
+                if (bad < 5) printf("  mismatch: alpha %a a %a: %a vs %a\n", al, w, q_v, t);
+                ++bad;
+            }
+        }
+        printf("activations: %llu quotients, %llu differ\n", pairs, bad);
+        if (bad) ++failed;
+    }
     return failed;
 }

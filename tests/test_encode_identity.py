@@ -40,3 +40,4 @@ def test_quotient_by_the_integer_path_scales_and_rounding_by_addition(tmp_path):
     words = out.stdout.split()
     pairs, ties, bad = (int(words[words.index(k) - 1]) for k in ("pairs,", "exact", "mismatches"))
     assert pairs > 50_000_000 and ties > 1000 and bad == 0, out.stdout
+    assert "60000000 quotients, 0 differ" in out.stdout, out.stdout

@@ -223,3 +223,17 @@ def test_weight_quantiser_panels_and_long_groups(K, N, g):
     W[:, 3] = 0
     W[K // 2, 5] = 65504.0
     _quantize_weights(W, g)
+
+
+@pytest.mark.parametrize("M,K", [(600, 2056), (513, 16384), (5, 2048), (5, 2056), (3, 65536), (2, 65544), (520, 16392)])
+def test_activation_quantiser_row_kernels(M, K):
+    """The row kernels (four waves for many rows or short ones, sixteen otherwise) at the edges of what their registers
+    hold, and beyond; rows whose alpha lies outside the range of the reciprocal (bf16: 1e-36, 3e38), zero rows."""
+    for dtype in ("f16", "bf16"):
+        A = workloads.activations(M, K, dtype, 900 + K).astype(np.float32)
+        A[0] *= np.float32(1e-36 if dtype == "bf16" else 2.0 ** -14)
+        A[1] *= np.float32(5e37 if dtype == "bf16" else 8000.0)
+        if M > 2:
+            A[2] = 0
+        A = A.astype(np.float16) if dtype == "f16" else workloads.round_to_bf16(A)
+        _quantize_acts(A, dtype)
