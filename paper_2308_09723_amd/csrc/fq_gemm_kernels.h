@@ -348,9 +348,9 @@ __device__ inline u32x2 quad_bcast(const u32x2& v) {
     return r;
 }
 
-// true (in every lane) when some lane of the wave holds an infinity or a NaN among its sums
+// true (in every lane) when some lane of the wave whose sums count holds an infinity or a NaN among them
 template <int MT, int NT>
-__device__ inline bool any_not_finite(const f32x4 (&acc)[MT][NT]) {
+__device__ inline bool any_not_finite(const f32x4 (&acc)[MT][NT], bool counts) {
     float t = 0.0f;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
@@ -358,7 +358,7 @@ __device__ inline bool any_not_finite(const f32x4 (&acc)[MT][NT]) {
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
             for (int i = 0; i < 4; ++i) t = __builtin_fmaf(acc[mt][nt][i], 0.0f, t);   // NaN from then on
-    return __builtin_amdgcn_ballot_w64(t != t) != 0;
+    return __builtin_amdgcn_ballot_w64(t != t && counts) != 0;
 }
 
 // acc[nt] += (this wave's k-block of the stage) x (activation fragments af[0..STEPS)).
@@ -700,7 +700,8 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_skinny_kernel(
         f32x4 again[1][NT];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) again[0][nt] = acc[nt];
-        if (any_not_finite<1, NT>(again)) {
+        // (not the lanes of rows past M: nothing is staged for them, they multiply what the LDS held before)
+        if (any_not_finite<1, NT>(again, m < M)) {
             multiply_unbiased<ACT, BITS, NT, 1>(again, A, M, N, K, wbase, sbase, g32, g32_recip, kw, kw_n, KB, lane);
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) acc[nt] = again[0][nt];
@@ -1023,7 +1024,7 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_kernel(
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = acc[mt][nt] * OP::BACK;
     }
-    if (any_not_finite<MT, NT>(acc))
+    if (any_not_finite<MT, NT>(acc, true))
         multiply_unbiased<ACT, BITS, NT, MT>(acc, A, M, N, K, wbase, sbase, g32, g32_recip, gsplit * kw_n + kw,
                                              grid_splits * kw_n, KB, lane);
     // the k-workers' sums of each column group, added by all threads of the block (as in the small-M kernel)
