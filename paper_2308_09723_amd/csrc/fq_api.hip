@@ -302,14 +302,26 @@ int fq_gemm_describe(int64_t M, int64_t N, int64_t K, int bits, int group_size, 
         return FQ_OK;
     }
     const fq_gemm_plan p = fq_plan_gemm(M, N, K, bits, g);
-    if (p.kind == 0)
+    if (p.kind == 0) {
         snprintf(buf, buf_bytes, "small-m variant=%d gp=%d kw=%d au=%d waves=%d splits=%d", p.variant, p.gp,
                  p.kw, p.au, p.waves, p.splits);
-    else if (p.kind == 2)
-        snprintf(buf, buf_bytes, "mid-m mt=%d gp=%d kw=%d waves=%d splits=%d", p.mt, p.gp, p.kw, p.waves, p.splits);
-    else
-        snprintf(buf, buf_bytes, "tiled mt=%d waves=%d splits=%d kb_per_split=%d tail=%dx%d", p.mt, p.waves, p.splits,
-                 p.kb_per_split, p.tail_tiles, p.tail_tiles > 0 ? p.tail_splits : 1);
+        return FQ_OK;
+    }
+    // One form for all products of more than 16 rows.  mt and waves are the class of the block shape (32, 64 or 128
+    // rows, 4 or 8 waves); a shape that is not its class's own follows behind it.
+    int kbs = p.kb_per_split;
+    if (p.kind == 2) {
+        const int KB = (int)(K / fq_kblk(bits));
+        kbs = (KB + p.splits - 1) / p.splits;
+    }
+    const int n = snprintf(buf, buf_bytes, "tiled mt=%d waves=%d splits=%d kb_per_split=%d tail=%dx%d",
+                           p.mt <= 2 ? 2 : (p.mt <= 4 ? 4 : 8), p.kind == 2 ? 8 : p.waves, p.splits, kbs, p.tail_tiles,
+                           p.tail_tiles > 0 ? p.tail_splits : 1);
+    if (n < 0 || (size_t)n >= buf_bytes) return FQ_OK;
+    if (p.kind == 2)
+        snprintf(buf + n, buf_bytes - n, " mid-m rows=%d gp=%d kw=%d waves=%d", 16 * p.mt, p.gp, p.kw, p.waves);
+    else if (fq_flexible(p))
+        snprintf(buf + n, buf_bytes - n, " rows=%d cols=%d", 16 * p.mt, p.waves * p.nt * FQ_NTILE);
     return FQ_OK;
 }
 

@@ -99,6 +99,72 @@ static void fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int nc
     }
 }
 
+// Tiled kernel, shapes between the classes of 64 and 128 rows: 80 .. 128 rows x 256 columns (two column tiles per wave)
+// and 80 rows x 384.  128 x 384 blocks leave the chip partly idle where the output has few of them (200 rows x 28656
+// columns: 150 blocks of which the second 75 are 44 % padding; split 3 ways along K they fill 1.8 rounds and move 70 MB
+// of partial sums), 112 x 256 makes it 224 blocks without padding or a split.  3- and 4-bit codes with one scale row
+// per k-block run post-scaled here (the second accumulator set of two column tiles fits the registers up to 112 rows).
+// `u` = microseconds per k-block of a block, fitted like fq_plan_gemm's to sweeps of (shape, split) over five matrices
+// (8192 x 28656, 12288 x 36864, 12288^2, 4096 x 16384, 8192^2) at sixteen M from 72 to 1000: rms error 5 % (7 % for
+// 8-bit codes).  Because the model of the other shapes is off by 10 %, these have to win by that much (15 % for 8-bit
+// codes with k-blocks of 64 rows), and by the rewrite of bfloat16 rows (3 us, see fq_via_f16) where the shape they
+// replace does without: over the 400 records of the sweeps 1.13x faster than the shapes below on average (1.16x if
+// every choice were the best), one choice 2 % slower than before.  fp16 int4, us: 8192 x 28656 g = 64 M = 200
+// 130 -> 103, M = 160 104 -> 80; 12288^2 M = 160 75 -> 57; 4096 x 16384 M = 384 71 -> 48.
+// Not below 65 rows (the lower classes measure the same), nor above 1024 (1408 x 15456 at M = 1847: 102 -> 109), nor for matrices narrower than 8192 columns, where bfloat16
+// products do not take the fp16 matrix path.  Two scale rows: the 32-row shape stays where it is chosen, because it is
+// the one that multiplies bfloat16 activations post-scaled (unrounded weights) and these would not.  Above 256 rows a
+// plan whose last round is split along K stays: it was the faster one in 26 of 37 such records (up to 1.27x).
+static void fq_plan_flexible(int64_t M, int64_t N, int64_t K, int bits, int g, int ncu, double best, fq_gemm_plan* p) {
+    static const struct { int mt, nt; } shapes[5] = {{5, 2}, {6, 2}, {7, 2}, {8, 2}, {5, 3}};
+    static const double consts[5][5] = {
+        {1.10, 1.22, 1.40, 1.53, 1.53},     // 3- and 4-bit, one scale row per k-block (post-scaled)
+        {1.16, 1.265, 1.43, 1.54, 1.585},   // two scale rows
+        {1.525, 1.60, 1.73, 1.84, 2.36},    // four
+        {1.19, 1.31, 1.46, 1.57, 1.67},     // 8-bit, k-blocks of 128 rows
+        {0.62, 0.74, 0.75, 0.85, 0.86}};    // 8-bit, k-blocks of 64 rows
+    if (M <= 64 || M > 1024 || N < 8192) return;
+    const int kblk = fq_mma_kblk(bits, 8, 8, K, g);
+    const int sr = g % kblk == 0 ? 1 : (kblk % g == 0 ? kblk / g : kblk / 32);
+    if (bits != 8 && sr == 2 && p->mt == 2) return;
+    if (M > 256 && p->tail_tiles > 0) return;
+    const double* u = consts[bits == 8 ? (kblk == 128 ? 3 : 4) : (sr == 1 ? 0 : (sr == 2 ? 1 : 2))];
+    const int KB = (int)(K / kblk);
+    const int ntiles = (int)(N / FQ_NTILE);
+    const int split_opts[5] = {1, 2, 3, 4, 6};
+    // what fq_gemm_noalloc's scratch held for the former shape it has to hold for the new one
+    const size_t rewrite = fq_a16_bytes(M, K) + fq_rowscale_bytes(M);
+    const size_t scratch = FQ_NOALLOC_SCRATCH_BYTES;
+    const size_t was_f16 = fq_partial_bytes(*p, M, N), was_bf16 = was_f16 + (p->mt == 8 ? rewrite : 0);
+    const size_t most_f16 = was_f16 > scratch ? was_f16 : scratch, most_bf16 = was_bf16 > scratch ? was_bf16 : scratch;
+    best = 0.90 * (p->mt < 8 ? best - 3.0 : best);
+    if (bits == 8 && kblk == 64) best *= 0.95;
+    for (int v = 0; v < 5; ++v) {
+        const int bm = shapes[v].mt * 16;
+        const int64_t blocks = ((ntiles + 8 * shapes[v].nt - 1) / (8 * shapes[v].nt)) * ((M + bm - 1) / bm);
+        for (int si = 0; si < 5; ++si) {
+            if (split_opts[si] > KB) break;
+            const int kbs = (KB + split_opts[si] - 1) / split_opts[si];
+            const int splits = (KB + kbs - 1) / kbs;
+            const size_t partial = splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(float) : 0;
+            if (partial > most_f16 || partial + rewrite > most_bf16) continue;
+            double t = (double)((blocks * splits + ncu - 1) / ncu) * kbs * u[v] + 1.3;
+            if (splits > 1) t += 2.0 * splits * (double)M * (double)N * 4.0 / 5e6 + 5.0;
+            if (t < best - 1e-9) {
+                best = t;
+                p->mt = shapes[v].mt;
+                p->nt = shapes[v].nt;
+                p->waves = 8;
+                p->splits = splits;
+                p->kb_per_split = kbs;
+                p->tail_tiles = 0;
+                p->tail_splits = 1;
+                p->tail_kbs = 0;
+            }
+        }
+    }
+}
+
 fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g) {
     fq_gemm_plan p = {};
     const int ncu = fq_cu_count();
@@ -194,6 +260,7 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g) {
         const double* cs = consts[bits == 8 ? 3 : (sr4 == 1 ? 0 : (sr4 == 2 ? 1 : 2))];
         const int split_opts[6] = {1, 2, 3, 4, 6, 8};
         double best = 1e30;
+        p.nt = MMA_NT;
         p.tail_tiles = 0;
         p.tail_splits = 1;
         p.tail_kbs = 0;
@@ -279,18 +346,11 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g) {
                 }
             }
         }
+        fq_plan_flexible(M, N, K, bits, g, ncu, best, &p);
     }
     return p;
 }
 
-// Block shape for the experts of the small-M kernel: the shape with the least
-//   (blocks / slots + 0.7) * (iterations * 1.5 us + ramp)
-// i.e. the rounds of blocks, with an average partly filled one, times the time of a block: 12 waves stream 36 KiB per
-// iteration, and a block's start and end cost 2.5 us (5 with the sum over k-workers).  Not rounded up to whole rounds:
-// the other row classes of the call hold an unknown part of the compute units.  Against sweeps of 64 experts of 16384 x
-// 4096 and 4096 x 16384 with 96 rows the model is within 10 %: e.g. 3 x 4 waves 224 us predicted / 239 measured, 12 x 1
-// 336 / 337 on the former, 12 x 1 224 / 222, 4 x 3 253 / 248 on the latter.  Blocks have 12 or 4 waves: two blocks of
-// six do not fit a compute unit's four SIMDs (310 us where 12 x 1 takes 222).
 bool fq_split_32_rows(const int32_t* offsets, int E) {
     int n16 = 0, n32 = 0;
     for (int e = 0; e < E; ++e) {
@@ -302,6 +362,14 @@ bool fq_split_32_rows(const int32_t* offsets, int E) {
     return n32 > 0 && 8 * n32 <= n16;
 }
 
+// Block shape for the experts of the small-M kernel: the shape with the least
+//   (blocks / slots + 0.7) * (iterations * 1.5 us + ramp)
+// i.e. the rounds of blocks, with an average partly filled one, times the time of a block: 12 waves stream 36 KiB per
+// iteration, and a block's start and end cost 2.5 us (5 with the sum over k-workers).  Not rounded up to whole rounds:
+// the other row classes of the call hold an unknown part of the compute units.  Against sweeps of 64 experts of 16384 x
+// 4096 and 4096 x 16384 with 96 rows the model is within 10 %: e.g. 3 x 4 waves 224 us predicted / 239 measured, 12 x 1
+// 336 / 337 on the former, 12 x 1 224 / 222, 4 x 3 253 / 248 on the latter.  Blocks have 12 or 4 waves: two blocks of
+// six do not fit a compute unit's four SIMDs (310 us where 12 x 1 takes 222).
 fq_small_shape fq_plan_grouped_small(int count, int units, int ngroups, int KB) {
     static const fq_small_shape shapes[7] = {{12, 1}, {6, 2}, {4, 3}, {3, 4}, {2, 6}, {4, 1}, {2, 2}};
     fq_small_shape best = {12, 1};

@@ -98,13 +98,15 @@ int launch_mid(const void* A, int64_t M, int64_t N, int64_t K, const void* codes
 }
 
 // rows whose units of 8 values fit four waves' registers take those, longer ones sixteen waves
-inline void launch_rows_to_f16(const void* A, int64_t M, int64_t K, uint16_t* A16, float* rowscale, hipStream_t stream) {
-    if (K <= 256 * ROW_UNITS * 8)
-        hipLaunchKernelGGL(fq_rows_to_f16_kernel<256>, dim3((unsigned)M), dim3(256), 0, stream, (const uint16_t*)A, (int)K,
-                           A16, rowscale);
-    else
-        hipLaunchKernelGGL(fq_rows_to_f16_kernel<1024>, dim3((unsigned)M), dim3(1024), 0, stream, (const uint16_t*)A, (int)K,
-                           A16, rowscale);
+// SCALES: the `count` bfloat16 scales are searched for their largest in the same launch
+template <bool SCALES>
+inline void launch_rows_to_f16(const void* A, int64_t M, int64_t K, uint16_t* A16, float* rowscale, const void* scales,
+                               int64_t count, hipStream_t stream) {
+    const bool small = K <= 256 * ROW_UNITS * 8;
+    auto kern = small ? fq_rows_to_f16_kernel<256, SCALES> : fq_rows_to_f16_kernel<1024, SCALES>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(M + (SCALES ? FQ_SCALE_PARTS : 0))), dim3(small ? 256 : 1024), 0, stream,
+                       (const uint16_t*)A, (int)K, A16, rowscale, (const uint16_t*)scales, count / 8,
+                       (uint32_t*)(rowscale + M + 2));
 }
 
 template <int ACT, int BITS>
@@ -129,26 +131,30 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
         if (st != FQ_OK) return st;
     } else {
         // rows of K per k-block of this block shape (two layout blocks at a time for 8-bit codes in the
-        // 128-row, 8-wave shape), and the scale rows such a k-block spans: 1, kblk / g, or one per 32-row step
+        // 8-wave shapes of 80 rows and more), and the scale rows such a k-block spans: 1, kblk / g, or one per 32-row step
         const int kblk = fq_mma_kblk(BITS, plan.mt, plan.waves, K, g);
         const bool wide = kblk != fq_kblk(BITS);
         const int sr = (g % kblk) == 0 ? 1 : ((kblk % g) == 0 ? kblk / g : kblk / 32);
         const int bm = plan.mt * 16;
-        const int nblocks_n = (ntiles + plan.waves * MMA_NT - 1) / (plan.waves * MMA_NT);
+        const int nblocks_n = (ntiles + plan.waves * plan.nt - 1) / (plan.waves * plan.nt);
         const int nblocks_m = (int)((M + bm - 1) / bm);
         // ring depth of the pipelined form per block shape (0 = two-buffer form); must match the
         // instantiations below
-        const int ring = plan.mt == 8 ? (plan.waves == 8 ? 2 : 0) : (plan.mt == 4 ? FQ_RING_MT4 : FQ_RING_MT2);
-        const size_t lds = (size_t)(ring ? ring + 1 : 2) * (kblk / 8) * bm * 16;
+        const bool flexible = fq_flexible(plan);
+        const int ring = plan.mt >= 5 ? (plan.waves == 8 ? 2 : 0) : (plan.mt == 4 ? FQ_RING_MT4 : FQ_RING_MT2);
+        // (an LDS tile of the flexible shapes is a whole number of rounds of their eight waves' direct loads)
+        const int units = flexible ? ((kblk / 8) * bm + 511) / 512 * 512 : (kblk / 8) * bm;
+        const size_t lds = (size_t)(ring ? ring + 1 : 2) * units * 16;
         const int64_t tiles = (int64_t)nblocks_n * nblocks_m;
         dim3 grid((unsigned)(plan.tail_tiles > 0 ? tiles - plan.tail_tiles + (int64_t)plan.tail_tiles * plan.tail_splits
                                                  : tiles * plan.splits));
         fq_group_items none;
         none.count = 0;
 #define FQ_MMA_LAUNCH_SR(ACT_, A_, RS_, MT_, W_, PIPE_, SR_, KREC_)                                       \
+    FQ_MMA_LAUNCH_NT(ACT_, A_, RS_, MT_, MMA_NT, W_, PIPE_, SR_, use_post(ACT_, BITS, MT_, SR_, PIPE_), KREC_)
+#define FQ_MMA_LAUNCH_NT(ACT_, A_, RS_, MT_, NT_, W_, PIPE_, SR_, POST_, KREC_)                           \
     do {                                                                                                \
-        auto kern = fq_gemm_mma_kernel<ACT_, BITS, MT_, MMA_NT, W_, SR_, false, PIPE_,                 \
-                                       use_post(ACT_, BITS, MT_, SR_, PIPE_), KREC_>;                   \
+        auto kern = fq_gemm_mma_kernel<ACT_, BITS, MT_, NT_, W_, SR_, false, PIPE_, POST_, KREC_>;      \
         if (lds > 65536) {                                                                              \
             static std::atomic<uint64_t> raised;                                                        \
             if (raise_lds_limit((const void*)kern, raised) != FQ_OK) return FQ_ERR_HIP;                 \
@@ -178,6 +184,28 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
             FQ_MMA_LAUNCH_ACT(ACT_, A_, RS_, 8, 8, 2);                                                  \
         }                                                                                               \
     } while (0)
+// the flexible shapes
+#define FQ_MMA_LAUNCH_FLEX(ACT_, A_, RS_, MT_, NT_)                                                     \
+    do {                                                                                                \
+        if constexpr (BITS == 8) {                                                                      \
+            if (wide) FQ_MMA_LAUNCH_NT(ACT_, A_, RS_, MT_, NT_, 8, 2, 1, false, 2);                     \
+            else if (sr == 1) FQ_MMA_LAUNCH_NT(ACT_, A_, RS_, MT_, NT_, 8, 2, 1, false, 1);             \
+            else FQ_MMA_LAUNCH_NT(ACT_, A_, RS_, MT_, NT_, 8, 2, 2, false, 1);                          \
+        } else {                                                                                        \
+            if (sr == 1) FQ_MMA_LAUNCH_NT(ACT_, A_, RS_, MT_, NT_, 8, 2, 1, true, 1);                   \
+            else if (sr == 2) FQ_MMA_LAUNCH_NT(ACT_, A_, RS_, MT_, NT_, 8, 2, 2, false, 1);             \
+            else FQ_MMA_LAUNCH_NT(ACT_, A_, RS_, MT_, NT_, 8, 2, 4, false, 1);                          \
+        }                                                                                               \
+    } while (0)
+#define FQ_MMA_LAUNCH_FLEXIBLE(ACT_, A_, RS_)                                                           \
+    do {                                                                                                \
+        if (plan.nt == 2 && plan.mt == 5) FQ_MMA_LAUNCH_FLEX(ACT_, A_, RS_, 5, 2);                      \
+        else if (plan.nt == 2 && plan.mt == 6) FQ_MMA_LAUNCH_FLEX(ACT_, A_, RS_, 6, 2);                 \
+        else if (plan.nt == 2 && plan.mt == 7) FQ_MMA_LAUNCH_FLEX(ACT_, A_, RS_, 7, 2);                 \
+        else if (plan.nt == 2 && plan.mt == 8) FQ_MMA_LAUNCH_FLEX(ACT_, A_, RS_, 8, 2);                 \
+        else if (plan.nt == 3 && plan.mt == 5) FQ_MMA_LAUNCH_FLEX(ACT_, A_, RS_, 5, 3);                 \
+        else return FQ_ERR_UNSUPPORTED;                                                                 \
+    } while (0)
 #define FQ_MMA_LAUNCH(MT_, W_, PIPE_) FQ_MMA_LAUNCH_ACT(ACT, A, nullptr, MT_, W_, PIPE_)
         bool launched = false;
         if constexpr (ACT == FQ_BF16) {
@@ -187,31 +215,31 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
                 char* extra = (char*)workspace + fq_partial_bytes(plan, M, N);
                 uint16_t* A16 = (uint16_t*)extra;
                 float* rs = (float*)(extra + fq_a16_bytes(M, K));
-                launch_rows_to_f16(A, M, K, A16, rs, stream);
-                if (plan.waves == 8) FQ_MMA_LAUNCH_BIG(FQ_BF16_VIA_F16, A16, rs);
+                launch_rows_to_f16<false>(A, M, K, A16, rs, nullptr, 0, stream);
+                if (flexible) FQ_MMA_LAUNCH_FLEXIBLE(FQ_BF16_VIA_F16, A16, rs);
+                else if (plan.waves == 8) FQ_MMA_LAUNCH_BIG(FQ_BF16_VIA_F16, A16, rs);
                 else FQ_MMA_LAUNCH_ACT(FQ_BF16_VIA_F16, A16, rs, 8, 4, 0);
                 launched = true;
             }
         }
         if constexpr (ACT == FQ_BF16_BS) {
             if (fq_via_f16(FQ_BF16, FQ_SCALE_BF16, plan, N)) {
-                // the same with bfloat16 scales: their common power of two is found first
+                // the same with bfloat16 scales: their common power of two is searched in the same launch
                 char* extra = (char*)workspace + fq_partial_bytes(plan, M, N);
                 uint16_t* A16 = (uint16_t*)extra;
                 float* rs = (float*)(extra + fq_a16_bytes(M, K));
-                uint32_t* parts = (uint32_t*)(rs + M + 2);
-                const int64_t count = (K / g) * N;
-                hipLaunchKernelGGL(fq_scale_max_kernel<256>, dim3(FQ_SCALE_PARTS), dim3(256), 0, stream,
-                                   (const uint16_t*)scales, count, parts);
-                hipLaunchKernelGGL(fq_scale_exp_kernel<256>, dim3(1), dim3(256), 0, stream, (const uint32_t*)parts,
-                                   FQ_SCALE_PARTS, rs + M);
-                launch_rows_to_f16(A, M, K, A16, rs, stream);
-                if (plan.waves == 8) FQ_MMA_LAUNCH_BIG(FQ_BF16S_VIA_F16, A16, rs);
+                launch_rows_to_f16<true>(A, M, K, A16, rs, scales, (K / g) * N, stream);
+                if (flexible) FQ_MMA_LAUNCH_FLEXIBLE(FQ_BF16S_VIA_F16, A16, rs);
+                else if (plan.waves == 8) FQ_MMA_LAUNCH_BIG(FQ_BF16S_VIA_F16, A16, rs);
                 else FQ_MMA_LAUNCH_ACT(FQ_BF16S_VIA_F16, A16, rs, 8, 4, 0);
                 launched = true;
             }
         }
         if (launched) {
+        } else if (flexible) {
+            // (bf16 activations take these shapes on the fp16 matrix path only)
+            if constexpr (ACT == FQ_F16) FQ_MMA_LAUNCH_FLEXIBLE(ACT, A, nullptr);
+            else return FQ_ERR_UNSUPPORTED;
         } else if (plan.waves == 8) {
             if (plan.mt == 2) FQ_MMA_LAUNCH(2, 8, FQ_RING_MT2);
             else if (plan.mt == 4) FQ_MMA_LAUNCH(4, 8, FQ_RING_MT4);
@@ -225,11 +253,14 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
 #undef FQ_MMA_LAUNCH_BIG
 #undef FQ_MMA_LAUNCH_ACT
 #undef FQ_MMA_LAUNCH_SR
+#undef FQ_MMA_LAUNCH_NT
+#undef FQ_MMA_LAUNCH_FLEX
+#undef FQ_MMA_LAUNCH_FLEXIBLE
     }
     if (plan.kind == 1 && plan.tail_tiles > 0) {
         const int bm = plan.mt * 16;
-        const int bn_cols = plan.waves * MMA_NT * FQ_NTILE;
-        const int nblocks_n = (ntiles + plan.waves * MMA_NT - 1) / (plan.waves * MMA_NT);
+        const int bn_cols = plan.waves * plan.nt * FQ_NTILE;
+        const int nblocks_n = (ntiles + plan.waves * plan.nt - 1) / (plan.waves * plan.nt);
         const int nblocks_m = (int)((M + bm - 1) / bm);
         hipLaunchKernelGGL(fq_reduce_tail_kernel<(ACT == FQ_F16 ? FQ_F16 : FQ_BF16)>, dim3((unsigned)plan.tail_tiles, (unsigned)plan.mt), dim3(256), 0, stream,
                            (const float*)partial, plan.tail_splits, (int)M, (int)N, nblocks_n, nblocks_m,

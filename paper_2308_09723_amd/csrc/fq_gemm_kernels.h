@@ -45,7 +45,7 @@ namespace fqk {
 #define FQ_BF16_VIA_F16 3
 // Fifth value: the same path for bfloat16 SCALES (FQ_BF16_BS computed with fp16 MFMAs).  A bfloat16 scale has
 // eight significant bits but binary32's exponent range, so the scales are first multiplied by 2^-E, E the
-// exponent of the largest scale of the matrix (found by fq_scale_maxexp_kernel): they then lie in (0, 2) and
+// exponent of the largest scale of the matrix (searched by fq_rows_to_f16_kernel's first blocks): they then lie in (0, 2) and
 // convert to binary16 exactly unless they are more than 2^14 times smaller than the largest one (those lose
 // low bits or vanish: their weights are below 2^-14 of the matrix's widest group).  q * s * 2^-E is rounded
 // once to binary16 (at most 4 + 8 significant bits: usually exact), and the epilogue multiplies by 2^E.
@@ -327,7 +327,7 @@ struct SkinnyStage {
 // four stored scales -> binary32
 template <int ACT>
 __device__ inline f32x4 scales4(const u32x2& v) {
-    if constexpr (ACT == FQ_BF16_BS) {
+    if constexpr (ACT == FQ_BF16_BS || ACT == FQ_BF16S_VIA_F16) {
         f32x4 r = {bitcast<float>(v[0] << 16), bitcast<float>(v[0] & 0xffff0000u),
                    bitcast<float>(v[1] << 16), bitcast<float>(v[1] & 0xffff0000u)};
         return r;
@@ -1262,23 +1262,52 @@ __global__ __launch_bounds__(256) void fq_reduce_tail_kernel(const float* __rest
 // normal binary32 number; the product kernel applies it in two halves).
 // Rows of up to THREADS * ROW_UNITS units of 8 values are read once and kept in registers across the search for the
 // largest element (2048 x 12288: 25.5 -> 18.8 us); what lies beyond is read a second time.
+// SCALES (bfloat16 scales, FQ_BF16S_VIA_F16): the first FQ_SCALE_PARTS blocks look for the largest scale instead, each
+// writing the largest bit pattern it saw to part[block]; the product kernel folds those (scale_exponent below).  As two
+// kernels of their own in front of this one they cost 10 us of a 42 us product (2048 x 13520, 8-bit codes, M = 210).
 constexpr int ROW_UNITS = 8;
-template <int THREADS>   // (a template so that every translation unit may hold a copy)
+template <int THREADS, bool SCALES>   // (a template so that every translation unit may hold a copy)
 __global__ __launch_bounds__(THREADS) void fq_rows_to_f16_kernel(const uint16_t* __restrict__ A, int K,
-                                                             uint16_t* __restrict__ A16,
-                                                             float* __restrict__ rowscale) {
+                                                                 uint16_t* __restrict__ A16,
+                                                                 float* __restrict__ rowscale,
+                                                                 const uint16_t* __restrict__ scales, int64_t scale_units,
+                                                                 uint32_t* __restrict__ part) {
     __shared__ uint32_t red[THREADS / 64];
     typedef uint16_t u16x2r __attribute__((ext_vector_type(2)));
-    const int64_t r = blockIdx.x;
-    const u32x4* src = reinterpret_cast<const u32x4*>(A + r * K);
-    u32x4* dst = reinterpret_cast<u32x4*>(A16 + r * K);
-    const int units = K / 8;
-    u32x4 v[ROW_UNITS];
+    // largest 16-bit magnitude of the block's values, from each thread's two
+    auto block_largest = [&](const u16x2r& m2) -> uint32_t {
+        uint32_t m = m2[0] > m2[1] ? m2[0] : m2[1];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const uint32_t t = (uint32_t)__shfl_xor((int)m, o, 64);
+            m = t > m ? t : m;
+        }
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < THREADS / 64; ++i) m = red[i] > m ? red[i] : m;
+        return m;
+    };
     u16x2r m2 = {0, 0};
     auto largest = [&](const u32x4& x) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) m2 = __builtin_elementwise_max(m2, bitcast<u16x2r>(x[i] & 0x7fff7fffu));
     };
+    if constexpr (SCALES) {
+        if (blockIdx.x < FQ_SCALE_PARTS) {
+            const u32x4* s = reinterpret_cast<const u32x4*>(scales);      // (the scale matrix is a multiple of 16 wide)
+            for (int64_t u = (int64_t)blockIdx.x * THREADS + threadIdx.x; u < scale_units; u += (int64_t)FQ_SCALE_PARTS * THREADS)
+                largest(s[u]);
+            const uint32_t m = block_largest(m2);
+            if (threadIdx.x == 0) part[blockIdx.x] = m;
+            return;
+        }
+    }
+    const int64_t r = blockIdx.x - (SCALES ? FQ_SCALE_PARTS : 0);
+    const u32x4* src = reinterpret_cast<const u32x4*>(A + r * K);
+    u32x4* dst = reinterpret_cast<u32x4*>(A16 + r * K);
+    const int units = K / 8;
+    u32x4 v[ROW_UNITS];
 #pragma unroll
     for (int i = 0; i < ROW_UNITS; ++i) {
         const int u = threadIdx.x + i * THREADS;
@@ -1288,16 +1317,7 @@ __global__ __launch_bounds__(THREADS) void fq_rows_to_f16_kernel(const uint16_t*
     for (int i = 0; i < ROW_UNITS; ++i) largest(v[i]);
 #pragma unroll 1
     for (int u = threadIdx.x + ROW_UNITS * THREADS; u < units; u += THREADS) largest(src[u]);
-    uint32_t m = m2[0] > m2[1] ? m2[0] : m2[1];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint32_t t = (uint32_t)__shfl_xor((int)m, o, 64);
-        m = t > m ? t : m;
-    }
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < THREADS / 64; ++i) m = red[i] > m ? red[i] : m;
+    const uint32_t m = block_largest(m2);
     const int e = (int)(m >> 7) - 127 - 14;
     if (threadIdx.x == 0) rowscale[r] = (float)e;
     auto rewrite = [&](const u32x4& x) -> u32x4 {
@@ -1322,47 +1342,23 @@ __global__ __launch_bounds__(THREADS) void fq_rows_to_f16_kernel(const uint16_t*
     for (int u = threadIdx.x + ROW_UNITS * THREADS; u < units; u += THREADS) dst[u] = rewrite(src[u]);
 }
 
-// Largest scale of a bfloat16 scale matrix (FQ_BF16S_VIA_F16), in two steps without atomics: every block
-// writes the largest bit pattern it saw, then one block folds those and writes 2^-E and 2^E (E = exponent of
-// the largest scale, kept within +-120; 0 for an all-zero matrix) to out2[0], out2[1].
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void fq_scale_max_kernel(const uint16_t* __restrict__ scales, int64_t count,
-                                                               uint32_t* __restrict__ part) {
-    static_assert(THREADS == 256, "four waves are reduced below");
-    __shared__ uint32_t red[4];
+// Exponent E of the largest scale of a bfloat16 scale matrix (FQ_BF16S_VIA_F16), kept within +-120 (0 for an all-zero
+// matrix), from the FQ_SCALE_PARTS bit patterns fq_rows_to_f16_kernel left; called by whole waves.
+__device__ inline int scale_exponent(const uint32_t* part, int lane) {
     uint32_t m = 0;
-    const int64_t units = count / 8;                               // the scale matrix is a multiple of 16 wide
-    for (int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x; u < units; u += (int64_t)gridDim.x * 256) {
-        const u32x4 v = reinterpret_cast<const u32x4*>(scales)[u];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t a0 = v[i] & 0x7fffu, a1 = (v[i] >> 16) & 0x7fffu;
-            m = a0 > m ? a0 : m;
-            m = a1 > m ? a1 : m;
-        }
+    for (int i = 0; i < FQ_SCALE_PARTS / 64; ++i) {
+        const uint32_t t = part[lane + 64 * i];
+        m = t > m ? t : m;
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const uint32_t t = (uint32_t)__shfl_xor((int)m, o, 64);
         m = t > m ? t : m;
     }
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 1; i < 4; ++i) m = red[i] > m ? red[i] : m;
-        part[blockIdx.x] = m;
-    }
-}
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void fq_scale_exp_kernel(const uint32_t* __restrict__ part, int nparts,
-                                                               float* __restrict__ out2) {
-    if (threadIdx.x != 0) return;
-    uint32_t m = 0;
-    for (int i = 0; i < nparts; ++i) m = part[i] > m ? part[i] : m;
-    int e = m == 0 ? 0 : (int)(m >> 7) - 127;
-    e = e < -120 ? -120 : (e > 120 ? 120 : e);
-    out2[0] = ldexpf(1.0f, -e);
-    out2[1] = ldexpf(1.0f, e);
+    m = (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
+    const int e = m == 0 ? 0 : (int)(m >> 7) - 127;
+    return e < -120 ? -120 : (e > 120 ? 120 : e);
 }
 
 // KREC = k-blocks of the packed layout that make one k-block of this kernel (lane records per column tile
@@ -1494,12 +1490,12 @@ __global__ __launch_bounds__(WAVES * 64, (POST && MT == 2 && WAVES == 4 && ACT =
 
     const uint32_t magic = Dequant<ACT, BITS>::init();
     const u32x4 zero4 = {0u, 0u, 0u, 0u};
-    // FQ_BF16S_VIA_F16: the two floats behind the M row scales are 2^-E and 2^E (E: exponent of the largest scale)
-    float sshift = 1.0f;
+    // FQ_BF16S_VIA_F16: FQ_SCALE_PARTS words behind the M row scales (and two unused ones) hold the largest scales
+    float sshift = 1.0f;     // 2^-E
     int sback_exp = 0;       // E
     if constexpr (ACT == FQ_BF16S_VIA_F16) {
-        sshift = rowscale[M];
-        sback_exp = (int)((bitcast<uint32_t>(rowscale[M + 1]) >> 23) & 255u) - 127;   // 2^E is a normal number
+        sback_exp = scale_exponent(reinterpret_cast<const uint32_t*>(rowscale) + M + 2, lane);
+        sshift = bitcast<float>((uint32_t)(127 - sback_exp) << 23);
     }
     constexpr int NQ = KREC * NT;                // lane records of a k-block: [record][column tile]
     u32x4 wq[NQ], wq_n[NQ], areg[UPT];
@@ -1519,8 +1515,8 @@ __global__ __launch_bounds__(WAVES * 64, (POST && MT == 2 && WAVES == 4 && ACT =
     SC sc[SREG][NT], sc_n[SREG][NT];
     // addresses are formed as (wave-uniform 64-bit base) + (32-bit lane offset), which the loads take as
     // they are (scalar base + vector offset), instead of 64-bit vector arithmetic per load
-    // (used by the 128-row shapes; in the lower ones it costs registers they do not have)
-    constexpr bool SADDR = MT == 8;
+    // (used by the shapes of 80 rows and more; in the lower ones it costs registers they do not have)
+    constexpr bool SADDR = MT >= 5;
     const uint32_t lane_rec = (uint32_t)lane * RB;
     auto load_q = [&](u32x4 (&q)[NQ], int kb) {
 #pragma unroll
@@ -1545,7 +1541,8 @@ __global__ __launch_bounds__(WAVES * 64, (POST && MT == 2 && WAVES == 4 && ACT =
                 const int64_t srow = (int64_t)((kb * KBLK + r * (KBLK / SROWS)) / g) * N;
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
-                    s[r][nt] = *reinterpret_cast<const u32x2*>(sbase[nt] + srow + 4 * j);
+                    s[r][nt] = SADDR ? *reinterpret_cast<const FQ_GLOBAL u32x2*>(scalar_ptr(sbase[nt] + srow) + (uint32_t)j * 4u)
+                                     : *reinterpret_cast<const u32x2*>(sbase[nt] + srow + 4 * j);
             } else if constexpr (SPK == 1) {
                 const int64_t srow = (int64_t)((kb * KBLK + r * (KBLK / SROWS)) / g) * N;
 #pragma unroll
@@ -1610,10 +1607,11 @@ __global__ __launch_bounds__(WAVES * 64, (POST && MT == 2 && WAVES == 4 && ACT =
     };
 
     constexpr int NFR = STEPS * MT;
-    constexpr int APD = NFR >= 8 ? 3 : 1;   // fragments read ahead of their MFMAs
+    constexpr int APD = NFR >= 8 && NFR % 4 == 0 ? 3 : 1;   // fragments read ahead of their MFMAs
     static_assert(NFR % (APD + 1) == 0, "the fragment window must wrap at a k-block boundary");
     static_assert(STEPS % 2 == 0, "fragment sets alternate per k-step");
-    constexpr int abuf_units = KC * BM;
+    // units of one LDS tile; the pipelined form loads whole rounds of its waves (rows past the tile repeat its last row)
+    constexpr int abuf_units = PIPE == 0 || UNITS < NTHR ? UNITS : (UNITS + NTHR - 1) / NTHR * NTHR;
     int a_rd[STEPS];   // unit of this lane's fragment row for k-step t (row tile 0)
 #pragma unroll
     for (int t = 0; t < STEPS; ++t) a_rd[t] = (4 * t + j) * BM + (ml ^ (((4 * t + j) * SWZ) & 15));
@@ -1641,7 +1639,7 @@ __global__ __launch_bounds__(WAVES * 64, (POST && MT == 2 && WAVES == 4 && ACT =
         // different bank groups.  Rows past the end of the matrix load the last valid row; their
         // results are never stored.
         constexpr int D = PIPE;
-        constexpr int NI = UNITS / 64;                  // wave-level direct loads per tile
+        constexpr int NI = abuf_units / 64;             // wave-level direct loads per tile
         constexpr int DPT = NI >= WAVES ? NI / WAVES : 1;   // of which this wave issues DPT (or none)
         static_assert(UNITS % 64 == 0 && 64 % KC == 0 && (NI % WAVES == 0 || NI < WAVES),
                       "every wave issues the same number of direct loads, or none");
@@ -1712,11 +1710,15 @@ __global__ __launch_bounds__(WAVES * 64, (POST && MT == 2 && WAVES == 4 && ACT =
             for (int nt = 0; nt < NT; ++nt) w[0][nt] = convert(wqs[0], scs[0], 0, nt);
         }
         // one k-block; (qa, sa) hold its weights, (qb, sb) those of the next one
+        f32x4 sfold[POST ? NT : 1];      // scales of the fold under way (MT >= 5: widened once per scale row)
         auto fold = [&](const SC (&sa)[SREG][NT], int srow, int mt) {
             if constexpr (POST) {
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    flush<ACT, BITS>(acc[mt][nt], pg[mt][nt], scales4<ACT>(sa[srow][nt]), rsum[mt][0]);
+                for (int nt = 0; nt < NT; ++nt) {
+                    if (MT < 5 || mt == 0) sfold[nt] = scales4<ACT>(sa[srow][nt]);
+                    if (ACT == FQ_BF16S_VIA_F16 && mt == 0) sfold[nt] = sfold[nt] * sshift;
+                    flush<ACT, BITS>(acc[mt][nt], pg[mt][nt], sfold[nt], rsum[mt][0]);
+                }
             }
         };
         auto kblock = [&](int kb, u32x4 (&qa)[NQ], SC (&sa)[SREG][NT], u32x4 (&qb)[NQ],

@@ -30,6 +30,7 @@ int fq_launch_mfma_rate_probe(const void* operands, void* sink, int iterations, 
 struct fq_gemm_plan {
     int kind;      // 0 = skinny (M <= 16), 1 = tiled, 2 = mid-M streaming (17 <= M <= 48)
     int mt;        // row tiles of 16 per block (tiled and mid-M kernel)
+    int nt;        // tiled kernel: column tiles of 16 per wave (3, or 2 in the flexible shapes)
     int waves;     // waves per block
     int variant;   // small-M kernel: which compiled variant (NT, ring depth, register class)
     int gp, kw;    // small-M and mid-M kernel: column groups x k-workers per block
@@ -40,6 +41,8 @@ struct fq_gemm_plan {
     // of blocks) are split `tail_splits` ways along K so that they fill the idle compute units
     int tail_tiles, tail_splits, tail_kbs;
 };
+// Block shapes of the tiled kernel beside 32, 64 and 128 rows x 3 column tiles per wave (see fq_plan_flexible)
+inline bool fq_flexible(const fq_gemm_plan& p) { return p.kind == 1 && p.mt >= 5 && !(p.mt == 8 && p.nt == 3); }
 fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g);
 // Grouped products in which no expert has more than 32 rows and at most one in nine has more than 16 give those few to
 // the small-M kernel as two items of 16 rows (their weights are read twice, mostly from a cache the second time):
@@ -53,14 +56,14 @@ fq_small_shape fq_plan_grouped_small(int count, int units, int ngroups, int KB);
 // compute units of the device (asked once per process; 256 without a device)
 int fq_cu_count();
 // Rows of K per k-block of the tiled kernel for a block shape (the unit of kb_per_split and tail_kbs):
-// the layout's k-block, except that the 128-row, 8-wave shape takes two 64-row blocks of 8-bit codes at a
+// the layout's k-block, except that the 8-wave shapes of 80 rows and more take two 64-row blocks of 8-bit codes at a
 // time when K allows it and such a k-block lies inside one scale group (with two scale rows the wider
 // kernel spills and gains nothing, with four it loses).
 inline int fq_mma_kblk(int bits, int mt, int waves, int64_t K, int g) {
-    return (bits == 8 && mt == 8 && waves == 8 && K % 128 == 0 && g % 128 == 0) ? 128 : (bits == 8 ? 64 : 128);
+    return (bits == 8 && mt >= 5 && waves == 8 && K % 128 == 0 && g % 128 == 0) ? 128 : (bits == 8 ? 64 : 128);
 }
 // Workspace layout of fq_gemm: [split-K partial tiles][bf16 activations rewritten as binary16][their M row scales,
-// then 2^-E and 2^E of the scale matrix (bfloat16 scales), then FQ_SCALE_PARTS words of the search for E]
+// two unused words, then (bfloat16 scales) FQ_SCALE_PARTS words of the search for the largest scale's exponent]
 inline size_t fq_partial_bytes(const fq_gemm_plan& p, int64_t M, int64_t N) {
     const int parts = p.splits > 1 ? p.splits : (p.tail_tiles > 0 ? p.tail_splits : 0);
     return (size_t)parts * (size_t)M * (size_t)N * sizeof(float);
@@ -68,11 +71,11 @@ inline size_t fq_partial_bytes(const fq_gemm_plan& p, int64_t M, int64_t N) {
 inline size_t fq_a16_bytes(int64_t M, int64_t K) { return (((size_t)M * (size_t)K * 2) + 255) / 256 * 256; }
 #define FQ_SCALE_PARTS 256
 inline size_t fq_rowscale_bytes(int64_t M) { return ((size_t)M + 2 + FQ_SCALE_PARTS) * sizeof(float); }
-// bf16 activations (binary16 or bfloat16 scales) take the fp16 matrix path for the 128-row shapes of wide
+// bf16 activations (binary16 or bfloat16 scales) take the fp16 matrix path for the shapes of 80 rows and more of wide
 // matrices: the rewrite of the rows costs 4 M K bytes of traffic against 2 M N K flops
 inline bool fq_via_f16(int act_dtype, int scale_format, const fq_gemm_plan& p, int64_t N) {
     (void)scale_format;
-    return act_dtype == FQ_BF16 && p.kind == 1 && p.mt == 8 && N >= 8192;
+    return act_dtype == FQ_BF16 && p.kind == 1 && p.mt >= 5 && N >= 8192;
 }
 // act: FQ_F16, FQ_BF16, or 2 = bf16 activations with bf16 scales
 int fq_launch_gemm(const void* A, int act, int64_t M, int64_t N, int64_t K, const void* codes,

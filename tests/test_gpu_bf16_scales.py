@@ -113,6 +113,15 @@ def test_gemm_wide_matrix_bf16_scales_on_the_fp16_matrix_path(bits, g, M):
     _gemm_case(M, K, N, bits, g, seed=6200 + M + bits + g)
 
 
+@pytest.mark.parametrize("M,K,N", [(257, 640, 8208), (563, 640, 12304), (386, 640, 16400)])
+@pytest.mark.parametrize("bits,g", [(4, 128), (4, 64), (4, 32), (8, 128), (3, 128)])
+def test_gemm_shapes_between_64_and_128_rows_bf16_scales(bits, g, M, K, N):
+    """80 x 256, 128 x 256 and 80 x 384 blocks: post-scaled with one scale row per k-block, where the scales are widened as
+    they are, times the matrix's common power of two; pre-scaled otherwise."""
+    _say(f"gemm bf16 scales M={M} K={K} N={N} int{bits} g={g}")
+    _gemm_case(M, K, N, bits, g, seed=6400 + M + bits + g)
+
+
 def test_gemm_wide_matrix_bf16_scales_spread_over_many_binades():
     """Columns scaled by powers of two from 2^-12 to 2^3 (scales spread over 15 binades inside one matrix), a
     zero column and a matrix that is tiny as a whole (every scale near 2^-22): the common power of two follows

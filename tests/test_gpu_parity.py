@@ -584,3 +584,18 @@ def test_rows_with_infinities_nans_and_the_largest_magnitudes(dtype, bits, form)
         ok = np.isfinite(want)
         if ok.any():
             assert_gemm_close(C[r][ok], want[ok], dtype, f"row {r}")
+
+
+@pytest.mark.parametrize("M,K,N,rows,cols", [(257, 640, 8208, 80, 256), (563, 1152, 8208, 96, 256), (578, 640, 10256, 112, 256),
+                                             (563, 640, 12304, 128, 256), (386, 640, 16400, 80, 384), (200, 6016, 8208, 112, 256)])
+@pytest.mark.parametrize("dtype,bits,g", [("f16", 4, 128), ("bf16", 4, 128), ("bf16", 4, 64), ("f16", 4, 32), ("f16", 3, 128),
+                                          ("bf16", 8, 128), ("f16", 8, 64), ("bf16", 8, 32)])
+def test_gemm_shapes_between_64_and_128_rows(dtype, bits, g, M, K, N, rows, cols):
+    """Every block shape of 80 .. 128 rows beside 128 x 384 (odd numbers of row tiles load padded LDS tiles), ragged in rows
+    and columns, odd numbers of k-blocks, every number of scale rows per k-block, and K split over the grid."""
+    desc = _fq().gemm_describe(M, N, K, bits, g)
+    _say(f"gemm {dtype} int{bits} g={g} M={M} K={K} N={N}: {desc}")
+    if (N, bits, g) != (16400, 4, 32):   # (keeps the former shape)
+        assert f"rows={rows} cols={cols}" in desc
+        assert (K == 6016) == ("splits=1 " not in desc)
+    _gemm_case(M, K, N, dtype, bits, g, seed=9700 + M + K + bits)
