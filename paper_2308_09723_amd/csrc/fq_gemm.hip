@@ -351,15 +351,28 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g) {
     return p;
 }
 
-bool fq_split_32_rows(const int32_t* offsets, int E) {
-    int n16 = 0, n32 = 0;
+// 16 (the small-M kernel for experts of at most 16 rows) with two exceptions:
+//  - 32: no expert has more than 32 rows and at most one in nine more than 16.  Those few become two items each (their
+//    weights are read twice, mostly from a cache the second time): a kernel of their own beside it costs the fork to
+//    another stream and more compute units than the second reading (64 experts, 96 rows: 237 -> 216 us).
+//  - 0: some expert has more rows and the tiles of all experts are resident at once.  The call then takes as long as its
+//    taller tiles walk K, which the small-M kernel cannot shorten, while its blocks take compute units away from them
+//    (16 experts of 15488 x 4320, 8-bit, 174 rows: 284 us with it, 241 without).
+int32_t fq_small_rows_most(const int32_t* offsets, int E, int64_t N) {
+    const int waves_cols = 3 * (N / FQ_NTILE >= 48 ? 8 : 4);       // column tiles of a 32- or 64-row tile's block
+    const int64_t nblocks_n = (N / FQ_NTILE + waves_cols - 1) / waves_cols;
+    int n16 = 0, n32 = 0, more = 0;
+    int64_t tiles = 0;
     for (int e = 0; e < E; ++e) {
         const int32_t rows = offsets[e + 1] - offsets[e];
-        if (rows > 32) return false;
         n16 += rows > 0 && rows <= 16;
-        n32 += rows > 16;
+        n32 += rows > 16 && rows <= 32;
+        more += rows > 32;
+        tiles += (rows + 127) / 128;
     }
-    return n32 > 0 && 8 * n32 <= n16;
+    if (more == 0 && n32 == 0) return 16;
+    if (more == 0 && 8 * n32 <= n16) return 32;
+    return tiles * nblocks_n <= fq_cu_count() ? 0 : 16;
 }
 
 // Block shape for the experts of the small-M kernel: the shape with the least
@@ -439,12 +452,12 @@ int fq_launch_gemm_grouped(const void* A, int act, const int32_t* offsets, int E
                            const void* codes, const void* scales, int bits, int g, void* C,
                            hipStream_t stream) {
     // which tile sizes occur (same cutting rule as the launcher)
-    const bool split32 = fq_split_32_rows(offsets, E);
+    const int32_t small_most = fq_small_rows_most(offsets, E, N);
     bool has[4] = {false, false, false, false};
     for (int e = 0; e < E; ++e) {
         const int32_t rows = offsets[e + 1] - offsets[e];
         if (rows <= 0) continue;
-        if (rows <= (split32 ? 32 : 16)) {
+        if (rows <= small_most) {
             has[3] = true;
             continue;
         }

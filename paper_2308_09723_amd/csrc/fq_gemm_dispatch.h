@@ -303,19 +303,17 @@ int launch_grouped_small(const void* A, const fq_small_items& items, int count, 
     return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_HIP;
 }
 
-// Grouped (per-expert) product.  Every expert's rows are cut into row tiles of 128, 64, 32 or 16
-// rows (the smallest that holds what is left; 16 only where the expert has no more than 16 rows in all, or 32: see
-// fq_split_32_rows), and the tiles
-// of each size go to the kernel instantiated for that size: experts with few rows then stream their weights through
-// small tiles instead of multiplying mostly padding, those with at most 16 through the small-M kernel.  Experts without
-// rows produce no tile.
+// Grouped (per-expert) product.  Every expert's rows are cut into row tiles of 128, 64, 32 or 16 rows (the smallest that
+// holds what is left; 16 only for the experts that fq_small_rows_most names), and the tiles of each size go to the kernel
+// instantiated for that size: experts with few rows then stream their weights through small tiles instead of multiplying
+// mostly padding, those with at most 16 through the small-M kernel.  Experts without rows produce no tile.
 template <int ACT, int BITS>
 int launch_grouped_typed(const void* A, const int32_t* offsets, int E, int64_t N, int64_t K,
                          const void* codes, const void* scales, int g, void* C, const hipStream_t* streams) {
     const int ntiles = (int)(N / FQ_NTILE);
     const int64_t codes_stride16 = (int64_t)(K * N * BITS / 8) / 16;
     const int64_t scales_stride = (K / g) * N;
-    const int32_t small_most = fq_split_32_rows(offsets, E) ? 32 : 16;   // experts up to here take the small-M kernel
+    const int32_t small_most = fq_small_rows_most(offsets, E, N);   // experts up to here take the small-M kernel
     fq_group_items items;
     for (int mt = 8; mt >= 2; mt /= 2) {
         const int bm = mt * 16;

@@ -44,11 +44,8 @@ struct fq_gemm_plan {
 // Block shapes of the tiled kernel beside 32, 64 and 128 rows x 3 column tiles per wave (see fq_plan_flexible)
 inline bool fq_flexible(const fq_gemm_plan& p) { return p.kind == 1 && p.mt >= 5 && !(p.mt == 8 && p.nt == 3); }
 fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g);
-// Grouped products in which no expert has more than 32 rows and at most one in nine has more than 16 give those few to
-// the small-M kernel as two items of 16 rows (their weights are read twice, mostly from a cache the second time):
-// a kernel of their own beside it costs the fork to another stream and more compute units than the second reading
-// (64 experts, 96 rows: 237 -> 216 us).
-bool fq_split_32_rows(const int32_t* offsets, int E);
+// Rows up to which an expert of a grouped product takes the small-M kernel: 0, 16 or 32
+int32_t fq_small_rows_most(const int32_t* offsets, int E, int64_t N);
 // Block shape of the small-M kernel for `count` items of a grouped product (at most 16 rows each);
 // units = activation units (16 bytes) of a k-block in the tallest of them, ngroups = groups of three column tiles.
 struct fq_small_shape { int gp, kw; };

@@ -513,10 +513,12 @@ def test_grouped_gemm_int8_two_layout_blocks_per_k_block(dtype, g, K):
 @pytest.mark.parametrize("rows", [[16, 1, 0, 15, 4], [1], [17, 16, 1, 2, 3, 16, 4, 5, 16], [32, 16, 3], [130, 16, 0, 33, 9, 20]],
                          ids=["at-most-16", "one-row", "one-of-nine-17", "32-and-16", "every-size"])
 @pytest.mark.parametrize("dtype,bits,g,K,N", [("f16", 4, 64, 640, 112), ("bf16", 4, 128, 1664, 1040), ("bf16", 8, 0, 192, 48),
-                                              ("f16", 8, 32, 256, 816), ("f16", 3, 96, 384, 16)])
+                                              ("f16", 8, 32, 256, 816), ("f16", 3, 96, 384, 16),
+                                              ("f16", 4, 128, 128, 33200), ("bf16", 4, 64, 256, 33200)])
 def test_grouped_gemm_few_rows_per_expert(dtype, bits, g, K, N, rows):
     """Experts of at most 16 rows take the small-M kernel, those of 17 .. 32 too (as two items) where they are few and
-    nobody has more; neighbours with more rows take the tiled kernel.  Column counts that leave idle column groups, k
+    nobody has more; neighbours with more rows take the tiled kernel, and so does every expert beside such a neighbour
+    where all tiles are resident at once (the narrow matrices here, not the wide ones).  Column counts that leave idle column groups, k
     ranges shorter than the k-workers' turn, and every expert's rows next to another expert's."""
     _say(f"grouped few rows {dtype} int{bits} g={g} {rows}")
     fq = _fq()
