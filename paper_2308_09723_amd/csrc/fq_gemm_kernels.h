@@ -280,6 +280,16 @@ __device__ inline void flush(f32x4& acc, const f32x4& p, const f32x4& s, float r
     }
 }
 
+// Direct load global -> LDS, 16 bytes per lane (lane l to lds_base + 16 l; lds_base wave-uniform).  Written as assembly on
+// purpose: issued through the compiler's builtin, these loads make its wait-count pass drain the whole memory queue
+// (vmcnt(0)) at every later wait, which would undo the weight prefetch.  The compiler's own waits stay correct without
+// knowing about them (the counter retires in order, so a wait for an older load only gets stricter); the waits for these
+// loads themselves are written out where they are used.  A load that takes its LDS address from M0 needs one wait state
+// behind the scalar write of M0; the compiler inserts it for its own loads but does not look inside assembly.
+__device__ inline void load_lds16(uint32_t lds_base, const void* src) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(src) : "memory", "m0");
+}
+
 // s_waitcnt vmcnt(N) only (the other counters left alone); gfx9 encoding: vmcnt in bits 3:0 and 15:14
 template <int N>
 __device__ inline void wait_vmcnt() {
@@ -873,13 +883,7 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_kernel(
             const int row = i * (64 / KC) + lane / KC, pos = lane % KC;
             const int rowc = row < M ? row : M - 1;                            // (their results are never stored)
             const uint16_t* src = base + (uint32_t)rowc * (uint32_t)K + (uint32_t)((pos ^ swz(row)) * 8);
-            // (assembly on purpose: issued through the compiler's builtin these loads make its wait-count pass drain
-            // the whole memory queue at every later wait)
-            const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_tile + i * 1024);
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
-                         :
-                         : "s"(m0), "v"(src)
-                         : "memory", "m0");
+            load_lds16(__builtin_amdgcn_readfirstlane(lds_tile + i * 1024), src);
         }
     };
     auto load_stage = [&](Stage& sl, int it) {
@@ -1664,21 +1668,10 @@ __global__ __launch_bounds__(WAVES * 64, (POST && MT == 2 && WAVES == 4 && ACT =
         auto load_a_lds = [&](int kb, int bufi) {
             if (!a_loader) return;
             const uint16_t* base = Arow + (int64_t)kb * KBLK;
-            // Written as assembly on purpose: issued through the compiler's builtin, these loads make
-            // its wait-count pass drain the whole memory queue (vmcnt(0)) at every later wait, which
-            // would undo the weight prefetch.  The compiler's own waits stay correct without knowing
-            // about them (the counter retires in order, so a wait for an older load only gets
-            // stricter); the waits for these loads themselves are written out below.
             const uint32_t lds_base = __builtin_amdgcn_readfirstlane(
                 (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)(lds + bufi * abuf_units + wave * DPT * 64));
 #pragma unroll
-            for (int r = 0; r < DPT; ++r) {
-                const uint16_t* src = base + d_off[r];
-                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
-                             :
-                             : "s"(lds_base + r * 1024), "v"(src)
-                             : "memory", "m0");
-            }
+            for (int r = 0; r < DPT; ++r) load_lds16(lds_base + r * 1024, base + d_off[r]);
         };
 #pragma unroll
         for (int t = 0; t < STEPS; ++t) a_rd[t] = ml * KC + ((4 * t + j) ^ swz(ml));

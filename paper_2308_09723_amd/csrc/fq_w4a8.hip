@@ -433,18 +433,10 @@ __global__ __launch_bounds__(W8_WAVES * 64) void fq_gemm_w4a8_kernel(
     auto load_a_lds = [&](int kb, int tile_i) {
         if (!a_loader) return;
         const int8_t* base = Aq + (int64_t)kb * 128;
-        // (assembly on purpose: issued through the compiler's builtin these loads make its wait-count pass drain
-        // the whole memory queue at every later wait; the waits for them are written out below)
         const uint32_t lds_base = __builtin_amdgcn_readfirstlane(
             (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)(lds + tile_i * UNITS + wave * DPT * 64));
 #pragma unroll
-        for (int r = 0; r < DPT; ++r) {
-            const int8_t* src = base + d_off[r];
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
-                         :
-                         : "s"(lds_base + r * 1024), "v"(src)
-                         : "memory", "m0");
-        }
+        for (int r = 0; r < DPT; ++r) load_lds16(lds_base + r * 1024, base + d_off[r]);
     };
     int a_rd[2];
 #pragma unroll
