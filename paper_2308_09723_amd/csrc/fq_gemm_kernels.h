@@ -243,6 +243,51 @@ struct Dequant<FQ_BF16_VIA_F16, BITS> : Dequant<FQ_F16, BITS> {};
 template <int BITS>
 struct Dequant<FQ_BF16S_VIA_F16, BITS> : Dequant<FQ_F16, BITS> {};
 
+// ------------------------------------------------------------------------------------------
+// Operands without a bias for either activation type: run() holds q / BACK exactly, BACK a power of two.
+//   fp16: Dequant's.
+//   bf16, 8-bit codes: the bytes as signed numbers (u ^ 0x80), converted to binary32 and cut to the upper halves:
+//         14 vector instructions per eight weights where the biased operand takes 12.
+//   bf16, 3 and 4 bits: v_cvt_off_f32_i4 turns a nibble in two's complement into its sixteenth: 14 where the biased
+//         operand takes 7.
+// A biased operand adds rounding errors of 2^-24 * OFFSET * |a| s to every sum, whatever the weight: nothing beside
+// activations of similar size, but an activation 10^6 times its neighbours that meets zero codes loses the result in
+// them (bf16, 4-bit codes, rows of N(0, 1) with 10^6 in every 96th place, whose weights are zero: relative error 0.7).
+// ------------------------------------------------------------------------------------------
+template <int ACT, int BITS>
+struct ExactOperand {
+    static constexpr float OFFSET = 0.0f;
+    static constexpr float BACK = BITS == 8 ? 1.0f : (BITS == 4 ? 16.0f : 8.0f);
+    static __device__ inline uint32_t init() { return 0u; }
+    template <int T>
+    static __device__ inline u32x4 run(const u32x4& rec, uint32_t) {
+        u32x4 r;
+        if constexpr (BITS == 8) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {                // elements 2 i, 2 i + 1
+                const uint32_t w = rec[2 * T + (i >> 1)] ^ 0x80808080u;
+                const float f0 = (float)(int8_t)(w >> (16 * (i & 1))), f1 = (float)(int8_t)(w >> (16 * (i & 1) + 8));
+                r[i] = __builtin_amdgcn_perm(bitcast<uint32_t>(f1), bitcast<uint32_t>(f0), 0x07060302u);
+            }
+        } else {
+            const uint32_t u = code_word<BITS, T>(rec);
+            // 3 bits: (2 u) ^ 8 = 2 q in two's complement
+            const uint32_t w = (BITS == 4 ? u : (u << 1) & 0xeeeeeeeeu) ^ 0x88888888u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float f0 = __builtin_amdgcn_cvt_off_f32_i4(w >> (4 * i));
+                const float f1 = __builtin_amdgcn_cvt_off_f32_i4(w >> (4 * i + 16));
+                r[i] = __builtin_amdgcn_perm(bitcast<uint32_t>(f1), bitcast<uint32_t>(f0), 0x07060302u);
+            }
+        }
+        return r;
+    }
+};
+template <int BITS>
+struct ExactOperand<FQ_F16, BITS> : Dequant<FQ_F16, BITS> {
+    static constexpr float BACK = 1.0f;
+};
+
 template <int ACT>
 __device__ inline u32x4 ones_operand() {
     const uint32_t one2 = ACT == FQ_F16 ? 0x3c003c00u : 0x3f803f80u;
@@ -359,15 +404,13 @@ __device__ inline u32x2 quad_bcast(const u32x2& v) {
 }
 
 // true (in every lane) when some lane of the wave whose sums count holds an infinity or a NaN among them
-template <int MT, int NT>
-__device__ inline bool any_not_finite(const f32x4 (&acc)[MT][NT], bool counts) {
+template <int NT>
+__device__ inline bool any_not_finite(const f32x4 (&acc)[NT], bool counts) {
     float t = 0.0f;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) t = __builtin_fmaf(acc[mt][nt][i], 0.0f, t);   // NaN from then on
+        for (int i = 0; i < 4; ++i) t = __builtin_fmaf(acc[nt][i], 0.0f, t);   // NaN from then on
     return __builtin_amdgcn_ballot_w64(t != t && counts) != 0;
 }
 
@@ -420,52 +463,26 @@ __device__ inline void skinny_block(const SkinnyStage<BITS, NT, SR, AU>& sl,
     }
 }
 
-// Biased operands remove their bias with the activations' row sums.  In a row with an infinity, or with values so near
-// the top of binary32's range that the biased sums overflow, that leaves a NaN where the product itself is an infinity
-// or finite.  A wave that ends with a sum that is not finite therefore computes its share once more here, with operands
-// that hold q itself.  Not a fast path: no ring, activations from global memory.
-template <int ACT, int BITS, int T>
-__device__ inline u32x4 unbiased_operand(const u32x4& rec) {
-    if constexpr (ACT == FQ_F16) {
-        return Dequant<FQ_F16, BITS>::template run<T>(rec, Dequant<FQ_F16, BITS>::init());
-    } else {
-        constexpr float BIAS = BITS == 8 ? 128.0f : (BITS == 4 ? 8.0f : 4.0f);
-        constexpr uint32_t MASK = BITS == 8 ? 0xffu : (BITS == 4 ? 0xfu : 0x7u);
-        u32x4 r;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {                    // elements 2 i, 2 i + 1
-            uint32_t lo, hi;
-            if constexpr (BITS == 8) {
-                const uint32_t w = rec[2 * T + (i >> 1)] >> (16 * (i & 1));
-                lo = w;
-                hi = w >> 8;
-            } else {
-                const uint32_t w = code_word<BITS, T>(rec) >> (4 * i);
-                lo = w;
-                hi = w >> 16;
-            }
-            const float f0 = (float)(lo & MASK) - BIAS, f1 = (float)(hi & MASK) - BIAS;
-            // upper halves of the two binary32 values (exact: at most 8 significant bits)
-            r[i] = __builtin_amdgcn_perm(bitcast<uint32_t>(f1), bitcast<uint32_t>(f0), 0x07060302u);
-        }
-        return r;
-    }
-}
-
-// acc = this wave's tiles over the k-blocks kb, kb + kb_step, ... < KB (one 32-row step after the other)
-template <int ACT, int BITS, int NT, int MT>
-__device__ inline void multiply_unbiased(f32x4 (&acc)[MT][NT], const uint16_t* A, int M, int N, int K,
-                                         const char* const (&wbase)[NT], const uint16_t* const (&sbase)[NT], uint32_t g32,
-                                         uint32_t g32_recip, int kb, int kb_step, int KB, int lane) {
+// bf16 sums that are not finite, computed once more.  Biased operands remove their bias with the activations' row sums:
+// in a row with an infinity that leaves a NaN where the product itself is an infinity; and values near the top of
+// binary32's range overflow in the sums of a q, before the scale brings them back.  A wave that ends with such a sum
+// computes the 16 rows at hand once more here, with operands that hold q.
+// acc = this wave's column tiles over the k-blocks kb, kb + kb_step, ... < KB, for rows row0 .. row0 + 15.
+// Not a fast path: no ring, activations from global memory, one 32-row step after the other.
+template <int ACT, int BITS, int NT>
+__device__ inline void recompute_not_finite(f32x4 (&acc)[NT], const uint16_t* A, int row0, int M, int N, int K,
+                                            const char* const (&wbase)[NT], const uint16_t* const (&sbase)[NT], uint32_t g32,
+                                            uint32_t g32_recip, int kb, int kb_step, int KB, int lane) {
+    typedef ExactOperand<ACT, BITS> OP;
     constexpr int STEPS = fq_kblk(BITS) / FQ_KSTEP;
     constexpr int RB = fq_rec_bytes(BITS);
     const int64_t kb_stride = (int64_t)(N / FQ_NTILE) * 64;
     const int ml = lane & 15, j = lane >> 4;
+    const int row = row0 + ml < M ? row0 + ml : M - 1;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 again[NT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = zero;
+    for (int nt = 0; nt < NT; ++nt) again[nt] = zero;
 #pragma unroll 1
     for (; kb < KB; kb += kb_step) {
         u32x4 q[NT];
@@ -475,60 +492,51 @@ __device__ inline void multiply_unbiased(f32x4 (&acc)[MT][NT], const uint16_t* A
         for (int t = 0; t < STEPS; ++t) {
             const uint32_t step = (uint32_t)kb * STEPS + t;
             const int64_t srow = (int64_t)(g32 == 1 ? step : __umulhi(step, g32_recip)) * N;
-            u32x4 a[MT];
+            u32x4 a = *reinterpret_cast<const u32x4*>(A + (int64_t)row * K + ((int64_t)step * FQ_KSTEP + 8 * j));
+            // rows near the top of the range are brought down by 2^-16 for this step, so that the sums of a q stay in
+            // range before their scale (a lane's fragments and its results belong to the same row)
+            uint32_t m = 0;
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const int row = mt * 16 + ml < M ? mt * 16 + ml : M - 1;
-                a[mt] = *reinterpret_cast<const u32x4*>(A + (int64_t)row * K + ((int64_t)step * FQ_KSTEP + 8 * j));
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t lo = a[i] & 0x7fffu, hi = (a[i] >> 16) & 0x7fffu;
+                m = m > lo ? m : lo;
+                m = m > hi ? m : hi;
             }
-            // bfloat16 rows near the top of the range are brought down by 2^-16 for this step, so that the sums of
-            // a q stay in range before their scale (a lane's fragments and its results belong to the same row)
-            float back[MT];
+            const uint32_t m1 = (uint32_t)__shfl_xor((int)m, 16, 64);
+            m = m > m1 ? m : m1;
+            const uint32_t m2 = (uint32_t)__shfl_xor((int)m, 32, 64);
+            m = m > m2 ? m : m2;
+            float back = 1.0f;
+            if (m >= 0x7180u) {                          // 2^100
+                back = 65536.0f;
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                back[mt] = 1.0f;
-                if constexpr (ACT != FQ_F16) {
-                    uint32_t m = 0;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const uint32_t lo = a[mt][i] & 0x7fffu, hi = (a[mt][i] >> 16) & 0x7fffu;
-                        m = m > lo ? m : lo;
-                        m = m > hi ? m : hi;
-                    }
-                    const uint32_t m1 = (uint32_t)__shfl_xor((int)m, 16, 64);
-                    m = m > m1 ? m : m1;
-                    const uint32_t m2 = (uint32_t)__shfl_xor((int)m, 32, 64);
-                    m = m > m2 ? m : m2;
-                    if (m >= 0x7180u) {                  // 2^100
-                        back[mt] = 65536.0f;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float lo = bitcast<float>(a[mt][i] << 16) * 0x1p-16f;
-                            const float hi = bitcast<float>(a[mt][i] & 0xffff0000u) * 0x1p-16f;
-                            a[mt][i] = __builtin_amdgcn_perm(bitcast<uint32_t>(hi), bitcast<uint32_t>(lo), 0x07060302u);
-                        }
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    const float lo = bitcast<float>(a[i] << 16) * 0x1p-16f;
+                    const float hi = bitcast<float>(a[i] & 0xffff0000u) * 0x1p-16f;
+                    a[i] = __builtin_amdgcn_perm(bitcast<uint32_t>(hi), bitcast<uint32_t>(lo), 0x07060302u);
                 }
             }
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
                 u32x4 w;
-                if (t == 0) w = unbiased_operand<ACT, BITS, 0>(q[nt]);
-                if (t == 1) w = unbiased_operand<ACT, BITS, 1>(q[nt]);
-                if (STEPS > 2 && t == 2) w = unbiased_operand<ACT, BITS, 2 % STEPS>(q[nt]);
-                if (STEPS > 2 && t == 3) w = unbiased_operand<ACT, BITS, 3 % STEPS>(q[nt]);
+                if (t == 0) w = OP::template run<0>(q[nt], 0u);
+                if (t == 1) w = OP::template run<1>(q[nt], 0u);
+                if (STEPS > 2 && t == 2) w = OP::template run<2 % STEPS>(q[nt], 0u);
+                if (STEPS > 2 && t == 3) w = OP::template run<3 % STEPS>(q[nt], 0u);
                 __builtin_amdgcn_sched_barrier(0);       // (one tile after the other: few registers, not speed)
                 const f32x4 s = scales4<ACT>(*reinterpret_cast<const u32x2*>(sbase[nt] + srow + 4 * j));
+                const f32x4 p = mfma16x16x32<ACT>(w, a, zero);
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const f32x4 p = mfma16x16x32<ACT>(w, a[mt], zero);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[mt][nt][i] = __builtin_fmaf(s[i] * back[mt], p[i], acc[mt][nt][i]);
-                }
+                for (int i = 0; i < 4; ++i) again[nt][i] = __builtin_fmaf(s[i] * back, p[i] * OP::BACK, again[nt][i]);
             }
         }
     }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[nt][i] = again[nt][i];
 }
+
 // LDS row pitch of the activation buffer in 16-byte units: 16 rows + 1 pad, so that both the
 // fragment reads (16 lanes = 16 rows of one unit column) and the staging writes (consecutive
 // lanes = consecutive unit columns of one row) spread over the banks.
@@ -706,16 +714,10 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_skinny_kernel(
         }
     }
 
-    if constexpr (ITEMS::grouped && Dequant<ACT, BITS>::OFFSET != 0.0f) {
-        f32x4 again[1][NT];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) again[0][nt] = acc[nt];
+    if constexpr (ITEMS::grouped && ACT != FQ_F16) {
         // (not the lanes of rows past M: nothing is staged for them, they multiply what the LDS held before)
-        if (any_not_finite<1, NT>(again, m < M)) {
-            multiply_unbiased<ACT, BITS, NT, 1>(again, A, M, N, K, wbase, sbase, g32, g32_recip, kw, kw_n, KB, lane);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) acc[nt] = again[0][nt];
-        }
+        if (any_not_finite<NT>(acc, m < M))
+            recompute_not_finite<ACT, BITS, NT>(acc, A, 0, M, N, K, wbase, sbase, g32, g32_recip, kw, kw_n, KB, lane);
     }
 
     // Combine the k-workers of each column group in fixed order (worker 0 + worker 1 + worker 2 ...).  Every
@@ -766,58 +768,29 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_skinny_kernel(
 //    staging them through the ring spilled), NBUF - 1 iterations ahead into one of NBUF LDS tiles.  Their waits are
 //    explicit; the counter retires in order, and every wave leaves at most the loads of the last NBUF - 1 iterations'
 //    weights in flight at the barrier, whatever its own share of the activation loads was.
-//  - The weights keep their storage bias (MidOperand): the first MFMA of a scale group starts from -BIAS * rowsum,
-//    which MFMAs of the activations against a constant operand provide (one per row tile and k-step for all column tiles),
-//    instead of from zero with the bias removed by vector instructions afterwards: the fold is one fused
-//    multiply-add per element.
+//  - Where the weights keep their storage bias (MidOperand, bf16), the first MFMA of a scale group starts from
+//    -BIAS * rowsum, which MFMAs of the activations against a constant operand provide (one per row tile and k-step for
+//    all column tiles), instead of from zero with the bias removed by vector instructions afterwards: the fold is one
+//    fused multiply-add per element.
 // Against the tiled kernel with 32 rows per block: no split of K over the grid (no partial sums through memory, no
 // second kernel), and a barrier per KW k-blocks instead of one per k-block.  12288 x 36864, int4 g = 128, M = 32
 // (us): bf16 60 -> 49.5 (4.8 TB/s of weights), fp16 56 -> 49; M = 48: 94 -> 64.
 // LDS tile of k-worker kw, in 16-byte units: unit(row, kc) = row * KC + (kc ^ swz(row)): a wave-level direct load
 // fills whole rows, a fragment read (16 rows of one kc) touches 16 different bank groups.
 // ==========================================================================================
-// Operand of this kernel: (u - BIAS) * UNIT with the stored value u in place and -BIAS * UNIT as the start of the
-// accumulation (NEG, the constant 16-bit operand of the row-sum MFMAs).
-//   bf16: Dequant's biased operand (128 + u, or u), UNIT = 1
-//   fp16: the stored value alone in the low bits of the 16-bit lane, i.e. the subnormal u * 2^-24 (the matrix cores
-//         honour fp16 subnormals); the results are multiplied by 2^24 once at the end.  Products and sums are those of
-//         the integers, scaled by a power of two: exact as before, and with 7 (4 for bytes) vector instructions per
-//         eight weights instead of the 9 (8) that normal numbers without a bias take.
-template <int ACT, int BITS>
-struct MidOperand {
+// fp16 products have exact operands at every number of rows.
+constexpr bool mid_exact(int act) { return act == FQ_F16; }
+// Operand of this kernel: q itself (EXACT, times a power of two), or Dequant's biased one, whose bias the start of the
+// accumulation takes back (NEG, the constant 16-bit operand of the row-sum MFMAs).
+template <int ACT, int BITS, bool EXACT>
+struct MidOperand : Dequant<ACT, BITS> {
     static constexpr float OFF = Dequant<ACT, BITS>::OFFSET;      // 128, 132 or 136: exact in bfloat16
     static constexpr uint32_t NEG = OFF == 136.0f ? 0xc308u : (OFF == 132.0f ? 0xc304u : 0xc300u);
     static constexpr float BACK = 1.0f;
-    static __device__ inline uint32_t init() { return Dequant<ACT, BITS>::init(); }
-    template <int T>
-    static __device__ inline u32x4 run(const u32x4& rec, uint32_t magic) {
-        return Dequant<ACT, BITS>::template run<T>(rec, magic);
-    }
 };
-template <int BITS>
-struct MidOperand<FQ_F16, BITS> {
-    static constexpr uint32_t NEG = BITS == 8 ? 0x8080u : (BITS == 4 ? 0x8008u : 0x8004u);
-    static constexpr float BACK = 16777216.0f;
-    static __device__ inline uint32_t init() { return 0u; }
-    template <int T>
-    static __device__ inline u32x4 run(const u32x4& rec, uint32_t) {
-        u32x4 r;
-        if constexpr (BITS == 8) {
-            const uint32_t w0 = rec[2 * T], w1 = rec[2 * T + 1];
-            r[0] = __builtin_amdgcn_perm(0u, w0, 0x0c010c00u);
-            r[1] = __builtin_amdgcn_perm(0u, w0, 0x0c030c02u);
-            r[2] = __builtin_amdgcn_perm(0u, w1, 0x0c010c00u);
-            r[3] = __builtin_amdgcn_perm(0u, w1, 0x0c030c02u);
-        } else {
-            constexpr uint32_t M = BITS == 4 ? 0x000f000fu : 0x00070007u;
-            const uint32_t w = code_word<BITS, T>(rec);
-            r[0] = w & M;
-            r[1] = (w >> 4) & M;
-            r[2] = (w >> 8) & M;
-            r[3] = (w >> 12) & M;
-        }
-        return r;
-    }
+template <int ACT, int BITS>
+struct MidOperand<ACT, BITS, true> : ExactOperand<ACT, BITS> {
+    static constexpr uint32_t NEG = 0u;
 };
 
 template <int ACT, int BITS, int NT, int MT, int DEPTH, int NBUF, int SR, int MAXW>
@@ -833,7 +806,7 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_kernel(
     constexpr int NI = TILE / 64;                   // wave-level direct loads of such a tile
     constexpr int RB = fq_rec_bytes(BITS);
     constexpr int NW = 2 * NT;                      // vector loads of one stage
-    typedef MidOperand<ACT, BITS> OP;
+    typedef MidOperand<ACT, BITS, mid_exact(ACT)> OP;
     static_assert(STEPS % SR == 0 && (NBUF == 2 || NBUF == 3) && DEPTH >= 2 && (DEPTH - 1) * NW < 64, "");
     constexpr int AHEAD = NBUF - 1;                 // iterations the activations are loaded ahead
     typedef SkinnyStage<BITS, NT, SR, 0> Stage;
@@ -933,11 +906,13 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_kernel(
             f32x4 start[MT];
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) start[mt] = zero;
-            const u32x4 neg = {OP::NEG * 0x10001u, OP::NEG * 0x10001u, OP::NEG * 0x10001u, OP::NEG * 0x10001u};
+            if constexpr (OP::NEG != 0u) {
+                const u32x4 neg = {OP::NEG * 0x10001u, OP::NEG * 0x10001u, OP::NEG * 0x10001u, OP::NEG * 0x10001u};
 #pragma unroll
-            for (int u = 0; u < GSTEPS; ++u)
+                for (int u = 0; u < GSTEPS; ++u)
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) start[mt] = mfma16x16x32<ACT>(neg, af[u][mt], start[mt]);
+                    for (int mt = 0; mt < MT; ++mt) start[mt] = mfma16x16x32<ACT>(neg, af[u][mt], start[mt]);
+            }
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
                 f32x4 p[MT];
@@ -1028,9 +1003,28 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_kernel(
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = acc[mt][nt] * OP::BACK;
     }
-    if (any_not_finite<MT, NT>(acc, true))
-        multiply_unbiased<ACT, BITS, NT, MT>(acc, A, M, N, K, wbase, sbase, g32, g32_recip, gsplit * kw_n + kw,
-                                             grid_splits * kw_n, KB, lane);
+    if constexpr (ACT != FQ_F16) {
+        // one row tile after the other (one copy of the code)
+#pragma unroll 1
+        for (int r = 0; r < MT; ++r) {
+            f32x4 cur[NT];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                cur[nt] = acc[0][nt];
+#pragma unroll
+                for (int mt = 1; mt < MT; ++mt)
+                    if (r == mt) cur[nt] = acc[mt][nt];
+            }
+            if (!any_not_finite<NT>(cur, true)) continue;
+            recompute_not_finite<ACT, BITS, NT>(cur, A, 16 * r, M, N, K, wbase, sbase, g32, g32_recip, gsplit * kw_n + kw,
+                                                grid_splits * kw_n, KB, lane);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    if (r == mt) acc[mt][nt] = cur[nt];
+        }
+    }
     // the k-workers' sums of each column group, added by all threads of the block (as in the small-M kernel)
     auto store_quad = [&](const f32x4& v, int group, int mt, int nt, int ln) {
         const int mq = mt * 16 + (ln & 15), jq = ln >> 4;

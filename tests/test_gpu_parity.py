@@ -588,6 +588,26 @@ def test_rows_with_infinities_nans_and_the_largest_magnitudes(dtype, bits, form)
             assert_gemm_close(C[r][ok], want[ok], dtype, f"row {r}")
 
 
+@pytest.mark.parametrize("M", [20, 40])
+@pytest.mark.parametrize("dtype,bits,g", [("f16", 3, 128), ("f16", 4, 128), ("f16", 4, 64), ("f16", 4, 32), ("f16", 8, 128), ("f16", 8, 32)])
+def test_outlying_activations_on_zero_weights(dtype, bits, g, M):
+    """Every 96th activation is near the top of binary16's range and its weights are zero.  Such a product adds nothing,
+    and what it leaves behind is bounded by the other terms alone: the weights' and the result's roundings to 16 bits,
+    2^-11 relative each, and the sums' to binary32 (operands with a bias leave 2^-24 * bias * 60000 * s per sum: 30 to 500
+    times as much)."""
+    _say(f"outliers on zero weights {dtype} int{bits} g={g} M={M}")
+    K, N = 768, 112
+    W = workloads.weights_gaussian(K, N, 41)
+    W[::96] = 0
+    A = workloads.activations(M, K, dtype, 42).astype(np.float32)
+    A[:, ::96] = 60000.0
+    codes, scales, q_ref, s_ref = assert_quantizer_parity(W, bits, g)
+    C = from_dev_act(_fq().gemm(to_dev_act(A.astype(np.float16), dtype), codes, scales, bits, g), dtype)
+    Wd = q_ref.astype(np.float64) * np.repeat(s_ref.astype(np.float64), g, axis=0)
+    terms = np.abs(A.astype(np.float64)) @ np.abs(Wd)
+    assert np.max(np.abs(C - A.astype(np.float64) @ Wd) / terms) <= 2 * 2.0 ** -11 + 2.0 ** -20
+
+
 @pytest.mark.parametrize("M,K,N,rows,cols", [(257, 640, 8208, 80, 256), (563, 1152, 8208, 96, 256), (578, 640, 10256, 112, 256),
                                              (563, 640, 12304, 128, 256), (386, 640, 16400, 80, 384), (200, 6016, 8208, 112, 256)])
 @pytest.mark.parametrize("dtype,bits,g", [("f16", 4, 128), ("bf16", 4, 128), ("bf16", 4, 64), ("f16", 4, 32), ("f16", 3, 128),
