@@ -466,7 +466,8 @@ __device__ inline void skinny_block(const SkinnyStage<BITS, NT, SR, AU>& sl,
 // bf16 sums that are not finite, computed once more.  Biased operands remove their bias with the activations' row sums:
 // in a row with an infinity that leaves a NaN where the product itself is an infinity; and values near the top of
 // binary32's range overflow in the sums of a q, before the scale brings them back.  A wave that ends with such a sum
-// computes the 16 rows at hand once more here, with operands that hold q.
+// computes the 16 rows at hand once more here, with operands that hold q, and takes the new value for the sums that
+// were not finite (the others keep theirs: a row's results do not depend on what another row holds).
 // acc = this wave's column tiles over the k-blocks kb, kb + kb_step, ... < KB, for rows row0 .. row0 + 15.
 // Not a fast path: no ring, activations from global memory, one 32-row step after the other.
 template <int ACT, int BITS, int NT>
@@ -534,7 +535,7 @@ __device__ inline void recompute_not_finite(f32x4 (&acc)[NT], const uint16_t* A,
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[nt][i] = again[nt][i];
+        for (int i = 0; i < 4; ++i) acc[nt][i] = acc[nt][i] * 0.0f == 0.0f ? acc[nt][i] : again[nt][i];
 }
 
 // LDS row pitch of the activation buffer in 16-byte units: 16 rows + 1 pad, so that both the

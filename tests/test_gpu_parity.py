@@ -588,6 +588,30 @@ def test_rows_with_infinities_nans_and_the_largest_magnitudes(dtype, bits, form)
             assert_gemm_close(C[r][ok], want[ok], dtype, f"row {r}")
 
 
+@pytest.mark.parametrize("form", ["M=20", "M=40", "grouped"])
+@pytest.mark.parametrize("dtype,bits,g", [("f16", 4, 128), ("bf16", 4, 128), ("bf16", 3, 64), ("bf16", 4, 32), ("bf16", 8, 128)])
+def test_rows_do_not_depend_on_another_row_that_is_not_finite(dtype, bits, g, form):
+    """Infinities and a NaN in three rows: every other row gives the same bits as without them."""
+    _say(f"rows beside non-finite ones {dtype} int{bits} g={g} {form}")
+    fq = _fq()
+    torch = torch_mod()
+    K, N = 2048, 1040
+    rows = [16, 9] if form == "grouped" else [int(form[2:])]
+    M = sum(rows)
+    codes, scales, _, _ = assert_quantizer_parity(workloads.weights_gaussian(K, N, 51, outlier_prob=1e-3), bits, g)
+    A = to_dev_act(workloads.activations(M, K, dtype, 52), dtype)
+    B = A.clone()
+    B[1, 3], B[7, 2000], B[M - 1, 77] = float("inf"), float("nan"), float("-inf")
+
+    def product(X):
+        if form == "grouped":
+            return fq.gemm_grouped(X, [0, rows[0], M], torch.cat([codes] * 2), torch.cat([scales.reshape(-1)] * 2), bits, g, N)
+        return fq.gemm(X, codes, scales, bits, g)
+
+    keep = [r for r in range(M) if r not in (1, 7, M - 1)]
+    assert torch.equal(product(A)[keep], product(B)[keep])
+
+
 @pytest.mark.parametrize("M", [20, 40])
 @pytest.mark.parametrize("dtype,bits,g", [("f16", 3, 128), ("f16", 4, 128), ("f16", 4, 64), ("f16", 4, 32), ("f16", 8, 128), ("f16", 8, 32)])
 def test_outlying_activations_on_zero_weights(dtype, bits, g, M):
