@@ -416,15 +416,16 @@ __device__ inline bool any_not_finite(const f32x4 (&acc)[NT], bool counts) {
 
 // acc[nt] += (this wave's k-block of the stage) x (activation fragments af[0..STEPS)).
 // The k-steps of one scale row (STEPS / SR of them) accumulate in p, which is then folded into acc with
-// that row's scales.
-template <int ACT, int BITS, int NT, int SR, int AU>
+// that row's scales.  EXACT: ExactOperand's operands, acc in units of 1 / BACK.
+template <int ACT, int BITS, int NT, int SR, int AU, bool EXACT>
 __device__ inline void skinny_block(const SkinnyStage<BITS, NT, SR, AU>& sl,
                                     const u32x4 (&af)[SkinnyStage<BITS, NT, SR, AU>::STEPS], uint32_t magic,
                                     f32x4 (&acc)[NT]) {
     constexpr int STEPS = SkinnyStage<BITS, NT, SR, AU>::STEPS;
     constexpr int GSTEPS = STEPS / SR;
     static_assert(SR >= 1 && STEPS % SR == 0, "");
-    constexpr float OFF = Dequant<ACT, BITS>::OFFSET;
+    typedef typename std::conditional<EXACT, ExactOperand<ACT, BITS>, Dequant<ACT, BITS>>::type OP;
+    constexpr float OFF = OP::OFFSET;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int r = 0; r < SR; ++r) {
@@ -440,10 +441,10 @@ __device__ inline void skinny_block(const SkinnyStage<BITS, NT, SR, AU>& sl,
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
                 u32x4 w;
-                if (t == 0) w = Dequant<ACT, BITS>::template run<0>(sl.wq[nt], magic);
-                if (t == 1) w = Dequant<ACT, BITS>::template run<1>(sl.wq[nt], magic);
-                if (STEPS > 2 && t == 2) w = Dequant<ACT, BITS>::template run<2 % STEPS>(sl.wq[nt], magic);
-                if (STEPS > 2 && t == 3) w = Dequant<ACT, BITS>::template run<3 % STEPS>(sl.wq[nt], magic);
+                if (t == 0) w = OP::template run<0>(sl.wq[nt], magic);
+                if (t == 1) w = OP::template run<1>(sl.wq[nt], magic);
+                if (STEPS > 2 && t == 2) w = OP::template run<2 % STEPS>(sl.wq[nt], magic);
+                if (STEPS > 2 && t == 3) w = OP::template run<3 % STEPS>(sl.wq[nt], magic);
                 p[nt] = mfma16x16x32<ACT>(w, a, p[nt]);
             }
         }
@@ -458,7 +459,13 @@ __device__ inline void skinny_block(const SkinnyStage<BITS, NT, SR, AU>& sl,
                 if (STEPS > 2 && t0 == 2) sq = quad_bcast<2 % STEPS>(sl.sc[nt]);
                 if (STEPS > 2 && t0 == 3) sq = quad_bcast<3 % STEPS>(sl.sc[nt]);
             }
-            flush<ACT, BITS>(acc[nt], p[nt], scales4<ACT>(sq), psa[0]);
+            if constexpr (EXACT) {
+                const f32x4 s = scales4<ACT>(sq);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[nt][i] = __builtin_fmaf(s[i], p[nt][i], acc[nt][i]);
+            } else {
+                flush<ACT, BITS>(acc[nt], p[nt], scales4<ACT>(sq), psa[0]);
+            }
         }
     }
 }
@@ -598,6 +605,8 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_skinny_kernel(
     const int n_it = gsplit < SB ? (SB - gsplit + grid_splits - 1) / grid_splits : 0;   // block-uniform
     const int64_t kb_stride = (int64_t)ntiles * 64;   // records between consecutive k-blocks of a tile
     const int m = lane & 15, j = lane >> 4;
+    // grouped: no bias in the operands where the tiled kernel's 32-row tiles have none
+    constexpr bool EXACT = ITEMS::grouped && ACT != FQ_F16 && (BITS == 8 || SR > 2);
     const uint32_t magic = Dequant<ACT, BITS>::init();
     const int abuf_units = kw_n * KC * FQ_SK_PITCH;
 
@@ -674,7 +683,7 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_skinny_kernel(
         const u32x4* abuf = lds + (it & 1) * abuf_units + (kw * KC + j) * FQ_SK_PITCH + m;
 #pragma unroll
         for (int t = 0; t < STEPS; ++t) af[t] = abuf[t * 4 * FQ_SK_PITCH];
-        if (gvalid && kb < KB) skinny_block<ACT, BITS, NT, SR, AU>(sl, af, magic, acc);
+        if (gvalid && kb < KB) skinny_block<ACT, BITS, NT, SR, AU, EXACT>(sl, af, magic, acc);
     };
 
     if (n_it > 0) {
@@ -715,6 +724,10 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_skinny_kernel(
         }
     }
 
+    if constexpr (EXACT && ExactOperand<ACT, BITS>::BACK != 1.0f) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[nt] = acc[nt] * ExactOperand<ACT, BITS>::BACK;
+    }
     if constexpr (ITEMS::grouped && ACT != FQ_F16) {
         // (not the lanes of rows past M: nothing is staged for them, they multiply what the LDS held before)
         if (any_not_finite<NT>(acc, m < M))
@@ -779,8 +792,11 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_skinny_kernel(
 // LDS tile of k-worker kw, in 16-byte units: unit(row, kc) = row * KC + (kc ^ swz(row)): a wave-level direct load
 // fills whole rows, a fragment read (16 rows of one kc) touches 16 different bank groups.
 // ==========================================================================================
-// fp16 products have exact operands at every number of rows.
-constexpr bool mid_exact(int act) { return act == FQ_F16; }
+// Where the tiled kernel's operands have no bias (use_post: fp16, 8-bit codes, four scale rows per k-block, and two with
+// more than 32 rows), this kernel's have none either.
+constexpr bool mid_exact(int act, int bits, int mt, int sr) {
+    return act == FQ_F16 || bits == 8 || sr > 2 || (mt == 3 && sr == 2);
+}
 // Operand of this kernel: q itself (EXACT, times a power of two), or Dequant's biased one, whose bias the start of the
 // accumulation takes back (NEG, the constant 16-bit operand of the row-sum MFMAs).
 template <int ACT, int BITS, bool EXACT>
@@ -807,7 +823,7 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_kernel(
     constexpr int NI = TILE / 64;                   // wave-level direct loads of such a tile
     constexpr int RB = fq_rec_bytes(BITS);
     constexpr int NW = 2 * NT;                      // vector loads of one stage
-    typedef MidOperand<ACT, BITS, mid_exact(ACT)> OP;
+    typedef MidOperand<ACT, BITS, mid_exact(ACT, BITS, MT, SR)> OP;
     static_assert(STEPS % SR == 0 && (NBUF == 2 || NBUF == 3) && DEPTH >= 2 && (DEPTH - 1) * NW < 64, "");
     constexpr int AHEAD = NBUF - 1;                 // iterations the activations are loaded ahead
     typedef SkinnyStage<BITS, NT, SR, 0> Stage;

@@ -612,24 +612,33 @@ def test_rows_do_not_depend_on_another_row_that_is_not_finite(dtype, bits, g, fo
     assert torch.equal(product(A)[keep], product(B)[keep])
 
 
-@pytest.mark.parametrize("M", [20, 40])
-@pytest.mark.parametrize("dtype,bits,g", [("f16", 3, 128), ("f16", 4, 128), ("f16", 4, 64), ("f16", 4, 32), ("f16", 8, 128), ("f16", 8, 32)])
-def test_outlying_activations_on_zero_weights(dtype, bits, g, M):
-    """Every 96th activation is near the top of binary16's range and its weights are zero.  Such a product adds nothing,
-    and what it leaves behind is bounded by the other terms alone: the weights' and the result's roundings to 16 bits,
-    2^-11 relative each, and the sums' to binary32 (operands with a bias leave 2^-24 * bias * 60000 * s per sum: 30 to 500
-    times as much)."""
-    _say(f"outliers on zero weights {dtype} int{bits} g={g} M={M}")
+@pytest.mark.parametrize("form", ["M=20", "M=40", "grouped"])
+@pytest.mark.parametrize("dtype,bits,g", [("f16", 3, 128), ("f16", 4, 128), ("f16", 4, 64), ("f16", 4, 32), ("f16", 8, 128),
+                                          ("f16", 8, 32), ("bf16", 8, 128), ("bf16", 8, 32), ("bf16", 4, 32), ("bf16", 3, 96)])
+def test_outlying_activations_on_zero_weights(dtype, bits, g, form):
+    """Every 96th activation is huge (near the top of binary16's range; 10^8 in bfloat16) and its weights are zero.  Such a
+    product adds nothing, and what it leaves behind is bounded by the other terms alone: the weights' and the result's
+    roundings to 16 bits, 2^-11 (2^-8) relative each, and the sums' to binary32 (operands with a bias leave 2^-24 * bias
+    * a * s per sum: 30 to 500 times as much)."""
+    _say(f"outliers on zero weights {dtype} int{bits} g={g} {form}")
+    fq = _fq()
+    torch = torch_mod()
     K, N = 768, 112
+    rows = [16, 9] if form == "grouped" else [int(form[2:])]
     W = workloads.weights_gaussian(K, N, 41)
     W[::96] = 0
-    A = workloads.activations(M, K, dtype, 42).astype(np.float32)
-    A[:, ::96] = 60000.0
+    A = workloads.activations(sum(rows), K, dtype, 42).astype(np.float32)
+    A[:, ::96] = 60000.0 if dtype == "f16" else workloads.round_to_bf16(np.float32([1e8]))[0]
     codes, scales, q_ref, s_ref = assert_quantizer_parity(W, bits, g)
-    C = from_dev_act(_fq().gemm(to_dev_act(A.astype(np.float16), dtype), codes, scales, bits, g), dtype)
+    Ad = to_dev_act(A.astype(np.float16) if dtype == "f16" else A, dtype)
+    if form == "grouped":
+        C = fq.gemm_grouped(Ad, [0, rows[0], sum(rows)], torch.cat([codes] * 2), torch.cat([scales.reshape(-1)] * 2), bits, g, N)
+    else:
+        C = fq.gemm(Ad, codes, scales, bits, g)
     Wd = q_ref.astype(np.float64) * np.repeat(s_ref.astype(np.float64), g, axis=0)
     terms = np.abs(A.astype(np.float64)) @ np.abs(Wd)
-    assert np.max(np.abs(C - A.astype(np.float64) @ Wd) / terms) <= 2 * 2.0 ** -11 + 2.0 ** -20
+    err = np.abs(from_dev_act(C, dtype) - A.astype(np.float64) @ Wd)
+    assert np.max(err / terms) <= 2 * (2.0 ** -11 if dtype == "f16" else 2.0 ** -8) + 2.0 ** -20
 
 
 @pytest.mark.parametrize("M,K,N,rows,cols", [(257, 640, 8208, 80, 256), (563, 1152, 8208, 96, 256), (578, 640, 10256, 112, 256),
