@@ -35,6 +35,13 @@ int halving_levels(int64_t g_top, int g_min) {
     return levels;
 }
 
+// workspace bytes of a planned product
+size_t plan_bytes(const fq_gemm_plan& plan, int64_t M, int64_t N, int64_t K, int act_dtype, int scale_format) {
+    size_t need = fq_partial_bytes(plan, M, N);
+    if (fq_via_f16(act_dtype, scale_format, plan, N)) need += fq_a16_bytes(M, K) + fq_rowscale_bytes(M);
+    return need;
+}
+
 }  // namespace
 
 extern "C" {
@@ -55,10 +62,7 @@ size_t fq_gemm_workspace_bytes_for(int64_t M, int64_t N, int64_t K, int bits, in
                                    int scale_format) {
     int g = 0;
     if (M <= 0 || check_shape(K, N, bits, group_size, &g) != FQ_OK) return 0;
-    const fq_gemm_plan plan = fq_plan_gemm(M, N, K, bits, g);
-    size_t need = fq_partial_bytes(plan, M, N);
-    if (fq_via_f16(act_dtype, scale_format, plan, N)) need += fq_a16_bytes(M, K) + fq_rowscale_bytes(M);
-    return need;
+    return plan_bytes(fq_plan_gemm(M, N, K, bits, g), M, N, K, act_dtype, scale_format);
 }
 
 size_t fq_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int bits, int group_size) {
@@ -194,9 +198,10 @@ int fq_gemm_sf(const void* A, int act_dtype, int64_t M, int64_t N, int64_t K, co
     if (M == 0) return FQ_OK;
     if (!A || !codes || !scales_f16 || !C) return FQ_ERR_INVALID_ARG;
     if (M > (int64_t)1 << 24) return FQ_ERR_UNSUPPORTED;
-    const size_t need = fq_gemm_workspace_bytes_for(M, N, K, bits, group_size, act_dtype, scale_format);
+    const fq_gemm_plan plan = fq_plan_gemm(M, N, K, bits, g);
+    const size_t need = plan_bytes(plan, M, N, K, act_dtype, scale_format);
     if (need > 0 && (!workspace || workspace_bytes < need)) return FQ_ERR_WORKSPACE;
-    return fq_launch_gemm(A, kind, M, N, K, codes, scales_f16, bits, g, C, workspace,
+    return fq_launch_gemm(plan, A, kind, M, N, K, codes, scales_f16, bits, g, C, workspace,
                           (hipStream_t)stream);
 }
 
@@ -247,7 +252,8 @@ int fq_gemm_noalloc(const void* A, int act_dtype, int64_t M, int64_t N, int64_t 
     if (M == 0) return FQ_OK;
     if (!A || !codes || !scales_f16 || !C) return FQ_ERR_INVALID_ARG;
     if (M > (int64_t)1 << 24) return FQ_ERR_UNSUPPORTED;
-    const size_t need = fq_gemm_workspace_bytes_for(M, N, K, bits, group_size, act_dtype, FQ_SCALE_F16);
+    const fq_gemm_plan plan = fq_plan_gemm(M, N, K, bits, g);
+    const size_t need = plan_bytes(plan, M, N, K, act_dtype, FQ_SCALE_F16);
     if (need > (size_t)FQ_NOALLOC_SCRATCH_BYTES) return FQ_ERR_WORKSPACE;   // beyond the static scratch
     void* ws = nullptr;
     if (need > 0) {
@@ -257,7 +263,7 @@ int fq_gemm_noalloc(const void* A, int act_dtype, int64_t M, int64_t N, int64_t 
     }
     // Nothing in the scratch has to start at zero: every partial sum and every rewritten activation row a
     // kernel of this call reads was written by an earlier kernel of the same call.
-    return fq_launch_gemm(A, kind, M, N, K, codes, scales_f16, bits, g, C, ws, (hipStream_t)stream);
+    return fq_launch_gemm(plan, A, kind, M, N, K, codes, scales_f16, bits, g, C, ws, (hipStream_t)stream);
 }
 
 size_t fq_gemm_noalloc_scratch_bytes(void) { return (size_t)FQ_NOALLOC_SCRATCH_BYTES; }

@@ -57,7 +57,7 @@ static void fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int nc
     const int mt = M <= 32 ? 2 : 3;
     const int kblk = fq_kblk(bits);
     const int KB = (int)(K / kblk);
-    const int64_t ngroups = (N / FQ_NTILE + MMA_NT - 1) / MMA_NT;
+    const int ngroups = (int)((N / FQ_NTILE + MMA_NT - 1) / MMA_NT);
     const int sr = g % kblk == 0 ? 1 : (kblk % g == 0 ? kblk / g : kblk / 32);
     // microseconds of vector / matrix work per iteration of a full block (12 waves, one k-block of 48 columns each)
     double work = mt == 2 ? (bits == 8 ? 0.85 : (bits == 3 ? 1.75 : 1.5)) : (bits == 8 ? 1.3 : (bits == 3 ? 2.6 : 2.4));
@@ -71,14 +71,14 @@ static void fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int nc
         if (kw > fit) kw = fit;
         if (kw > KB) kw = KB;
         const int waves = gp * kw;
-        const int64_t blocks = (ngroups + gp - 1) / gp;
+        const int blocks = (ngroups + gp - 1) / gp;
         const int SB = (KB + kw - 1) / kw;
         const double t_work = work * (double)((waves + 3) / 4) / 3.0;
         for (int gs = 1; gs <= 8 && gs <= SB; ++gs) {
-            const int64_t grid = blocks * gs;
-            if (gs > 1 && grid > 2 * (int64_t)ncu) break;
+            const int grid = blocks * gs;
+            if (gs > 1 && grid > 2 * ncu) break;
             const int n_it = (SB + gs - 1) / gs;
-            const int64_t full = grid / ncu, rest = grid % ncu;
+            const int full = grid / ncu, rest = grid % ncu;
             auto round_us = [&](double active) {
                 const double t_mem = active * waves * rec_bytes / 5.4e6;
                 const double t_it = t_mem > t_work ? t_mem : t_work;
@@ -401,9 +401,8 @@ fq_small_shape fq_plan_grouped_small(int count, int units, int ngroups, int KB) 
     return best;
 }
 
-int fq_launch_gemm(const void* A, int act, int64_t M, int64_t N, int64_t K, const void* codes,
+int fq_launch_gemm(const fq_gemm_plan& plan, const void* A, int act, int64_t M, int64_t N, int64_t K, const void* codes,
                    const void* scales, int bits, int g, void* C, void* workspace, hipStream_t stream) {
-    const fq_gemm_plan plan = fq_plan_gemm(M, N, K, bits, g);
 #define FQ_PICK(ACT)                                                                                        \
     (bits == 3   ? fq_launch_typed_##ACT##_3(A, M, N, K, codes, scales, g, C, workspace, plan, stream)      \
      : bits == 4 ? fq_launch_typed_##ACT##_4(A, M, N, K, codes, scales, g, C, workspace, plan, stream)      \

@@ -75,7 +75,8 @@ inline bool fq_via_f16(int act_dtype, int scale_format, const fq_gemm_plan& p, i
     return act_dtype == FQ_BF16 && p.kind == 1 && p.mt >= 5 && N >= 8192;
 }
 // act: FQ_F16, FQ_BF16, or 2 = bf16 activations with bf16 scales
-int fq_launch_gemm(const void* A, int act, int64_t M, int64_t N, int64_t K, const void* codes,
+// plan: fq_plan_gemm's for these sizes (made once per call: on small matrices making it is a tenth of the call)
+int fq_launch_gemm(const fq_gemm_plan& plan, const void* A, int act, int64_t M, int64_t N, int64_t K, const void* codes,
                    const void* scales, int bits, int g, void* C, void* workspace, hipStream_t stream);
 int fq_launch_gemm_grouped(const void* A, int act, const int32_t* offsets, int E, int64_t N, int64_t K,
                            const void* codes, const void* scales, int bits, int g, void* C,

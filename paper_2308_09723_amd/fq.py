@@ -358,14 +358,22 @@ def gemm(A, codes, scales, bits, group_size, out=None, workspace=None):
     M, K = A.shape
     N = scales.shape[1]
     C = out if out is not None else torch.empty((M, N), dtype=A.dtype, device=A.device)
-    need = gemm_workspace_bytes(M, N, K, bits, group_size)
-    if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = torch.empty(need, dtype=torch.uint8, device=A.device)
-    ws_ptr = workspace.data_ptr() if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _check(gemm_sf_raw(A.data_ptr(), _act_code(A), M, N, K, codes.data_ptr(), scales.data_ptr(),
-                       _scale_format_of(scales), bits, group_size, C.data_ptr(), ws_ptr, ws_bytes, _stream()),
-           "fq_gemm_sf")
+    size = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    if workspace is None:
+        size = gemm_workspace_bytes(M, N, K, bits, group_size)
+        workspace = torch.empty(size, dtype=torch.uint8, device=A.device) if size else None
+
+    def call():
+        return gemm_sf_raw(A.data_ptr(), _act_code(A), M, N, K, codes.data_ptr(), scales.data_ptr(),
+                           _scale_format_of(scales), bits, group_size, C.data_ptr(),
+                           workspace.data_ptr() if workspace is not None else None, size, _stream())
+
+    status = call()
+    if status == FQ_ERR_WORKSPACE:      # the caller's is too small (asked only now: the query plans the product once more)
+        size = gemm_workspace_bytes(M, N, K, bits, group_size)
+        workspace = torch.empty(size, dtype=torch.uint8, device=A.device)
+        status = call()
+    _check(status, "fq_gemm_sf")
     return C
 
 
