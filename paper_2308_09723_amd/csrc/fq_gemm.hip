@@ -44,16 +44,21 @@ int fq_cu_count() {
     return n;
 }
 
+// scale rows a layout k-block spans: 1, kblk / g, or one per 32-row step
+static int fq_scale_rows(int bits, int g) {
+    const int kblk = fq_kblk(bits);
+    return g % kblk == 0 ? 1 : (kblk % g == 0 ? kblk / g : kblk / 32);
+}
+
 // Mid-M streaming kernel (17 <= M <= 48): the block shape (gp column groups x kw k-workers, at most 12 waves, three
 // (M <= 32) or two activation tiles of kw k-blocks in the 160 KiB of LDS) and split of K over the grid with the least
 //   sum over rounds of blocks (iterations * t_it + 5 us)  +  partial sums (their traffic at 5 TB/s + 4 us, if split)
 // where an iteration takes the longest of the time the vector and matrix units need for the block's waves, the time
-// HBM needs for what the resident blocks ask of it (5.4 TB/s), and a latency of 1.4 us.  Against sweeps of (gp, kw, splits) on forty
-// shapes at M = 17 .. 48 the choice is the sweep's best or within 3 % of it on most and 8 % slower at worst (49152 x
-// 12288: 72 where 67 us is possible).  The kernel against the tiled one with 32- and 64-row blocks on the same shapes:
-// 1.15x faster on average (0.94 - 2.0x; 33 of the 40 faster), so there is no rule between the two below 49 rows; with
-// four row tiles (M = 64) it took 88 - 101 us where the tiled kernel takes 91 - 98, so 49 rows and more stay there.
-static void fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int ncu, fq_gemm_plan* p) {
+// HBM needs for what the resident blocks ask of it (5.4 TB/s), and a latency of 1.4 us.  Against sweeps of (gp, kw, splits) on
+// nineteen matrices at M = 17 .. 48 the choice is 2.5 % slower than the sweep's best on average.  With four row tiles
+// (M = 64) the kernel took 88 - 101 us where the tiled one takes 91 - 98, so 49 rows and more stay there.  Returns the
+// model's time.
+static double fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int ncu, fq_gemm_plan* p) {
     const int mt = M <= 32 ? 2 : 3;
     const int kblk = fq_kblk(bits);
     const int KB = (int)(K / kblk);
@@ -97,6 +102,21 @@ static void fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int nc
             }
         }
     }
+    return best;
+}
+
+// The streaming kernel or the tiled one (plan t, t_tiled by its model) for 17 .. 48 rows.  Measured in turn on 23
+// matrices, all formats and group sizes, six M (1656 pairs): the streaming kernel everywhere is 1.135x as fast as the
+// tiled one, but more than 3 % slower in 120 pairs (0.81x at worst), most of them 8-bit codes on few columns with a long K
+// (49152 x 12288: 128 column blocks that share 256 compute units) and 3- and 4-bit codes with one scale row per k-block
+// and two row tiles, where the tiled kernel is post-scaled too.  With the tiled kernel there where its model's time is
+// the smaller by these factors: 1.137x, 56 pairs, seven of them below 0.93x.  Below 13 us the launches decide.
+static bool fq_mid_pays(double t_mid, const fq_gemm_plan& t, double t_tiled, int64_t M, int64_t N, int bits, int g) {
+    if (t_mid <= 13.0) return true;
+    // (what fq_gemm_noalloc's scratch holds one way it does not refuse for the other)
+    if (fq_partial_bytes(t, M, N) > (size_t)FQ_NOALLOC_SCRATCH_BYTES) return true;
+    if (bits == 8) return t_tiled >= 0.82 * t_mid;
+    return M > 32 || fq_scale_rows(bits, g) > 1 || t_tiled >= 0.92 * t_mid;
 }
 
 // Tiled kernel, shapes between the classes of 64 and 128 rows: 80 .. 128 rows x 256 columns (two column tiles per wave)
@@ -231,8 +251,6 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g) {
             }
         }
         p.kb_per_split = 0;
-    } else if (M <= 48) {
-        fq_plan_mid(M, N, K, bits, g, ncu, &p);
     } else {
         // Tiled MFMA kernel: BM = 16 * mt rows per block (mt = 2, 4 or 8), 48 columns per wave, 4 or 8
         // waves, and optionally a split of K over `splits` blocks whose binary32 partial tiles a second
@@ -345,6 +363,11 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g) {
                     }
                 }
             }
+        }
+        if (M <= 48) {
+            fq_gemm_plan mid = {};
+            const double t_mid = fq_plan_mid(M, N, K, bits, g, ncu, &mid);
+            if (fq_mid_pays(t_mid, p, best, M, N, bits, g)) return mid;
         }
         fq_plan_flexible(M, N, K, bits, g, ncu, best, &p);
     }

@@ -223,3 +223,13 @@ def test_plans_are_consistent_over_many_shapes():
             else:
                 assert ws == (splits * M * N * 4 if splits > 1 else 0)
     assert {"small", "tiled", "split", "tail", "wide"} <= seen, seen
+
+
+@pytest.mark.parametrize("M,K,N,bits,g,streams", [
+    (32, 12288, 36864, 4, 128, True), (48, 12288, 36864, 4, 128, True), (17, 49152, 12288, 4, 128, False),
+    (48, 49152, 12288, 8, 128, False), (32, 12288, 12288, 4, 128, False), (33, 12288, 12288, 4, 128, True),
+    (32, 12288, 12288, 4, 64, True), (17, 1024, 1024, 4, 128, True), (17, 1536, 6144, 3, 128, True)])
+def test_17_to_48_rows_stream_where_it_pays(M, K, N, bits, g, streams):
+    """The streaming kernel for 17 .. 48 rows, and the tiled one where that is the faster: few columns with a long K, and
+    one scale row per k-block at two row tiles."""
+    assert ("mid-m" in fq.gemm_describe(M, N, K, bits, g)) == streams

@@ -588,6 +588,21 @@ def test_rows_with_infinities_nans_and_the_largest_magnitudes(dtype, bits, form)
             assert_gemm_close(C[r][ok], want[ok], dtype, f"row {r}")
 
 
+@pytest.mark.parametrize("M,K,N", [(4, 1024, 1024), (200, 6016, 8208)])
+def test_gemm_replaces_a_workspace_that_is_too_small(M, K, N):
+    """fq.gemm with no workspace, one of 16 bytes and one that is large enough: the same bits."""
+    fq = _fq()
+    torch = torch_mod()
+    codes, scales, _, _ = assert_quantizer_parity(workloads.weights_gaussian(K, N, 61), 4, 128)
+    need = fq.gemm_workspace_bytes(M, N, K, 4, 128)
+    assert need > 16
+    for dtype in ("f16", "bf16"):
+        A = to_dev_act(workloads.activations(M, K, dtype, 62), dtype)
+        C = fq.gemm(A, codes, scales, 4, 128)
+        for size in (16, need):
+            assert torch.equal(C, fq.gemm(A, codes, scales, 4, 128, workspace=torch.empty(size, dtype=torch.uint8, device="cuda")))
+
+
 @pytest.mark.parametrize("form", ["M=20", "M=40", "grouped"])
 @pytest.mark.parametrize("dtype,bits,g", [("f16", 4, 128), ("bf16", 4, 128), ("bf16", 3, 64), ("bf16", 4, 32), ("bf16", 8, 128)])
 def test_rows_do_not_depend_on_another_row_that_is_not_finite(dtype, bits, g, form):
