@@ -62,7 +62,7 @@ size_t fq_gemm_workspace_bytes_for(int64_t M, int64_t N, int64_t K, int bits, in
                                    int scale_format) {
     int g = 0;
     if (M <= 0 || check_shape(K, N, bits, group_size, &g) != FQ_OK) return 0;
-    return plan_bytes(fq_plan_gemm(M, N, K, bits, g), M, N, K, act_dtype, scale_format);
+    return plan_bytes(fq_plan_gemm(M, N, K, bits, g, act_dtype), M, N, K, act_dtype, scale_format);
 }
 
 size_t fq_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int bits, int group_size) {
@@ -198,7 +198,7 @@ int fq_gemm_sf(const void* A, int act_dtype, int64_t M, int64_t N, int64_t K, co
     if (M == 0) return FQ_OK;
     if (!A || !codes || !scales_f16 || !C) return FQ_ERR_INVALID_ARG;
     if (M > (int64_t)1 << 24) return FQ_ERR_UNSUPPORTED;
-    const fq_gemm_plan plan = fq_plan_gemm(M, N, K, bits, g);
+    const fq_gemm_plan plan = fq_plan_gemm(M, N, K, bits, g, act_dtype);
     const size_t need = plan_bytes(plan, M, N, K, act_dtype, scale_format);
     if (need > 0 && (!workspace || workspace_bytes < need)) return FQ_ERR_WORKSPACE;
     return fq_launch_gemm(plan, A, kind, M, N, K, codes, scales_f16, bits, g, C, workspace,
@@ -252,7 +252,7 @@ int fq_gemm_noalloc(const void* A, int act_dtype, int64_t M, int64_t N, int64_t 
     if (M == 0) return FQ_OK;
     if (!A || !codes || !scales_f16 || !C) return FQ_ERR_INVALID_ARG;
     if (M > (int64_t)1 << 24) return FQ_ERR_UNSUPPORTED;
-    const fq_gemm_plan plan = fq_plan_gemm(M, N, K, bits, g);
+    const fq_gemm_plan plan = fq_plan_gemm(M, N, K, bits, g, act_dtype);
     const size_t need = plan_bytes(plan, M, N, K, act_dtype, FQ_SCALE_F16);
     if (need > (size_t)FQ_NOALLOC_SCRATCH_BYTES) return FQ_ERR_WORKSPACE;   // beyond the static scratch
     void* ws = nullptr;
@@ -307,14 +307,15 @@ int fq_gemm_describe(int64_t M, int64_t N, int64_t K, int bits, int group_size, 
         snprintf(buf, buf_bytes, "empty");
         return FQ_OK;
     }
-    const fq_gemm_plan p = fq_plan_gemm(M, N, K, bits, g);
+    const fq_gemm_plan p = fq_plan_gemm(M, N, K, bits, g, FQ_BF16);
     if (p.kind == 0) {
         snprintf(buf, buf_bytes, "small-m variant=%d gp=%d kw=%d au=%d waves=%d splits=%d", p.variant, p.gp,
                  p.kw, p.au, p.waves, p.splits);
         return FQ_OK;
     }
     // One form for all products of more than 16 rows.  mt and waves are the class of the block shape (32, 64 or 128
-    // rows, 4 or 8 waves); a shape that is not its class's own follows behind it.
+    // rows, 4 or 8 waves); a shape that is not its class's own follows behind it.  Described for bfloat16 activations; the
+    // shape that binary16 ones take instead needs the same scratch.
     int kbs = p.kb_per_split;
     if (p.kind == 2) {
         const int KB = (int)(K / fq_kblk(bits));
@@ -324,10 +325,13 @@ int fq_gemm_describe(int64_t M, int64_t N, int64_t K, int bits, int group_size, 
                            p.mt <= 2 ? 2 : (p.mt <= 4 ? 4 : 8), p.kind == 2 ? 8 : p.waves, p.splits, kbs, p.tail_tiles,
                            p.tail_tiles > 0 ? p.tail_splits : 1);
     if (n < 0 || (size_t)n >= buf_bytes) return FQ_OK;
+    const fq_gemm_plan f = fq_plan_gemm(M, N, K, bits, g, FQ_F16);
     if (p.kind == 2)
         snprintf(buf + n, buf_bytes - n, " mid-m rows=%d gp=%d kw=%d waves=%d", 16 * p.mt, p.gp, p.kw, p.waves);
     else if (fq_flexible(p))
         snprintf(buf + n, buf_bytes - n, " rows=%d cols=%d", 16 * p.mt, p.waves * p.nt * FQ_NTILE);
+    else if (fq_flexible(f))
+        snprintf(buf + n, buf_bytes - n, " f16: rows=%d cols=%d", 16 * f.mt, f.waves * f.nt * FQ_NTILE);
     return FQ_OK;
 }
 

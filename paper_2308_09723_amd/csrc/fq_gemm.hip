@@ -127,15 +127,21 @@ static bool fq_mid_pays(double t_mid, const fq_gemm_plan& t, double t_tiled, int
 // `u` = microseconds per k-block of a block, fitted like fq_plan_gemm's to sweeps of (shape, split) over five matrices
 // (8192 x 28656, 12288 x 36864, 12288^2, 4096 x 16384, 8192^2) at sixteen M from 72 to 1000: rms error 5 % (7 % for
 // 8-bit codes).  Because the model of the other shapes is off by 10 %, these have to win by that much (15 % for 8-bit
-// codes with k-blocks of 64 rows), and by the rewrite of bfloat16 rows (3 us, see fq_via_f16) where the shape they
-// replace does without: over the 400 records of the sweeps 1.13x faster than the shapes below on average (1.16x if
-// every choice were the best), one choice 2 % slower than before.  fp16 int4, us: 8192 x 28656 g = 64 M = 200
+// codes with k-blocks of 64 rows), and by 3 us more where they replace 32- or 64-row blocks: of the 400 records of the
+// sweeps 186 take them, 1.23x faster on average, one choice 2 % slower than before.  fp16 int4, us: 8192 x 28656 g = 64 M = 200
 // 130 -> 103, M = 160 104 -> 80; 12288^2 M = 160 75 -> 57; 4096 x 16384 M = 384 71 -> 48.
+// bfloat16 activations take these shapes on the fp16 matrix path (fq_via_f16), whose range is binary16's beside a power of
+// two per row and, for bfloat16 scales, one for the matrix.  That is what the 128-row blocks of wide matrices do; the 32- and 64-row
+// blocks multiply bfloat16 operands as they are, so where those are chosen bfloat16 products keep them (a column whose
+// scales lie 2^14 .. 2^20 below the widest came out with errors of 2 % instead of 0.3 %), and binary16 ones leave them
+// only for shapes that need no scratch either (one size serves both types).  A split whose partial sums exceed
+// fq_gemm_noalloc's scratch gives way for both, to these shapes or to the same blocks without a split.
 // Not below 65 rows (the lower classes measure the same), nor above 1024 (1408 x 15456 at M = 1847: 102 -> 109), nor for matrices narrower than 8192 columns, where bfloat16
-// products do not take the fp16 matrix path.  Two scale rows: the 32-row shape stays where it is chosen, because it is
-// the one that multiplies bfloat16 activations post-scaled (unrounded weights) and these would not.  Above 256 rows a
-// plan whose last round is split along K stays: it was the faster one in 26 of 37 such records (up to 1.27x).
-static void fq_plan_flexible(int64_t M, int64_t N, int64_t K, int bits, int g, int ncu, double best, fq_gemm_plan* p) {
+// products do not take the fp16 matrix path.  Two scale rows: the 32-row shape stays where it is chosen (41 against 40 us
+// in the one record).  Above 256 rows a plan whose last round is split along K stays: it was the faster one in 26 of 37 such
+// records (up to 1.27x).
+static void fq_plan_flexible(int64_t M, int64_t N, int64_t K, int bits, int g, int act_dtype, int ncu, double best,
+                             fq_gemm_plan* p) {
     static const struct { int mt, nt; } shapes[5] = {{5, 2}, {6, 2}, {7, 2}, {8, 2}, {5, 3}};
     static const double consts[5][5] = {
         {1.10, 1.22, 1.40, 1.53, 1.53},     // 3- and 4-bit, one scale row per k-block (post-scaled)
@@ -144,6 +150,10 @@ static void fq_plan_flexible(int64_t M, int64_t N, int64_t K, int bits, int g, i
         {1.19, 1.31, 1.46, 1.57, 1.67},     // 8-bit, k-blocks of 128 rows
         {0.62, 0.74, 0.75, 0.85, 0.86}};    // 8-bit, k-blocks of 64 rows
     if (M <= 64 || M > 1024 || N < 8192) return;
+    const bool low = p->mt < 8;      // replaces 32- or 64-row blocks
+    const size_t scratch = FQ_NOALLOC_SCRATCH_BYTES;
+    const bool fits = fq_partial_bytes(*p, M, N) <= scratch;
+    if (low && fits && (act_dtype != FQ_F16 || p->splits > 1 || p->tail_tiles > 0)) return;
     const int kblk = fq_mma_kblk(bits, 8, 8, K, g);
     const int sr = g % kblk == 0 ? 1 : (kblk % g == 0 ? kblk / g : kblk / 32);
     if (bits != 8 && sr == 2 && p->mt == 2) return;
@@ -154,16 +164,17 @@ static void fq_plan_flexible(int64_t M, int64_t N, int64_t K, int bits, int g, i
     const int split_opts[5] = {1, 2, 3, 4, 6};
     // what fq_gemm_noalloc's scratch held for the former shape it has to hold for the new one
     const size_t rewrite = fq_a16_bytes(M, K) + fq_rowscale_bytes(M);
-    const size_t scratch = FQ_NOALLOC_SCRATCH_BYTES;
-    const size_t was_f16 = fq_partial_bytes(*p, M, N), was_bf16 = was_f16 + (p->mt == 8 ? rewrite : 0);
+    const size_t was_f16 = fq_partial_bytes(*p, M, N), was_bf16 = was_f16 + (low ? 0 : rewrite);
     const size_t most_f16 = was_f16 > scratch ? was_f16 : scratch, most_bf16 = was_bf16 > scratch ? was_bf16 : scratch;
-    best = 0.90 * (p->mt < 8 ? best - 3.0 : best);
+    best = 0.90 * (low ? best - 3.0 : best);
     if (bits == 8 && kblk == 64) best *= 0.95;
+    fq_gemm_plan chosen = *p;
+    chosen.splits = 0;
     for (int v = 0; v < 5; ++v) {
         const int bm = shapes[v].mt * 16;
         const int64_t blocks = ((ntiles + 8 * shapes[v].nt - 1) / (8 * shapes[v].nt)) * ((M + bm - 1) / bm);
         for (int si = 0; si < 5; ++si) {
-            if (split_opts[si] > KB) break;
+            if (split_opts[si] > (low && fits ? 1 : KB)) break;
             const int kbs = (KB + split_opts[si] - 1) / split_opts[si];
             const int splits = (KB + kbs - 1) / kbs;
             const size_t partial = splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(float) : 0;
@@ -172,20 +183,28 @@ static void fq_plan_flexible(int64_t M, int64_t N, int64_t K, int bits, int g, i
             if (splits > 1) t += 2.0 * splits * (double)M * (double)N * 4.0 / 5e6 + 5.0;
             if (t < best - 1e-9) {
                 best = t;
-                p->mt = shapes[v].mt;
-                p->nt = shapes[v].nt;
-                p->waves = 8;
-                p->splits = splits;
-                p->kb_per_split = kbs;
-                p->tail_tiles = 0;
-                p->tail_splits = 1;
-                p->tail_kbs = 0;
+                chosen.mt = shapes[v].mt;
+                chosen.nt = shapes[v].nt;
+                chosen.waves = 8;
+                chosen.splits = splits;
+                chosen.kb_per_split = kbs;
             }
         }
     }
+    if (chosen.splits == 0) return;
+    if (low && (act_dtype != FQ_F16 || chosen.splits > 1)) {
+        // (the split does not fit fq_gemm_noalloc's scratch: the same blocks without it)
+        chosen = *p;
+        chosen.splits = 1;
+        chosen.kb_per_split = (int)(K / fq_mma_kblk(bits, p->mt, p->waves, K, g));
+    }
+    chosen.tail_tiles = 0;
+    chosen.tail_splits = 1;
+    chosen.tail_kbs = 0;
+    *p = chosen;
 }
 
-fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g) {
+fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int act_dtype) {
     fq_gemm_plan p = {};
     const int ncu = fq_cu_count();
     const int kblk = fq_kblk(bits);
@@ -369,7 +388,7 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g) {
             const double t_mid = fq_plan_mid(M, N, K, bits, g, ncu, &mid);
             if (fq_mid_pays(t_mid, p, best, M, N, bits, g)) return mid;
         }
-        fq_plan_flexible(M, N, K, bits, g, ncu, best, &p);
+        fq_plan_flexible(M, N, K, bits, g, act_dtype, ncu, best, &p);
     }
     return p;
 }

@@ -41,14 +41,16 @@ namespace fqk {
 // dequantised to binary16 (three more significand bits than bfloat16), and the epilogue multiplies the
 // binary32 sums by the row's power of two before rounding to bfloat16.  The fp16 conversion of the
 // codes is packed (13 vector instructions per 8 weights against 23 for bf16), which is what the large-M
-// loop is short of.  Used by the 128-row shapes only.
+// loop is short of.  Used by the 128-row shapes of wide matrices and by those of 80 rows and more that take their
+// place (not where 32- and 64-row shapes are the choice: those multiply bfloat16 operands).
 #define FQ_BF16_VIA_F16 3
 // Fifth value: the same path for bfloat16 SCALES (FQ_BF16_BS computed with fp16 MFMAs).  A bfloat16 scale has
 // eight significant bits but binary32's exponent range, so the scales are first multiplied by 2^-E, E the
 // exponent of the largest scale of the matrix (searched by fq_rows_to_f16_kernel's first blocks): they then lie in (0, 2) and
 // convert to binary16 exactly unless they are more than 2^14 times smaller than the largest one (those lose
 // low bits or vanish: their weights are below 2^-14 of the matrix's widest group).  q * s * 2^-E is rounded
-// once to binary16 (at most 4 + 8 significant bits: usually exact), and the epilogue multiplies by 2^E.
+// once to binary16 (at most 4 + 8 significant bits: usually exact), and the epilogue multiplies by 2^E.  Post-scaled
+// shapes keep the scales in binary32 and lose nothing.
 #define FQ_BF16S_VIA_F16 4
 
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));

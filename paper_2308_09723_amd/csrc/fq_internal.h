@@ -43,7 +43,8 @@ struct fq_gemm_plan {
 };
 // Block shapes of the tiled kernel beside 32, 64 and 128 rows x 3 column tiles per wave (see fq_plan_flexible)
 inline bool fq_flexible(const fq_gemm_plan& p) { return p.kind == 1 && p.mt >= 5 && !(p.mt == 8 && p.nt == 3); }
-fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g);
+// act_dtype: FQ_F16 or FQ_BF16; the plans differ in the block shape alone (see fq_plan_flexible), not in the scratch
+fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int act_dtype);
 // Rows up to which an expert of a grouped product takes the small-M kernel: 0, 16 or 32
 int32_t fq_small_rows_most(const int32_t* offsets, int E, int64_t N);
 // Block shape of the small-M kernel for `count` items of a grouped product (at most 16 rows each);
@@ -68,8 +69,8 @@ inline size_t fq_partial_bytes(const fq_gemm_plan& p, int64_t M, int64_t N) {
 inline size_t fq_a16_bytes(int64_t M, int64_t K) { return (((size_t)M * (size_t)K * 2) + 255) / 256 * 256; }
 #define FQ_SCALE_PARTS 256
 inline size_t fq_rowscale_bytes(int64_t M) { return ((size_t)M + 2 + FQ_SCALE_PARTS) * sizeof(float); }
-// bf16 activations (binary16 or bfloat16 scales) take the fp16 matrix path for the shapes of 80 rows and more of wide
-// matrices: the rewrite of the rows costs 4 M K bytes of traffic against 2 M N K flops
+// bf16 activations (binary16 or bfloat16 scales) take the fp16 matrix path for the 128-row shapes of wide matrices and the
+// shapes of 80 rows and more that fq_plan_flexible puts in their place: the rewrite of the rows costs 4 M K bytes of traffic against 2 M N K flops
 inline bool fq_via_f16(int act_dtype, int scale_format, const fq_gemm_plan& p, int64_t N) {
     (void)scale_format;
     return act_dtype == FQ_BF16 && p.kind == 1 && p.mt >= 5 && N >= 8192;

@@ -233,3 +233,17 @@ def test_17_to_48_rows_stream_where_it_pays(M, K, N, bits, g, streams):
     """The streaming kernel for 17 .. 48 rows, and the tiled one where that is the faster: few columns with a long K, and
     one scale row per k-block at two row tiles."""
     assert ("mid-m" in fq.gemm_describe(M, N, K, bits, g)) == streams
+
+
+@pytest.mark.parametrize("M,K,N,bits,g,f16", [
+    (250, 2048, 12304, 4, 64, "rows=80 cols=256"), (250, 2048, 12304, 8, 128, "rows=80 cols=256"),
+    (130, 2048, 24592, 4, 32, "rows=80 cols=256"), (200, 2048, 24592, 4, 128, "rows=112 cols=256"),
+    (200, 6016, 8208, 4, 128, None), (160, 28672, 8192, 4, 64, None)])
+def test_32_and_64_row_blocks_give_way_for_binary16_activations_only(M, K, N, bits, g, f16):
+    """The shapes of 80 rows and more take bfloat16 activations (and scales) to the fp16 matrix path, whose range is smaller:
+    where they stand in for 32- and 64-row blocks bfloat16 products keep those, and neither type needs scratch."""
+    desc = fq.gemm_describe(M, N, K, bits, g)
+    assert (f" f16: {f16}" in desc) if f16 else ("f16:" not in desc), desc
+    if f16:
+        assert re.match(r"tiled mt=[24] ", desc) and "splits=1 " in desc and "tail=0x1" in desc
+        assert {fq.gemm_workspace_bytes_for(M, N, K, bits, g, a, s) for a, s in ((0, 0), (1, 0), (1, 1))} == {0}

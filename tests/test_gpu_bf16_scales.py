@@ -147,6 +147,66 @@ def test_gemm_wide_matrix_bf16_scales_spread_over_many_binades():
         assert np.all(err[big] <= 1.6e-2 * col_scale[big])
 
 
+def _columns_over_binades(K, N, binades, seed):
+    """N(0, 0.02) weights, columns times powers of two from 2^14 down over `binades` binades, and a zero column."""
+    W = workloads.weights_gaussian(K, N, seed, outlier_prob=1e-3).astype(np.float32)
+    W *= (2.0 ** (14.0 - (np.arange(N) * 7) % (binades + 1))).astype(np.float32)[None, :]
+    W[:, 5] = 0
+    return W.astype(np.float16)
+
+
+@pytest.mark.parametrize("bits,g,M,K,N", [(4, 64, 250, 2048, 12304), (8, 128, 250, 2048, 12304), (4, 32, 130, 2048, 24592)])
+@pytest.mark.parametrize("what", ["scales", "activations"])
+def test_gemm_65_to_256_rows_keep_bfloat16_range(bits, g, M, K, N, what):
+    """Where binary16 activations take blocks of 80 rows and more in place of 32- and 64-row ones, bfloat16 ones do not: their operands
+    stay bfloat16.  Scales over 24 binades, and activations 2^40 times their neighbours on zero weights: every result
+    within the roundings of its terms' weights and of itself to bfloat16, 2^-9 each (a column or a neighbour that vanishes
+    is off by some 20 times that)."""
+    fq = _fq()
+    torch = torch_mod()
+    desc = fq.gemm_describe(M, N, K, bits, g)
+    _say(f"range int{bits} g={g} M={M} {what}: {desc}")
+    assert "f16: rows=" in desc and "mt=8" not in desc
+    A = workloads.activations(M, K, "bf16", 6602)
+    if what == "scales":
+        W = _columns_over_binades(K, N, 24, 6601)
+        codes, scales, q_ref, s_ref = _quantize_parity(W, bits, g)
+    else:
+        W = workloads.weights_gaussian(K, N, 6601)
+        W[::96] = 0
+        A[:, ::96] = 2.0 ** 40
+        codes, scales = fq.quantize(torch.from_numpy(W).cuda(), bits, g)
+        q_ref, s_ref = oracle.quantize(W, bits, g)
+    C_ref = oracle.gemm_ref(A, q_ref, s_ref)
+    C = from_dev_act(fq.gemm(to_dev_act(A, "bf16"), codes, scales, bits, g), "bf16")
+    terms = np.abs(A.astype(np.float64)) @ np.abs(oracle.dequantize(q_ref, s_ref))
+    assert np.all(np.abs(C - C_ref) <= 1.01 * 2.0 ** -9 * (np.abs(C_ref) + terms))
+
+
+@pytest.mark.parametrize("bits,g,M,K,N,shape", [(4, 64, 300, 512, 8192, "rows=80 cols=256"), (4, 32, 300, 512, 8192, "rows=80 cols=256"),
+                                                (8, 64, 300, 512, 8192, "rows=80 cols=256"), (4, 128, 300, 512, 8192, "rows=80 cols=256"),
+                                                (4, 64, 578, 640, 10256, "rows=112 cols=256"), (4, 128, 1040, 512, 8208, "mt=8 waves=8"),
+                                                (4, 64, 1040, 512, 8208, "mt=8 waves=8"), (8, 128, 1040, 512, 8208, "mt=8 waves=8")])
+def test_gemm_bf16_scales_over_many_binades_on_the_fp16_matrix_path(bits, g, M, K, N, shape):
+    """Scales over 20 binades on the shapes that bring them to binary16 (and the post-scaled one, which does not): with 2^E
+    the largest scale's power of two a scale times its code is off by at most 2^-24 2^E |q| beside the roundings of the
+    weight (2^-11) and the result (2^-9)."""
+    fq = _fq()
+    desc = fq.gemm_describe(M, N, K, bits, g)
+    _say(f"binades int{bits} g={g} M={M}: {desc}")
+    assert shape in desc and ("rows=" in shape or "rows=" not in desc)
+    W = _columns_over_binades(K, N, 20, 6701)
+    codes, scales, q_ref, s_ref = _quantize_parity(W, bits, g)
+    A = workloads.activations(M, K, "bf16", 6702)
+    C = from_dev_act(fq.gemm(to_dev_act(A, "bf16"), codes, scales, bits, g), "bf16")
+    C_ref = oracle.gemm_ref(A, q_ref, s_ref)
+    top = 2.0 ** np.floor(np.log2(s_ref.astype(np.float64).max()))
+    mag = np.abs(A.astype(np.float64))
+    terms = mag @ np.abs(oracle.dequantize(q_ref, s_ref))
+    lost = 2.0 ** -24 * top * (mag @ np.abs(q_ref.astype(np.float64)))
+    assert np.all(np.abs(C - C_ref) <= 2.0 ** -8 * np.abs(C_ref) + 2.0 ** -10 * terms + lost)
+
+
 def test_gemm_split_k_bf16_scales():
     """A shape whose plan splits K (few column blocks, many k-blocks)."""
     _say("gemm bf16 scales split-K")
