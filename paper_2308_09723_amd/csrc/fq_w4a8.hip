@@ -121,7 +121,7 @@ __global__ __launch_bounds__(256) void w8_encode_kernel(const uint16_t* __restri
                                                          uint32_t* __restrict__ codes) {
     __shared__ __align__(16) uint16_t panel[FQ_QP_ROWS * FQ_QP_PITCH];
     __shared__ __align__(16) float sub_scale[4][FQ_QP_COLS];      // z t of the group each 32-row sub-block belongs to
-    __shared__ __align__(16) float sub_rscale[4][FQ_QP_COLS];     // its reciprocal (0 for an all-zero column)
+    __shared__ __align__(16) float sub_rscale[4][FQ_QP_COLS];     // its reciprocal (0 for a step of 0)
     const int tid = threadIdx.x;
     const int64_t n0 = (int64_t)blockIdx.x * FQ_QP_COLS;
     // (bottom of the matrix first: the abs-max pass went top to bottom, and its end is what the Infinity Cache still holds)
@@ -136,6 +136,9 @@ __global__ __launch_bounds__(256) void w8_encode_kernel(const uint16_t* __restri
             const int sb = (tid >> 7) + 2 * h;
             float v = 0.0f;
             if (c < cols) v = (float)z[((k0 + sb * 32) / g) * N + n0 + c] * f16_bits_to_float(tstep[n0 + c]);   // exact
+            // an infinite weight makes its column's step infinite: w / infinity = 0 for the finite ones (fq_encode_biased
+            // would form 0 * infinity; with 0 for the step it gives 0 for them and what a NaN gives for the infinite one)
+            if (v == __builtin_inff()) v = 0.0f;
             sub_scale[sb][c] = v;
             sub_rscale[sb][c] = v == 0.0f ? 0.0f : __fdiv_rn(1.0f, v);
         }

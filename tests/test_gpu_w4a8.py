@@ -225,6 +225,31 @@ def test_weight_quantiser_panels_and_long_groups(K, N, g):
     _quantize_weights(W, g)
 
 
+@pytest.mark.parametrize("g", [32, 128, 0])
+def test_weight_quantiser_columns_with_infinities_and_nans(g):
+    """An infinite weight makes its column's step infinite: the finite weights of the column become 0 (w / infinity), the
+    infinite one what a NaN becomes, the lowest code.  A NaN makes the step a NaN and every code the lowest.  Other
+    columns do not change."""
+    from paper_2308_09723_amd import fq
+    torch = torch_mod()
+    K, N = 512, 144
+    W = workloads.weights_gaussian(K, N, 71)
+    _, _, _, q_ref, z_ref, t_ref = _quantize_weights(W, g)
+    Wn = W.copy()
+    Wn[5, 3], Wn[400, 9], Wn[40, 20] = np.inf, -np.inf, np.nan
+    codes, z, t = fq.quantize_w4a8(torch.from_numpy(Wn).cuda(), g)
+    q = fq.unpack_w4a8(codes, K, N).cpu().numpy()
+    t = t.cpu().numpy()
+    want = q_ref.copy()
+    want[:, [3, 9]] = 0
+    want[5, 3] = want[400, 9] = -7
+    want[:, 20] = -7
+    assert np.array_equal(q, want)
+    keep = [n for n in range(N) if n not in (3, 9, 20)]
+    assert np.isinf(t[[3, 9]]).all() and np.isnan(t[20]) and np.array_equal(t[keep], t_ref[keep])
+    assert np.array_equal(z.cpu().numpy()[:, keep], z_ref[:, keep]) and (z.cpu().numpy()[:, [3, 9, 20]] == 1).all()
+
+
 @pytest.mark.parametrize("M,K", [(600, 2056), (513, 16384), (5, 2048), (5, 2056), (3, 65536), (2, 65544), (520, 16392)])
 def test_activation_quantiser_row_kernels(M, K):
     """The row kernels (four waves for many rows or short ones, sixteen otherwise) at the edges of what their registers
