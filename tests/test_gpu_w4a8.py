@@ -262,3 +262,13 @@ def test_activation_quantiser_row_kernels(M, K):
             A[2] = 0
         A = A.astype(np.float16) if dtype == "f16" else workloads.round_to_bf16(A)
         _quantize_acts(A, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("M,K", [(3, 65544), (3, 65543), (2, 131072)])
+def test_activation_quantiser_rows_longer_than_the_registers(M, K, dtype):
+    """Rows of more than 65536 values, in whole 16-byte units and not: the kernel that reads them twice."""
+    A = workloads.activations(M, K, dtype, 950 + M).astype(np.float32)
+    A[1] *= np.float32(1e-36 if dtype == "bf16" else 2.0 ** -14)
+    A[0, K - 1] = 40.0
+    _quantize_acts(A.astype(np.float16) if dtype == "f16" else workloads.round_to_bf16(A), dtype)
