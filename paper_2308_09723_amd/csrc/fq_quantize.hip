@@ -458,7 +458,7 @@ __global__ __launch_bounds__(256) void fq_quant_error_kernel(const uint16_t* __r
                 const uint32_t s2 = *reinterpret_cast<const uint32_t*>(scales + ((k0 + krel) / g) * N + n0 + c);
                 const float f0 = scale_bits_to_float((uint16_t)s2, sfmt), f1 = scale_bits_to_float((uint16_t)(s2 >> 16), sfmt);
                 const uint32_t w0 = BITS == 8 ? 0u : step_word<BITS>(d0, t), w1 = BITS == 8 ? 0u : step_word<BITS>(d1, t);
-                const float u0 = CODE_UNIT<BITS> * f0, u1 = CODE_UNIT<BITS> * f1;   // exact
+                const float u0 = CODE_UNIT<BITS> * f0, u1 = CODE_UNIT<BITS> * f1;   // exact (binary16 scales)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const uint32_t w2 = *reinterpret_cast<const uint32_t*>(&panel[(krel + e) * FQ_QP_PITCH + c]);
@@ -470,9 +470,9 @@ __global__ __launch_bounds__(256) void fq_quant_error_kernel(const uint16_t* __r
                         sse = __builtin_fma((double)e1, (double)e1, sse);
                         mxf = fmaxf(mxf, fmaxf(fabsf(e0), fabsf(e1)));
                     } else {
-                        // (the products and differences are exact in binary64)
-                        const double e0 = __builtin_fma(-(double)q0, (double)u0, (double)wf0);
-                        const double e1 = __builtin_fma(-(double)q1, (double)u1, (double)wf1);
+                        // (the products and differences are exact in binary64; a bfloat16 scale may reach 2^127)
+                        const double e0 = __builtin_fma(-(double)(CODE_UNIT<BITS> * q0), (double)f0, (double)wf0);
+                        const double e1 = __builtin_fma(-(double)(CODE_UNIT<BITS> * q1), (double)f1, (double)wf1);
                         sse = __builtin_fma(e0, e0, sse);
                         sse = __builtin_fma(e1, e1, sse);
                         mx = fmax(mx, fmax(fabs(e0), fabs(e1)));

@@ -273,6 +273,21 @@ def test_quant_error_bf16_scales():
         assert abs(sse - sse_ref) <= 1e-11 * sse_ref
 
 
+@pytest.mark.parametrize("bits", [3, 4, 8])
+def test_quant_error_of_the_largest_bf16_scales(bits):
+    """A caller's bfloat16 scales next to binary32's largest: the error is that scale times the code, in binary64."""
+    fq = _fq()
+    torch = torch_mod()
+    W = workloads.weights_gaussian(256, 48, 6401)
+    codes, scales, q_ref, s_ref = _quantize_parity(W, bits, 64)
+    scales[1, 7] = 2.0 ** 127
+    s64 = s_ref.astype(np.float64)
+    s64[1, 7] = 2.0 ** 127
+    err = W.astype(np.float64) - q_ref.astype(np.float64) * np.repeat(s64, 64, axis=0)
+    sse, mx = fq.quant_error(torch.from_numpy(W).cuda(), codes, scales, bits, 64)
+    assert mx == np.abs(err).max() and abs(sse - np.sum(err * err)) <= 1e-11 * np.sum(err * err)
+
+
 def test_bf16_scales_need_bf16_activations():
     fq = _fq()
     torch = torch_mod()
