@@ -54,10 +54,12 @@ static int fq_scale_rows(int bits, int g) {
 // (M <= 32) or two activation tiles of kw k-blocks in the 160 KiB of LDS) and split of K over the grid with the least
 //   sum over rounds of blocks (iterations * t_it + 5 us)  +  partial sums (their traffic at 5 TB/s + 4 us, if split)
 // where an iteration takes the longest of the time the vector and matrix units need for the block's waves, the time
-// HBM needs for what the resident blocks ask of it (5.4 TB/s), and a latency of 1.4 us.  Against sweeps of (gp, kw, splits) on
-// nineteen matrices at M = 17 .. 48 the choice is 2.5 % slower than the sweep's best on average.  With four row tiles
-// (M = 64) the kernel took 88 - 101 us where the tiled one takes 91 - 98, so 49 rows and more stay there.  Returns the
-// model's time.
+// memory needs for what the resident blocks ask of it (weights, and three tenths of the activations, which come from the L2
+// caches, at 7 TB/s), and a latency of 1.4 us.  (Without the activations shapes of one column group and twelve k-workers won,
+// which load twice their weights in activations: 8-bit codes on 49152 x 12288, M = 32 125 us where 4 x 3 in four splits takes
+// 104.)  Against sweeps of (gp, kw, splits) on nineteen matrices at M = 17 .. 48 the choice is 2 % slower than the sweep's
+// best on average.  With four row tiles (M = 64) the kernel took 88 - 101 us where the tiled one takes 91 - 98, so 49 rows
+// and more stay there.  Returns the model's time.
 static double fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int ncu, fq_gemm_plan* p) {
     const int mt = M <= 32 ? 2 : 3;
     const int kblk = fq_kblk(bits);
@@ -85,7 +87,7 @@ static double fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int 
             const int n_it = (SB + gs - 1) / gs;
             const int full = grid / ncu, rest = grid % ncu;
             auto round_us = [&](double active) {
-                const double t_mem = active * waves * rec_bytes / 5.4e6;
+                const double t_mem = active * (waves * rec_bytes + 0.3 * kw * tile_bytes) / 7e6;
                 const double t_it = t_mem > t_work ? t_mem : t_work;
                 return n_it * (t_it > 1.4 ? t_it : 1.4) + 5.0;
             };
@@ -106,17 +108,15 @@ static double fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int 
 }
 
 // The streaming kernel or the tiled one (plan t, t_tiled by its model) for 17 .. 48 rows.  Measured in turn on 23
-// matrices, all formats and group sizes, six M (1656 pairs): the streaming kernel everywhere is 1.135x as fast as the
-// tiled one, but more than 3 % slower in 120 pairs (0.81x at worst), most of them 8-bit codes on few columns with a long K
-// (49152 x 12288: 128 column blocks that share 256 compute units) and 3- and 4-bit codes with one scale row per k-block
-// and two row tiles, where the tiled kernel is post-scaled too.  With the tiled kernel there where its model's time is
-// the smaller by these factors: 1.137x, 56 pairs, seven of them below 0.93x.  Below 13 us the launches decide.
+// matrices, all formats and group sizes, six M (1656 pairs): the streaming kernel everywhere is 1.142x as fast as the
+// tiled one, but more than 3 % slower in 103 pairs (down to 0.86x; 50 pairs differ that much when both sides are the
+// same kernel), most of them 3- and 4-bit codes with one scale row per k-block and two row tiles, where the tiled kernel
+// is post-scaled too.  With the tiled kernel there where its model's time is 0.92 of the other's or less: 1.143x, 69 pairs.
+// Below 13 us the launches decide.
 static bool fq_mid_pays(double t_mid, const fq_gemm_plan& t, double t_tiled, int64_t M, int64_t N, int bits, int g) {
-    if (t_mid <= 13.0) return true;
+    if (t_mid <= 13.0 || bits == 8 || M > 32 || fq_scale_rows(bits, g) > 1) return true;
     // (what fq_gemm_noalloc's scratch holds one way it does not refuse for the other)
-    if (fq_partial_bytes(t, M, N) > (size_t)FQ_NOALLOC_SCRATCH_BYTES) return true;
-    if (bits == 8) return t_tiled >= 0.82 * t_mid;
-    return M > 32 || fq_scale_rows(bits, g) > 1 || t_tiled >= 0.92 * t_mid;
+    return t_tiled >= 0.92 * t_mid || fq_partial_bytes(t, M, N) > (size_t)FQ_NOALLOC_SCRATCH_BYTES;
 }
 
 // Tiled kernel, shapes between the classes of 64 and 128 rows: 80 .. 128 rows x 256 columns (two column tiles per wave)

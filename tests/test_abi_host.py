@@ -227,11 +227,11 @@ def test_plans_are_consistent_over_many_shapes():
 
 @pytest.mark.parametrize("M,K,N,bits,g,streams", [
     (32, 12288, 36864, 4, 128, True), (48, 12288, 36864, 4, 128, True), (17, 49152, 12288, 4, 128, False),
-    (48, 49152, 12288, 8, 128, False), (32, 12288, 12288, 4, 128, False), (33, 12288, 12288, 4, 128, True),
+    (48, 49152, 12288, 8, 128, True), (32, 12288, 36864, 8, 128, True), (32, 12288, 12288, 4, 128, False), (33, 12288, 12288, 4, 128, True),
     (32, 12288, 12288, 4, 64, True), (17, 1024, 1024, 4, 128, True), (17, 1536, 6144, 3, 128, True)])
 def test_17_to_48_rows_stream_where_it_pays(M, K, N, bits, g, streams):
-    """The streaming kernel for 17 .. 48 rows, and the tiled one where that is the faster: few columns with a long K, and
-    one scale row per k-block at two row tiles."""
+    """The streaming kernel for 17 .. 48 rows, and the tiled one where that is the faster: one scale row per k-block at two
+    row tiles, on few columns."""
     assert ("mid-m" in fq.gemm_describe(M, N, K, bits, g)) == streams
 
 
@@ -247,3 +247,30 @@ def test_32_and_64_row_blocks_give_way_for_binary16_activations_only(M, K, N, bi
     if f16:
         assert re.match(r"tiled mt=[24] ", desc) and "splits=1 " in desc and "tail=0x1" in desc
         assert {fq.gemm_workspace_bytes_for(M, N, K, bits, g, a, s) for a, s in ((0, 0), (1, 0), (1, 1))} == {0}
+
+
+def test_streaming_plans_fit_the_block_and_the_scratch():
+    """Plans of the streaming kernel over a seeded sweep: waves, activation tiles and sums within a block's limits, no more
+    splits than super-blocks, scratch of exactly the split's partial sums and never more than fq_gemm_noalloc holds."""
+    import numpy as np
+    rng = np.random.default_rng(23)
+    seen = 0
+    for _ in range(800):
+        bits = int(rng.choice([3, 4, 8]))
+        kblk = 64 if bits == 8 else 128
+        K, N, M = kblk * int(rng.integers(1, 800)), 16 * int(2.0 ** rng.uniform(0, 14)), int(rng.integers(17, 49))
+        g = int(rng.choice([g for g in (32, 64, 96, 128, 256, 0) if g == 0 or K % g == 0]))
+        desc = fq.gemm_describe(M, N, K, bits, g)
+        m = re.search(r" mid-m rows=(\d+) gp=(\d+) kw=(\d+) waves=(\d+)$", desc)
+        ws = {fq.gemm_workspace_bytes_for(M, N, K, bits, g, a, s) for a, s in ((0, 0), (1, 0), (1, 1))}
+        if m is None:
+            continue
+        seen += 1
+        rows, gp, kw, waves = map(int, m.groups())
+        splits = int(re.search(r"splits=(\d+)", desc).group(1))
+        assert rows == (32 if M <= 32 else 48) and 1 <= gp * kw == waves <= 12
+        assert (3 if rows == 32 else 2) * kw * rows * kblk * 2 <= 160 * 1024 and waves * rows * 48 * 4 <= 160 * 1024
+        KB = K // kblk
+        assert kw <= KB and 1 <= splits <= -(-KB // kw)
+        assert ws == {splits * M * N * 4 if splits > 1 else 0} and max(ws) <= fq.gemm_noalloc_scratch_bytes()
+    assert seen > 500
