@@ -136,8 +136,8 @@ static bool fq_mid_pays(double t_mid, const fq_gemm_plan& t, double t_tiled, int
 // scales lie 2^14 .. 2^20 below the widest came out with errors of 2 % instead of 0.3 %), and binary16 ones leave them
 // only for shapes that need no scratch either (one size serves both types).  A split whose partial sums exceed
 // fq_gemm_noalloc's scratch gives way for both, to these shapes or to the same blocks without a split.
-// Not below 65 rows (the lower classes measure the same), nor above 1024 (1408 x 15456 at M = 1847: 102 -> 109), nor for matrices narrower than 8192 columns, where bfloat16
-// products do not take the fp16 matrix path.  Two scale rows: the 32-row shape stays where it is chosen (41 against 40 us
+// Not below 65 rows (the lower classes measure the same), nor above 1024 (1408 x 15456 at M = 1847: 102 -> 109), nor for
+// matrices narrower than 8192 columns, where bfloat16 products do not take the fp16 matrix path.  Two scale rows: the 32-row shape stays where it is chosen (41 against 40 us
 // in the one record).  Above 256 rows a plan whose last round is split along K stays: it was the faster one in 26 of 37 such
 // records (up to 1.27x).
 static void fq_plan_flexible(int64_t M, int64_t N, int64_t K, int bits, int g, int act_dtype, int ncu, double best,

@@ -790,7 +790,7 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_skinny_kernel(
 //    fused multiply-add per element.
 // Against the tiled kernel with 32 rows per block: no split of K over the grid (no partial sums through memory, no
 // second kernel), and a barrier per KW k-blocks instead of one per k-block.  12288 x 36864, int4 g = 128, M = 32
-// (us): bf16 60 -> 49.5 (4.8 TB/s of weights), fp16 56 -> 49; M = 48: 94 -> 64.
+// (us): bf16 60 -> 49 (4.8 TB/s of weights), fp16 53 -> 50; M = 48: 85 -> 61 and 81 -> 60; g = 32, M = 32: 88 -> 68 and 77 -> 60.
 // LDS tile of k-worker kw, in 16-byte units: unit(row, kc) = row * KC + (kc ^ swz(row)): a wave-level direct load
 // fills whole rows, a fragment read (16 rows of one kc) touches 16 different bank groups.
 // ==========================================================================================

@@ -104,8 +104,9 @@ def test_gemm_tiled_bf16_scales(bits, g, M):
 
 @pytest.mark.parametrize("bits,g,M", [(4, 128, 300), (4, 64, 130), (4, 32, 260), (8, 0, 300), (8, 64, 140), (3, 128, 300)])
 def test_gemm_wide_matrix_bf16_scales_on_the_fp16_matrix_path(bits, g, M):
-    """128-row blocks of a wide matrix (N >= 8192): bfloat16 scales are brought to binary16 through a common
-    power of two and the product runs on the fp16 matrix path (the plan's description names the block shape)."""
+    """Wide matrices (N >= 8192): at 260 and 300 rows bfloat16 scales are brought to binary16 through a common power of
+    two and the product runs on the fp16 matrix path; at 130 and 140 rows it keeps 32-row blocks and bfloat16 operands
+    (the plan's description names the block shape)."""
     fq = _fq()
     K, N = 512, 8192
     desc = fq.gemm_describe(M, N, K, bits, g)
