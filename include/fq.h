@@ -315,6 +315,15 @@ int fq_gemm_describe(int64_t M, int64_t N, int64_t K, int bits, int group_size, 
                      size_t buf_bytes);
 
 /*
+ * fq_gemm_grouped_describe -- the same for fq_gemm_grouped: "rows128=.. rows64=.. mid-m=.. (gp=.. kw=..) small-m=..
+ * streams=..", the number of row tiles per kernel (128 and 64 rows of the tiled kernel, up to 48 of the streaming one, up
+ * to 16 of the small-M one) and the number of streams their launches are spread over.
+ * Returns FQ_OK, or the status fq_gemm_grouped would return for these sizes and offsets.
+ */
+int fq_gemm_grouped_describe(const int32_t* offsets_host, int E, int64_t N, int64_t K, int bits, int group_size,
+                             char* buf, size_t buf_bytes);
+
+/*
  * fq_stream_read_probe -- measurement helper, not part of the method: one kernel that reads
  * `bytes` bytes of device memory (16 bytes per lane, grid-stride, 256 blocks of 768 threads: the
  * launch shape of the small-M product) and writes one 32-bit checksum word per block to `sink`

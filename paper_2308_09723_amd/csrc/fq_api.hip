@@ -268,6 +268,16 @@ int fq_gemm_noalloc(const void* A, int act_dtype, int64_t M, int64_t N, int64_t 
 
 size_t fq_gemm_noalloc_scratch_bytes(void) { return (size_t)FQ_NOALLOC_SCRATCH_BYTES; }
 
+static int check_grouped(const int32_t* offsets_host, int E, int64_t N, int64_t K, int bits, int group_size, int* g) {
+    if (E > 256) return FQ_ERR_UNSUPPORTED;
+    const int st = check_shape(K, N, bits, group_size, g);
+    if (st != FQ_OK || E == 0) return st;
+    if (offsets_host[0] != 0) return FQ_ERR_INVALID_ARG;
+    for (int e = 0; e < E; ++e)
+        if (offsets_host[e + 1] < offsets_host[e]) return FQ_ERR_INVALID_ARG;
+    return FQ_OK;
+}
+
 int fq_gemm_grouped(const void* A, int act_dtype, const int32_t* offsets_host, int E, int64_t N,
                     int64_t K, const void* codes, const void* scales_f16, int bits, int group_size,
                     void* C, void* workspace, size_t workspace_bytes, void* stream) {
@@ -283,18 +293,33 @@ int fq_gemm_grouped_sf(const void* A, int act_dtype, const int32_t* offsets_host
     int kst = FQ_OK;
     const int kind = act_kind(act_dtype, scale_format, &kst);
     if (kst != FQ_OK) return kst;
-    if (E > 256) return FQ_ERR_UNSUPPORTED;
     int g = 0;
-    const int st = check_shape(K, N, bits, group_size, &g);
+    const int st = check_grouped(offsets_host, E, N, K, bits, group_size, &g);
     if (st != FQ_OK) return st;
-    if (E == 0) return FQ_OK;
-    if (offsets_host[0] != 0) return FQ_ERR_INVALID_ARG;
-    for (int e = 0; e < E; ++e)
-        if (offsets_host[e + 1] < offsets_host[e]) return FQ_ERR_INVALID_ARG;
-    if (offsets_host[E] == 0) return FQ_OK;
+    if (E == 0 || offsets_host[E] == 0) return FQ_OK;
     if (!A || !codes || !scales_f16 || !C) return FQ_ERR_INVALID_ARG;
     return fq_launch_gemm_grouped(A, kind, offsets_host, E, N, K, codes, scales_f16, bits, g, C,
                                   (hipStream_t)stream);
+}
+
+int fq_gemm_grouped_describe(const int32_t* offsets_host, int E, int64_t N, int64_t K, int bits, int group_size,
+                             char* buf, size_t buf_bytes) {
+    if (!offsets_host || E < 0 || !buf || buf_bytes == 0) return FQ_ERR_INVALID_ARG;
+    int g = 0;
+    const int st = check_grouped(offsets_host, E, N, K, bits, group_size, &g);
+    if (st != FQ_OK) return st;
+    if (E == 0 || offsets_host[E] == 0) {
+        snprintf(buf, buf_bytes, "empty");
+        return FQ_OK;
+    }
+    const fq_grouped_plan p = fq_plan_grouped(offsets_host, E, N, K, bits, g);
+    int count[FQ_TILE_CLASSES] = {}, classes = 0;
+    for (int e = 0; e < E; ++e)
+        for (int32_t left = offsets_host[e + 1] - offsets_host[e], take = 0; left > 0; left -= take)
+            classes += count[fq_next_tile(p, left, &take)]++ == 0;
+    snprintf(buf, buf_bytes, "rows128=%d rows64=%d mid-m=%d (gp=%d kw=%d) small-m=%d streams=%d", count[FQ_TILE_128],
+             count[FQ_TILE_64], count[FQ_TILE_MID], p.mid.gp, p.mid.kw, count[FQ_TILE_SMALL], p.fork ? classes : 1);
+    return FQ_OK;
 }
 
 int fq_gemm_describe(int64_t M, int64_t N, int64_t K, int bits, int group_size, char* buf,

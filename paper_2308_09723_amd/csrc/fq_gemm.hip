@@ -17,9 +17,10 @@ using namespace fqd;
     int fq_launch_typed_##ACT##_##BITS(const void* A, int64_t M, int64_t N, int64_t K, const void* codes,  \
                                        const void* scales, int g, void* C, void* workspace,                \
                                        const fq_gemm_plan& plan, hipStream_t stream);                      \
-    int fq_launch_grouped_typed_##ACT##_##BITS(const void* A, const int32_t* offsets, int E, int64_t N,    \
-                                               int64_t K, const void* codes, const void* scales, int g,    \
-                                               void* C, const hipStream_t* streams);
+    int fq_launch_grouped_typed_##ACT##_##BITS(const void* A, const int32_t* offsets, int E,               \
+                                               const fq_grouped_plan& plan, int64_t N, int64_t K,          \
+                                               const void* codes, const void* scales, int g, void* C,      \
+                                               const hipStream_t* streams);
 FQ_DECLARE_GEMM(0, 4)
 FQ_DECLARE_GEMM(0, 8)
 FQ_DECLARE_GEMM(1, 4)
@@ -60,37 +61,53 @@ static int fq_scale_rows(int bits, int g) {
 // 104.)  Against sweeps of (gp, kw, splits) on nineteen matrices at M = 17 .. 48 the choice is 2 % slower than the sweep's
 // best on average.  With four row tiles (M = 64) the kernel took 88 - 101 us where the tiled one takes 91 - 98, so 49 rows
 // and more stay there.  Returns the model's time.
+struct fq_mid_model {
+    int KB, fit;         // k-blocks; k-workers whose activation tiles fit the LDS
+    double work;         // microseconds of vector / matrix work per iteration of a full block (12 waves, a k-block of 48 columns each)
+    double rec_bytes;    // codes and scales a wave loads per iteration
+    int tile_bytes;      // activation tile of a k-worker
+    fq_mid_model(int mt, int64_t K, int bits, int g) {
+        const int kblk = fq_kblk(bits), sr = fq_scale_rows(bits, g);
+        KB = (int)(K / kblk);
+        work = mt <= 2 ? (bits == 8 ? 0.85 : (bits == 3 ? 1.75 : 1.5)) : (bits == 8 ? 1.3 : (bits == 3 ? 2.6 : 2.4));
+        work += (sr - 1) * (mt <= 2 ? 0.27 : 0.4);
+        rec_bytes = MMA_NT * 64.0 * fq_rec_bytes(bits) + MMA_NT * 32.0 * sr;
+        tile_bytes = mt * 16 * kblk * 2;
+        fit = 160 * 1024 / ((mt == 3 ? 2 : 3) * tile_bytes);
+    }
+    // the most k-workers for gp column groups
+    int workers(int gp) const {
+        int kw = 12 / gp;
+        if (kw > fit) kw = fit;
+        return kw > KB ? KB : kw;
+    }
+    // one iteration of a block: vector / matrix work, and memory at `rate` bytes per microsecond when `active` blocks are resident
+    double compute(int waves) const { return work * (double)((waves + 3) / 4) / 3.0; }
+    double memory(int gp, int kw, double active, double rate) const {
+        return active * (gp * kw * rec_bytes + 0.3 * kw * tile_bytes) / rate;
+    }
+    double iteration(int gp, int kw, double active) const {
+        const double t_work = compute(gp * kw), t_mem = memory(gp, kw, active, 7e6);
+        const double t_it = t_mem > t_work ? t_mem : t_work;
+        return t_it > 1.4 ? t_it : 1.4;
+    }
+};
+
 static double fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int ncu, fq_gemm_plan* p) {
     const int mt = M <= 32 ? 2 : 3;
-    const int kblk = fq_kblk(bits);
-    const int KB = (int)(K / kblk);
+    const fq_mid_model model(mt, K, bits, g);
     const int ngroups = (int)((N / FQ_NTILE + MMA_NT - 1) / MMA_NT);
-    const int sr = g % kblk == 0 ? 1 : (kblk % g == 0 ? kblk / g : kblk / 32);
-    // microseconds of vector / matrix work per iteration of a full block (12 waves, one k-block of 48 columns each)
-    double work = mt == 2 ? (bits == 8 ? 0.85 : (bits == 3 ? 1.75 : 1.5)) : (bits == 8 ? 1.3 : (bits == 3 ? 2.6 : 2.4));
-    work += (sr - 1) * (mt == 2 ? 0.27 : 0.4);
-    const double rec_bytes = MMA_NT * 64.0 * fq_rec_bytes(bits) + MMA_NT * 32.0 * sr;   // per wave and iteration
-    const int tile_bytes = mt * 16 * kblk * 2;
     double best = 1e30;
     for (int gp = 1; gp <= 12; ++gp) {
-        int kw = 12 / gp;
-        const int fit = 160 * 1024 / ((mt == 2 ? 3 : 2) * tile_bytes);
-        if (kw > fit) kw = fit;
-        if (kw > KB) kw = KB;
-        const int waves = gp * kw;
+        const int kw = model.workers(gp);
         const int blocks = (ngroups + gp - 1) / gp;
-        const int SB = (KB + kw - 1) / kw;
-        const double t_work = work * (double)((waves + 3) / 4) / 3.0;
+        const int SB = (model.KB + kw - 1) / kw;
         for (int gs = 1; gs <= 8 && gs <= SB; ++gs) {
             const int grid = blocks * gs;
             if (gs > 1 && grid > 2 * ncu) break;
             const int n_it = (SB + gs - 1) / gs;
             const int full = grid / ncu, rest = grid % ncu;
-            auto round_us = [&](double active) {
-                const double t_mem = active * (waves * rec_bytes + 0.3 * kw * tile_bytes) / 7e6;
-                const double t_it = t_mem > t_work ? t_mem : t_work;
-                return n_it * (t_it > 1.4 ? t_it : 1.4) + 5.0;
-            };
+            auto round_us = [&](double active) { return n_it * model.iteration(gp, kw, active) + 5.0; };
             double t = (double)full * round_us((double)ncu) + (rest ? round_us((double)rest) : 0.0);
             if (gs > 1) t += 2.0 * gs * (double)M * (double)N * 4.0 / 5e6 + 4.0;
             if (t < best - 1e-9) {
@@ -99,7 +116,7 @@ static double fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int 
                 p->mt = mt;
                 p->gp = gp;
                 p->kw = kw;
-                p->waves = waves;
+                p->waves = gp * kw;
                 p->splits = gs;
             }
         }
@@ -204,6 +221,18 @@ static void fq_plan_flexible(int64_t M, int64_t N, int64_t K, int bits, int g, i
     *p = chosen;
 }
 
+// Microseconds a block of the tiled kernel spends on 128 rows of K (see fq_plan_gemm):
+//   u8(mt=2) u4(mt=2) u8(mt=4) u4(mt=4) u8(mt=8) u4(mt=8)  lone 4-wave block factor (mt < 8, mt = 8)
+static const double* fq_tiled_costs(int bits, int g) {
+    static const double consts[4][8] = {
+        {0.99, 0.506, 1.43, 0.83, 2.33, 1.43, 1.2, 1.2},     // 4-bit, one scale row per k-block
+        {1.17, 0.634, 1.60, 0.884, 2.34, 1.46, 1.2, 1.2},    // 4-bit, two scale rows
+        {1.64, 0.731, 2.16, 1.29, 2.70, 1.57, 1.5, 1.35},    // 4-bit, four scale rows
+        {1.73, 0.77, 1.73, 1.035, 2.50, 1.47, 1.2, 1.35}};   // 8-bit
+    const int sr = g % 128 == 0 ? 1 : (128 % g == 0 ? 128 / g : 4);
+    return consts[bits == 8 ? 3 : (sr == 1 ? 0 : (sr == 2 ? 1 : 2))];
+}
+
 fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int act_dtype) {
     fq_gemm_plan p = {};
     const int ncu = fq_cu_count();
@@ -287,14 +316,7 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
         // converting the weights again) and often win there, e.g. QKV at M = 128 in two 64-row blocks
         // and no split of K; beyond 256 rows only the 128-row shapes are candidates.
         p.kind = 1;
-        //   u8(mt=2) u4(mt=2) u8(mt=4) u4(mt=4) u8(mt=8) u4(mt=8)  lone 4-wave block factor (mt < 8, mt = 8)
-        static const double consts[4][8] = {
-            {0.99, 0.506, 1.43, 0.83, 2.33, 1.43, 1.2, 1.2},     // 4-bit, one scale row per k-block
-            {1.17, 0.634, 1.60, 0.884, 2.34, 1.46, 1.2, 1.2},    // 4-bit, two scale rows
-            {1.64, 0.731, 2.16, 1.29, 2.70, 1.57, 1.5, 1.35},    // 4-bit, four scale rows
-            {1.73, 0.77, 1.73, 1.035, 2.50, 1.47, 1.2, 1.35}};   // 8-bit
-        const int sr4 = g % 128 == 0 ? 1 : (128 % g == 0 ? 128 / g : 4);
-        const double* cs = consts[bits == 8 ? 3 : (sr4 == 1 ? 0 : (sr4 == 2 ? 1 : 2))];
+        const double* cs = fq_tiled_costs(bits, g);
         const int split_opts[6] = {1, 2, 3, 4, 6, 8};
         double best = 1e30;
         p.nt = MMA_NT;
@@ -393,28 +415,18 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
     return p;
 }
 
-// 16 (the small-M kernel for experts of at most 16 rows) with two exceptions:
-//  - 32: no expert has more than 32 rows and at most one in nine more than 16.  Those few become two items each (their
-//    weights are read twice, mostly from a cache the second time): a kernel of their own beside it costs the fork to
-//    another stream and more compute units than the second reading (64 experts, 96 rows: 237 -> 216 us).
-//  - 0: some expert has more rows and the tiles of all experts are resident at once.  The call then takes as long as its
-//    taller tiles walk K, which the small-M kernel cannot shorten, while its blocks take compute units away from them
-//    (16 experts of 15488 x 4320, 8-bit, 174 rows: 284 us with it, 241 without).
-int32_t fq_small_rows_most(const int32_t* offsets, int E, int64_t N) {
-    const int waves_cols = 3 * (N / FQ_NTILE >= 48 ? 8 : 4);       // column tiles of a 32- or 64-row tile's block
-    const int64_t nblocks_n = (N / FQ_NTILE + waves_cols - 1) / waves_cols;
-    int n16 = 0, n32 = 0, more = 0;
-    int64_t tiles = 0;
+// Whether all experts of a grouped product may take the small-M kernel: none has more than 16 rows, or none more than 32
+// and at most one in nine more than 16 (those few become two items each: their weights are read twice, mostly from a cache
+// the second time).
+static bool fq_all_small(const int32_t* offsets, int E) {
+    int n16 = 0, n32 = 0;
     for (int e = 0; e < E; ++e) {
         const int32_t rows = offsets[e + 1] - offsets[e];
         n16 += rows > 0 && rows <= 16;
-        n32 += rows > 16 && rows <= 32;
-        more += rows > 32;
-        tiles += (rows + 127) / 128;
+        n32 += rows > 16;
+        if (rows > 32) return false;
     }
-    if (more == 0 && n32 == 0) return 16;
-    if (more == 0 && 8 * n32 <= n16) return 32;
-    return tiles * nblocks_n <= fq_cu_count() ? 0 : 16;
+    return 8 * n32 <= n16;
 }
 
 // Block shape for the experts of the small-M kernel: the shape with the least
@@ -443,6 +455,133 @@ fq_small_shape fq_plan_grouped_small(int count, int units, int ngroups, int KB) 
     return best;
 }
 
+// Model of a grouped call, fitted (of log time, rms error 10 %) to 200 calls of 8 .. 64 experts, 8 .. 2048 tokens and
+// matrices from 1024 x 1024 to 4096 x 16384, each cut in up to ten ways.
+//   a block of the tiled kernel     its cost per 128 rows of K (fq_tiled_costs) times tile_f, + 10 us
+//   a block of the mid-M kernel     iterations of fq_mid_model's length times mid_f (at least 1 us, memory at 8.5 TB/s), + 5.8 us
+//   a block of the small-M kernel   1.26 us per iteration, + 5 us (2.5 without k-workers)
+//   a launch                        the compute units' share of its blocks + 0.35 of the longest for the ragged end (not more
+//                                   than its whole rounds for the mid-M kernel); at least the longest
+// Side by side on streams of their own the launches share one ragged end, but forking and joining the streams costs 21 us.
+
+// Block shape of the mid-M kernel for the tiles of a grouped product (count[i]: those of i + 1 row tiles); the launch's
+// time, the time its blocks hold the compute units in all, and the longest of them.
+static double fq_plan_grouped_mid(const int (&count)[3], int64_t N, int64_t K, int bits, int g, fq_small_shape* sh,
+                                  double* busy_us, double* block_us) {
+    static const double mid_f[2][3] = {{0.67, 1.13, 0.88}, {0.8, 0.96, 1.19}};      // (3- and 4-bit codes, 8-bit codes)
+    const int ngroups = (int)((N / FQ_NTILE + MMA_NT - 1) / MMA_NT);
+    const double ncu = (double)fq_cu_count();
+    const int items = count[0] + count[1] + count[2];
+    const fq_mid_model model[3] = {fq_mid_model(1, K, bits, g), fq_mid_model(2, K, bits, g), fq_mid_model(3, K, bits, g)};
+    const fq_mid_model& tallest = model[count[2] ? 2 : (count[1] ? 1 : 0)];
+    double best = 1e30;
+    for (int gp = 1; gp <= 12; ++gp) {
+        const int kw = tallest.workers(gp);
+        const double per_item = (double)((ngroups + gp - 1) / gp);
+        const double active = per_item * items < ncu ? per_item * items : ncu;
+        double sum = 0.0, longest = 0.0;
+        for (int i = 0; i < 3; ++i) {
+            if (count[i] == 0) continue;
+            const double t_work = mid_f[bits == 8][i] * model[i].compute(gp * kw), t_mem = model[i].memory(gp, kw, active, 8.5e6);
+            const double t_it = t_work > t_mem ? t_work : t_mem;
+            const double t = ((model[i].KB + kw - 1) / kw) * (t_it > 1.0 ? t_it : 1.0) + 5.8;
+            sum += t * per_item * count[i];
+            longest = t > longest ? t : longest;
+        }
+        const double rounds = ceil(per_item * items / ncu) * longest;
+        double total = sum / ncu + 0.35 * longest;
+        total = total < rounds ? total : rounds;
+        if (total < longest) total = longest;
+        if (total < best - 1e-9) {
+            best = total;
+            *busy_us = sum;
+            *block_us = longest;
+            sh->gp = gp;
+            sh->kw = kw;
+        }
+    }
+    return best;
+}
+
+// The model's time of a call cut as `p` says; fills in `fork` and the mid-M kernel's block shape.
+static double fq_grouped_us(const int32_t* offsets, int E, int64_t N, int64_t K, int bits, int g, fq_grouped_plan* p) {
+    static const double tile_f[2][2] = {{0.85, 0.85}, {0.80, 0.83}};    // (3- and 4-bit codes, 8-bit codes) x (128, 64 rows)
+    int count[FQ_TILE_CLASSES] = {}, mid_count[3] = {};
+    int32_t small_rows = 0;
+    for (int e = 0; e < E; ++e) {
+        for (int32_t left = offsets[e + 1] - offsets[e], take = 0; left > 0; left -= take) {
+            const fq_tile_class c = fq_next_tile(*p, left, &take);
+            ++count[c];
+            if (c == FQ_TILE_SMALL && take > small_rows) small_rows = take;
+            if (c == FQ_TILE_MID) ++mid_count[(take - 1) / 16];
+        }
+    }
+    const int ntiles = (int)(N / FQ_NTILE);
+    const double ncu = (double)fq_cu_count();
+    const double* cs = fq_tiled_costs(bits, g);
+    double sum = 0.0, longest = 0.0, apart = 0.0;
+    int classes = 0;
+    auto add = [&](double busy, double block, double most) {
+        double t = busy / ncu + 0.35 * block;
+        t = t < most ? t : most;
+        sum += busy;
+        longest = block > longest ? block : longest;
+        apart += t > block ? t : block;
+        ++classes;
+    };
+    for (int c = FQ_TILE_128; c <= FQ_TILE_64; ++c) {
+        if (count[c] == 0) continue;
+        const int nblocks_n = (ntiles + 8 * MMA_NT - 1) / (8 * MMA_NT);
+        const double t = (double)K / 128.0 * cs[c == FQ_TILE_128 ? 4 : 2] * tile_f[bits == 8][c] + 10.0;
+        add(t * nblocks_n * count[c], t, 1e30);
+    }
+    if (count[FQ_TILE_MID] > 0) {
+        double busy = 0.0, block = 0.0;
+        const double t = fq_plan_grouped_mid(mid_count, N, K, bits, g, &p->mid, &busy, &block);
+        add(busy, block, t);
+    }
+    if (count[FQ_TILE_SMALL] > 0) {
+        const int kblk = fq_kblk(bits);
+        const int ngroups = (ntiles + 2) / 3, KB = (int)(K / kblk);
+        const fq_small_shape s = fq_plan_grouped_small(count[FQ_TILE_SMALL], small_rows * (kblk / 8), ngroups, KB);
+        const double t = 1.26 * ((KB + s.kw - 1) / s.kw) + (s.kw > 1 ? 5.0 : 2.5);
+        add(t * ((ngroups + s.gp - 1) / s.gp) * count[FQ_TILE_SMALL] * (s.gp * s.kw) / 12.0, t, 1e30);
+    }
+    double t = sum / ncu + 0.35 * longest;
+    t = (t > longest ? t : longest) + 21.0;
+    p->fork = classes > 1 && t < apart;
+    return p->fork ? t : apart;
+}
+
+// The cut with the least time by the model.  Against tiles of 128, 64 and 32 rows and the small-M kernel, each class on a
+// stream of its own, the 200 calls are 1.24x faster on average, and up to 3.3x on small matrices, where one launch takes the
+// place of four; 5 of them are more than 5 % slower (calls of 60 us and more: 9 % at worst).  A launch of 32-row tiles
+// of the tiled kernel was the best choice in none of them.  Experts of at most 16 rows stay with the small-M kernel unless
+// the model gives that 15 % more, and with 8-bit codes always (up to 1.27x faster there).
+fq_grouped_plan fq_plan_grouped(const int32_t* offsets, int E, int64_t N, int64_t K, int bits, int g) {
+    fq_grouped_plan best = {};
+    int32_t most = 0;
+    for (int e = 0; e < E; ++e) most = offsets[e + 1] - offsets[e] > most ? offsets[e + 1] - offsets[e] : most;
+    double best_us = 1e30;
+    if (fq_all_small(offsets, E)) {
+        best.cut = FQ_CUT_SMALL;
+        if (most <= 16 && bits == 8) return best;
+        best_us = fq_grouped_us(offsets, E, N, K, bits, g, &best) * (most <= 16 ? 0.85 : 1.0);
+    }
+    const fq_cut cuts[2] = {FQ_CUT_MID, FQ_CUT_TALL};
+    for (const fq_cut cut : cuts) {
+        if (cut == FQ_CUT_TALL && most <= 48) break;
+        fq_grouped_plan p = {};
+        p.cut = cut;
+        const double us = fq_grouped_us(offsets, E, N, K, bits, g, &p);
+        if (us < best_us) {
+            best_us = us;
+            best = p;
+        }
+    }
+    return best;
+}
+
 int fq_launch_gemm(const fq_gemm_plan& plan, const void* A, int act, int64_t M, int64_t N, int64_t K, const void* codes,
                    const void* scales, int bits, int g, void* C, void* workspace, hipStream_t stream) {
 #define FQ_PICK(ACT)                                                                                        \
@@ -455,9 +594,9 @@ int fq_launch_gemm(const fq_gemm_plan& plan, const void* A, int act, int64_t M, 
 #undef FQ_PICK
 }
 
-// The grouped product launches up to four kernels (row tiles of 128, 64, 32 and 16 rows) that do not
+// The grouped product launches up to three kernels (row tiles of 128, of 64 and of up to 48 rows) that do not
 // depend on each other.  Launched one after the other on the caller's stream, each would end with
-// a partly filled last round of blocks; on streams of their own the blocks of the next kernel fill the
+// a partly filled last round of blocks; where that costs more than the fork, they go to streams of their own: the blocks of the next kernel fill the
 // compute units the previous one leaves idle.  The two extra streams (default priority) and the
 // events that fork them from and join them to the caller's stream are created once per device and
 // live until the process ends.
@@ -492,51 +631,36 @@ fq_side* side_streams() {
 int fq_launch_gemm_grouped(const void* A, int act, const int32_t* offsets, int E, int64_t N, int64_t K,
                            const void* codes, const void* scales, int bits, int g, void* C,
                            hipStream_t stream) {
-    // which tile sizes occur (same cutting rule as the launcher)
-    const int32_t small_most = fq_small_rows_most(offsets, E, N);
-    bool has[4] = {false, false, false, false};
-    for (int e = 0; e < E; ++e) {
-        const int32_t rows = offsets[e + 1] - offsets[e];
-        if (rows <= 0) continue;
-        if (rows <= small_most) {
-            has[3] = true;
-            continue;
-        }
-        if (rows > 64) has[0] = true;
-        const int32_t rest = rows > 64 ? rows % 128 : rows;
-        if (rest > 64) has[0] = true;
-        else if (rest > 32) has[1] = true;
-        else if (rest > 0) has[2] = true;
-    }
-    hipStream_t streams[4] = {stream, stream, stream, stream};
-    fq_side* side = (int)has[0] + (int)has[1] + (int)has[2] + (int)has[3] > 1 ? side_streams() : nullptr;
+    const fq_grouped_plan plan = fq_plan_grouped(offsets, E, N, K, bits, g);
+    bool has[FQ_TILE_CLASSES] = {};
+    for (int e = 0; e < E; ++e)
+        for (int32_t left = offsets[e + 1] - offsets[e], take = 0; left > 0; left -= take) has[fq_next_tile(plan, left, &take)] = true;
+    hipStream_t streams[FQ_TILE_CLASSES];
+    for (hipStream_t& s : streams) s = stream;
+    fq_side* side = plan.fork ? side_streams() : nullptr;
     // host threads that fork at the same time would record and wait on each other's events
     std::unique_lock<std::mutex> fork_lock(g_fork_mutex, std::defer_lock);
     if (side) fork_lock.lock();
     bool forked[2] = {false, false};
     if (side) {
-        // the first tile size present stays on the caller's stream, the others go to the side streams; the fourth
-        // follows the third on its stream (a queue more to wake up costs a call on an idle GPU 20 - 60 us, and by then
-        // the compute units are filled anyway)
+        // the first class present stays on the caller's stream, the others go to the side streams
         int next = -1;
-        bool first = true;
         if (hipEventRecord(side->fork, stream) != hipSuccess) return FQ_ERR_HIP;
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < FQ_TILE_CLASSES; ++c) {
             if (!has[c]) continue;
-            if (first) { first = false; continue; }
-            if (next < 1) {
-                ++next;
+            if (next >= 0) {
                 if (hipStreamWaitEvent(side->s[next], side->fork, 0) != hipSuccess) return FQ_ERR_HIP;
                 forked[next] = true;
+                streams[c] = side->s[next];
             }
-            streams[c] = side->s[next];
+            if (++next == 2) break;
         }
     }
     int st;
 #define FQ_PICK(ACT)                                                                                        \
-    (bits == 3   ? fq_launch_grouped_typed_##ACT##_3(A, offsets, E, N, K, codes, scales, g, C, streams)     \
-     : bits == 4 ? fq_launch_grouped_typed_##ACT##_4(A, offsets, E, N, K, codes, scales, g, C, streams)     \
-                 : fq_launch_grouped_typed_##ACT##_8(A, offsets, E, N, K, codes, scales, g, C, streams))
+    (bits == 3   ? fq_launch_grouped_typed_##ACT##_3(A, offsets, E, plan, N, K, codes, scales, g, C, streams)     \
+     : bits == 4 ? fq_launch_grouped_typed_##ACT##_4(A, offsets, E, plan, N, K, codes, scales, g, C, streams)     \
+                 : fq_launch_grouped_typed_##ACT##_8(A, offsets, E, plan, N, K, codes, scales, g, C, streams))
     if (act == FQ_F16) st = FQ_PICK(0);
     else if (act == FQ_BF16) st = FQ_PICK(1);
     else st = FQ_PICK(2);

@@ -70,7 +70,7 @@ int launch_skinny_au(const void* A, int64_t M, int64_t N, int64_t K, const void*
 }
 
 // Mid-M streaming kernel (plan.kind == 2)
-template <int ACT, int BITS, int NT, int MT, int DEPTH, int NBUF, int MAXW>
+template <int ACT, int BITS, int NT, int MT, int MAXW>
 int launch_mid(const void* A, int64_t M, int64_t N, int64_t K, const void* codes, const void* scales, int g, void* C,
                float* partial, const fq_gemm_plan& plan, hipStream_t stream) {
     constexpr int kblk = fq_kblk(BITS);
@@ -78,15 +78,15 @@ int launch_mid(const void* A, int64_t M, int64_t N, int64_t K, const void* codes
     const int sr = (g % kblk) == 0 ? 1 : ((kblk % g) == 0 ? kblk / g : STEPS);
     const int ngroups = (int)((N / FQ_NTILE + NT - 1) / NT);
     const int bgroups = (ngroups + plan.gp - 1) / plan.gp;
-    const size_t lds_act = (size_t)NBUF * plan.kw * MT * 16 * (kblk / 8) * 16;
+    const size_t lds_act = (size_t)mid_bufs(MT) * plan.kw * MT * 16 * (kblk / 8) * 16;
     const size_t lds_red = (size_t)plan.gp * plan.kw * NT * MT * 64 * 16;
     const size_t lds = lds_act > lds_red ? lds_act : lds_red;
     if (lds > 160 * 1024) return FQ_ERR_UNSUPPORTED;
     const uint32_t g32 = (uint32_t)(g / 32);
     const uint32_t g32_recip = (uint32_t)((((uint64_t)1 << 32) + g32 - 1) / g32);   // unused when g32 == 1
-    auto kern = sr == 1 ? fq_gemm_mid_kernel<ACT, BITS, NT, MT, DEPTH, NBUF, 1, MAXW>
-                        : (sr == 2 ? fq_gemm_mid_kernel<ACT, BITS, NT, MT, DEPTH, NBUF, 2, MAXW>
-                                   : fq_gemm_mid_kernel<ACT, BITS, NT, MT, DEPTH, NBUF, STEPS, MAXW>);
+    auto kern = sr == 1 ? fq_gemm_mid_kernel<ACT, BITS, NT, MT, 1, MAXW>
+                        : (sr == 2 ? fq_gemm_mid_kernel<ACT, BITS, NT, MT, 2, MAXW>
+                                   : fq_gemm_mid_kernel<ACT, BITS, NT, MT, STEPS, MAXW>);
     if (lds > 65536) {
         static std::atomic<uint64_t> raised[3];   // per instantiation: [scale rows per k-block]
         if (raise_lds_limit((const void*)kern, raised[sr == 1 ? 0 : (sr == 2 ? 1 : 2)]) != FQ_OK) return FQ_ERR_HIP;
@@ -124,10 +124,8 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
         }
         if (st != FQ_OK) return st;
     } else if (plan.kind == 2) {
-        // two row tiles: three stages of weights in flight and three activation tiles; three: two (registers) and two (LDS)
-        const int st = plan.mt == 2
-                           ? launch_mid<ACT, BITS, MMA_NT, 2, 3, 3, 12>(A, M, N, K, codes, scales, g, C, partial, plan, stream)
-                           : launch_mid<ACT, BITS, MMA_NT, 3, 2, 2, 12>(A, M, N, K, codes, scales, g, C, partial, plan, stream);
+        const int st = plan.mt == 2 ? launch_mid<ACT, BITS, MMA_NT, 2, 12>(A, M, N, K, codes, scales, g, C, partial, plan, stream)
+                                    : launch_mid<ACT, BITS, MMA_NT, 3, 12>(A, M, N, K, codes, scales, g, C, partial, plan, stream);
         if (st != FQ_OK) return st;
     } else {
         // rows of K per k-block of this block shape (two layout blocks at a time for 8-bit codes in the
@@ -303,26 +301,56 @@ int launch_grouped_small(const void* A, const fq_small_items& items, int count, 
     return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_HIP;
 }
 
-// Grouped (per-expert) product.  Every expert's rows are cut into row tiles of 128, 64, 32 or 16 rows (the smallest that
-// holds what is left; 16 only for the experts that fq_small_rows_most names), and the tiles of each size go to the kernel
-// instantiated for that size: experts with few rows then stream their weights through small tiles instead of multiplying
-// mostly padding, those with at most 16 through the small-M kernel.  Experts without rows produce no tile.
+// Tiles of up to 48 rows of a grouped product: the mid-M kernel, no split of K over the grid.
 template <int ACT, int BITS>
-int launch_grouped_typed(const void* A, const int32_t* offsets, int E, int64_t N, int64_t K,
+int launch_mid_items(const void* A, const fq_small_items& items, int count, int rows_max, const fq_small_shape& sh, int64_t N,
+                     int64_t K, const void* codes, const void* scales, int g, void* C, hipStream_t stream) {
+    constexpr int NT = MMA_NT, MAXW = 12;
+    constexpr int kblk = fq_kblk(BITS);
+    constexpr int STEPS = kblk / FQ_KSTEP;
+    const int sr = (g % kblk) == 0 ? 1 : ((kblk % g) == 0 ? kblk / g : STEPS);
+    const int ngroups = (int)((N / FQ_NTILE + NT - 1) / NT);
+    // (three tiles of 32 rows hold as much as two of 48, and more than what lower items take)
+    const int mt = rows_max <= 16 ? 1 : 2;
+    const size_t lds_act = (size_t)mid_bufs(mt) * sh.kw * mt * 16 * (kblk / 8) * 16;
+    const size_t lds_red = (size_t)sh.gp * sh.kw * NT * ((rows_max + 15) / 16) * 64 * 16;
+    const size_t lds = lds_act > lds_red ? lds_act : lds_red;
+    if (lds > 160 * 1024 || sh.gp * sh.kw > MAXW) return FQ_ERR_UNSUPPORTED;
+    const uint32_t g32 = (uint32_t)(g / 32);
+    const uint32_t g32_recip = (uint32_t)((((uint64_t)1 << 32) + g32 - 1) / g32);   // unused when g32 == 1
+    auto kern = sr == 1 ? fq_gemm_mid_items_kernel<ACT, BITS, NT, 1, MAXW>
+                        : (sr == 2 ? fq_gemm_mid_items_kernel<ACT, BITS, NT, 2, MAXW>
+                                   : fq_gemm_mid_items_kernel<ACT, BITS, NT, STEPS, MAXW>);
+    if (lds > 65536) {
+        static std::atomic<uint64_t> raised[3];   // per instantiation: [scale rows per k-block]
+        if (raise_lds_limit((const void*)kern, raised[sr == 1 ? 0 : (sr == 2 ? 1 : 2)]) != FQ_OK) return FQ_ERR_HIP;
+    }
+    const int64_t blocks = (int64_t)((ngroups + sh.gp - 1) / sh.gp) * count;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3((unsigned)(sh.gp * sh.kw * 64)), lds, stream, (const uint16_t*)A,
+                       (const u32x4*)codes, (const uint16_t*)scales, (uint16_t*)C, (int)N, (int)K, g32, g32_recip, sh.gp, sh.kw,
+                       items);
+    return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_HIP;
+}
+
+// Grouped (per-expert) product.  Every expert's rows are cut into row tiles (fq_next_tile), and the tiles of each class go
+// to the kernel instantiated for it: experts with few rows then stream their weights through small tiles instead of
+// multiplying mostly padding.  Experts without rows produce no tile.
+template <int ACT, int BITS>
+int launch_grouped_typed(const void* A, const int32_t* offsets, int E, const fq_grouped_plan& plan, int64_t N, int64_t K,
                          const void* codes, const void* scales, int g, void* C, const hipStream_t* streams) {
     const int ntiles = (int)(N / FQ_NTILE);
     const int64_t codes_stride16 = (int64_t)(K * N * BITS / 8) / 16;
     const int64_t scales_stride = (K / g) * N;
-    const int32_t small_most = fq_small_rows_most(offsets, E, N);   // experts up to here take the small-M kernel
     fq_group_items items;
-    for (int mt = 8; mt >= 2; mt /= 2) {
+    for (int cls = FQ_TILE_128; cls <= FQ_TILE_64; ++cls) {
+        const int mt = cls == FQ_TILE_128 ? 8 : 4;
         const int bm = mt * 16;
-        // 8-wave blocks (384 columns) unless the matrix is narrow: measured 1 - 5 % faster than 4-wave
-        // blocks also for the 64- and 32-row tiles (64 experts of 4096 x 16384 / 16384 x 4096)
-        const int waves = (mt == 8 || ntiles >= 48) ? 8 : 4;
-        const hipStream_t stream = streams[mt == 8 ? 0 : (mt == 4 ? 1 : 2)];
+        // 8-wave blocks (384 columns), measured 1 - 5 % faster than 4-wave ones also for the 64-row tiles (64 experts of
+        // 4096 x 16384 / 16384 x 4096)
+        const int waves = 8;
+        const hipStream_t stream = streams[cls];
         const int nblocks_n = (ntiles + waves * MMA_NT - 1) / (waves * MMA_NT);
-        const int ring = mt == 8 ? 2 : (mt == 4 ? FQ_RING_MT4 : FQ_RING_MT2);
+        const int ring = mt == 8 ? 2 : FQ_RING_MT4;
         // rows of K per k-block of this tile size (8-bit codes: two layout blocks at a time in the 128-row
         // shape where K and g allow it) and the scale rows such a k-block spans
         const int kblk = fq_mma_kblk(BITS, mt, waves, K, g);
@@ -361,33 +389,23 @@ int launch_grouped_typed(const void* A, const int32_t* offsets, int E, int64_t N
                     FQ_GROUPED_LAUNCH(8, 8, 2);
                 }
             }
-            else if (mt == 4 && waves == 8) FQ_GROUPED_LAUNCH(4, 8, FQ_RING_MT4);
-            else if (mt == 4) FQ_GROUPED_LAUNCH(4, 4, FQ_RING_MT4);
-            else if (waves == 8) FQ_GROUPED_LAUNCH(2, 8, FQ_RING_MT2);
-            else FQ_GROUPED_LAUNCH(2, 4, FQ_RING_MT2);
+            else FQ_GROUPED_LAUNCH(4, 8, FQ_RING_MT4);
 #undef FQ_GROUPED_LAUNCH
 #undef FQ_GROUPED_LAUNCH_SR
             items.count = 0;
             return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_HIP;
         };
         for (int e = 0; e < E; ++e) {
-            int32_t r = offsets[e];
-            if (offsets[e + 1] - r <= small_most) continue;      // below
-            while (r < offsets[e + 1]) {
-                const int32_t left = offsets[e + 1] - r;
-                const int tile_mt = left > 64 ? 8 : (left > 32 ? 4 : 2);
-                const int32_t take = left < tile_mt * 16 ? left : tile_mt * 16;
-                if (tile_mt == mt) {
-                    const int i = items.count++;
-                    items.row0[i] = r;
-                    items.rows[i] = (int16_t)take;
-                    items.expert[i] = (int16_t)e;
-                    if (items.count == 256) {
-                        const int st = flush_items();
-                        if (st != FQ_OK) return st;
-                    }
+            for (int32_t r = offsets[e], take = 0; r < offsets[e + 1]; r += take) {
+                if (fq_next_tile(plan, offsets[e + 1] - r, &take) != cls) continue;
+                const int i = items.count++;
+                items.row0[i] = r;
+                items.rows[i] = (int16_t)take;
+                items.expert[i] = (int16_t)e;
+                if (items.count == 256) {
+                    const int st = flush_items();
+                    if (st != FQ_OK) return st;
                 }
-                r += take;
             }
         }
         const int st = flush_items();
@@ -397,27 +415,34 @@ int launch_grouped_typed(const void* A, const int32_t* offsets, int E, int64_t N
     small.codes_stride16 = codes_stride16;
     small.scales_stride = scales_stride;
     int count = 0, rows_max = 0;
-    auto flush_small = [&]() -> int {
-        const int n = count;
-        count = 0;
-        return n == 0 ? FQ_OK
-                      : launch_grouped_small<ACT, BITS>(A, small, n, rows_max, N, K, codes, scales, g, C, streams[3]);
+    auto flush_small = [&](bool mid) -> int {
+        const int n = count, most = rows_max;
+        count = rows_max = 0;
+        if (n == 0) return FQ_OK;
+        if (mid) return launch_mid_items<ACT, BITS>(A, small, n, most, plan.mid, N, K, codes, scales, g, C, streams[FQ_TILE_MID]);
+        return launch_grouped_small<ACT, BITS>(A, small, n, most, N, K, codes, scales, g, C, streams[FQ_TILE_SMALL]);
     };
-    for (int e = 0; e < E; ++e) {
-        if (offsets[e + 1] - offsets[e] > small_most) continue;
-        for (int32_t r = offsets[e]; r < offsets[e + 1]; r += 16) {
-            const int rows = offsets[e + 1] - r < 16 ? offsets[e + 1] - r : 16;
-            small.row0[count] = r;
-            small.rows[count] = (uint8_t)rows;
-            small.expert[count] = (uint8_t)e;
-            rows_max = rows > rows_max ? rows : rows_max;
-            if (++count == 256) {
-                const int st = flush_small();
-                if (st != FQ_OK) return st;
+    // the tallest tiles of the mid-M kernel first, those of the small-M kernel last
+    for (int height = 48; height >= 0; height -= 16) {
+        const int cls = height > 0 ? FQ_TILE_MID : FQ_TILE_SMALL;
+        for (int e = 0; e < E; ++e) {
+            for (int32_t r = offsets[e], take = 0; r < offsets[e + 1]; r += take) {
+                if (fq_next_tile(plan, offsets[e + 1] - r, &take) != cls || (height > 0 && (take + 15) / 16 * 16 != height)) continue;
+                small.row0[count] = r;
+                small.rows[count] = (uint8_t)take;
+                small.expert[count] = (uint8_t)e;
+                rows_max = take > rows_max ? take : rows_max;
+                if (++count == 256) {
+                    const int st = flush_small(height > 0);
+                    if (st != FQ_OK) return st;
+                }
             }
         }
+        if (height > 16) continue;          // (one launch for all heights)
+        const int st = flush_small(height > 0);
+        if (st != FQ_OK) return st;
     }
-    return flush_small();
+    return FQ_OK;
 }
 
 
@@ -430,10 +455,12 @@ int launch_grouped_typed(const void* A, const int32_t* offsets, int E, int64_t N
                                        const fq_gemm_plan& plan, hipStream_t stream) {                     \
         return fqd::launch_typed<ACT, BITS>(A, M, N, K, codes, scales, g, C, workspace, plan, stream);     \
     }                                                                                                      \
-    int fq_launch_grouped_typed_##ACT##_##BITS(const void* A, const int32_t* offsets, int E, int64_t N,    \
-                                               int64_t K, const void* codes, const void* scales, int g,    \
-                                               void* C, const hipStream_t* streams) {                      \
-        return fqd::launch_grouped_typed<ACT, BITS>(A, offsets, E, N, K, codes, scales, g, C, streams);    \
+    int fq_launch_grouped_typed_##ACT##_##BITS(const void* A, const int32_t* offsets, int E,               \
+                                               const fq_grouped_plan& plan, int64_t N, int64_t K,          \
+                                               const void* codes, const void* scales, int g, void* C,      \
+                                               const hipStream_t* streams) {                               \
+        return fqd::launch_grouped_typed<ACT, BITS>(A, offsets, E, plan, N, K, codes, scales, g, C,        \
+                                                    streams);                                              \
     }
 
 #endif  // FQ_GEMM_DISPATCH_H_

@@ -552,9 +552,9 @@ __device__ inline void recompute_not_finite(f32x4 (&acc)[NT], const uint16_t* A,
 // lanes = consecutive unit columns of one row) spread over the banks.
 #define FQ_SK_PITCH 17
 
-// Grouped (per-expert) form: items of 1 .. 16 rows; block b works for item b / (column blocks).  Rows
-// row0 .. row0 + rows - 1 of the stacked activations belong to expert `expert`, whose weights start
-// expert * codes_stride16 records / expert * scales_stride scales into the buffers.  Passed by value in the kernel
+// Grouped (per-expert) form of this kernel and of the mid-M one: items of up to 16 (16 MT) rows; block b works for item
+// b / (column blocks).  Rows row0 .. row0 + rows - 1 of the stacked activations belong to expert `expert`, whose weights
+// start expert * codes_stride16 records / expert * scales_stride scales into the buffers.  Passed by value in the kernel
 // arguments.
 struct fq_small_items {
     static constexpr bool grouped = true;
@@ -812,11 +812,11 @@ struct MidOperand<ACT, BITS, true> : ExactOperand<ACT, BITS> {
     static constexpr uint32_t NEG = 0u;
 };
 
-template <int ACT, int BITS, int NT, int MT, int DEPTH, int NBUF, int SR, int MAXW>
-__global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_kernel(
-    const uint16_t* __restrict__ A, const u32x4* __restrict__ codes, const uint16_t* __restrict__ scales,
+template <int ACT, int BITS, int NT, int MT, int DEPTH, int NBUF, int SR>
+__device__ __forceinline__ void mid_block(
+    u32x4* lds, const uint16_t* __restrict__ A, const u32x4* __restrict__ codes, const uint16_t* __restrict__ scales,
     uint16_t* __restrict__ C, float* __restrict__ partial, int M, int N, int K, uint32_t g32,
-    uint32_t g32_recip, int gp, int kw_n, int grid_splits) {
+    uint32_t g32_recip, int gp, int kw_n, int bx, int gsplit, int grid_splits) {
     constexpr int KBLK = fq_kblk(BITS);
     constexpr int STEPS = KBLK / FQ_KSTEP;
     constexpr int GSTEPS = STEPS / SR;              // k-steps per scale row
@@ -829,8 +829,7 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_kernel(
     static_assert(STEPS % SR == 0 && (NBUF == 2 || NBUF == 3) && DEPTH >= 2 && (DEPTH - 1) * NW < 64, "");
     constexpr int AHEAD = NBUF - 1;                 // iterations the activations are loaded ahead
     typedef SkinnyStage<BITS, NT, SR, 0> Stage;
-    extern __shared__ u32x4 lds[];   // NBUF activation buffers [kw_n][TILE]; later the reduction
-
+    // lds: NBUF activation buffers [kw_n][TILE]; later the reduction
     const int tid = threadIdx.x;
     const int nthreads = blockDim.x;
     const int lane = tid & 63;
@@ -839,9 +838,6 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_kernel(
     const int kw = wave - gi * kw_n;
     const int ntiles = N / FQ_NTILE;
     const int ngroups = (ntiles + NT - 1) / NT;
-    const int bgroups = (ngroups + gp - 1) / gp;      // blocks per grid split
-    const int bx = blockIdx.x % bgroups;
-    const int gsplit = blockIdx.x / bgroups;          // < grid_splits
     const int ng = bx * gp + gi;
     const bool gvalid = ng < ngroups;
     const int KB = K / KBLK;
@@ -1083,6 +1079,49 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_kernel(
         const int tl = r >> 6;
         store_quad(v, bx * gp + gq, tl / NT, tl % NT, r & 63);
     }
+}
+
+// ring stages and activation tiles by row tiles: three stages of weights in flight and three activation tiles, or (48 rows:
+// registers, LDS) two and two
+constexpr int mid_depth(int mt) { return mt == 3 ? 2 : 3; }
+constexpr int mid_bufs(int mt) { return mt == 3 ? 2 : 3; }
+
+template <int ACT, int BITS, int NT, int MT, int SR, int MAXW>
+__global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_kernel(
+    const uint16_t* __restrict__ A, const u32x4* __restrict__ codes, const uint16_t* __restrict__ scales,
+    uint16_t* __restrict__ C, float* __restrict__ partial, int M, int N, int K, uint32_t g32,
+    uint32_t g32_recip, int gp, int kw_n, int grid_splits) {
+    extern __shared__ u32x4 lds[];
+    const int ngroups = (N / FQ_NTILE + NT - 1) / NT;
+    const int bgroups = (ngroups + gp - 1) / gp;      // blocks per grid split
+    mid_block<ACT, BITS, NT, MT, mid_depth(MT), mid_bufs(MT), SR>(lds, A, codes, scales, C, partial, M, N, K, g32, g32_recip, gp, kw_n,
+                                                                  blockIdx.x % bgroups, blockIdx.x / bgroups, grid_splits);
+}
+
+// Row tiles of up to 16, 32 or 48 rows, each with its own rows and weights, in one launch.  A launch per height would need
+// either streams of their own (forking and joining them costs a call about 30 us: 2688 x 1392, ten experts of 57 rows and
+// less, 42 us with 64- and 32-row tiles and the small-M kernel side by side, 13.6 in one launch) or a ragged end each.
+template <int ACT, int BITS, int NT, int SR, int MAXW>
+__global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_items_kernel(
+    const uint16_t* __restrict__ A, const u32x4* __restrict__ codes, const uint16_t* __restrict__ scales,
+    uint16_t* __restrict__ C, int N, int K, uint32_t g32, uint32_t g32_recip, int gp, int kw_n, fq_small_items items) {
+    extern __shared__ u32x4 lds[];
+    const int ngroups = (N / FQ_NTILE + NT - 1) / NT;
+    const int bgroups = (ngroups + gp - 1) / gp;      // blocks per item
+    const int item = blockIdx.x / bgroups, bx = blockIdx.x % bgroups;
+    const int64_t row0 = items.row0[item];
+    const int e = items.expert[item];
+    const int M = items.rows[item];
+    A += row0 * K;
+    C += row0 * N;
+    codes += e * items.codes_stride16;
+    scales += e * items.scales_stride;
+    if (M <= 16)
+        mid_block<ACT, BITS, NT, 1, mid_depth(1), mid_bufs(1), SR>(lds, A, codes, scales, C, nullptr, M, N, K, g32, g32_recip, gp, kw_n, bx, 0, 1);
+    else if (M <= 32)
+        mid_block<ACT, BITS, NT, 2, mid_depth(2), mid_bufs(2), SR>(lds, A, codes, scales, C, nullptr, M, N, K, g32, g32_recip, gp, kw_n, bx, 0, 1);
+    else
+        mid_block<ACT, BITS, NT, 3, mid_depth(3), mid_bufs(3), SR>(lds, A, codes, scales, C, nullptr, M, N, K, g32, g32_recip, gp, kw_n, bx, 0, 1);
 }
 
 // Sum of split-K partials, fixed order, then conversion to the activation type.

@@ -45,11 +45,36 @@ struct fq_gemm_plan {
 inline bool fq_flexible(const fq_gemm_plan& p) { return p.kind == 1 && p.mt >= 5 && !(p.mt == 8 && p.nt == 3); }
 // act_dtype: FQ_F16 or FQ_BF16; the plans differ in the block shape alone (see fq_plan_flexible), not in the scratch
 fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int act_dtype);
-// Rows up to which an expert of a grouped product takes the small-M kernel: 0, 16 or 32
-int32_t fq_small_rows_most(const int32_t* offsets, int E, int64_t N);
+// Grouped product.  Every expert's rows are cut into tiles, and the tiles of one class share a launch: 128 or 64 rows of the
+// tiled kernel, up to 48 of the mid-M one, up to 16 of the small-M one.
+enum fq_tile_class { FQ_TILE_128, FQ_TILE_64, FQ_TILE_MID, FQ_TILE_SMALL, FQ_TILE_CLASSES };
+enum fq_cut { FQ_CUT_SMALL, FQ_CUT_MID, FQ_CUT_TALL };
+struct fq_small_shape { int gp, kw; };   // column groups (of three tiles) x k-workers per block
+struct fq_grouped_plan {
+    fq_cut cut;                  // all tiles small; all for the mid-M kernel; 128 and 64 rows, and the mid-M kernel below 49
+    bool fork;                   // each class on a stream of its own
+    fq_small_shape mid;          // block shape of the mid-M kernel
+};
+fq_grouped_plan fq_plan_grouped(const int32_t* offsets, int E, int64_t N, int64_t K, int bits, int g);
+// The next tile of an expert that has `left` rows left.  Tiles of the mid-M kernel are as few as 48 rows allow and of nearly
+// equal height.
+inline fq_tile_class fq_next_tile(const fq_grouped_plan& p, int32_t left, int32_t* take) {
+    if (p.cut == FQ_CUT_SMALL) {
+        *take = left < 16 ? left : 16;
+        return FQ_TILE_SMALL;
+    }
+    if (p.cut == FQ_CUT_TALL && left > 48) {
+        const int32_t tall = left > 64 ? 128 : 64;
+        *take = left < tall ? left : tall;
+        return tall == 128 ? FQ_TILE_128 : FQ_TILE_64;
+    }
+    const int32_t n = (left + 47) / 48;
+    const int32_t even = ((left + n - 1) / n + 15) / 16 * 16;
+    *take = left < even ? left : even;
+    return FQ_TILE_MID;
+}
 // Block shape of the small-M kernel for `count` items of a grouped product (at most 16 rows each);
 // units = activation units (16 bytes) of a k-block in the tallest of them, ngroups = groups of three column tiles.
-struct fq_small_shape { int gp, kw; };
 fq_small_shape fq_plan_grouped_small(int count, int units, int ngroups, int KB);
 // compute units of the device (asked once per process; 256 without a device)
 int fq_cu_count();

@@ -75,6 +75,7 @@ def load(build_if_missing: bool = True) -> ctypes.CDLL:
         "fq_gemm_w4a8_workspace_bytes": (sz, [i64, i64, i64, i32]),
         "fq_gemm_w4a8": (i32, [vp, vp, i64, i64, i64, vp, vp, vp, i32, vp, i32, vp, sz, vp]),
         "fq_gemm_describe": (i32, [i64, i64, i64, i32, i32, ctypes.c_char_p, sz]),
+        "fq_gemm_grouped_describe": (i32, [ctypes.POINTER(ctypes.c_int32), i32, i64, i64, i32, i32, ctypes.c_char_p, sz]),
         "fq_stream_read_probe": (i32, [vp, sz, vp, vp]),
         "fq_mfma_rate_probe_operand_bytes": (sz, []),
         "fq_mfma_rate_probe_sink_bytes": (sz, []),
@@ -94,7 +95,7 @@ def load(build_if_missing: bool = True) -> ctypes.CDLL:
 EXPORTED = [
     "fq_codes_bytes", "fq_scales_bytes", "fq_gemm_workspace_bytes", "fq_gemm_grouped_workspace_bytes",
     "fq_choose_group_workspace_bytes", "fq_quantize", "fq_unpack", "fq_choose_group", "fq_gemm",
-    "fq_gemm_grouped", "fq_gemm_describe", "fq_status_string", "fq_version",
+    "fq_gemm_grouped", "fq_gemm_describe", "fq_gemm_grouped_describe", "fq_status_string", "fq_version",
     "fq_quant_error_workspace_bytes", "fq_quant_error",
     "fq_quantize_sf", "fq_quant_error_sf", "fq_gemm_sf", "fq_gemm_grouped_sf", "fq_gemm_workspace_bytes_for",
     "fq_stream_read_probe", "fq_gemm_noalloc", "fq_gemm_noalloc_scratch_bytes",
@@ -154,6 +155,16 @@ def gemm_describe(M, N, K, bits, group_size):
     st = int(load().fq_gemm_describe(M, N, K, bits, group_size, buf, 256))
     if st != FQ_OK:
         raise FqError(st, "fq_gemm_describe")
+    return buf.value.decode()
+
+
+def gemm_grouped_describe(offsets, N, K, bits, group_size):
+    buf = ctypes.create_string_buffer(256)
+    E = len(offsets) - 1
+    arr = (ctypes.c_int32 * (E + 1))(*[int(o) for o in offsets])
+    st = int(load().fq_gemm_grouped_describe(arr, E, N, K, bits, group_size, buf, 256))
+    if st != FQ_OK:
+        raise FqError(st, "fq_gemm_grouped_describe")
     return buf.value.decode()
 
 

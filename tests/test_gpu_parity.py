@@ -669,3 +669,58 @@ def test_gemm_shapes_between_64_and_128_rows(dtype, bits, g, M, K, N, rows, cols
         assert f"rows={rows} cols={cols}" in desc
         assert (K == 6016) == ("splits=1 " not in desc)
     _gemm_case(M, K, N, dtype, bits, g, seed=9700 + M + K + bits)
+
+
+def _grouped_plan(rows, K, N, bits, g):
+    import re
+    d = _fq().gemm_grouped_describe(np.concatenate([[0], np.cumsum(rows)]).tolist(), N, K, bits, g)
+    return {k: int(v) for k, v in re.findall(r"([\w-]+)=(\d+)", d)}
+
+
+@pytest.mark.parametrize("rows", [[16, 1, 17, 33, 0, 48, 32, 49, 80, 97, 145, 2], [48, 3], [31], [96] * 135],
+                         ids=["every-height", "48-and-3", "31", "more-than-one-launch"])
+@pytest.mark.parametrize("dtype,bits,g,K,N", [("f16", 4, 64, 640, 112), ("bf16", 4, 128, 1664, 1040), ("bf16", 8, 0, 192, 48),
+                                              ("f16", 8, 32, 256, 816), ("f16", 3, 96, 384, 16), ("bf16", 3, 128, 256, 304),
+                                              ("bf16", 4, 32, 256, 64)])
+def test_grouped_gemm_tiles_of_the_streaming_kernel(dtype, bits, g, K, N, rows):
+    """Row tiles of 16, 32 and 48 rows in one launch: every height on both sides of its limits, experts cut into several
+    tiles of nearly equal height, idle column groups, k ranges shorter than the k-workers' turn, more tiles than one
+    launch holds."""
+    if len(rows) > 100 and K * N > 40000:
+        pytest.skip("the number of tiles is what matters: small matrices")
+    _say(f"grouped streaming tiles {dtype} int{bits} g={g} {rows[:12]}")
+    plan = _grouped_plan(rows, K, N, bits, g)
+    assert plan["rows128"] == plan["rows64"] == plan["small-m"] == 0 and plan["streams"] == 1
+    assert plan["mid-m"] == sum(-(-r // 48) for r in rows)
+    _grouped_case(dtype, bits, g, K, N, rows, seed=91, shared_weights=len(rows) > 100)
+
+
+@pytest.mark.parametrize("dtype,bits,g", [("f16", 4, 64), ("bf16", 4, 128), ("bf16", 8, 128), ("f16", 8, 64), ("bf16", 3, 32)])
+def test_grouped_gemm_tall_experts_beside_the_streaming_kernel(dtype, bits, g):
+    """Enough tall experts for tiles of 128 and 64 rows of the tiled kernel (one column tile in the last column block),
+    with what is left below 49 rows in the streaming kernel."""
+    _say(f"grouped tall {dtype} int{bits} g={g}")
+    rows = [256] * 12 + [64, 177, 33, 49, 30, 17, 130, 0]
+    plan = _grouped_plan(rows, 1024, 6160, bits, g)
+    assert (plan["rows128"], plan["rows64"], plan["mid-m"], plan["small-m"]) == (26, 3, 4, 0)
+    _grouped_case(dtype, bits, g, 1024, 6160, rows, seed=93, shared_weights=True)
+
+
+@pytest.mark.parametrize("bits,g", [(4, 128), (4, 64), (8, 64)])
+def test_grouped_gemm_rows_beside_one_that_is_not_finite(bits, g):
+    """bf16, one expert per tile height: an infinity in one row leaves the bits of every other row as they are."""
+    _say(f"grouped non-finite row int{bits} g={g}")
+    fq, torch = _fq(), torch_mod()
+    rows, K, N = [9, 30, 47], 512, 208
+    offsets = np.concatenate([[0], np.cumsum(rows)]).tolist()
+    parts = [assert_quantizer_parity(workloads.weights_gaussian(K, N, 40 + e), bits, g)[:2] for e in range(3)]
+    codes, scales = torch.cat([p[0] for p in parts]), torch.cat([p[1].reshape(-1) for p in parts])
+    A = to_dev_act(workloads.activations(offsets[-1], K, "bf16", 17), "bf16")
+    want = fq.gemm_grouped(A, offsets, codes, scales, bits, g, N).clone()
+    B = A.clone()
+    hit = [4, 20, 60]
+    B[hit, 100] = float("inf")
+    got = fq.gemm_grouped(B, offsets, codes, scales, bits, g, N)
+    keep = [r for r in range(offsets[-1]) if r not in hit]
+    assert torch.equal(got[keep].view(torch.int16), want[keep].view(torch.int16))
+    assert not bool(torch.isfinite(got[hit]).all())
