@@ -97,6 +97,37 @@ int launch_mid(const void* A, int64_t M, int64_t N, int64_t K, const void* codes
     return FQ_OK;
 }
 
+// Tiles of up to 48 rows of a grouped product: the mid-M kernel, no split of K over the grid.
+template <int ACT, int BITS>
+int launch_mid_items(const void* A, const fq_small_items& items, int count, int rows_max, const fq_small_shape& sh, int64_t N,
+                     int64_t K, const void* codes, const void* scales, int g, void* C, hipStream_t stream) {
+    constexpr int NT = MMA_NT, MAXW = 12;
+    constexpr int kblk = fq_kblk(BITS);
+    constexpr int STEPS = kblk / FQ_KSTEP;
+    const int sr = (g % kblk) == 0 ? 1 : ((kblk % g) == 0 ? kblk / g : STEPS);
+    const int ngroups = (int)((N / FQ_NTILE + NT - 1) / NT);
+    // (three tiles of 32 rows hold as much as two of 48, and more than what lower items take)
+    const int mt = rows_max <= 16 ? 1 : 2;
+    const size_t lds_act = (size_t)mid_bufs(mt) * sh.kw * mt * 16 * (kblk / 8) * 16;
+    const size_t lds_red = (size_t)sh.gp * sh.kw * NT * ((rows_max + 15) / 16) * 64 * 16;
+    const size_t lds = lds_act > lds_red ? lds_act : lds_red;
+    if (lds > 160 * 1024 || sh.gp * sh.kw > MAXW) return FQ_ERR_UNSUPPORTED;
+    const uint32_t g32 = (uint32_t)(g / 32);
+    const uint32_t g32_recip = (uint32_t)((((uint64_t)1 << 32) + g32 - 1) / g32);   // unused when g32 == 1
+    auto kern = sr == 1 ? fq_gemm_mid_items_kernel<ACT, BITS, NT, 1, MAXW>
+                        : (sr == 2 ? fq_gemm_mid_items_kernel<ACT, BITS, NT, 2, MAXW>
+                                   : fq_gemm_mid_items_kernel<ACT, BITS, NT, STEPS, MAXW>);
+    if (lds > 65536) {
+        static std::atomic<uint64_t> raised[3];   // per instantiation: [scale rows per k-block]
+        if (raise_lds_limit((const void*)kern, raised[sr == 1 ? 0 : (sr == 2 ? 1 : 2)]) != FQ_OK) return FQ_ERR_HIP;
+    }
+    const int64_t blocks = (int64_t)((ngroups + sh.gp - 1) / sh.gp) * count;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3((unsigned)(sh.gp * sh.kw * 64)), lds, stream, (const uint16_t*)A,
+                       (const u32x4*)codes, (const uint16_t*)scales, (uint16_t*)C, (int)N, (int)K, g32, g32_recip, sh.gp, sh.kw,
+                       items);
+    return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_HIP;
+}
+
 // rows whose units of 8 values fit four waves' registers take those, longer ones sixteen waves
 // SCALES: the `count` bfloat16 scales are searched for their largest in the same launch
 template <bool SCALES>
@@ -301,37 +332,6 @@ int launch_grouped_small(const void* A, const fq_small_items& items, int count, 
     return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_HIP;
 }
 
-// Tiles of up to 48 rows of a grouped product: the mid-M kernel, no split of K over the grid.
-template <int ACT, int BITS>
-int launch_mid_items(const void* A, const fq_small_items& items, int count, int rows_max, const fq_small_shape& sh, int64_t N,
-                     int64_t K, const void* codes, const void* scales, int g, void* C, hipStream_t stream) {
-    constexpr int NT = MMA_NT, MAXW = 12;
-    constexpr int kblk = fq_kblk(BITS);
-    constexpr int STEPS = kblk / FQ_KSTEP;
-    const int sr = (g % kblk) == 0 ? 1 : ((kblk % g) == 0 ? kblk / g : STEPS);
-    const int ngroups = (int)((N / FQ_NTILE + NT - 1) / NT);
-    // (three tiles of 32 rows hold as much as two of 48, and more than what lower items take)
-    const int mt = rows_max <= 16 ? 1 : 2;
-    const size_t lds_act = (size_t)mid_bufs(mt) * sh.kw * mt * 16 * (kblk / 8) * 16;
-    const size_t lds_red = (size_t)sh.gp * sh.kw * NT * ((rows_max + 15) / 16) * 64 * 16;
-    const size_t lds = lds_act > lds_red ? lds_act : lds_red;
-    if (lds > 160 * 1024 || sh.gp * sh.kw > MAXW) return FQ_ERR_UNSUPPORTED;
-    const uint32_t g32 = (uint32_t)(g / 32);
-    const uint32_t g32_recip = (uint32_t)((((uint64_t)1 << 32) + g32 - 1) / g32);   // unused when g32 == 1
-    auto kern = sr == 1 ? fq_gemm_mid_items_kernel<ACT, BITS, NT, 1, MAXW>
-                        : (sr == 2 ? fq_gemm_mid_items_kernel<ACT, BITS, NT, 2, MAXW>
-                                   : fq_gemm_mid_items_kernel<ACT, BITS, NT, STEPS, MAXW>);
-    if (lds > 65536) {
-        static std::atomic<uint64_t> raised[3];   // per instantiation: [scale rows per k-block]
-        if (raise_lds_limit((const void*)kern, raised[sr == 1 ? 0 : (sr == 2 ? 1 : 2)]) != FQ_OK) return FQ_ERR_HIP;
-    }
-    const int64_t blocks = (int64_t)((ngroups + sh.gp - 1) / sh.gp) * count;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3((unsigned)(sh.gp * sh.kw * 64)), lds, stream, (const uint16_t*)A,
-                       (const u32x4*)codes, (const uint16_t*)scales, (uint16_t*)C, (int)N, (int)K, g32, g32_recip, sh.gp, sh.kw,
-                       items);
-    return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_HIP;
-}
-
 // Grouped (per-expert) product.  Every expert's rows are cut into row tiles (fq_next_tile), and the tiles of each class go
 // to the kernel instantiated for it: experts with few rows then stream their weights through small tiles instead of
 // multiplying mostly padding.  Experts without rows produce no tile.
@@ -429,9 +429,12 @@ int launch_grouped_typed(const void* A, const int32_t* offsets, int E, const fq_
             for (int32_t r = offsets[e], take = 0; r < offsets[e + 1]; r += take) {
                 if (fq_next_tile(plan, offsets[e + 1] - r, &take) != cls || (height > 0 && (take + 15) / 16 * 16 != height)) continue;
                 small.row0[count] = r;
-                small.rows[count] = (uint8_t)take;
+                // (an expert of up to 48 rows, and what a 128- or 64-row tile leaves over, had lower tiles always)
+                const bool exact = plan.cut == FQ_CUT_MID && offsets[e + 1] - offsets[e] > 48;
+                small.rows[count] = (uint8_t)(take | (exact ? FQ_ITEM_EXACT : 0));
                 small.expert[count] = (uint8_t)e;
-                rows_max = take > rows_max ? take : rows_max;
+                const int32_t as = exact && take <= 16 ? 17 : take;      // (an exact item takes two row tiles at least)
+                rows_max = as > rows_max ? as : rows_max;
                 if (++count == 256) {
                     const int st = flush_small(height > 0);
                     if (st != FQ_OK) return st;

@@ -812,7 +812,7 @@ struct MidOperand<ACT, BITS, true> : ExactOperand<ACT, BITS> {
     static constexpr uint32_t NEG = 0u;
 };
 
-template <int ACT, int BITS, int NT, int MT, int DEPTH, int NBUF, int SR>
+template <int ACT, int BITS, int NT, int MT, int DEPTH, int NBUF, int SR, bool EXACT>
 __device__ __forceinline__ void mid_block(
     u32x4* lds, const uint16_t* __restrict__ A, const u32x4* __restrict__ codes, const uint16_t* __restrict__ scales,
     uint16_t* __restrict__ C, float* __restrict__ partial, int M, int N, int K, uint32_t g32,
@@ -825,7 +825,7 @@ __device__ __forceinline__ void mid_block(
     constexpr int NI = TILE / 64;                   // wave-level direct loads of such a tile
     constexpr int RB = fq_rec_bytes(BITS);
     constexpr int NW = 2 * NT;                      // vector loads of one stage
-    typedef MidOperand<ACT, BITS, mid_exact(ACT, BITS, MT, SR)> OP;
+    typedef MidOperand<ACT, BITS, EXACT> OP;
     static_assert(STEPS % SR == 0 && (NBUF == 2 || NBUF == 3) && DEPTH >= 2 && (DEPTH - 1) * NW < 64, "");
     constexpr int AHEAD = NBUF - 1;                 // iterations the activations are loaded ahead
     typedef SkinnyStage<BITS, NT, SR, 0> Stage;
@@ -1094,13 +1094,16 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_kernel(
     extern __shared__ u32x4 lds[];
     const int ngroups = (N / FQ_NTILE + NT - 1) / NT;
     const int bgroups = (ngroups + gp - 1) / gp;      // blocks per grid split
-    mid_block<ACT, BITS, NT, MT, mid_depth(MT), mid_bufs(MT), SR>(lds, A, codes, scales, C, partial, M, N, K, g32, g32_recip, gp, kw_n,
+    mid_block<ACT, BITS, NT, MT, mid_depth(MT), mid_bufs(MT), SR, mid_exact(ACT, BITS, MT, SR)>(lds, A, codes, scales, C, partial, M, N, K, g32, g32_recip, gp, kw_n,
                                                                   blockIdx.x % bgroups, blockIdx.x / bgroups, grid_splits);
 }
 
 // Row tiles of up to 16, 32 or 48 rows, each with its own rows and weights, in one launch.  A launch per height would need
 // either streams of their own (forking and joining them costs a call about 30 us: 2688 x 1392, ten experts of 57 rows and
 // less, 42 us with 64- and 32-row tiles and the small-M kernel side by side, 13.6 in one launch) or a ragged end each.
+// Items marked FQ_ITEM_EXACT (in `rows`) have no bias in their operands: those that the tiled kernel would give to its
+// 128- or 64-row tiles.  (Without a bias everywhere, bf16 calls of 4-bit codes would take 1.1 - 1.3x the time.)
+#define FQ_ITEM_EXACT 0x80
 template <int ACT, int BITS, int NT, int SR, int MAXW>
 __global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_items_kernel(
     const uint16_t* __restrict__ A, const u32x4* __restrict__ codes, const uint16_t* __restrict__ scales,
@@ -1111,17 +1114,22 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_items_kernel(
     const int item = blockIdx.x / bgroups, bx = blockIdx.x % bgroups;
     const int64_t row0 = items.row0[item];
     const int e = items.expert[item];
-    const int M = items.rows[item];
+    const int M = items.rows[item] & ~FQ_ITEM_EXACT;
+    const bool exact = items.rows[item] & FQ_ITEM_EXACT;
     A += row0 * K;
     C += row0 * N;
     codes += e * items.codes_stride16;
     scales += e * items.scales_stride;
-    if (M <= 16)
-        mid_block<ACT, BITS, NT, 1, mid_depth(1), mid_bufs(1), SR>(lds, A, codes, scales, C, nullptr, M, N, K, g32, g32_recip, gp, kw_n, bx, 0, 1);
-    else if (M <= 32)
-        mid_block<ACT, BITS, NT, 2, mid_depth(2), mid_bufs(2), SR>(lds, A, codes, scales, C, nullptr, M, N, K, g32, g32_recip, gp, kw_n, bx, 0, 1);
-    else
-        mid_block<ACT, BITS, NT, 3, mid_depth(3), mid_bufs(3), SR>(lds, A, codes, scales, C, nullptr, M, N, K, g32, g32_recip, gp, kw_n, bx, 0, 1);
+    constexpr bool EX2 = mid_exact(ACT, BITS, 2, SR), EX3 = mid_exact(ACT, BITS, 3, SR);
+#define FQ_MID_ITEM(MT_, EXACT_)                                                                                          \
+    mid_block<ACT, BITS, NT, MT_, mid_depth(MT_), mid_bufs(MT_), SR, EXACT_>(lds, A, codes, scales, C, nullptr, M, N, K, g32, \
+                                                                             g32_recip, gp, kw_n, bx, 0, 1)
+    if (!EX3 && exact && M > 32) FQ_MID_ITEM(3, true);
+    else if (M > 32) FQ_MID_ITEM(3, EX3);
+    else if (!EX2 && exact) FQ_MID_ITEM(2, true);
+    else if (M > 16) FQ_MID_ITEM(2, EX2);
+    else FQ_MID_ITEM(1, EX2);
+#undef FQ_MID_ITEM
 }
 
 // Sum of split-K partials, fixed order, then conversion to the activation type.

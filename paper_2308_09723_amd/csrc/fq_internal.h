@@ -45,6 +45,12 @@ struct fq_gemm_plan {
 inline bool fq_flexible(const fq_gemm_plan& p) { return p.kind == 1 && p.mt >= 5 && !(p.mt == 8 && p.nt == 3); }
 // act_dtype: FQ_F16 or FQ_BF16; the plans differ in the block shape alone (see fq_plan_flexible), not in the scratch
 fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int act_dtype);
+// Rows of the next tile of the mid-M kernel when `left` are left: as few tiles as 48 rows allow, of nearly equal height.
+inline int32_t fq_mid_rows(int32_t left) {
+    const int32_t n = (left + 47) / 48;
+    const int32_t even = ((left + n - 1) / n + 15) / 16 * 16;
+    return left < even ? left : even;
+}
 // Grouped product.  Every expert's rows are cut into tiles, and the tiles of one class share a launch: 128 or 64 rows of the
 // tiled kernel, up to 48 of the mid-M one, up to 16 of the small-M one.
 enum fq_tile_class { FQ_TILE_128, FQ_TILE_64, FQ_TILE_MID, FQ_TILE_SMALL, FQ_TILE_CLASSES };
@@ -56,8 +62,7 @@ struct fq_grouped_plan {
     fq_small_shape mid;          // block shape of the mid-M kernel
 };
 fq_grouped_plan fq_plan_grouped(const int32_t* offsets, int E, int64_t N, int64_t K, int bits, int g);
-// The next tile of an expert that has `left` rows left.  Tiles of the mid-M kernel are as few as 48 rows allow and of nearly
-// equal height.
+// The next tile of an expert that has `left` rows left.
 inline fq_tile_class fq_next_tile(const fq_grouped_plan& p, int32_t left, int32_t* take) {
     if (p.cut == FQ_CUT_SMALL) {
         *take = left < 16 ? left : 16;
@@ -68,9 +73,7 @@ inline fq_tile_class fq_next_tile(const fq_grouped_plan& p, int32_t left, int32_
         *take = left < tall ? left : tall;
         return tall == 128 ? FQ_TILE_128 : FQ_TILE_64;
     }
-    const int32_t n = (left + 47) / 48;
-    const int32_t even = ((left + n - 1) / n + 15) / 16 * 16;
-    *take = left < even ? left : even;
+    *take = fq_mid_rows(left);
     return FQ_TILE_MID;
 }
 // Block shape of the small-M kernel for `count` items of a grouped product (at most 16 rows each);

@@ -724,3 +724,31 @@ def test_grouped_gemm_rows_beside_one_that_is_not_finite(bits, g):
     keep = [r for r in range(offsets[-1]) if r not in hit]
     assert torch.equal(got[keep].view(torch.int16), want[keep].view(torch.int16))
     assert not bool(torch.isfinite(got[hit]).all())
+
+
+@pytest.mark.parametrize("form", ["grouped"])
+@pytest.mark.parametrize("dtype,bits,g", [("f16", 4, 128), ("bf16", 4, 128), ("bf16", 4, 64), ("bf16", 3, 64), ("bf16", 8, 128),
+                                          ("bf16", 4, 32)])
+def test_outlying_activations_on_zero_weights_in_row_blocks(dtype, bits, g, form):
+    """As test_outlying_activations_on_zero_weights: row blocks of more than 48 rows, and the tiles of experts of more than 48
+    rows, have no bias in their operands whatever the format."""
+    _say(f"outliers on zero weights in row blocks {dtype} int{bits} g={g} {form}")
+    fq, torch = _fq(), torch_mod()
+    K, N = 2304, (112 if form == "grouped" else 2064)
+    rows = [50, 97] if form == "grouped" else [int(form[2:])]
+    W = workloads.weights_gaussian(K, N, 41)
+    W[::96] = 0
+    A = workloads.activations(sum(rows), K, dtype, 42).astype(np.float32)
+    A[:, ::96] = 60000.0 if dtype == "f16" else workloads.round_to_bf16(np.float32([1e8]))[0]
+    codes, scales, q_ref, s_ref = assert_quantizer_parity(W, bits, g)
+    Ad = to_dev_act(A.astype(np.float16) if dtype == "f16" else A, dtype)
+    if form == "grouped":
+        assert _grouped_plan(rows, K, N, bits, g)["mid-m"] == 5
+        C = fq.gemm_grouped(Ad, [0, rows[0], sum(rows)], torch.cat([codes] * 2), torch.cat([scales.reshape(-1)] * 2), bits, g, N)
+    else:
+        assert "mid-m rows=48" in fq.gemm_describe(sum(rows), N, K, bits, g)
+        C = fq.gemm(Ad, codes, scales, bits, g)
+    Wd = q_ref.astype(np.float64) * np.repeat(s_ref.astype(np.float64), g, axis=0)
+    terms = np.abs(A.astype(np.float64)) @ np.abs(Wd)
+    err = np.abs(from_dev_act(C, dtype) - A.astype(np.float64) @ Wd)
+    assert np.max(err / terms) <= 2 * (2.0 ** -11 if dtype == "f16" else 2.0 ** -8) + 2.0 ** -20
