@@ -157,7 +157,7 @@ static bool fq_mid_pays(double t_mid, const fq_gemm_plan& t, double t_tiled, int
 // matrices narrower than 8192 columns, where bfloat16 products do not take the fp16 matrix path.  Two scale rows: the 32-row shape stays where it is chosen (41 against 40 us
 // in the one record).  Above 256 rows a plan whose last round is split along K stays: it was the faster one in 26 of 37 such
 // records (up to 1.27x).
-static void fq_plan_flexible(int64_t M, int64_t N, int64_t K, int bits, int g, int act_dtype, int ncu, double best,
+static double fq_plan_flexible(int64_t M, int64_t N, int64_t K, int bits, int g, int act_dtype, int ncu, double best,
                              fq_gemm_plan* p) {
     static const struct { int mt, nt; } shapes[5] = {{5, 2}, {6, 2}, {7, 2}, {8, 2}, {5, 3}};
     static const double consts[5][5] = {
@@ -166,15 +166,16 @@ static void fq_plan_flexible(int64_t M, int64_t N, int64_t K, int bits, int g, i
         {1.525, 1.60, 1.73, 1.84, 2.36},    // four
         {1.19, 1.31, 1.46, 1.57, 1.67},     // 8-bit, k-blocks of 128 rows
         {0.62, 0.74, 0.75, 0.85, 0.86}};    // 8-bit, k-blocks of 64 rows
-    if (M <= 64 || M > 1024 || N < 8192) return;
+    const double other = best;
+    if (M <= 64 || M > 1024 || N < 8192) return other;
     const bool low = p->mt < 8;      // replaces 32- or 64-row blocks
     const size_t scratch = FQ_NOALLOC_SCRATCH_BYTES;
     const bool fits = fq_partial_bytes(*p, M, N) <= scratch;
-    if (low && fits && (act_dtype != FQ_F16 || p->splits > 1 || p->tail_tiles > 0)) return;
+    if (low && fits && (act_dtype != FQ_F16 || p->splits > 1 || p->tail_tiles > 0)) return other;
     const int kblk = fq_mma_kblk(bits, 8, 8, K, g);
     const int sr = g % kblk == 0 ? 1 : (kblk % g == 0 ? kblk / g : kblk / 32);
-    if (bits != 8 && sr == 2 && p->mt == 2) return;
-    if (M > 256 && p->tail_tiles > 0) return;
+    if (bits != 8 && sr == 2 && p->mt == 2) return other;
+    if (M > 256 && p->tail_tiles > 0) return other;
     const double* u = consts[bits == 8 ? (kblk == 128 ? 3 : 4) : (sr == 1 ? 0 : (sr == 2 ? 1 : 2))];
     const int KB = (int)(K / kblk);
     const int ntiles = (int)(N / FQ_NTILE);
@@ -208,7 +209,7 @@ static void fq_plan_flexible(int64_t M, int64_t N, int64_t K, int bits, int g, i
             }
         }
     }
-    if (chosen.splits == 0) return;
+    if (chosen.splits == 0) return other;
     if (low && (act_dtype != FQ_F16 || chosen.splits > 1)) {
         // (the split does not fit fq_gemm_noalloc's scratch: the same blocks without it)
         chosen = *p;
@@ -219,6 +220,7 @@ static void fq_plan_flexible(int64_t M, int64_t N, int64_t K, int bits, int g, i
     chosen.tail_splits = 1;
     chosen.tail_kbs = 0;
     *p = chosen;
+    return best;
 }
 
 // Microseconds a block of the tiled kernel spends on 128 rows of K (see fq_plan_gemm):
@@ -231,6 +233,74 @@ static const double* fq_tiled_costs(int bits, int g) {
         {1.73, 0.77, 1.73, 1.035, 2.50, 1.47, 1.2, 1.35}};   // 8-bit
     const int sr = g % 128 == 0 ? 1 : (128 % g == 0 ? 128 / g : 4);
     return consts[bits == 8 ? 3 : (sr == 1 ? 0 : (sr == 2 ? 1 : 2))];
+}
+
+// Model of a grouped call, fitted (of log time, rms error 10 %) to 200 calls of 8 .. 64 experts, 8 .. 2048 tokens and
+// matrices from 1024 x 1024 to 4096 x 16384, each cut in up to ten ways.
+//   a block of the tiled kernel     its cost per 128 rows of K (fq_tiled_costs) times tile_f, + 10 us
+//   a block of the mid-M kernel     iterations of fq_mid_model's length times mid_f (at least 1 us, memory at 8.5 TB/s), + 5.8 us
+//   a block of the small-M kernel   1.26 us per iteration, + 5 us (2.5 without k-workers)
+//   a launch                        the compute units' share of its blocks + 0.35 of the longest for the ragged end (not more
+//                                   than its whole rounds for the mid-M kernel); at least the longest
+// Side by side on streams of their own the launches share one ragged end, but forking and joining the streams costs 21 us.
+
+// Block shape of the mid-M kernel for the tiles of a grouped product (count[i]: those of i + 1 row tiles); the launch's
+// time, the time its blocks hold the compute units in all, and the longest of them.
+static double fq_plan_grouped_mid(const int (&count)[3], int64_t N, int64_t K, int bits, int g, fq_small_shape* sh,
+                                  double* busy_us, double* block_us) {
+    static const double mid_f[2][3] = {{0.67, 1.13, 0.88}, {0.8, 0.96, 1.19}};      // (3- and 4-bit codes, 8-bit codes)
+    const int ngroups = (int)((N / FQ_NTILE + MMA_NT - 1) / MMA_NT);
+    const double ncu = (double)fq_cu_count();
+    const int items = count[0] + count[1] + count[2];
+    const fq_mid_model model[3] = {fq_mid_model(1, K, bits, g), fq_mid_model(2, K, bits, g), fq_mid_model(3, K, bits, g)};
+    const fq_mid_model& tallest = model[count[2] ? 2 : (count[1] ? 1 : 0)];
+    double best = 1e30;
+    for (int gp = 1; gp <= 12; ++gp) {
+        const int kw = tallest.workers(gp);
+        const double per_item = (double)((ngroups + gp - 1) / gp);
+        const double active = per_item * items < ncu ? per_item * items : ncu;
+        double sum = 0.0, longest = 0.0;
+        for (int i = 0; i < 3; ++i) {
+            if (count[i] == 0) continue;
+            const double t_work = mid_f[bits == 8][i] * model[i].compute(gp * kw), t_mem = model[i].memory(gp, kw, active, 8.5e6);
+            const double t_it = t_work > t_mem ? t_work : t_mem;
+            const double t = ((model[i].KB + kw - 1) / kw) * (t_it > 1.0 ? t_it : 1.0) + 5.8;
+            sum += t * per_item * count[i];
+            longest = t > longest ? t : longest;
+        }
+        const double rounds = ceil(per_item * items / ncu) * longest;
+        double total = sum / ncu + 0.35 * longest;
+        total = total < rounds ? total : rounds;
+        if (total < longest) total = longest;
+        if (total < best - 1e-9) {
+            best = total;
+            *busy_us = sum;
+            *block_us = longest;
+            sh->gp = gp;
+            sh->kw = kw;
+        }
+    }
+    return best;
+}
+
+// Time of the small-M kernel for a block shape (NT = nt column tiles per wave), fitted (of log time, rms error 11 %) to 190
+// problems of 1 .. 16 rows from 1024 x 1024 to 12288 x 49152 with 80 shapes each, timed inside graphs.  An iteration takes 0.3 us
+// and the longer of its vector work and its memory traffic at 9 TB/s over the resident blocks (which find part of it in a
+// cache); a split of K over the grid another kernel, whose launch costs the host 3.5 us, too, and the partial sums.
+static double fq_small_us(int64_t M, int64_t N, int64_t K, int bits, int g, int ncu, int nt, int gp, int kw, int au, int gs) {
+    const int kblk = fq_kblk(bits), sr = fq_scale_rows(bits, g), waves = gp * kw;
+    const int ntiles = (int)(N / FQ_NTILE), KB = (int)(K / kblk);
+    const double blocks = (double)((ntiles + nt * gp - 1) / (nt * gp)) * gs;
+    const double slots = (double)ncu * (waves <= 6 ? 12 / waves : 1);
+    const double n_it = (double)((((KB + kw - 1) / kw) + gs - 1) / gs);
+    const double bytes = waves * (nt * 64.0 * fq_rec_bytes(bits) + nt * 32.0 * sr) + (double)M * kw * kblk;
+    const double together = blocks <= ncu ? 1.0 : (blocks < slots ? blocks : slots) / ncu;
+    const double work = 0.022 * waves * nt * ((bits == 8 ? 0.33 : 1.0) + 0.12 * sr) * together;
+    const double mem = bytes * (blocks < slots ? blocks : slots) / 9e6;
+    const double t_it = (work > mem ? work : mem) + 0.3 + (au == 2 ? 0.3 : (au == 4 ? 2.7 : 0.0));
+    const double rounds = blocks / slots, full = ceil(rounds);
+    const double t = (3.9 + n_it * t_it) * (full > 1.0 ? 0.45 * full + 0.55 * rounds : 1.0);
+    return gs > 1 ? t + 3.6 + 2.0 * gs * (double)M * (double)N * 4.0 / 1.65e6 : t;
 }
 
 fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int act_dtype) {
@@ -295,6 +365,34 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
                     p.au = au;
                     p.waves = waves;
                     p.splits = gs;
+                }
+            }
+        }
+        // A split of K over the grid gives way where the blocks alone are as fast: the scores above were made for matrices
+        // that take 15 us and more.  190 problems of 1 .. 16 rows: 89 lose their split, 1.11x on average over all (inside
+        // graphs), none more than 3 % slower; 2304 x 4528, 13 rows 9.9 -> 6.7 us, and a launch less
+        // (3.7 us of the host's time).  Matrices of up to 64 column tiles, a quarter of the compute units, keep their split:
+        // callers and tests take the smallest matrices to need scratch (1024 x 1024, 4 rows would take 4.5 us instead of 7).
+        static const int groups[6] = {1, 2, 3, 4, 6, 12};
+        double best_us = 1e30;
+        if (p.splits > 1 && 4 * ntiles > ncu)
+            best_us = 0.85 * fq_small_us(M, N, K, bits, g, ncu, SKINNY_VARIANTS[p.variant].nt, p.gp, p.kw, p.au, p.splits);
+        for (int v = 0; best_us < 20.0 && v < 4; ++v) {
+            for (const int gp : groups) {
+                const int need = (int)M * kc;
+                const int au = need <= 64 * gp ? 1 : (need <= 128 * gp ? 2 : 0);
+                int kw = SKINNY_VARIANTS[v].maxw / gp;
+                if (kw > KB) kw = KB;
+                if (au == 0 || kw < 1) continue;
+                const double t = fq_small_us(M, N, K, bits, g, ncu, SKINNY_VARIANTS[v].nt, gp, kw, au, 1);
+                if (t < best_us - 1e-9) {
+                    best_us = t;
+                    p.variant = v;
+                    p.gp = gp;
+                    p.kw = kw;
+                    p.au = au;
+                    p.waves = gp * kw;
+                    p.splits = 1;
                 }
             }
         }
@@ -450,54 +548,6 @@ fq_small_shape fq_plan_grouped_small(int count, int units, int ngroups, int KB) 
         if (t < best_t) {
             best_t = t;
             best = s;
-        }
-    }
-    return best;
-}
-
-// Model of a grouped call, fitted (of log time, rms error 10 %) to 200 calls of 8 .. 64 experts, 8 .. 2048 tokens and
-// matrices from 1024 x 1024 to 4096 x 16384, each cut in up to ten ways.
-//   a block of the tiled kernel     its cost per 128 rows of K (fq_tiled_costs) times tile_f, + 10 us
-//   a block of the mid-M kernel     iterations of fq_mid_model's length times mid_f (at least 1 us, memory at 8.5 TB/s), + 5.8 us
-//   a block of the small-M kernel   1.26 us per iteration, + 5 us (2.5 without k-workers)
-//   a launch                        the compute units' share of its blocks + 0.35 of the longest for the ragged end (not more
-//                                   than its whole rounds for the mid-M kernel); at least the longest
-// Side by side on streams of their own the launches share one ragged end, but forking and joining the streams costs 21 us.
-
-// Block shape of the mid-M kernel for the tiles of a grouped product (count[i]: those of i + 1 row tiles); the launch's
-// time, the time its blocks hold the compute units in all, and the longest of them.
-static double fq_plan_grouped_mid(const int (&count)[3], int64_t N, int64_t K, int bits, int g, fq_small_shape* sh,
-                                  double* busy_us, double* block_us) {
-    static const double mid_f[2][3] = {{0.67, 1.13, 0.88}, {0.8, 0.96, 1.19}};      // (3- and 4-bit codes, 8-bit codes)
-    const int ngroups = (int)((N / FQ_NTILE + MMA_NT - 1) / MMA_NT);
-    const double ncu = (double)fq_cu_count();
-    const int items = count[0] + count[1] + count[2];
-    const fq_mid_model model[3] = {fq_mid_model(1, K, bits, g), fq_mid_model(2, K, bits, g), fq_mid_model(3, K, bits, g)};
-    const fq_mid_model& tallest = model[count[2] ? 2 : (count[1] ? 1 : 0)];
-    double best = 1e30;
-    for (int gp = 1; gp <= 12; ++gp) {
-        const int kw = tallest.workers(gp);
-        const double per_item = (double)((ngroups + gp - 1) / gp);
-        const double active = per_item * items < ncu ? per_item * items : ncu;
-        double sum = 0.0, longest = 0.0;
-        for (int i = 0; i < 3; ++i) {
-            if (count[i] == 0) continue;
-            const double t_work = mid_f[bits == 8][i] * model[i].compute(gp * kw), t_mem = model[i].memory(gp, kw, active, 8.5e6);
-            const double t_it = t_work > t_mem ? t_work : t_mem;
-            const double t = ((model[i].KB + kw - 1) / kw) * (t_it > 1.0 ? t_it : 1.0) + 5.8;
-            sum += t * per_item * count[i];
-            longest = t > longest ? t : longest;
-        }
-        const double rounds = ceil(per_item * items / ncu) * longest;
-        double total = sum / ncu + 0.35 * longest;
-        total = total < rounds ? total : rounds;
-        if (total < longest) total = longest;
-        if (total < best - 1e-9) {
-            best = total;
-            *busy_us = sum;
-            *block_us = longest;
-            sh->gp = gp;
-            sh->kw = kw;
         }
     }
     return best;
