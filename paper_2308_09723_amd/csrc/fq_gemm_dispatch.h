@@ -158,6 +158,20 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
         const int st = plan.mt == 2 ? launch_mid<ACT, BITS, MMA_NT, 2, 12>(A, M, N, K, codes, scales, g, C, partial, plan, stream)
                                     : launch_mid<ACT, BITS, MMA_NT, 3, 12>(A, M, N, K, codes, scales, g, C, partial, plan, stream);
         if (st != FQ_OK) return st;
+    } else if (plan.kind == 3) {
+        // row blocks of the mid-M kernel: as few as 48 rows allow, of nearly equal height, all without a bias
+        fq_small_items items;
+        items.codes_stride16 = items.scales_stride = 0;
+        int count = 0;
+        for (int32_t r = 0, take = 0; r < M; r += take) {
+            take = fq_mid_rows((int32_t)M - r);
+            items.row0[count] = r;
+            items.rows[count] = (uint8_t)(take | FQ_ITEM_EXACT);
+            items.expert[count] = 0;
+            ++count;
+        }
+        const int st = launch_mid_items<ACT, BITS>(A, items, count, 48, {plan.gp, plan.kw}, N, K, codes, scales, g, C, stream);
+        if (st != FQ_OK) return st;
     } else {
         // rows of K per k-block of this block shape (two layout blocks at a time for 8-bit codes in the
         // 8-wave shapes of 80 rows and more), and the scale rows such a k-block spans: 1, kblk / g, or one per 32-row step

@@ -28,7 +28,7 @@ int fq_launch_mfma_rate_probe(const void* operands, void* sink, int iterations, 
 
 // product side
 struct fq_gemm_plan {
-    int kind;      // 0 = skinny (M <= 16), 1 = tiled, 2 = mid-M streaming (17 <= M <= 48)
+    int kind;      // 0 = skinny (M <= 16), 1 = tiled, 2 = mid-M streaming (17 <= M <= 48), 3 = its row blocks (M > 48)
     int mt;        // row tiles of 16 per block (tiled and mid-M kernel)
     int nt;        // tiled kernel: column tiles of 16 per wave (3, or 2 in the flexible shapes)
     int waves;     // waves per block

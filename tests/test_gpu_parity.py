@@ -726,7 +726,20 @@ def test_grouped_gemm_rows_beside_one_that_is_not_finite(bits, g):
     assert not bool(torch.isfinite(got[hit]).all())
 
 
-@pytest.mark.parametrize("form", ["grouped"])
+@pytest.mark.parametrize("M", [49, 64, 97, 145])
+@pytest.mark.parametrize("dtype,bits,g,K,N", [("f16", 4, 128, 2304, 2064), ("bf16", 4, 128, 2304, 2064), ("f16", 4, 64, 1280, 1552),
+                                              ("bf16", 4, 64, 1280, 1552), ("bf16", 4, 32, 768, 784), ("bf16", 8, 128, 1024, 1552),
+                                              ("f16", 8, 64, 1152, 1552), ("f16", 3, 96, 768, 784), ("bf16", 3, 96, 768, 784)])
+def test_gemm_row_blocks_of_the_streaming_kernel(dtype, bits, g, K, N, M):
+    """49 rows and more on small matrices: row blocks of 48 and 32 rows and a lower last one, every number of scale rows per
+    k-block, last super-blocks that are not full, idle column groups."""
+    desc = _fq().gemm_describe(M, N, K, bits, g)
+    _say(f"gemm row blocks {dtype} int{bits} g={g} K={K} N={N} M={M}: {desc}")
+    assert "mid-m rows=48" in desc
+    _gemm_case(M, K, N, dtype, bits, g, seed=8100 + M + K + N)
+
+
+@pytest.mark.parametrize("form", ["M=97", "M=145", "grouped"])
 @pytest.mark.parametrize("dtype,bits,g", [("f16", 4, 128), ("bf16", 4, 128), ("bf16", 4, 64), ("bf16", 3, 64), ("bf16", 8, 128),
                                           ("bf16", 4, 32)])
 def test_outlying_activations_on_zero_weights_in_row_blocks(dtype, bits, g, form):
