@@ -937,6 +937,10 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K) {
     return p;
 }
 
+size_t w8_partial_bytes(const w8_plan& p, int64_t M, int64_t N) {
+    return p.splits > 1 ? (size_t)p.splits * (size_t)M * (size_t)N * sizeof(int32_t) : 0;
+}
+
 int w8_check(int64_t K, int64_t N, int group_size, int* g_eff) {
     if (K <= 0 || N <= 0 || group_size < 0) return FQ_ERR_INVALID_ARG;
     const int64_t g = group_size == 0 ? K : (int64_t)group_size;
@@ -978,9 +982,8 @@ int w8_launch_small(const w8_plan& p, int g, const int8_t* Aq, const float* alph
 }
 
 template <int OUT>
-int w8_gemm(const int8_t* Aq, const float* alpha, int64_t M, int64_t N, int64_t K, const void* codes, const uint8_t* z,
-            const void* tstep, int g, void* C, void* workspace, hipStream_t stream) {
-    const w8_plan p = w8_plan_of(M, N, K);
+int w8_gemm(const w8_plan& p, const int8_t* Aq, const float* alpha, int64_t M, int64_t N, int64_t K, const void* codes,
+            const uint8_t* z, const void* tstep, int g, void* C, void* workspace, hipStream_t stream) {
     int32_t* partial = (int32_t*)workspace;
     if (p.small) {
         const bool zr1 = g % 128 == 0;
@@ -1068,8 +1071,7 @@ int fq_quantize_act_i8(const void* A, int act_dtype, int64_t M, int64_t K, int8_
 size_t fq_gemm_w4a8_workspace_bytes(int64_t M, int64_t N, int64_t K, int group_size) {
     int g = 0;
     if (M <= 0 || w8_check(K, N, group_size, &g) != FQ_OK) return 0;
-    const w8_plan p = w8_plan_of(M, N, K);
-    return p.splits > 1 ? (size_t)p.splits * (size_t)M * (size_t)N * sizeof(int32_t) : 0;
+    return w8_partial_bytes(w8_plan_of(M, N, K), M, N);
 }
 
 int fq_gemm_w4a8(const int8_t* Aq, const float* alpha, int64_t M, int64_t N, int64_t K, const void* codes,
@@ -1083,11 +1085,12 @@ int fq_gemm_w4a8(const int8_t* Aq, const float* alpha, int64_t M, int64_t N, int
     if (M == 0) return FQ_OK;
     if (!Aq || !alpha || !codes || !zscale || !tstep_f16 || !C) return FQ_ERR_INVALID_ARG;
     if (M > (int64_t)1 << 24) return FQ_ERR_UNSUPPORTED;
-    const size_t need = fq_gemm_w4a8_workspace_bytes(M, N, K, group_size);
+    const w8_plan p = w8_plan_of(M, N, K);
+    const size_t need = w8_partial_bytes(p, M, N);
     if (need > 0 && (!workspace || workspace_bytes < need)) return FQ_ERR_WORKSPACE;
     if (out_dtype == FQ_F16)
-        return w8_gemm<FQ_F16>(Aq, alpha, M, N, K, codes, zscale, tstep_f16, g, C, workspace, (hipStream_t)stream);
-    return w8_gemm<FQ_BF16>(Aq, alpha, M, N, K, codes, zscale, tstep_f16, g, C, workspace, (hipStream_t)stream);
+        return w8_gemm<FQ_F16>(p, Aq, alpha, M, N, K, codes, zscale, tstep_f16, g, C, workspace, (hipStream_t)stream);
+    return w8_gemm<FQ_BF16>(p, Aq, alpha, M, N, K, codes, zscale, tstep_f16, g, C, workspace, (hipStream_t)stream);
 }
 
 }  // extern "C"

@@ -6,6 +6,7 @@ take torch tensors (torch is used for device memory and streams only).
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 
@@ -161,7 +162,7 @@ def gemm_describe(M, N, K, bits, group_size):
 def gemm_grouped_describe(offsets, N, K, bits, group_size):
     buf = ctypes.create_string_buffer(256)
     E = len(offsets) - 1
-    arr = (ctypes.c_int32 * (E + 1))(*[int(o) for o in offsets])
+    arr = _int32_array(offsets)
     st = int(load().fq_gemm_grouped_describe(arr, E, N, K, bits, group_size, buf, 256))
     if st != FQ_OK:
         raise FqError(st, "fq_gemm_grouped_describe")
@@ -233,10 +234,19 @@ def gemm_sf_raw(A_ptr, act_dtype, M, N, K, codes_ptr, scales_ptr, scale_format, 
                                  C_ptr, ws_ptr, ws_bytes, stream))
 
 
+def _int32_array(values):
+    """The values as a ctypes array."""
+    try:
+        packed = array.array("i", values)       # (a list of ints: a tenth of the time that converting each one takes)
+    except (TypeError, OverflowError):
+        return (ctypes.c_int32 * len(values))(*[int(v) for v in values])
+    return (ctypes.c_int32 * len(packed)).from_buffer(packed)
+
+
 def gemm_grouped_raw(A_ptr, act_dtype, offsets, N, K, codes_ptr, scales_ptr, bits, group_size, C_ptr,
                      ws_ptr=None, ws_bytes=0, stream=0):
     E = len(offsets) - 1
-    arr = (ctypes.c_int32 * (E + 1))(*[int(o) for o in offsets])
+    arr = _int32_array(offsets)
     return int(load().fq_gemm_grouped(A_ptr, act_dtype, arr, E, N, K, codes_ptr, scales_ptr, bits, group_size,
                                       C_ptr, ws_ptr, ws_bytes, stream))
 
@@ -244,7 +254,7 @@ def gemm_grouped_raw(A_ptr, act_dtype, offsets, N, K, codes_ptr, scales_ptr, bit
 def gemm_grouped_sf_raw(A_ptr, act_dtype, offsets, N, K, codes_ptr, scales_ptr, scale_format, bits, group_size,
                         C_ptr, ws_ptr=None, ws_bytes=0, stream=0):
     E = len(offsets) - 1
-    arr = (ctypes.c_int32 * (E + 1))(*[int(o) for o in offsets])
+    arr = _int32_array(offsets)
     return int(load().fq_gemm_grouped_sf(A_ptr, act_dtype, arr, E, N, K, codes_ptr, scales_ptr, scale_format, bits,
                                          group_size, C_ptr, ws_ptr, ws_bytes, stream))
 
@@ -276,10 +286,29 @@ def gemm_w4a8_raw(Aq_ptr, alpha_ptr, M, N, K, codes_ptr, z_ptr, t_ptr, group_siz
 
 
 # ------------------------------------------------------------------ torch-tensor conveniences
-def _stream():
+# (What a call spends here counts on small products: asking torch for its current stream as an object took 2.9 us of the
+# 9.1 us of a fq.gemm of one launch; the stream's address alone, and functions looked up once, leave 5.8.)
+def _torch():
+    """torch, and the function that gives a device's current stream as an address, looked up on the first call."""
+    global _torch_mod, _raw_stream, _device
     import torch
 
-    return torch.cuda.current_stream().cuda_stream
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if _raw_stream is None:
+        _raw_stream = lambda device: torch.cuda.current_stream(device).cuda_stream  # noqa: E731
+    _device = torch.cuda.current_device
+    _torch_mod = torch
+    return torch
+
+
+_torch_mod = _raw_stream = _device = None
+
+
+def _stream():
+    """Address of the current device's current stream."""
+    if _torch_mod is None:
+        _torch()
+    return _raw_stream(_device())
 
 
 def _check(status, where):
@@ -288,8 +317,7 @@ def _check(status, where):
 
 
 def _act_code(t):
-    import torch
-
+    torch = _torch_mod or _torch()
     if t.dtype == torch.float16:
         return FQ_F16
     if t.dtype == torch.bfloat16:
@@ -299,8 +327,7 @@ def _act_code(t):
 
 def _scale_format_of(scales):
     """The fq_scale_format a scale tensor's dtype stands for."""
-    import torch
-
+    torch = _torch_mod or _torch()
     if scales.dtype == torch.float16:
         return FQ_SCALE_F16
     if scales.dtype == torch.bfloat16:
@@ -311,8 +338,7 @@ def _scale_format_of(scales):
 def quantize(W, bits, group_size, scale_format=FQ_SCALE_F16):
     """W: cuda float16 [K, N] -> (codes uint8 [K*N*bits/8], scales [K/g, N] float16, or bfloat16 for
     scale_format=FQ_SCALE_BF16)."""
-    import torch
-
+    torch = _torch_mod or _torch()
     assert W.is_cuda and W.dtype == torch.float16 and W.is_contiguous()
     K, N = W.shape
     g = K if group_size in (0, K) else group_size
@@ -329,16 +355,14 @@ def quantize(W, bits, group_size, scale_format=FQ_SCALE_F16):
 
 
 def unpack(codes, K, N, bits):
-    import torch
-
+    torch = _torch_mod or _torch()
     q = torch.empty((K, N), dtype=torch.int8, device=codes.device)
     _check(unpack_raw(codes.data_ptr(), K, N, bits, q.data_ptr(), _stream()), "fq_unpack")
     return q
 
 
 def choose_group(W, g_start, g_min, alpha):
-    import torch
-
+    torch = _torch_mod or _torch()
     K, N = W.shape
     ws_bytes = choose_group_workspace_bytes(K, N, g_start, g_min)
     ws = torch.empty(max(ws_bytes, 16), dtype=torch.uint8, device=W.device)
@@ -349,8 +373,7 @@ def choose_group(W, g_start, g_min, alpha):
 
 def quant_error(W, codes, scales, bits, group_size):
     """Round-trip error of a quantised matrix: (sum of squared errors, largest absolute error)."""
-    import torch
-
+    torch = _torch_mod or _torch()
     assert W.is_cuda and W.dtype == torch.float16 and W.is_contiguous()
     K, N = W.shape
     ws_bytes = quant_error_workspace_bytes(K, N)
@@ -363,8 +386,7 @@ def quant_error(W, codes, scales, bits, group_size):
 
 def gemm(A, codes, scales, bits, group_size, out=None, workspace=None):
     """A: cuda [M, K] float16/bfloat16 -> C [M, N] of the same dtype."""
-    import torch
-
+    torch = _torch_mod or _torch()
     assert A.is_cuda and A.is_contiguous()
     M, K = A.shape
     N = scales.shape[1]
@@ -374,24 +396,20 @@ def gemm(A, codes, scales, bits, group_size, out=None, workspace=None):
         size = gemm_workspace_bytes(M, N, K, bits, group_size)
         workspace = torch.empty(size, dtype=torch.uint8, device=A.device) if size else None
 
-    def call():
-        return gemm_sf_raw(A.data_ptr(), _act_code(A), M, N, K, codes.data_ptr(), scales.data_ptr(),
-                           _scale_format_of(scales), bits, group_size, C.data_ptr(),
-                           workspace.data_ptr() if workspace is not None else None, size, _stream())
-
-    status = call()
+    args = (A.data_ptr(), _act_code(A), M, N, K, codes.data_ptr(), scales.data_ptr(), _scale_format_of(scales), bits,
+            group_size, C.data_ptr())
+    status = gemm_sf_raw(*args, workspace.data_ptr() if workspace is not None else None, size, _stream())
     if status == FQ_ERR_WORKSPACE:      # the caller's is too small (asked only now: the query plans the product once more)
         size = gemm_workspace_bytes(M, N, K, bits, group_size)
         workspace = torch.empty(size, dtype=torch.uint8, device=A.device)
-        status = call()
+        status = gemm_sf_raw(*args, workspace.data_ptr(), size, _stream())
     _check(status, "fq_gemm_sf")
     return C
 
 
 def gemm_grouped(A, offsets, codes, scales, bits, group_size, N, out=None):
     """A: cuda [rows, K]; codes / scales: the experts' buffers back to back."""
-    import torch
-
+    torch = _torch_mod or _torch()
     rows, K = A.shape
     C = out if out is not None else torch.empty((rows, N), dtype=A.dtype, device=A.device)
     _check(gemm_grouped_sf_raw(A.data_ptr(), _act_code(A), offsets, N, K, codes.data_ptr(), scales.data_ptr(),
@@ -402,8 +420,7 @@ def gemm_grouped(A, offsets, codes, scales, bits, group_size, N, out=None):
 
 def quantize_w4a8(W, group_size):
     """W: cuda float16 [K, N] -> (codes uint8 [K*N/2], z uint8 [K/g, N], t float16 [N]) of the integer path."""
-    import torch
-
+    torch = _torch_mod or _torch()
     assert W.is_cuda and W.dtype == torch.float16 and W.is_contiguous()
     K, N = W.shape
     g = K if group_size in (0, K) else group_size
@@ -419,8 +436,7 @@ def quantize_w4a8(W, group_size):
 
 
 def unpack_w4a8(codes, K, N):
-    import torch
-
+    torch = _torch_mod or _torch()
     q = torch.empty((K, N), dtype=torch.int8, device=codes.device)
     _check(unpack_w4a8_raw(codes.data_ptr(), K, N, q.data_ptr(), _stream()), "fq_unpack_w4a8")
     return q
@@ -428,8 +444,7 @@ def unpack_w4a8(codes, K, N):
 
 def quantize_act_i8(A):
     """A: cuda [M, K] float16/bfloat16 -> (Aq int8 [M, K], alpha float32 [M])."""
-    import torch
-
+    torch = _torch_mod or _torch()
     assert A.is_cuda and A.is_contiguous()
     M, K = A.shape
     Aq = torch.empty((M, K), dtype=torch.int8, device=A.device)
@@ -441,17 +456,20 @@ def quantize_act_i8(A):
 
 def gemm_w4a8(Aq, alpha, codes, z, t, group_size, out_dtype, out=None, workspace=None):
     """C [M, N] (torch dtype out_dtype: float16 or bfloat16) = alpha * t * (Aq . (q * z))."""
-    import torch
-
+    torch = _torch_mod or _torch()
     M, K = Aq.shape
     N = t.shape[0]
     C = out if out is not None else torch.empty((M, N), dtype=out_dtype, device=Aq.device)
-    need = gemm_w4a8_workspace_bytes(M, N, K, group_size)
-    if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = torch.empty(need, dtype=torch.uint8, device=Aq.device)
-    ws_ptr = workspace.data_ptr() if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _check(gemm_w4a8_raw(Aq.data_ptr(), alpha.data_ptr(), M, N, K, codes.data_ptr(), z.data_ptr(), t.data_ptr(),
-                         group_size, C.data_ptr(), FQ_F16 if out_dtype == torch.float16 else FQ_BF16, ws_ptr, ws_bytes,
-                         _stream()), "fq_gemm_w4a8")
+    size = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    if workspace is None:
+        size = gemm_w4a8_workspace_bytes(M, N, K, group_size)
+        workspace = torch.empty(size, dtype=torch.uint8, device=Aq.device) if size else None
+    args = (Aq.data_ptr(), alpha.data_ptr(), M, N, K, codes.data_ptr(), z.data_ptr(), t.data_ptr(), group_size, C.data_ptr(),
+            FQ_F16 if out_dtype == torch.float16 else FQ_BF16)
+    status = gemm_w4a8_raw(*args, workspace.data_ptr() if workspace is not None else None, size, _stream())
+    if status == FQ_ERR_WORKSPACE:      # the caller's is too small
+        size = gemm_w4a8_workspace_bytes(M, N, K, group_size)
+        workspace = torch.empty(size, dtype=torch.uint8, device=Aq.device)
+        status = gemm_w4a8_raw(*args, workspace.data_ptr(), size, _stream())
+    _check(status, "fq_gemm_w4a8")
     return C
