@@ -5,27 +5,14 @@
 
 #include <math.h>
 #include <stdint.h>
-#include <atomic>
 
 #include "fq_gemm_config.h"
 #include "fq_gemm_kernels.h"
+#include "fq_lds_limit.h"
 
 namespace fqd {
 
 using namespace fqk;
-
-// Kernels that need more than the default 64 KiB of dynamic LDS have their limit raised to the
-// 160 KiB of a compute unit, once per (kernel instantiation, device): `done` holds one bit per device.
-inline int raise_lds_limit(const void* kern, std::atomic<uint64_t>& done) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return FQ_ERR_HIP;
-    const uint64_t bit = (uint64_t)1 << (dev & 63);
-    if (done.load(std::memory_order_acquire) & bit) return FQ_OK;
-    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
-        return FQ_ERR_HIP;
-    done.fetch_or(bit, std::memory_order_release);
-    return FQ_OK;
-}
 
 template <int ACT, int BITS, int NT, int DEPTH, int MAXW, int AU>
 int launch_skinny(const void* A, int64_t M, int64_t N, int64_t K, const void* codes, const void* scales, int g,

@@ -27,6 +27,7 @@
 #include <stdint.h>
 
 #include "fq_gemm_kernels.h"
+#include "fq_lds_limit.h"
 #include "fq_internal.h"
 #include "fq_layout.h"
 #include "fq_panel.h"
@@ -348,7 +349,7 @@ void w8_launch_act_quant(const uint16_t* A, int64_t M, int64_t K, int8_t* Aq, fl
 // Product.  Same orientation as the floating-point kernels: 16 x 16 tiles of C^T, the weights the first
 // MFMA operand (16 columns n), the activations the second (16 rows m); a lane's packed record is, after the
 // conversion, its slice of the first operand, so weights never pass through LDS.
-// Block = 8 waves x 3 column tiles (384 columns), BM = 16 MT rows, k-block = 128 rows = two MFMA steps.
+// Block = 8 waves x 3 column tiles (384 columns), BM = 16 MT rows (MT = 4 or 8), k-block = 128 rows = two MFMA steps.
 // The k loop is one software pipeline, two k-blocks deep:
 //   * activation tiles (BM rows x 128 int8, natural order) go global -> LDS directly (global_load_lds_dwordx4),
 //     three LDS tiles; the eight 16-byte units of a row are XOR-swizzled with the row (through the global
@@ -508,7 +509,7 @@ __global__ __launch_bounds__(W8_WAVES * 64) void fq_gemm_w4a8_kernel(
     // k-block's first fragments, which follow it, have six MFMA groups to return in (measured 1 - 4 % faster
     // than ahead of the last two groups; the tile it waits for was requested a k-block earlier either way)
     // (with two multiplier rows per k-block the fragments held that much longer cost spilled registers)
-    constexpr int BAR_MT = MT >= 8 ? (ZR == 1 ? 1 : MT - 2) : (MT >= 4 ? MT - 2 : MT - 1);
+    constexpr int BAR_MT = MT >= 8 && ZR == 1 ? 1 : MT - 2;
     u32x4 wopA[NT], wopB[NT], af0[MT], af1[MT];
     // One k-block.  (qa, za): its weights, (qb, zb): those of k-block kb + 1, tile `cur`: its activations.
     // On entry wopA holds the converted operands of its step 0 and af0 that step's fragments (requested);
@@ -545,10 +546,8 @@ __global__ __launch_bounds__(W8_WAVES * 64) void fq_gemm_w4a8_kernel(
             if (mt == BAR_MT) {
                 // every fragment of this tile has been read (own LDS reads returned), and this wave's share of
                 // tile kb + 1 has landed once at most the loads issued after it are in flight
-                // (with a single MFMA group per step the loads of k-block kb + 2 are issued behind this point:
-                // then only the weights of kb + 1 are younger than its tile)
                 __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0) only
-                wait_vmcnt<(BAR_MT == 0 ? NW : DPT + NW)>();
+                wait_vmcnt<DPT + NW>();
                 __syncthreads();
 #pragma unroll
                 for (int m2 = 0; m2 < MT; ++m2) af0[m2] = nbuf[a_rd[0] + m2 * 128];
@@ -848,6 +847,242 @@ __global__ __launch_bounds__(MAXW * 64) void fq_w4a8_skinny_kernel(
     }
 }
 
+// ------------------------------------------------------------------------------------------------------
+// Mid-M kernel of the integer path: row blocks of 16 MT rows (MT = 2 .. 4), the structure of the floating-point
+// fq_gemm_mid_kernel.  A block is GP column groups x KW k-workers (at most 12 waves); codes and multipliers stream through a
+// register ring of W8M_DEPTH stages per wave, the int8 activations of a super-block (16 MT rows x KW k-blocks) go global -> LDS
+// directly, two iterations ahead into one of three tiles, the k-workers' int32 sums are added through LDS (exact in any
+// order).  Against the tiled kernel: K is split inside the block (no slabs through memory, no second kernel, unless the grid
+// is split, too), and blocks of 48 GP columns cut a small output finer.  12288 x 36864, g = 128, tiled kernel ->
+// this one, us: M = 17 55 -> 40 (5.9 TB/s of weights), M = 32 55 -> 41, M = 64 66 -> 46; 8192 x 8192, M = 128 30 -> 24.
+// ------------------------------------------------------------------------------------------------------
+constexpr int W8M_NT = 3, W8M_DEPTH = 3, W8M_MAXW = 12;
+
+template <int ZR>
+struct W8MStage {
+    u32x4 wq[W8M_NT];
+    uint32_t zq[ZR][W8M_NT];
+};
+
+template <int MT, int ZR, int OUT>
+__global__ __launch_bounds__(W8M_MAXW * 64) void fq_w4a8_mid_kernel(
+    const int8_t* __restrict__ Aq, const float* __restrict__ alpha, const u32x4* __restrict__ codes,
+    const uint8_t* __restrict__ z, const uint16_t* __restrict__ tstep, uint16_t* __restrict__ C,
+    int32_t* __restrict__ partial, int M, int N, int K, uint32_t g32, uint32_t g32_recip, int gp, int kw_n, int nblocks_m,
+    int grid_splits) {
+    constexpr int NT = W8M_NT, DEPTH = W8M_DEPTH;
+    constexpr int TILE = 16 * MT * 8;               // 16-byte units of one k-worker's activation tile
+    constexpr int NI = TILE / 64;                   // wave-level direct loads of such a tile
+    constexpr int NW = NT + ZR * NT;                // vector loads of one stage
+    static_assert((DEPTH - 1) * NW < 64, "wait counter range");
+    typedef W8MStage<ZR> Stage;
+    extern __shared__ u32x4 lds[];   // three activation buffers [kw_n][TILE]; later the reduction
+
+    const int tid = threadIdx.x;
+    const int nthreads = blockDim.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int gi = wave / kw_n;
+    const int kw = wave - gi * kw_n;
+    const int ntiles = N / FQ_NTILE;
+    const int ngroups = (ntiles + NT - 1) / NT;
+    const int bgroups = (ngroups + gp - 1) / gp;      // column blocks
+    // (the row blocks of a column block lie next to each other: they read the same weights)
+    const int bx = (blockIdx.x / nblocks_m) % bgroups;
+    const int gsplit = blockIdx.x / (bgroups * nblocks_m);   // < grid_splits
+    const int row0 = (blockIdx.x % nblocks_m) * (16 * MT);
+    const int rows = M - row0 < 16 * MT ? M - row0 : 16 * MT;
+    const int ng = bx * gp + gi;
+    const bool gvalid = ng < ngroups;
+    const int KB = K / 128;
+    const int SB = (KB + kw_n - 1) / kw_n;            // super-blocks of kw_n k-blocks
+    const int n_it = gsplit < SB ? (SB - gsplit + grid_splits - 1) / grid_splits : 0;   // block-uniform
+    const int64_t kb_stride = (int64_t)ntiles * 64;   // records between consecutive k-blocks of a tile
+    const int ml = lane & 15, j = lane >> 4;
+    const int abuf_units = kw_n * TILE;
+    Aq += (int64_t)row0 * K;
+    alpha += row0;
+    C += (int64_t)row0 * N;
+
+    const char* wbase[NT];
+    const uint8_t* zbase[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        const int tile = ng * NT + nt;
+        const int tc = gvalid && tile < ntiles ? tile : 0;
+        wbase[nt] = reinterpret_cast<const char*>(codes + fq_rec(tc, 0, ntiles, 0));
+        zbase[nt] = z + (int64_t)tc * FQ_NTILE;
+    }
+    const uint32_t lane_rec = (uint32_t)lane * 16u;
+
+    // activations of iteration `it`: this wave's share (every gp-th load) of its k-worker's tile.  Unit (row, position) holds
+    // the row's 16-byte unit position ^ (row & 7); rows past the end repeat the last one (never stored).
+    auto load_act = [&](int it) {
+        const int kb = (gsplit + it * grid_splits) * kw_n + kw;
+        const int8_t* base = Aq + (int64_t)(kb < KB ? kb : KB - 1) * 128;   // past the end: never multiplied
+        const uint32_t lds_tile = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)(
+            lds + (it % 3) * abuf_units + kw * TILE);
+        for (int i = gi; i < NI; i += gp) {
+            const int row = i * 8 + (lane >> 3), pos = lane & 7;
+            const int rowc = row < rows ? row : rows - 1;
+            const int8_t* src = base + (int64_t)rowc * K + 16 * (pos ^ (row & 7));
+            load_lds16(__builtin_amdgcn_readfirstlane(lds_tile + i * 1024), src);
+        }
+    };
+    auto load_stage = [&](Stage& sl, int it) {
+        int kb = (gsplit + it * grid_splits) * kw_n + kw;
+        kb = kb < KB ? kb : KB - 1;                      // tail super-block: idle workers re-read the last block
+        const int64_t kb_bytes = (int64_t)kb * kb_stride * 16;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) sl.wq[nt] = load_rec<4, true>(scalar_ptr(wbase[nt] + kb_bytes) + lane_rec);
+#pragma unroll
+        for (int r = 0; r < ZR; ++r) {
+            // group of the 32-row step at hand (ZR == 1: the k-block lies inside one group; else the group of this lane's 16
+            // rows of MFMA step r), by the rounded-up reciprocal as in the small-M kernel
+            const uint32_t step = (uint32_t)kb * 4u + (ZR == 1 ? 0u : 2u * r + (uint32_t)(j >> 1));
+            const uint32_t grp = g32 == 1 ? step : __umulhi(step, g32_recip);
+            const int64_t zrow = (int64_t)grp * N;
+            if constexpr (ZR == 1) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) sl.zq[r][nt] = scalar_ptr(zbase[nt] + zrow)[(uint32_t)ml];
+            } else {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) sl.zq[r][nt] = zbase[nt][zrow + ml];
+            }
+        }
+    };
+    int a_rd[2];
+#pragma unroll
+    for (int T = 0; T < 2; ++T) a_rd[T] = kw * TILE + ml * 8 + ((4 * T + j) ^ (ml & 7));
+
+    v4i acc[MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = v4i{0, 0, 0, 0};
+
+    auto multiply = [&](const Stage& sl, int it) {
+        const u32x4* abuf = lds + (it % 3) * abuf_units;
+        u32x4 af[2][MT];
+#pragma unroll
+        for (int T = 0; T < 2; ++T)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) af[T][mt] = abuf[a_rd[T] + mt * 128];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+            for (int T = 0; T < 2; ++T) {
+                const uint32_t zi = sl.zq[ZR == 1 ? 0 : T][nt];
+                const uint32_t ci = (uint32_t)(0x8080 - (int)zi * 0x0808);   // 128 - 8 z in both bytes
+                const u16x2v zz = {(uint16_t)zi, (uint16_t)zi};
+                const u16x2v cc = {(uint16_t)ci, (uint16_t)ci};
+                u32x4 wop;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint32_t w = sl.wq[nt][2 * T + h];
+                    wop[2 * h] = w8_scale_bytes(w & 0x0f0f0f0fu, zz, cc);
+                    wop[2 * h + 1] = w8_scale_bytes((w >> 4) & 0x0f0f0f0fu, zz, cc);
+                }
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    acc[mt][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bitcast<v4i>(wop), bitcast<v4i>(af[T][mt]), acc[mt][nt], 0, 0, 0);
+            }
+        }
+    };
+    // Iteration `it`.  On entry its activations and weights have landed; in flight: weights of it + 1, it + 2, activations of
+    // it + 1.
+    auto iterate = [&](Stage& sl, int it, bool more) {
+        // (every register of the stage is named here, so that the compiler places its waits for them in front of the
+        // loads issued below: in its count, which does not know of the direct loads, a later wait would reach into them)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            asm volatile("" : "+v"(sl.wq[nt][0]), "+v"(sl.wq[nt][1]), "+v"(sl.wq[nt][2]), "+v"(sl.wq[nt][3]));
+#pragma unroll
+            for (int r = 0; r < ZR; ++r) asm volatile("" : "+v"(sl.zq[r][nt]));
+        }
+        if (it + 2 < n_it) load_act(it + 2);             // into the tile read during it - 1
+        __builtin_amdgcn_sched_barrier(0);
+        if (gvalid && (gsplit + it * grid_splits) * kw_n + kw < KB) multiply(sl, it);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) {
+            load_stage(sl, it + DEPTH);
+            __builtin_amdgcn_sched_barrier(0);
+            // the activations of it + 1 have landed: younger than they are the weights issued at the end of this iteration and
+            // the one before, and this wave's share of the activations of it + 2 (left out of the count: it differs per wave)
+            wait_vmcnt<2 * NW>();
+        } else {
+            wait_vmcnt<0>();
+        }
+        __syncthreads();
+    };
+
+    if (n_it > 0) {
+        Stage ring[DEPTH];
+        load_act(0);
+        load_stage(ring[0], 0);
+        if (1 < n_it) load_act(1);
+#pragma unroll
+        for (int d = 1; d < DEPTH; ++d)
+            if (d < n_it) load_stage(ring[d], d);
+        __builtin_amdgcn_sched_barrier(0);
+        if (DEPTH <= n_it) wait_vmcnt<(DEPTH - 1) * NW>();     // (the loads younger than the activations of 0, at least)
+        else wait_vmcnt<0>();
+        __syncthreads();
+        int it = 0;
+        for (; it + 2 * DEPTH <= n_it; it += DEPTH) {
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) iterate(ring[d], it + d, true);
+        }
+        // drain: at most 2 * DEPTH - 1 iterations are left, the first min(DEPTH, left) already loaded
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d)
+            if (it + d < n_it) iterate(ring[d], it + d, it + d + DEPTH < n_it);
+#pragma unroll
+        for (int d = 0; d < DEPTH - 1; ++d)
+            if (it + d + DEPTH < n_it) iterate(ring[d], it + d + DEPTH, false);
+    }
+
+    auto store_quad = [&](const v4i& v, int group, int mt, int nt, int ln) {
+        const int mq = mt * 16 + (ln & 15), jq = ln >> 4;
+        const int tile = group * NT + nt;
+        if (mq >= rows || group >= ngroups || tile >= ntiles) return;
+        const int64_t n = (int64_t)tile * FQ_NTILE + jq * 4;
+        if (grid_splits == 1) {
+            float tn[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) tn[i] = f16_bits_to_float(tstep[n + i]);
+            w8_store4<OUT>(C + (int64_t)mq * N + n, v, alpha[mq], tn);
+        } else {
+            *reinterpret_cast<v4i*>(partial + ((int64_t)gsplit * M + row0 + mq) * N + n) = v;
+        }
+    };
+    if (kw_n == 1) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) store_quad(acc[mt][nt], ng, mt, nt, lane);
+        return;
+    }
+    // the k-workers' sums of each column group, added by all threads of the block (one result quad each)
+    constexpr int Q = MT * NT * 64;                // result quads of a column group
+    v4i* red = reinterpret_cast<v4i*>(lds);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) red[wave * Q + (mt * NT + nt) * 64 + lane] = acc[mt][nt];
+    __syncthreads();
+    for (int q = tid; q < gp * Q; q += nthreads) {
+        const int gq = q / Q;                      // column group of the block
+        const int r = q - gq * Q;
+        const v4i* src = red + gq * kw_n * Q + r;
+        v4i v = src[0];
+#pragma unroll 4
+        for (int w = 1; w < kw_n; ++w) v += src[w * Q];
+        const int tl = r >> 6;
+        store_quad(v, bx * gp + gq, tl / NT, tl % NT, r & 63);
+    }
+}
+
 template <int OUT>
 __global__ __launch_bounds__(256) void w8_finalize_kernel(const int32_t* __restrict__ S, int splits,
                                                            const float* __restrict__ alpha,
@@ -867,6 +1102,7 @@ __global__ __launch_bounds__(256) void w8_finalize_kernel(const int32_t* __restr
 struct w8_plan {
     int mt, splits, kb_per_split, nblocks_n, nblocks_m;
     int small, gp, kw, au;      // small-M kernel (M <= 16): column groups x k-workers per block, activation units per lane
+    int mid;                    // mid-M kernel (gp, kw as above, mt row tiles per block)
 };
 
 constexpr int W8S_NT = 3, W8S_MAXW = 12;   // the small-M kernel that is compiled in
@@ -874,7 +1110,12 @@ constexpr int W8S_NT = 3, W8S_MAXW = 12;   // the small-M kernel that is compile
 // activation unit per lane: 164 registers; measured 4 - 6 % faster than two on the OPT-175B shapes), else two
 constexpr int w8s_depth(int zr, int au) { return zr == 1 && au == 1 ? 3 : 2; }
 
-w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K) {
+constexpr size_t w8m_lds(int mt, int gp, int kw) {
+    const size_t act = (size_t)3 * kw * mt * 16 * 8 * 16, red = (size_t)gp * kw * mt * W8M_NT * 64 * 16;
+    return act > red ? act : red;
+}
+
+w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
     w8_plan p = {};
     if (M <= 16) {
         // One block per compute unit, all resident at once; the block shape that fills the compute units most
@@ -922,18 +1163,83 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K) {
         p.nblocks_m = 1;
         return p;
     }
-    p.mt = M <= 32 ? 2 : (M <= 64 ? 4 : 8);
+    // More rows: the mid-M kernel (32, 48 or 64 rows per block, up to 700 rows) or the tiled one (64 or 128), whichever shape
+    // and split of K the model gives the least time.  The model was fitted (of log time, rms error 10 %) to 123 problems of
+    // 17 .. 2048 rows, K from 1152 to 16256, N from 1168 to 45856, in 35 shapes each:
+    //   a block     mid-M: 6.7 us + iterations * the longest of 0.94 us, its vector and matrix work (0.92, 1.09 or 1.27 us for
+    //               twelve waves, 0.37 more with two multiplier rows per k-block), its memory traffic at 8.1 TB/s;
+    //               tiled: 6.5 us + k-blocks * 0.80 or 1.18 us
+    //   the launch  blocks per compute unit and 0.47 for the ragged end, at most whole rounds, at least one
+    //   a split     2.5 us for the second kernel and the slabs' traffic at 5 TB/s
+    // Against the tiled kernel alone (32, 64 or 128 rows, K split until 192 tiles): 0.76 of the time on average inside
+    // graphs, never more than 3 % slower; 12288 x 36864 us: M = 17 55 -> 40, M = 64 66 -> 46; 2816 x 5184, M = 95 22 -> 10.
+    const int ncu = fq_cu_count();
     const int ntiles = (int)(N / FQ_NTILE);
-    p.nblocks_n = (ntiles + W8_WAVES * W8_NT - 1) / (W8_WAVES * W8_NT);
-    p.nblocks_m = (int)((M + p.mt * 16 - 1) / (p.mt * 16));
-    const int64_t tiles = (int64_t)p.nblocks_n * p.nblocks_m;
+    const int ngroups = (ntiles + W8M_NT - 1) / W8M_NT;
     const int KB = (int)(K / 128);
-    int splits = 1;
-    if (tiles < 192) splits = (int)(256 / tiles);      // fill the compute units when there are few tiles
-    if (splits > 8) splits = 8;
-    if (splits > KB) splits = KB;
-    p.kb_per_split = (KB + splits - 1) / splits;
-    p.splits = (KB + p.kb_per_split - 1) / p.kb_per_split;
+    const int zr = g % 128 == 0 ? 1 : 2;
+    double best = 1e30;
+    auto launch_us = [&](double blocks, double block_us, int splits) {
+        const double r = blocks / ncu, full = ceil(r);
+        double t = (r <= 1.0 ? 1.0 : (r + 0.47 < full ? r + 0.47 : full)) * block_us;
+        if (splits > 1) t += 2.5 + 2.0 * splits * (double)M * (double)N * 4.0 / 5e6;
+        return t;
+    };
+    static const double mid_work[5] = {0.0, 0.0, 0.92, 1.09, 1.27};
+    static const int groups[6] = {1, 2, 3, 4, 6, 12};
+    const int mt_low = M <= 32 ? 2 : 3, mt_high = M <= 32 ? 2 : (M <= 48 ? 3 : 4);
+    for (int mt = M > 48 && M <= 64 ? 4 : mt_low; M <= 700 && mt <= mt_high; ++mt) {
+        const int nblocks_m = (int)((M + mt * 16 - 1) / (mt * 16));
+        const int fit = (int)(160 * 1024 / w8m_lds(mt, 1, 1));
+        for (const int gp : groups) {
+            int kw = W8M_MAXW / gp;
+            kw = kw < fit ? kw : fit;
+            kw = kw < KB ? kw : KB;
+            const int nblocks_n = (ngroups + gp - 1) / gp;
+            const int SB = (KB + kw - 1) / kw;
+            const double work = (mid_work[mt] + 0.37 * (zr - 1)) * (double)((gp * kw + 3) / 4) / 3.0;
+            for (int gs = 1; gs <= 4 && gs <= SB; gs *= 2) {
+                const double blocks = (double)nblocks_n * nblocks_m * gs;
+                if (gs > 1 && blocks > 300) break;
+                const double mem = (blocks < ncu ? blocks : ncu) * (gp * kw * (3072.0 + 48.0 * zr) + 0.3 * kw * mt * 2048.0) / 8.1e6;
+                double t_it = work > mem ? work : mem;
+                if (t_it < 0.94) t_it = 0.94;
+                const double t = launch_us(blocks, 6.7 + ((SB + gs - 1) / gs) * t_it, gs);
+                if (t < best - 1e-9) {
+                    best = t;
+                    p.mid = 1;
+                    p.mt = mt;
+                    p.gp = gp;
+                    p.kw = kw;
+                    p.splits = gs;
+                    p.nblocks_n = nblocks_n;
+                    p.nblocks_m = nblocks_m;
+                }
+            }
+        }
+    }
+    static const int split_opts[6] = {1, 2, 3, 4, 6, 8};
+    for (int mt = M > 32 && M <= 600 ? 4 : 8; mt <= 8; mt += 4) {
+        if (mt == 8 && M <= 64) break;
+        const int nblocks_n = (ntiles + W8_WAVES * W8_NT - 1) / (W8_WAVES * W8_NT);
+        const int nblocks_m = (int)((M + mt * 16 - 1) / (mt * 16));
+        const int64_t tiles = (int64_t)nblocks_n * nblocks_m;
+        for (int splits : split_opts) {
+            if (splits > KB || (splits > 1 && tiles * splits > 600)) break;
+            const int kbs = (KB + splits - 1) / splits;
+            splits = (KB + kbs - 1) / kbs;
+            const double t = launch_us((double)tiles * splits, 6.5 + kbs * ((mt == 8 ? 1.18 : 0.80) + 0.03 * (zr - 1)), splits);
+            if (t < best - 1e-9) {
+                best = t;
+                p.mid = 0;
+                p.mt = mt;
+                p.splits = splits;
+                p.kb_per_split = kbs;
+                p.nblocks_n = nblocks_n;
+                p.nblocks_m = nblocks_m;
+            }
+        }
+    }
     return p;
 }
 
@@ -981,11 +1287,40 @@ int w8_launch_small(const w8_plan& p, int g, const int8_t* Aq, const float* alph
     return FQ_OK;
 }
 
+template <int MT, int ZR, int OUT>
+int w8_launch_mid(const w8_plan& p, int g, const int8_t* Aq, const float* alpha, const void* codes, const uint8_t* z,
+                  const void* tstep, void* C, int32_t* partial, int64_t M, int64_t N, int64_t K, hipStream_t stream) {
+    const size_t lds = w8m_lds(MT, p.gp, p.kw);
+    const uint32_t g32 = (uint32_t)(g / 32);
+    const uint32_t g32_recip = (uint32_t)((((uint64_t)1 << 32) + g32 - 1) / g32);   // unused when g32 == 1
+    auto kern = fq_w4a8_mid_kernel<MT, ZR, OUT>;
+    if (lds > 160 * 1024 || p.gp * p.kw > W8M_MAXW) return FQ_ERR_UNSUPPORTED;
+    if (lds > 65536) {
+        static std::atomic<uint64_t> raised;
+        if (fqd::raise_lds_limit((const void*)kern, raised) != FQ_OK) return FQ_ERR_HIP;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)(p.nblocks_n * p.nblocks_m * p.splits)), dim3((unsigned)(p.gp * p.kw * 64)), lds,
+                       stream, Aq, alpha, (const u32x4*)codes, z, (const uint16_t*)tstep, (uint16_t*)C, partial, (int)M, (int)N,
+                       (int)K, g32, g32_recip, p.gp, p.kw, p.nblocks_m, p.splits);
+    return FQ_OK;
+}
+
 template <int OUT>
 int w8_gemm(const w8_plan& p, const int8_t* Aq, const float* alpha, int64_t M, int64_t N, int64_t K, const void* codes,
             const uint8_t* z, const void* tstep, int g, void* C, void* workspace, hipStream_t stream) {
     int32_t* partial = (int32_t*)workspace;
-    if (p.small) {
+    if (p.mid) {
+        const bool zr1 = g % 128 == 0;
+        int st;
+#define W8_MID(MT_)                                                                                                   \
+    st = zr1 ? w8_launch_mid<MT_, 1, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream)              \
+             : w8_launch_mid<MT_, 2, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream)
+        if (p.mt == 2) W8_MID(2);
+        else if (p.mt == 3) W8_MID(3);
+        else W8_MID(4);
+#undef W8_MID
+        if (st != FQ_OK) return st;
+    } else if (p.small) {
         const bool zr1 = g % 128 == 0;
         if (zr1 && p.au == 1) w8_launch_small<OUT, 1, 1>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream);
         else if (zr1) w8_launch_small<OUT, 1, 2>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream);
@@ -993,7 +1328,6 @@ int w8_gemm(const w8_plan& p, const int8_t* Aq, const float* alpha, int64_t M, i
         else w8_launch_small<OUT, 2, 2>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream);
     } else
     switch (p.mt) {
-        case 2: w8_launch<2, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream); break;
         case 4: w8_launch<4, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream); break;
         default: w8_launch<8, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream); break;
     }
@@ -1071,7 +1405,7 @@ int fq_quantize_act_i8(const void* A, int act_dtype, int64_t M, int64_t K, int8_
 size_t fq_gemm_w4a8_workspace_bytes(int64_t M, int64_t N, int64_t K, int group_size) {
     int g = 0;
     if (M <= 0 || w8_check(K, N, group_size, &g) != FQ_OK) return 0;
-    return w8_partial_bytes(w8_plan_of(M, N, K), M, N);
+    return w8_partial_bytes(w8_plan_of(M, N, K, g), M, N);
 }
 
 int fq_gemm_w4a8(const int8_t* Aq, const float* alpha, int64_t M, int64_t N, int64_t K, const void* codes,
@@ -1085,7 +1419,7 @@ int fq_gemm_w4a8(const int8_t* Aq, const float* alpha, int64_t M, int64_t N, int
     if (M == 0) return FQ_OK;
     if (!Aq || !alpha || !codes || !zscale || !tstep_f16 || !C) return FQ_ERR_INVALID_ARG;
     if (M > (int64_t)1 << 24) return FQ_ERR_UNSUPPORTED;
-    const w8_plan p = w8_plan_of(M, N, K);
+    const w8_plan p = w8_plan_of(M, N, K, g);
     const size_t need = w8_partial_bytes(p, M, N);
     if (need > 0 && (!workspace || workspace_bytes < need)) return FQ_ERR_WORKSPACE;
     if (out_dtype == FQ_F16)

@@ -272,3 +272,46 @@ def test_activation_quantiser_rows_longer_than_the_registers(M, K, dtype):
     A[1] *= np.float32(1e-36 if dtype == "bf16" else 2.0 ** -14)
     A[0, K - 1] = 40.0
     _quantize_acts(A.astype(np.float16) if dtype == "f16" else workloads.round_to_bf16(A), dtype)
+
+
+@pytest.mark.parametrize("M,K,N,g", [(17, 128, 16, 128), (32, 640, 336, 64), (33, 384, 48, 96), (48, 1664, 1040, 0), (49, 640, 144, 32),
+                                     (64, 256, 400, 128), (65, 1664, 1040, 128), (145, 768, 208, 64), (450, 768, 1200, 64),
+                                     (24, 6656, 1040, 128), (64, 8192, 272, 128), (130, 16384, 272, 32)])
+def test_mid_m_row_blocks(M, K, N, g):
+    """The mid-M kernel of the integer path: 32, 48 and 64 rows per block at their edges, several row blocks and a lower last
+    one, fewer k-blocks than k-workers, last super-blocks that are not full, idle column groups, K split over the grid (the
+    last three), both numbers of multiplier rows per k-block."""
+    from paper_2308_09723_amd import fq
+    torch = torch_mod()
+    codes, z, t, q_ref, z_ref, t_ref = _quantize_weights(workloads.weights_gaussian(K, N, seed=400 + M, outlier_prob=2e-3), g)
+    assert (fq.gemm_w4a8_workspace_bytes(M, N, K, g) > 0) == (K > 4096)
+    for dtype in ("f16", "bf16"):
+        Aq, alpha, a_ref, alpha_ref = _quantize_acts(workloads.activations(M, K, dtype, 410 + M), dtype)
+        out = torch.full((M + 1, N), 7.0, dtype=torch.float16 if dtype == "f16" else torch.bfloat16, device="cuda")
+        fq.gemm_w4a8(Aq, alpha, codes, z, t, g, out.dtype, out=out[:M])
+        _, C_ref = oracle.gemm_ref_int(a_ref, alpha_ref, q_ref, z_ref, t_ref)
+        _check_product(from_dev_act(out[:M], dtype), C_ref, dtype, f"M={M} K={K} N={N} g={g}")
+        assert bool((out[M] == 7.0).all())
+
+
+@pytest.mark.parametrize("M,K,N,g", [(705, 256, 400, 128), (1030, 640, 784, 32), (720, 4096, 272, 64), (801, 384, 400, 128)])
+def test_more_rows_than_the_mid_m_kernel_takes(M, K, N, g):
+    """Above 700 rows every product is the tiled kernel's: 128-row blocks with a lower last one, an odd number of k-blocks, K
+    split over the grid."""
+    from paper_2308_09723_amd import fq
+    codes, z, t, q_ref, z_ref, t_ref = _quantize_weights(workloads.weights_gaussian(K, N, seed=500 + M, outlier_prob=2e-3), g)
+    Aq, alpha, a_ref, alpha_ref = _quantize_acts(workloads.activations(M, K, "f16", 510 + M), "f16")
+    C = from_dev_act(fq.gemm_w4a8(Aq, alpha, codes, z, t, g, torch_mod().float16), "f16")
+    _, C_ref = oracle.gemm_ref_int(a_ref, alpha_ref, q_ref, z_ref, t_ref)
+    _check_product(C, C_ref, "f16", f"M={M} K={K} N={N} g={g}")
+
+
+@pytest.mark.parametrize("M,K,N,g", [(600, 256, 8208, 128), (420, 640, 12304, 32), (101, 2816, 20320, 32)])
+def test_wide_matrices_of_some_hundred_rows(M, K, N, g):
+    """Few rows on many columns, where the plan weighs the mid-M kernel against 64- and 128-row blocks of the tiled one."""
+    from paper_2308_09723_amd import fq
+    codes, z, t, q_ref, z_ref, t_ref = _quantize_weights(workloads.weights_gaussian(K, N, seed=600 + M, outlier_prob=2e-3), g)
+    Aq, alpha, a_ref, alpha_ref = _quantize_acts(workloads.activations(M, K, "bf16", 610 + M), "bf16")
+    C = from_dev_act(fq.gemm_w4a8(Aq, alpha, codes, z, t, g, torch_mod().bfloat16), "bf16")
+    _, C_ref = oracle.gemm_ref_int(a_ref, alpha_ref, q_ref, z_ref, t_ref)
+    _check_product(C, C_ref, "bf16", f"M={M} K={K} N={N} g={g}")
