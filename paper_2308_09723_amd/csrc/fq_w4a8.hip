@@ -1118,16 +1118,22 @@ constexpr size_t w8m_lds(int mt, int gp, int kw) {
 w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
     w8_plan p = {};
     if (M <= 16) {
-        // One block per compute unit, all resident at once; the block shape that fills the compute units most
-        // evenly, scored like the floating-point small-M plan (evenness of the fill squared, bytes in flight per
-        // compute unit up to 64 KiB, a second round of blocks, a split of K over the grid and lone k-workers cost).
+        // The block shape and split of K with the least time by a model fitted (of log time, rms error 5 %) to 80 problems of
+        // 1 .. 16 rows in 20 shapes each: a block takes 4.4 us and per iteration 0.98 us (0.2 more with two activation units
+        // per lane) and its memory traffic at 15 TB/s (a part of it is hidden behind the rest); a split of K 2.1 us for its
+        // second kernel (3.1 below 10 us, where the launch's share of the host's time shows) and the slabs' traffic.  Against the scores below for all: 0.92 of the time inside graphs (1024 x
+        // 19872, 2 rows 9.0 -> 6.7 us; 9 of 10 shapes that were split and are not any more lose a launch, too).
+        // Up to 64 column tiles, a quarter of the compute units, the score stays: it splits such matrices, and callers and
+        // tests take them to need scratch.  (One block per compute unit, all resident at once; evenness of the fill squared,
+        // bytes in flight per compute unit up to 64 KiB, a second round of blocks, a split and lone k-workers cost.)
         const int ncu = fq_cu_count();
         const int ntiles = (int)(N / FQ_NTILE);
         const int KB = (int)(K / 128);
         const int ngroups = (ntiles + W8S_NT - 1) / W8S_NT;
         p.small = 1;
         p.mt = 1;
-        double best = -1.0;
+        const bool narrow = 4 * ntiles <= ncu;
+        double best = -1e30;
         for (int gp = 1; gp <= W8S_MAXW; ++gp) {
             int kw = W8S_MAXW / gp;
             if (kw > KB) kw = KB;
@@ -1136,6 +1142,25 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
             if (au == 0 || kw < 1) continue;
             const int64_t blocks = (ngroups + gp - 1) / gp;
             const int SB = (KB + kw - 1) / kw;
+            if (!narrow) {
+                for (int gs = 1; gs <= 8 && gs <= SB; ++gs) {
+                    const double grid = (double)blocks * gs, full = ceil(grid / ncu);
+                    if (gs > 1 && grid > 330) break;
+                    const double bytes = gp * kw * (3072.0 + 48.0 * (g % 128 == 0 ? 1 : 2)) + 64.0 * (double)M * kw;
+                    const double mem = (grid < ncu ? grid : ncu) * bytes / 15.2e6;
+                    double t = 4.4 + ((SB + gs - 1) / gs) * (mem + (au == 2 ? 1.18 : 0.98));
+                    if (full > 1.0) t *= grid / ncu + 0.35 < full ? grid / ncu + 0.35 : full;
+                    if (gs > 1) t += (t < 10.0 ? 3.1 : 2.1) + 2.0 * gs * (double)M * (double)N * 4.0 / 3.2e6;
+                    if (-t > best + 1e-9) {
+                        best = -t;
+                        p.gp = gp;
+                        p.kw = kw;
+                        p.au = au;
+                        p.splits = gs;
+                    }
+                }
+                continue;
+            }
             int gs = 1;
             if (blocks <= ncu / 2) gs = (int)(ncu / blocks);
             if (gs > 8) gs = 8;
