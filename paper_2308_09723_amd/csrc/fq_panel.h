@@ -59,7 +59,7 @@ __device__ inline uint4 absmax8_block(uint4 mine, uint4 (&red)[16][16], int tx, 
 
 // Abs-max of blocks of f rows -> fine[K / f, N] as binary16 bit patterns; block = 16 x 16 threads, thread (tx, ty)
 // takes 8 consecutive columns (16-byte loads) of the rows ty, ty + 16, ...; grid (N / 128 rounded up, K / f).
-// `clear` (may be null): a word set to zero for the kernels that follow.
+// `clear` (may be null): two words set to zero for the kernels that follow.
 template <int THREADS>   // (a template so that every translation unit may hold a copy)
 __global__ __launch_bounds__(THREADS) void fq_fine_absmax_kernel(const uint16_t* __restrict__ W, int64_t N, int f,
                                                                  uint16_t* __restrict__ fine,
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(THREADS) void fq_fine_absmax_kernel(const uint16_t*
     const int tx = threadIdx.x, ty = threadIdx.y;
     const int64_t n = ((int64_t)blockIdx.x * 16 + tx) * 8;      // N is a multiple of 16
     const int64_t blk = blockIdx.y;
-    if (clear != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && tx == 0 && ty == 0) *clear = 0u;
+    if (clear != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && tx == 0 && ty == 0) clear[0] = clear[1] = 0u;
     uint4 m = make_uint4(0u, 0u, 0u, 0u);
     if (n < N) m = absmax8_slice(W + (blk * f) * N + n, N, f, ty);
     m = absmax8_block(m, red, tx, ty);

@@ -6,7 +6,9 @@
 // clamp) are stated in fq.h.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
+#include <mutex>
 #include <stdint.h>
+#include <string.h>
 
 #include "fq_internal.h"
 #include "fq_layout.h"
@@ -253,19 +255,33 @@ __global__ __launch_bounds__(256) void fq_unpack_kernel(const uint32_t* __restri
 // fine values pairwise, level by level, and sets flag[level] when the smaller child is
 // below thr * parent.  The host then walks the flags from the coarsest level down.
 // ---------------------------------------------------------------------------------
+// Adds a thread's flags.  (Both words live at the memory's point of coherence, where device-wide atomics are performed; an
+// atomic that has returned its old value has been performed.  That order is all publish_flags needs: a __threadfence() in
+// every block, which writes the caches back, made the call 15 us longer on 8192 x 28672.)
+__device__ inline void add_flags(uint32_t* flags, uint32_t hits) {
+    uint32_t old = *(volatile uint32_t*)flags;
+    if (hits & ~old) old = atomicOr(flags, hits);
+    asm volatile("" : : "v"(old) : "memory");
+}
+// The last block to end hands the flags to the host: flags[1] counts the blocks whose flags have been added.  (Copied back by
+// a transfer of their own they cost a call another 10 us.)  Called by one thread, behind the block's add_flags.
+__device__ inline void publish_flags(uint32_t* flags, uint32_t blocks, uint32_t* host) {
+    if (atomicAdd(flags + 1, 1u) == blocks - 1) *host = atomicOr(flags, 0u);
+}
+
 // levels = number of halvings covered; a top group spans 2^levels fine blocks.
-// Bit l of *flags (l = 0 is the coarsest transition g_start -> g_start/2; fq_fine_absmax_kernel clears the word) is
-// set when any parent at that level has min(child) < thr * parent.  One word, and a block or wave that has nothing to
+// Bit l of *flags (l = 0 is the coarsest transition g_start -> g_start/2; fq_fine_absmax_kernel clears the word and the count
+// behind it) is set when any parent at that level has min(child) < thr * parent.  One word, and a block or wave that has nothing to
 // add leaves it alone: every block setting one word per level cost 28 us on 8192 x 28672, nearly all of it atomics
 // waiting for each other (now 15 us).
 __global__ __launch_bounds__(256) void fq_halving_flags_kernel(const uint16_t* __restrict__ fine,
                                                                int64_t N, int64_t tops, int levels,
-                                                               float thr, uint32_t* __restrict__ flags) {
+                                                               float thr, uint32_t* __restrict__ flags,
+                                                               uint32_t* __restrict__ host) {
     const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t top = blockIdx.y;
-    if (n >= N || top >= tops) return;
+    const int64_t top = blockIdx.y;                      // < tops: the grid's height
     const int64_t span = (int64_t)1 << levels;
-    const uint16_t* col = fine + (top * span) * N + n;
+    const uint16_t* col = fine + (top * span) * N + (n < N ? n : 0);
     // Level d = blockIdx.z (d = levels - 1 is the finest transition): parents are pairs of nodes of
     // 2^(levels-1-d) fine blocks, recomputed from the fine array, so a thread reads span values; one
     // grid layer per level keeps enough threads in flight when there are few top groups.
@@ -289,7 +305,9 @@ __global__ __launch_bounds__(256) void fq_halving_flags_kernel(const uint16_t* _
             node = 0;
         }
     }
-    if (hit && !(*(volatile uint32_t*)flags >> d & 1u)) atomicOr(flags, 1u << d);
+    if (hit) add_flags(flags, 1u << d);
+    __syncthreads();
+    if (threadIdx.x == 0) publish_flags(flags, gridDim.x * gridDim.y * gridDim.z, host);
 }
 
 // The same test with the pairwise fold done in LDS (a top group of at most 1024 fine blocks): a block
@@ -300,7 +318,8 @@ __global__ __launch_bounds__(256) void fq_halving_flags_kernel(const uint16_t* _
 // binary16 order like their bit patterns).  Dynamic LDS: 3 * 2^levels * cols bytes.
 __global__ __launch_bounds__(256) void fq_halving_tree_kernel(const uint16_t* __restrict__ fine, int64_t N,
                                                               int levels, float thr, int cols,
-                                                              uint32_t* __restrict__ flags) {
+                                                              uint32_t* __restrict__ flags,
+                                                              uint32_t* __restrict__ host) {
     extern __shared__ uint32_t tree[];     // [span][cols / 2], then [span / 2][cols / 2]: pairs of columns
     const int tid = threadIdx.x;
     const int span = 1 << levels;
@@ -349,7 +368,10 @@ __global__ __launch_bounds__(256) void fq_halving_tree_kernel(const uint16_t* __
         dst = t;
         len = parents;
     }
-    if (tid == 0 && (hits & ~*(volatile uint32_t*)flags)) atomicOr(flags, hits);
+    if (tid == 0) {
+        if (hits) add_flags(flags, hits);
+        publish_flags(flags, gridDim.x * gridDim.y, host);
+    }
 }
 
 // ---------------------------------------------------------------------------------
@@ -569,6 +591,61 @@ __global__ __launch_bounds__(FQ_PROBE_THREADS) void fq_stream_read_kernel(const 
 }
 
 // ----------------------------------------------------------------------------- launchers
+namespace {
+// Results that a call hands back to the host (a word of flags, two sums) are written by its last kernel into pinned host
+// memory instead of being copied there behind it: a copy adds 8 - 12 us (fq_choose_group of 1792 x 2464 33 -> 22 us,
+// fq_quant_error 35 -> 23; with fq_quantize between them 85 -> 60, on 8192 x 28672 454 -> 436).
+// One page for the process, allocated by the first such call, in 64 slots of 64 bytes; a call holds one from before its
+// launches until its stream has been waited for, whatever the thread, stream or device.  With all slots taken, or without the
+// page, results go to the workspace and are copied.
+constexpr int HOST_SLOTS = 64, HOST_SLOT_BYTES = 64;
+std::mutex g_slots_mutex;
+char* g_slots = nullptr;
+bool g_slots_tried = false;
+uint64_t g_slots_taken = 0;
+
+struct host_slot {
+    char* ptr = nullptr;
+    host_slot() {
+        std::lock_guard<std::mutex> lock(g_slots_mutex);
+        if (!g_slots_tried) {
+            g_slots_tried = true;
+            // (another thread may be capturing a graph: this thread's allocation is none of its business)
+            hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+            const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+            void* p = nullptr;
+            if (hipHostMalloc(&p, HOST_SLOTS * HOST_SLOT_BYTES, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+                g_slots = (char*)p;
+            if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+            (void)hipGetLastError();
+        }
+        if (!g_slots || g_slots_taken == ~(uint64_t)0) return;
+        const int i = __builtin_ctzll(~g_slots_taken);
+        g_slots_taken |= (uint64_t)1 << i;
+        ptr = g_slots + i * HOST_SLOT_BYTES;
+    }
+    host_slot(const host_slot&) = delete;
+    ~host_slot() {
+        if (!ptr) return;
+        std::lock_guard<std::mutex> lock(g_slots_mutex);
+        g_slots_taken &= ~((uint64_t)1 << ((ptr - g_slots) / HOST_SLOT_BYTES));
+    }
+    // waits for the stream and takes the result from `out` (the slot, or device memory)
+    int read(void* to, const void* out, size_t bytes, hipStream_t stream) {
+        const bool launched = hipGetLastError() == hipSuccess;
+        bool copied = true;
+        if (launched && !ptr) copied = hipMemcpyAsync(to, out, bytes, hipMemcpyDeviceToHost, stream) == hipSuccess;
+        if (hipStreamSynchronize(stream) != hipSuccess) {
+            ptr = nullptr;          // a kernel may still write there: the slot is not given back
+            return FQ_ERR_HIP;
+        }
+        if (!launched || !copied) return FQ_ERR_HIP;
+        if (ptr) memcpy(to, ptr, bytes);
+        return FQ_OK;
+    }
+};
+}  // namespace
+
 int fq_launch_stream_read_probe(const void* buf, size_t bytes, void* sink, hipStream_t stream) {
     hipLaunchKernelGGL(fq_stream_read_kernel, dim3(FQ_PROBE_BLOCKS), dim3(FQ_PROBE_THREADS), 0, stream, (const probe_u32x4*)buf, bytes / 16,
                        (uint32_t*)sink);
@@ -634,8 +711,10 @@ int fq_launch_unpack(const void* codes, int64_t K, int64_t N, int bits, int8_t* 
 
 int fq_launch_choose_group(const void* W, int64_t K, int64_t N, int g_top, int levels, float alpha,
                            uint32_t* flags_host, void* workspace, hipStream_t stream) {
-    // workspace: [flags: one word, 256 bytes][fine: (K / f) * N binary16]
+    // workspace: [flags: flags, blocks that are done, copy for the host; 256 bytes][fine: (K / f) * N binary16]
     uint32_t* flags = (uint32_t*)workspace;
+    host_slot slot;
+    uint32_t* out = slot.ptr ? (uint32_t*)slot.ptr : flags + 2;
     uint16_t* fine = (uint16_t*)((char*)workspace + 256);
     const int f = g_top >> levels;
     {
@@ -650,19 +729,15 @@ int fq_launch_choose_group(const void* W, int64_t K, int64_t N, int g_top, int l
             const int cols = levels <= 8 ? 64 : (levels == 9 ? 32 : 16);
             dim3 grid((unsigned)((N + cols - 1) / cols), (unsigned)(K / g_top));
             hipLaunchKernelGGL(fq_halving_tree_kernel, grid, dim3(256), (size_t)3 * ((size_t)1 << levels) * cols,
-                               stream, (const uint16_t*)fine, N, levels, thr, cols, flags);
+                               stream, (const uint16_t*)fine, N, levels, thr, cols, flags, out);
         } else {
             dim3 block(256);
             dim3 grid((unsigned)((N + 255) / 256), (unsigned)(K / g_top), (unsigned)levels);   // levels >= 1
             hipLaunchKernelGGL(fq_halving_flags_kernel, grid, block, 0, stream, (const uint16_t*)fine, N,
-                               K / g_top, levels, thr, flags);
+                               K / g_top, levels, thr, flags, out);
         }
     }
-    if (hipGetLastError() != hipSuccess) return FQ_ERR_HIP;
-    if (hipMemcpyAsync(flags_host, flags, sizeof(uint32_t), hipMemcpyDeviceToHost, stream) != hipSuccess)
-        return FQ_ERR_HIP;
-    if (hipStreamSynchronize(stream) != hipSuccess) return FQ_ERR_HIP;
-    return FQ_OK;
+    return slot.read(flags_host, out, sizeof(uint32_t), stream);
 }
 
 int64_t fq_quant_error_blocks(int64_t K, int64_t N) {
@@ -673,8 +748,9 @@ int64_t fq_quant_error_blocks(int64_t K, int64_t N) {
 int fq_launch_quant_error(const void* W, int64_t K, int64_t N, int bits, int g, int sfmt, const void* codes,
                           const void* scales, double* out_host2, void* workspace, hipStream_t stream) {
     // workspace: [out: 2 doubles][partials: 2 * nblk doubles]
-    double* out = (double*)workspace;
-    double* part = out + 2;
+    double* part = (double*)workspace + 2;
+    host_slot slot;
+    double* out = slot.ptr ? (double*)slot.ptr : (double*)workspace;
     const int64_t nblk = fq_quant_error_blocks(K, N);
     dim3 grid((unsigned)nblk);
 #define FQ_QE_GO(B_, X_)                                                                                    \
@@ -686,9 +762,5 @@ int fq_launch_quant_error(const void* W, int64_t K, int64_t N, int bits, int g, 
     else { if (x32) FQ_QE_GO(8, true); else FQ_QE_GO(8, false); }
 #undef FQ_QE_GO
     hipLaunchKernelGGL(fq_quant_error_final_kernel, dim3(1), dim3(1024), 0, stream, (const double*)part, nblk, out);
-    if (hipGetLastError() != hipSuccess) return FQ_ERR_HIP;
-    if (hipMemcpyAsync(out_host2, out, sizeof(double) * 2, hipMemcpyDeviceToHost, stream) != hipSuccess)
-        return FQ_ERR_HIP;
-    if (hipStreamSynchronize(stream) != hipSuccess) return FQ_ERR_HIP;
-    return FQ_OK;
+    return slot.read(out_host2, out, sizeof(double) * 2, stream);
 }
