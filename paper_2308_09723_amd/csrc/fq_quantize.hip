@@ -310,67 +310,83 @@ __global__ __launch_bounds__(256) void fq_halving_flags_kernel(const uint16_t* _
     if (threadIdx.x == 0) publish_flags(flags, gridDim.x * gridDim.y * gridDim.z, host);
 }
 
-// The same test with the pairwise fold done in LDS (a top group of at most 1024 fine blocks): a block
-// takes `cols` neighbouring columns of one top group, loads their 2^levels fine values with coalesced
-// 4-byte loads, and folds them level by level from the finest transition up, alternating between two LDS
-// arrays; every fine value is read from memory once instead of once per level, and no thread walks a
-// whole column.  A thread folds pairs of columns (4-byte LDS accesses, packed 16-bit minima and maxima: magnitudes of
-// binary16 order like their bit patterns).  Dynamic LDS: 3 * 2^levels * cols bytes.
-__global__ __launch_bounds__(256) void fq_halving_tree_kernel(const uint16_t* __restrict__ fine, int64_t N,
-                                                              int levels, float thr, int cols,
-                                                              uint32_t* __restrict__ flags,
-                                                              uint32_t* __restrict__ host) {
-    extern __shared__ uint32_t tree[];     // [span][cols / 2], then [span / 2][cols / 2]: pairs of columns
+// The same test with every fine value read from memory once (a top group of at most 1024 fine blocks).  An item is one top
+// group of 8 * 2^lu columns; a thread takes eight neighbouring columns of R = 2^LR neighbouring fine blocks (16-byte loads, all
+// in flight), folds those in registers, and the rest of the tree by exchange with the thread whose number differs in one bit:
+// inside a wave by shuffles, between waves through LDS.  Both partners form the same parent.  (Packed 16-bit minima and
+// maxima: magnitudes of binary16 order like their bit patterns.)
+// Bound by the count that each block adds to at its end, on one address: about 40 ns a block.  So blocks are large and walk
+// the items, at most FQ_TREE_BLOCKS of them.  With a block of 256 threads per 64 columns and the fold in LDS level by
+// level: 1536 x 37408 down to g = 96 (585 blocks) 23 us, 8192 x 28672 down to 64 (448 blocks) 22 us;
+// now 6 and 10 us (blocks of 256 threads 6 and 12, of 1024 threads 8 and 10.5).
+constexpr int FQ_TREE_THREADS = 512;
+constexpr int FQ_TREE_BLOCKS = 256;
+template <int LR>
+__global__ __launch_bounds__(FQ_TREE_THREADS) void fq_halving_tree_kernel(const uint16_t* __restrict__ fine, int64_t N,
+                                                                          int levels, int lu, float thr, int64_t items_n,
+                                                                          int64_t items, uint32_t* __restrict__ flags,
+                                                                          uint32_t* __restrict__ host) {
+    constexpr int R = 1 << LR;
+    __shared__ uint4 other[FQ_TREE_THREADS];
+    __shared__ uint32_t wave_hits[FQ_TREE_THREADS / 64];
     const int tid = threadIdx.x;
-    const int span = 1 << levels;
-    const int64_t n0 = (int64_t)blockIdx.x * cols;
-    const uint16_t* base = fine + ((int64_t)blockIdx.y * span) * N + n0;
-    const int pairs = cols / 2;            // 8, 16 or 32
-    const int lp = 31 - __clz(pairs);
-    {
-        const int c2 = (tid & (pairs - 1)) * 2;
-        const bool ok = n0 + c2 < N;       // N is even
-        const int step = 256 >> lp;
-        for (int r0 = tid >> lp; r0 < span; r0 += 8 * step) {     // eight loads in flight
-            uint32_t v[8];
+    const int unit = tid & ((1 << lu) - 1);
+    const int64_t row = (int64_t)(tid >> lu) * R;
+    uint32_t hits = 0;                                          // (the same in every lane of a wave)
+    auto fold = [&](uint4& a, const uint4& b, bool& hit) {
+        uint32_t x[4] = {a.x, a.y, a.z, a.w};
+        const uint32_t y[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int r = r0 + u * step;
-                v[u] = (ok && r < span) ? *reinterpret_cast<const uint32_t*>(base + (int64_t)r * N + c2) : 0u;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int r = r0 + u * step;
-                if (r < span) tree[(r << lp) + (c2 >> 1)] = v[u];
-            }
-        }
-    }
-    __syncthreads();
-    uint32_t* src = tree;
-    uint32_t* dst = tree + span * pairs;
-    int len = span;                        // nodes per column at the level being folded
-    uint32_t hits = 0;                     // (the same in every thread)
-    for (int d = levels - 1; d >= 0; --d) {
-        const int parents = len / 2;
-        bool hit = false;
-        for (int i = tid; i < parents * pairs; i += 256) {
-            const int p = i >> lp, c = i & (pairs - 1);
-            const u16x2_t a = __builtin_bit_cast(u16x2_t, src[((2 * p) << lp) + c]);
-            const u16x2_t b = __builtin_bit_cast(u16x2_t, src[((2 * p + 1) << lp) + c]);
-            const u16x2_t lo = __builtin_elementwise_min(a, b), hi = __builtin_elementwise_max(a, b);
+        for (int i = 0; i < 4; ++i) {
+            const u16x2_t p = __builtin_bit_cast(u16x2_t, x[i]), q = __builtin_bit_cast(u16x2_t, y[i]);
+            const u16x2_t lo = __builtin_elementwise_min(p, q), hi = __builtin_elementwise_max(p, q);
             hit = hit || (half_bits_to_float(lo[0]) < __fmul_rn(thr, half_bits_to_float(hi[0])));
             hit = hit || (half_bits_to_float(lo[1]) < __fmul_rn(thr, half_bits_to_float(hi[1])));
-            dst[(p << lp) + c] = __builtin_bit_cast(uint32_t, hi);
+            x[i] = __builtin_bit_cast(uint32_t, hi);
         }
-        if (__syncthreads_or(hit)) hits |= 1u << d;
-        uint32_t* t = src;
-        src = dst;
-        dst = t;
-        len = parents;
+        a = make_uint4(x[0], x[1], x[2], x[3]);
+    };
+    for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+        const int64_t n = (((item % items_n) << lu) + unit) * 8;
+        uint4 m[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) m[r] = make_uint4(0u, 0u, 0u, 0u);
+        if (n < N) {                                            // N is a multiple of 16: whole units
+            const uint16_t* base = fine + (((item / items_n) << levels) + row) * N + n;
+#pragma unroll
+            for (int r = 0; r < R; ++r) m[r] = *reinterpret_cast<const uint4*>(base + (int64_t)r * N);
+        }
+#pragma unroll
+        for (int s = 0; s < LR; ++s) {                          // halving step levels - 1 - s
+            bool hit = false;
+#pragma unroll
+            for (int r = 0; r < R; r += 2 << s) fold(m[r], m[r + (1 << s)], hit);
+            if (__any(hit)) hits |= 1u << (levels - 1 - s);
+        }
+        for (int s = LR; s < levels; ++s) {
+            const int bit = 1 << (lu + s - LR);
+            uint4 o;
+            if (bit < 64) {
+                o = make_uint4(__shfl_xor(m[0].x, bit), __shfl_xor(m[0].y, bit), __shfl_xor(m[0].z, bit),
+                               __shfl_xor(m[0].w, bit));
+            } else {
+                __syncthreads();                                // what was written before has been read
+                other[tid] = m[0];
+                __syncthreads();
+                o = other[tid ^ bit];
+            }
+            bool hit = false;
+            fold(m[0], o, hit);
+            if (__any(hit)) hits |= 1u << (levels - 1 - s);
+        }
     }
+    if ((tid & 63) == 0) wave_hits[tid >> 6] = hits;
+    __syncthreads();
     if (tid == 0) {
+#pragma unroll
+        for (int i = 1; i < FQ_TREE_THREADS / 64; ++i) hits |= wave_hits[i];
         if (hits) add_flags(flags, hits);
-        publish_flags(flags, gridDim.x * gridDim.y, host);
+        publish_flags(flags, gridDim.x, host);
     }
 }
 
@@ -725,11 +741,19 @@ int fq_launch_choose_group(const void* W, int64_t K, int64_t N, int g_top, int l
     {
         const float thr = 1.0f - alpha;
         if (levels <= 10) {
-            // fold in LDS: 64 / 32 / 16 columns per block for up to 256 / 512 / 1024 fine blocks (<= 48 KiB)
-            const int cols = levels <= 8 ? 64 : (levels == 9 ? 32 : 16);
-            dim3 grid((unsigned)((N + cols - 1) / cols), (unsigned)(K / g_top));
-            hipLaunchKernelGGL(fq_halving_tree_kernel, grid, dim3(256), (size_t)3 * ((size_t)1 << levels) * cols,
-                               stream, (const uint16_t*)fine, N, levels, thr, cols, flags, out);
+            // threads * R values per item: 8 * 2^lu columns of 2^levels fine blocks
+            const int lr = levels < 3 ? levels : 3;
+            int lu = lr - levels;
+            while ((1 << (lu - lr + levels)) < FQ_TREE_THREADS) ++lu;
+            const int64_t items_n = (N + ((int64_t)8 << lu) - 1) / ((int64_t)8 << lu), items = items_n * (K / g_top);
+            const dim3 grid((unsigned)(items < FQ_TREE_BLOCKS ? items : FQ_TREE_BLOCKS));
+#define FQ_TREE_GO(LR_)                                                                                               \
+    hipLaunchKernelGGL(fq_halving_tree_kernel<LR_>, grid, dim3(FQ_TREE_THREADS), 0, stream, (const uint16_t*)fine, N, \
+                       levels, lu, thr, items_n, items, flags, out)
+            if (lr == 1) FQ_TREE_GO(1);
+            else if (lr == 2) FQ_TREE_GO(2);
+            else FQ_TREE_GO(3);
+#undef FQ_TREE_GO
         } else {
             dim3 block(256);
             dim3 grid((unsigned)((N + 255) / 256), (unsigned)(K / g_top), (unsigned)levels);   // levels >= 1

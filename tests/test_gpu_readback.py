@@ -55,3 +55,21 @@ def test_choose_group_flags_of_many_blocks(K, N, g_min):
             X[row, col] = 8.0
         for alpha in (0.0, 0.5, 0.99):
             assert fq.choose_group(torch.from_numpy(X).cuda(), 0, g_min, alpha) == oracle.choose_group(X, 0, g_min, alpha), (row, alpha)
+
+
+@pytest.mark.parametrize("K,N,g_start,g_min", [(8320, 4112, 64, 32), (16640, 48, 128, 32), (2048, 4112, 256, 32), (512, 8208, 512, 32)])
+def test_choose_group_items_of_the_halving_tree(K, N, g_start, g_min):
+    """1 - 4 halvings below several top groups: more items than blocks, ragged last items; the one group that halves stands anywhere."""
+    from paper_2308_09723_amd import fq
+    torch = torch_mod()
+    W = np.ones((K, N), dtype=np.float16)
+    for row, col in ((None, None), (0, 0), (K - 1, N - 1), (K // 2, N // 2 + 5), (K - g_start, 17)):
+        X = W.copy()
+        if row is not None:
+            X[row, col] = 8.0
+        for alpha in (0.5, 0.9):
+            assert fq.choose_group(torch.from_numpy(X).cuda(), g_start, g_min, alpha) == oracle.choose_group(X, g_start, g_min, alpha), (row, alpha)
+    X = (np.random.default_rng(K + N).standard_normal((K, N)) * 0.02).astype(np.float16)
+    X[K // 3, 5], X[K // 2, 9], X[1, N - 1] = np.inf, np.nan, -np.inf
+    for alpha in (0.2, 0.6, 0.9):
+        assert fq.choose_group(torch.from_numpy(X).cuda(), g_start, g_min, alpha) == oracle.choose_group(X, g_start, g_min, alpha), alpha
