@@ -344,17 +344,20 @@ int fq_gemm_describe(int64_t M, int64_t N, int64_t K, int bits, int group_size, 
     int kbs = p.kb_per_split, cls = p.mt <= 2 ? 2 : (p.mt <= 4 ? 4 : 8);
     const bool streams = p.kind == 2 || p.kind == 3;
     if (p.kind == 3 && M > 256) cls = 8;
+    // (32- and 64-row blocks of more than 256 rows stand in the class of 128 rows and 4 waves, whose k-blocks are as long as theirs)
+    const bool low = p.kind == 1 && cls < 8 && M > 256;
+    if (low) cls = 8;
     if (streams) {
         const int KB = (int)(K / fq_mma_kblk(bits, cls, 8, K, g));
         kbs = (KB + p.splits - 1) / p.splits;
     }
     const int n = snprintf(buf, buf_bytes, "tiled mt=%d waves=%d splits=%d kb_per_split=%d tail=%dx%d", cls,
-                           streams ? 8 : p.waves, p.splits, kbs, p.tail_tiles, p.tail_tiles > 0 ? p.tail_splits : 1);
+                           streams ? 8 : (low ? 4 : p.waves), p.splits, kbs, p.tail_tiles, p.tail_tiles > 0 ? p.tail_splits : 1);
     if (n < 0 || (size_t)n >= buf_bytes) return FQ_OK;
     const fq_gemm_plan f = fq_plan_gemm(M, N, K, bits, g, FQ_F16);
     if (streams)
         snprintf(buf + n, buf_bytes - n, " mid-m rows=%d gp=%d kw=%d waves=%d", 16 * p.mt, p.gp, p.kw, p.waves);
-    else if (fq_flexible(p))
+    else if (low || fq_flexible(p))
         snprintf(buf + n, buf_bytes - n, " rows=%d cols=%d", 16 * p.mt, p.waves * p.nt * FQ_NTILE);
     else if (fq_flexible(f))
         snprintf(buf + n, buf_bytes - n, " f16: rows=%d cols=%d", 16 * f.mt, f.waves * f.nt * FQ_NTILE);

@@ -416,7 +416,8 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
         // converting the weights again) and often win there, e.g. QKV at M = 128 in two 64-row blocks
         // and no split of K.  Beyond 256 rows a narrow matrix makes few 128-row blocks, so the smaller ones compete there too
         // where the matrix has less than 8192 columns (wider bfloat16 products take the fp16 matrix path, in 128-row
-        // blocks only).  They have to win by 5 % and to need no more scratch than the 128-row plan.  97 problems of 257 .. 2048
+        // blocks only).  They have to win by 5 % and to need no more scratch than the 128-row plan; 8-bit
+        // plans in k-blocks of 128 rows stay (none of the problems below would leave them).  97 problems of 257 .. 2048
         // rows: 13 change, 1.16x faster on average; 70 others: 15 change, 1.15x, none more than 1 % slower; 1152 x 2640, M = 1035 3-bit 22 -> 14 us,
         // 5376 x 4816, M = 1212 106 -> 81, 9472 x 3504, M = 1546 137 -> 118.
         p.kind = 1;
@@ -429,12 +430,13 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
         p.tail_kbs = 0;
         double best128 = 1e30;       // the 128-row blocks' time and split of K
         int splits128 = 1;
+        bool wide128 = false;        // 8-bit codes in k-blocks of 128 rows
         for (int mt = 8; mt >= 2; mt /= 2) {
             // a block shape is a candidate when the matrix has more rows than half its height (the
             // smallest always is), and the small ones up to 256 rows, or 2048 on narrow matrices
             if (mt > 2 && (int64_t)mt * 8 >= M) continue;
             const bool tall = mt < 8 && M > 256;
-            if (tall && (N >= 8192 || M > 2048)) continue;
+            if (tall && (N >= 8192 || M > 2048 || wide128)) continue;
             const int bm = mt * 16;
             const int64_t nbm = (M + bm - 1) / bm;
             const double u8 = mt == 8 ? cs[4] : (mt == 4 ? cs[2] : cs[0]);
@@ -515,6 +517,7 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
             if (mt == 8) {
                 best128 = best;
                 splits128 = p.splits;
+                wide128 = fq_mma_kblk(bits, 8, p.waves, K, g) != kblk;
             }
         }
         if (M <= 48) {

@@ -773,5 +773,5 @@ def test_gemm_small_row_blocks_above_256_rows(M, K, N, dtype, bits, g, mt):
     """Narrow matrices: 32- and 64-row blocks of the tiled kernel for 257 .. 2048 rows (last row blocks of 1 .. 28 rows, split K)."""
     desc = _fq().gemm_describe(M, N, K, bits, g)
     _say(f"M={M} K={K} N={N} {dtype} int{bits} g={g}: {desc}")
-    assert f"mt={mt} " in desc and "rows=" not in desc, desc
+    assert f" rows={16 * mt} cols=" in desc, desc
     _gemm_case(M, K, N, dtype, bits, g, seed=9700 + M)
