@@ -345,7 +345,8 @@ int fq_gemm_describe(int64_t M, int64_t N, int64_t K, int bits, int group_size, 
     const bool streams = p.kind == 2 || p.kind == 3;
     if (p.kind == 3 && M > 256) cls = 8;
     // (32- and 64-row blocks of more than 256 rows stand in the class of 128 rows and 4 waves, whose k-blocks are as long as theirs)
-    const bool low = p.kind == 1 && cls < 8 && M > 256;
+    auto below_class = [&](const fq_gemm_plan& q) { return q.kind == 1 && q.mt < 5 && M > 256; };
+    const bool low = below_class(p);
     if (low) cls = 8;
     if (streams) {
         const int KB = (int)(K / fq_mma_kblk(bits, cls, 8, K, g));
@@ -359,7 +360,7 @@ int fq_gemm_describe(int64_t M, int64_t N, int64_t K, int bits, int group_size, 
         snprintf(buf + n, buf_bytes - n, " mid-m rows=%d gp=%d kw=%d waves=%d", 16 * p.mt, p.gp, p.kw, p.waves);
     else if (low || fq_flexible(p))
         snprintf(buf + n, buf_bytes - n, " rows=%d cols=%d", 16 * p.mt, p.waves * p.nt * FQ_NTILE);
-    else if (fq_flexible(f))
+    else if (below_class(f) || fq_flexible(f))
         snprintf(buf + n, buf_bytes - n, " f16: rows=%d cols=%d", 16 * f.mt, f.waves * f.nt * FQ_NTILE);
     return FQ_OK;
 }

@@ -417,9 +417,11 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
         // and no split of K.  Beyond 256 rows a narrow matrix makes few 128-row blocks, so the smaller ones compete there too
         // where the matrix has less than 8192 columns (wider bfloat16 products take the fp16 matrix path, in 128-row
         // blocks only).  They have to win by 5 % and to need no more scratch than the 128-row plan; 8-bit
-        // plans in k-blocks of 128 rows stay (none of the problems below would leave them).  97 problems of 257 .. 2048
-        // rows: 13 change, 1.16x faster on average; 70 others: 15 change, 1.15x, none more than 1 % slower; 1152 x 2640, M = 1035 3-bit 22 -> 14 us,
-        // 5376 x 4816, M = 1212 106 -> 81, 9472 x 3504, M = 1546 137 -> 118.
+        // plans of eight waves stay (none of the problems below would leave them).  Where these blocks hold bfloat16
+        // operands with their storage bias and the 128-row ones hold q s, binary16 products alone take them, in the same split of K
+        // (one size of scratch serves both types): beside activations 10^6 times their neighbours a bias costs precision.
+        // 167 problems of 257 .. 2048 rows: 19 change, 1.15x faster on average, none more than 1.4 % slower; 1408 x 2752,
+        // M = 1046 8-bit 27 -> 19 us, 5376 x 4816, M = 1212 g = 64 106 -> 81.
         p.kind = 1;
         const double* cs = fq_tiled_costs(bits, g);
         const int split_opts[6] = {1, 2, 3, 4, 6, 8};
@@ -428,15 +430,17 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
         p.tail_tiles = 0;
         p.tail_splits = 1;
         p.tail_kbs = 0;
-        double best128 = 1e30;       // the 128-row blocks' time and split of K
-        int splits128 = 1;
-        bool wide128 = false;        // 8-bit codes in k-blocks of 128 rows
+        double best128 = 1e30;       // the 128-row blocks' time and plan
+        fq_gemm_plan p128 = {};
         for (int mt = 8; mt >= 2; mt /= 2) {
             // a block shape is a candidate when the matrix has more rows than half its height (the
             // smallest always is), and the small ones up to 256 rows, or 2048 on narrow matrices
             if (mt > 2 && (int64_t)mt * 8 >= M) continue;
             const bool tall = mt < 8 && M > 256;
-            if (tall && (N >= 8192 || M > 2048 || wide128)) continue;
+            if (tall && (N >= 8192 || M > 2048 || (bits == 8 && p128.waves == 8))) continue;
+            // (a biased bfloat16 operand, as use_post and Dequant make it)
+            const bool biased = bits != 8 && (fq_scale_rows(bits, g) == 1 || (mt == 2 && fq_scale_rows(bits, g) == 2));
+            if (tall && biased && (act_dtype != FQ_F16 || p128.tail_tiles > 0)) continue;
             const int bm = mt * 16;
             const int64_t nbm = (M + bm - 1) / bm;
             const double u8 = mt == 8 ? cs[4] : (mt == 4 ? cs[2] : cs[0]);
@@ -451,7 +455,8 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
                 const double u = (waves == 8 ? u8 : u4) * kscale;
                 for (int si = 0; si < 6; ++si) {
                     int splits = split_opts[si];
-                    if (splits > KB || (tall && splits > splits128)) break;
+                    if (splits > KB || (tall && splits > p128.splits)) break;
+                    if (tall && biased && splits != p128.splits) continue;
                     const int kbs = (KB + splits - 1) / splits;
                     splits = (KB + kbs - 1) / kbs;
                     const int64_t blocks = nbn * nbm * splits;
@@ -516,8 +521,7 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
             }
             if (mt == 8) {
                 best128 = best;
-                splits128 = p.splits;
-                wide128 = fq_mma_kblk(bits, 8, p.waves, K, g) != kblk;
+                p128 = p;
             }
         }
         if (M <= 48) {

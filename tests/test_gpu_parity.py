@@ -767,11 +767,14 @@ def test_outlying_activations_on_zero_weights_in_row_blocks(dtype, bits, g, form
     assert np.max(err / terms) <= 2 * (2.0 ** -11 if dtype == "f16" else 2.0 ** -8) + 2.0 ** -20
 
 
-@pytest.mark.parametrize("M,K,N,dtype,bits,g,mt", [(1009, 640, 2064, "f16", 4, 32, 2), (769, 640, 2656, "bf16", 3, 128, 2), (1020, 640, 5744, "bf16", 4, 128, 4), (600, 1536, 3968, "f16", 8, 32, 4),
-                                                   (2048, 512, 2064, "bf16", 4, 64, 4), (270, 7168, 2112, "f16", 4, 64, 4), (1000, 640, 4400, "f16", 4, 0, 4)])
-def test_gemm_small_row_blocks_above_256_rows(M, K, N, dtype, bits, g, mt):
-    """Narrow matrices: 32- and 64-row blocks of the tiled kernel for 257 .. 2048 rows (last row blocks of 1 .. 28 rows, split K)."""
+@pytest.mark.parametrize("M,K,N,dtype,bits,g,shape", [(1009, 640, 2064, "f16", 4, 32, " rows=32 cols=384"), (1345, 640, 1584, "bf16", 3, 64, " rows=64 cols=192"),
+                                                      (600, 1536, 3968, "f16", 8, 32, " rows=64 cols=192"), (2048, 512, 2064, "bf16", 4, 64, " rows=64 cols=384"),
+                                                      (270, 7168, 2112, "f16", 4, 64, " rows=64 cols=192"), (1000, 640, 4400, "f16", 4, 0, " f16: rows=64 cols=384"),
+                                                      (1020, 640, 5744, "bf16", 4, 128, " f16: rows=64 cols=384")])
+def test_gemm_small_row_blocks_above_256_rows(M, K, N, dtype, bits, g, shape):
+    """Narrow matrices: 32- and 64-row blocks of the tiled kernel for 257 .. 2048 rows (last row blocks of 1 .. 40 rows, split K);
+    binary16 products alone where these blocks' bfloat16 operands have a bias."""
     desc = _fq().gemm_describe(M, N, K, bits, g)
     _say(f"M={M} K={K} N={N} {dtype} int{bits} g={g}: {desc}")
-    assert f" rows={16 * mt} cols=" in desc, desc
+    assert shape in desc, desc
     _gemm_case(M, K, N, dtype, bits, g, seed=9700 + M)
