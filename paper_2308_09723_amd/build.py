@@ -56,6 +56,10 @@ NO_SPILL = [
     "fq_gemm_mid_kernel<0, 4, 3, 2, 1, 12>",                # QKV / FC1 at M = 32, fp16
     "fq_gemm_mid_kernel<1, 4, 3, 2, 1, 12>",                # the same, bf16
     "fq_gemm_mid_kernel<0, 4, 3, 3, 1, 12>",                # M = 48, fp16
+    "fq_gemm_mid_items_kernel<0, 4, 3, 2, 12>",             # experts of 17 - 48 rows, fp16 int4 g = 64
+    "fq_gemm_mid_items_kernel<1, 4, 3, 2, 12>",             # the same, bf16
+    "fq_w4a8_mid_kernel<2, 1, 0>",                          # integer path, 17 - 32 rows
+    "fq_w4a8_mid_kernel<4, 1, 0>",                          # integer path, 49 - 64 rows
     "fq_gemm_mma_kernel<0, 4, 2, 3, 8, 1, false, 2, true, 1>",    # out-proj / FC2 at M = 32, fp16, post-scaled
     "fq_gemm_mma_kernel<0, 4, 7, 2, 8, 2, false, 2, false, 1>",   # 200 rows, fp16 int4 g = 64: 112 x 256
     "fq_gemm_mma_kernel<0, 4, 8, 3, 8, 1, false, 2, false, 1>",   # prefill, fp16
