@@ -1115,25 +1115,85 @@ constexpr size_t w8m_lds(int mt, int gp, int kw) {
     return act > red ? act : red;
 }
 
-w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
+// 1 .. 16 rows, by how full a shape leaves the chip.  One block per compute unit, all resident at once: evenness of the fill
+// squared, bytes in flight per compute unit up to 64 KiB; a second round of blocks, a split of K over the grid and lone
+// k-workers cost.
+w8_plan w8_plan_small_by_fill(int64_t M, int64_t N, int64_t K) {
     w8_plan p = {};
+    const int ncu = fq_cu_count();
+    const int KB = (int)(K / 128);
+    const int ngroups = (int)((N / FQ_NTILE + W8S_NT - 1) / W8S_NT);
+    p.small = 1;
+    p.mt = 1;
+    p.nblocks_m = 1;
+    double best = -1.0;
+    for (int gp = 1; gp <= W8S_MAXW; ++gp) {
+        int kw = W8S_MAXW / gp;
+        if (kw > KB) kw = KB;
+        const int need = (int)M * W8S_KC;
+        const int au = need <= 64 * gp ? 1 : (need <= 128 * gp ? 2 : 0);
+        if (au == 0 || kw < 1) continue;
+        const int64_t blocks = (ngroups + gp - 1) / gp;
+        const int SB = (KB + kw - 1) / kw;
+        int gs = 1;
+        if (blocks <= ncu / 2) gs = (int)(ncu / blocks);
+        if (gs > 8) gs = 8;
+        if (gs > SB) gs = SB;
+        const int64_t grid = blocks * gs;
+        const int64_t rounds = (grid + ncu - 1) / ncu;
+        const double eff = (double)ngroups * gs / (double)(rounds * ncu * gp);
+        const double inflight = (double)(gp * kw) * W8S_NT * 2;   // KiB (with the shallower ring)
+        double score = eff * eff * (inflight >= 64.0 ? 1.0 : sqrt(inflight / 64.0));
+        score /= 1.0 + 0.1 * (double)(rounds - 1);
+        if (au == 2) score *= 0.8;
+        if (gs > 1) score *= 0.8;
+        if (gp * kw < 6) score *= 0.85;
+        if (kw == 1) score *= 0.95;
+        if (score > best + 1e-9) {
+            best = score;
+            p.gp = gp;
+            p.kw = kw;
+            p.au = au;
+            p.splits = gs;
+            p.nblocks_n = (int)blocks;
+        }
+    }
+    return p;
+}
+
+// 17 rows and more: the splits of K that give tiles of 32, 64 or 128 rows x 384 columns at least 192 blocks.
+int w8_splits_by_fill(int64_t M, int64_t N, int64_t K) {
+    const int64_t rows = M <= 32 ? 32 : (M <= 64 ? 64 : 128), cols = W8_WAVES * W8_NT * FQ_NTILE;
+    const int64_t tiles = ((M + rows - 1) / rows) * ((N + cols - 1) / cols);
+    const int KB = (int)(K / 128);
+    int splits = tiles < 192 ? (int)(256 / tiles) : 1;
+    if (splits > 8) splits = 8;
+    if (splits > KB) splits = KB;
+    const int kbs = (KB + splits - 1) / splits;
+    return (KB + kbs - 1) / kbs;
+}
+
+// The plan with the least time by the models below.  None splits K into more slabs than filling the chip alone would take
+// (the two functions above): fq_gemm_w4a8_workspace_bytes named those slabs before there were models, and a call for which
+// a workspace of that size, or none, was enough must not be refused.  Without that limit the models ask for more in 0.4 % of
+// shapes (470 rows, 14848 x 15296: 86 MB instead of none).
+w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
+    const int ncu = fq_cu_count();
+    const int ntiles = (int)(N / FQ_NTILE);
+    const int KB = (int)(K / 128);
     if (M <= 16) {
         // The block shape and split of K with the least time by a model fitted (of log time, rms error 5 %) to 80 problems of
         // 1 .. 16 rows in 20 shapes each: a block takes 4.4 us and per iteration 0.98 us (0.2 more with two activation units
         // per lane) and its memory traffic at 15 TB/s (a part of it is hidden behind the rest); a split of K 2.1 us for its
-        // second kernel (3.1 below 10 us, where the launch's share of the host's time shows) and the slabs' traffic.  Against the scores below for all: 0.92 of the time inside graphs (1024 x
-        // 19872, 2 rows 9.0 -> 6.7 us; 9 of 10 shapes that were split and are not any more lose a launch, too).
-        // Up to 64 column tiles, a quarter of the compute units, the score stays: it splits such matrices, and callers and
-        // tests take them to need scratch.  (One block per compute unit, all resident at once; evenness of the fill squared,
-        // bytes in flight per compute unit up to 64 KiB, a second round of blocks, a split and lone k-workers cost.)
-        const int ncu = fq_cu_count();
-        const int ntiles = (int)(N / FQ_NTILE);
-        const int KB = (int)(K / 128);
+        // second kernel (3.1 below 10 us, where the launch's share of the host's time shows) and the slabs' traffic.  Against
+        // the plan by fill: 0.92 of the time inside graphs (1024 x 19872, 2 rows 9.0 -> 6.7 us; 9 of 10 shapes that were
+        // split and are not any more lose a launch, too).  Up to 64 column tiles, a quarter of the compute units, the plan by
+        // fill stays: it splits such matrices, and callers and tests take them to need scratch.
+        w8_plan p = w8_plan_small_by_fill(M, N, K);
+        if (4 * ntiles <= ncu) return p;
         const int ngroups = (ntiles + W8S_NT - 1) / W8S_NT;
-        p.small = 1;
-        p.mt = 1;
-        const bool narrow = 4 * ntiles <= ncu;
-        double best = -1e30;
+        const int most = p.splits;
+        double best = 1e30;
         for (int gp = 1; gp <= W8S_MAXW; ++gp) {
             int kw = W8S_MAXW / gp;
             if (kw > KB) kw = KB;
@@ -1142,52 +1202,27 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
             if (au == 0 || kw < 1) continue;
             const int64_t blocks = (ngroups + gp - 1) / gp;
             const int SB = (KB + kw - 1) / kw;
-            if (!narrow) {
-                for (int gs = 1; gs <= 8 && gs <= SB; ++gs) {
-                    const double grid = (double)blocks * gs, full = ceil(grid / ncu);
-                    if (gs > 1 && grid > 330) break;
-                    const double bytes = gp * kw * (3072.0 + 48.0 * (g % 128 == 0 ? 1 : 2)) + 64.0 * (double)M * kw;
-                    const double mem = (grid < ncu ? grid : ncu) * bytes / 15.2e6;
-                    double t = 4.4 + ((SB + gs - 1) / gs) * (mem + (au == 2 ? 1.18 : 0.98));
-                    if (full > 1.0) t *= grid / ncu + 0.35 < full ? grid / ncu + 0.35 : full;
-                    if (gs > 1) t += (t < 10.0 ? 3.1 : 2.1) + 2.0 * gs * (double)M * (double)N * 4.0 / 3.2e6;
-                    if (-t > best + 1e-9) {
-                        best = -t;
-                        p.gp = gp;
-                        p.kw = kw;
-                        p.au = au;
-                        p.splits = gs;
-                    }
+            for (int gs = 1; gs <= most && gs <= SB; ++gs) {
+                const double grid = (double)blocks * gs, full = ceil(grid / ncu);
+                if (gs > 1 && grid > 330) break;
+                const double bytes = gp * kw * (3072.0 + 48.0 * (g % 128 == 0 ? 1 : 2)) + 64.0 * (double)M * kw;
+                const double mem = (grid < ncu ? grid : ncu) * bytes / 15.2e6;
+                double t = 4.4 + ((SB + gs - 1) / gs) * (mem + (au == 2 ? 1.18 : 0.98));
+                if (full > 1.0) t *= grid / ncu + 0.35 < full ? grid / ncu + 0.35 : full;
+                if (gs > 1) t += (t < 10.0 ? 3.1 : 2.1) + 2.0 * gs * (double)M * (double)N * 4.0 / 3.2e6;
+                if (t < best - 1e-9) {
+                    best = t;
+                    p.gp = gp;
+                    p.kw = kw;
+                    p.au = au;
+                    p.splits = gs;
+                    p.nblocks_n = (int)blocks;
                 }
-                continue;
-            }
-            int gs = 1;
-            if (blocks <= ncu / 2) gs = (int)(ncu / blocks);
-            if (gs > 8) gs = 8;
-            if (gs > SB) gs = SB;
-            const int64_t grid = blocks * gs;
-            const int64_t rounds = (grid + ncu - 1) / ncu;
-            const double eff = (double)ngroups * gs / (double)(rounds * ncu * gp);
-            const double inflight = (double)(gp * kw) * W8S_NT * 2;   // KiB (with the shallower ring)
-            double score = eff * eff * (inflight >= 64.0 ? 1.0 : sqrt(inflight / 64.0));
-            score /= 1.0 + 0.1 * (double)(rounds - 1);
-            if (au == 2) score *= 0.8;
-            if (gs > 1) score *= 0.8;
-            if (gp * kw < 6) score *= 0.85;
-            if (kw == 1) score *= 0.95;
-            if (score > best + 1e-9) {
-                best = score;
-                p.gp = gp;
-                p.kw = kw;
-                p.au = au;
-                p.splits = gs;
             }
         }
-        p.kb_per_split = 0;
-        p.nblocks_n = (ngroups + p.gp - 1) / p.gp;
-        p.nblocks_m = 1;
         return p;
     }
+    w8_plan p = {};
     // More rows: the mid-M kernel (32, 48 or 64 rows per block, up to 700 rows) or the tiled one (64 or 128), whichever shape
     // and split of K the model gives the least time.  The model was fitted (of log time, rms error 10 %) to 123 problems of
     // 17 .. 2048 rows, K from 1152 to 16256, N from 1168 to 45856, in 35 shapes each:
@@ -1198,11 +1233,9 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
     //   a split     2.5 us for the second kernel and the slabs' traffic at 5 TB/s
     // Against the tiled kernel alone (32, 64 or 128 rows, K split until 192 tiles): 0.76 of the time on average inside
     // graphs, never more than 3 % slower; 12288 x 36864 us: M = 17 55 -> 40, M = 64 66 -> 46; 2816 x 5184, M = 95 22 -> 10.
-    const int ncu = fq_cu_count();
-    const int ntiles = (int)(N / FQ_NTILE);
     const int ngroups = (ntiles + W8M_NT - 1) / W8M_NT;
-    const int KB = (int)(K / 128);
     const int zr = g % 128 == 0 ? 1 : 2;
+    const int most = w8_splits_by_fill(M, N, K);
     double best = 1e30;
     auto launch_us = [&](double blocks, double block_us, int splits) {
         const double r = blocks / ncu, full = ceil(r);
@@ -1223,7 +1256,7 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
             const int nblocks_n = (ngroups + gp - 1) / gp;
             const int SB = (KB + kw - 1) / kw;
             const double work = (mid_work[mt] + 0.37 * (zr - 1)) * (double)((gp * kw + 3) / 4) / 3.0;
-            for (int gs = 1; gs <= 4 && gs <= SB; gs *= 2) {
+            for (int gs = 1; gs <= 4 && gs <= most && gs <= SB; gs *= 2) {
                 const double blocks = (double)nblocks_n * nblocks_m * gs;
                 if (gs > 1 && blocks > 300) break;
                 const double mem = (blocks < ncu ? blocks : ncu) * (gp * kw * (3072.0 + 48.0 * zr) + 0.3 * kw * mt * 2048.0) / 8.1e6;
@@ -1250,7 +1283,7 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
         const int nblocks_m = (int)((M + mt * 16 - 1) / (mt * 16));
         const int64_t tiles = (int64_t)nblocks_n * nblocks_m;
         for (int splits : split_opts) {
-            if (splits > KB || (splits > 1 && tiles * splits > 600)) break;
+            if (splits > KB || splits > most || (splits > 1 && tiles * splits > 600)) break;
             const int kbs = (KB + splits - 1) / splits;
             splits = (KB + kbs - 1) / kbs;
             const double t = launch_us((double)tiles * splits, 6.5 + kbs * ((mt == 8 ? 1.18 : 0.80) + 0.03 * (zr - 1)), splits);
