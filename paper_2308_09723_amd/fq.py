@@ -236,11 +236,13 @@ def gemm_sf_raw(A_ptr, act_dtype, M, N, K, codes_ptr, scales_ptr, scale_format, 
 
 def _int32_array(values):
     """The values as a ctypes array."""
-    try:
-        packed = array.array("i", values)       # (a list of ints: a tenth of the time that converting each one takes)
-    except (TypeError, OverflowError):
-        return (ctypes.c_int32 * len(values))(*[int(v) for v in values])
-    return (ctypes.c_int32 * len(packed)).from_buffer(packed)
+    if isinstance(values, (list, tuple)) and values:     # (ints packed at once: a tenth of the time that converting each one takes)
+        try:
+            packed = array.array("i", values)
+            return (ctypes.c_int32 * len(packed)).from_buffer(packed)
+        except (TypeError, OverflowError):
+            pass
+    return (ctypes.c_int32 * len(values))(*[int(v) for v in values])
 
 
 def gemm_grouped_raw(A_ptr, act_dtype, offsets, N, K, codes_ptr, scales_ptr, bits, group_size, C_ptr,

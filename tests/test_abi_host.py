@@ -274,3 +274,16 @@ def test_streaming_plans_fit_the_block_and_the_scratch():
         assert kw <= KB and 1 <= splits <= -(-KB // kw)
         assert ws == {splits * M * N * 4 if splits > 1 else 0} and max(ws) <= fq.gemm_noalloc_scratch_bytes()
     assert seen > 500
+
+
+@pytest.mark.parametrize("form", ["list", "tuple", "range", "bytes", "bytearray", "int64 array", "float array", "floats", "beyond 32 bits",
+                                  "empty"])
+def test_offsets_in_any_form_of_sequence(form):
+    """The expert offsets of the binding: whatever sequence holds them, one 32-bit integer per element."""
+    import numpy as np
+    v = [0, 4, 8, 9, 9]
+    values = {"list": v, "tuple": tuple(v), "range": range(5), "bytes": bytes(v[:4]), "bytearray": bytearray(v), "int64 array": np.array(v),
+              "float array": np.array(v, dtype=np.float64), "floats": [0.0, 4.9, 8.0], "beyond 32 bits": [0, 2 ** 32 + 5],
+              "empty": []}[form]
+    want = [5 if int(x) > 2 ** 32 else int(x) for x in values]
+    assert list(fq._int32_array(values)) == want
