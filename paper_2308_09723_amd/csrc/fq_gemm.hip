@@ -245,8 +245,11 @@ static const double* fq_tiled_costs(int bits, int g) {
 // Side by side on streams of their own the launches share one ragged end, but forking and joining the streams costs 21 us.
 
 // Block shape of the mid-M kernel for the tiles of a grouped product (count[i]: those of i + 1 row tiles); the launch's
-// time, the time its blocks hold the compute units in all, and the longest of them.
-static double fq_plan_grouped_mid(const int (&count)[3], int64_t N, int64_t K, int bits, int g, fq_small_shape* sh,
+// time, the time its blocks hold the compute units in all, and the longest of them.  even: row blocks of one product, all as
+// long as each other, so that a launch of 280 blocks takes two whole rounds.  The shape is the best by that (140 such products
+// that it changes: 1.33x, 2332 x 288, K = 2176, 8-bit 25 -> 17 us); the time returned stays the one above, by which these products
+// take this kernel and no scratch, unless the tiled plan needs none either.
+static double fq_plan_grouped_mid(const int (&count)[3], int64_t N, int64_t K, int bits, int g, bool even, fq_small_shape* sh,
                                   double* busy_us, double* block_us) {
     static const double mid_f[2][3] = {{0.67, 1.13, 0.88}, {0.8, 0.96, 1.19}};      // (3- and 4-bit codes, 8-bit codes)
     const int ngroups = (int)((N / FQ_NTILE + MMA_NT - 1) / MMA_NT);
@@ -254,7 +257,7 @@ static double fq_plan_grouped_mid(const int (&count)[3], int64_t N, int64_t K, i
     const int items = count[0] + count[1] + count[2];
     const fq_mid_model model[3] = {fq_mid_model(1, K, bits, g), fq_mid_model(2, K, bits, g), fq_mid_model(3, K, bits, g)};
     const fq_mid_model& tallest = model[count[2] ? 2 : (count[1] ? 1 : 0)];
-    double best = 1e30;
+    double best = 1e30, best_rank = 1e30;
     for (int gp = 1; gp <= 12; ++gp) {
         const int kw = tallest.workers(gp);
         const double per_item = (double)((ngroups + gp - 1) / gp);
@@ -272,8 +275,10 @@ static double fq_plan_grouped_mid(const int (&count)[3], int64_t N, int64_t K, i
         double total = sum / ncu + 0.35 * longest;
         total = total < rounds ? total : rounds;
         if (total < longest) total = longest;
-        if (total < best - 1e-9) {
-            best = total;
+        if (total < best) best = total;
+        const double rank = even ? rounds : total;
+        if (rank < best_rank - 1e-9) {
+            best_rank = rank;
             *busy_us = sum;
             *block_us = longest;
             sh->gp = gp;
@@ -532,10 +537,14 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
         best = fq_plan_flexible(M, N, K, bits, g, act_dtype, ncu, best, &p);
         if (M > 48 && K <= FQ_ROW_BLOCKS_MOST_K && (M <= 256 || (N < 8192 && M <= 48 * 256))) {
             // Row blocks of the mid-M kernel (kind 3): as k-workers inside a block they split K without partial sums or a
-            // second kernel, and 48 rows x 48 columns cut a small output finer than the tiled kernel's blocks.  180 problems
-            // of 49 .. 600 rows, K from 1024 to 14720: chosen in 42, 1.23x faster on average there (up to 1.75x: 1408 x 1056,
-            // 324 rows, 8-bit 16.5 -> 9.4 us), 3 of them more than 3 % slower (6 % at worst); longer K lost up to 15 %.  Above 256 rows
-            // bfloat16 products of wide matrices stay on the fp16 matrix path.
+            // second kernel, and 48 rows x 48 columns cut a small output finer than the tiled kernel's blocks.  Longer K lost up
+            // to 15 %.  Above 256 rows bfloat16 products of wide matrices stay on the fp16 matrix path.  650 products that take
+            // them, K from 256 to 6272 and N from 128 on, against the tiled plan:
+            //   49 .. 256 rows       220   1.19x on average, 16 more than 3 % slower (15 % at worst: 50 - 64 rows, K of 3000 and more)
+            //   257 .. 600 rows      150   1.19x, 23 slower (3 of them than the 128-row blocks, 4 % at worst)
+            //   601 .. 12288 rows    280   1.24x, 29 slower (7 of them than the 128-row blocks, 8 %)
+            // (1408 x 1056, 324 rows, 8-bit 16.5 -> 9.4 us.)  The slower ones have K of 3000 and more beside few columns: the
+            // tiled kernel's split of K wins there, but needs scratch that these products do not ask for.
             int count[3] = {};
             for (int32_t left = (int32_t)M, take = 0; left > 0; left -= take) {
                 take = fq_mid_rows(left);
@@ -546,7 +555,13 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
             // (above 256 rows weighed against the 128-row blocks as it was measured: the model does not rank it among the smaller
             // ones, which lost by up to 1.4x where they took its place)
             const double rival = M > 256 && p.mt < 8 ? best128 : best;
-            if (fq_plan_grouped_mid(count, N, K, bits, g, &sh, &busy, &longest) < 0.95 * (rival + 2.0)) {
+            const double limit = 0.95 * (rival + 2.0);
+            bool pays = fq_plan_grouped_mid(count, N, K, bits, g, true, &sh, &busy, &longest) < limit;
+            if (pays && fq_partial_bytes(p, M, N) == 0 && !fq_via_f16(act_dtype, FQ_SCALE_F16, p, N)) {
+                const int blocks = ((ntiles + MMA_NT - 1) / MMA_NT + sh.gp - 1) / sh.gp * (count[0] + count[1] + count[2]);
+                pays = longest * ((blocks + ncu - 1) / ncu) < limit;
+            }
+            if (pays) {
                 p = fq_gemm_plan{};
                 p.kind = 3;
                 p.mt = 3;
@@ -636,7 +651,7 @@ static double fq_grouped_us(const int32_t* offsets, int E, int64_t N, int64_t K,
     }
     if (count[FQ_TILE_MID] > 0) {
         double busy = 0.0, block = 0.0;
-        const double t = fq_plan_grouped_mid(mid_count, N, K, bits, g, &p->mid, &busy, &block);
+        const double t = fq_plan_grouped_mid(mid_count, N, K, bits, g, false, &p->mid, &busy, &block);
         add(busy, block, t);
     }
     if (count[FQ_TILE_SMALL] > 0) {

@@ -287,3 +287,13 @@ def test_offsets_in_any_form_of_sequence(form):
               "empty": []}[form]
     want = [5 if int(x) > 2 ** 32 else int(x) for x in values]
     assert list(fq._int32_array(values)) == want
+
+
+@pytest.mark.parametrize("M,K,N,bits,g", [(2332, 2176, 288, 8, 32), (1786, 2816, 336, 8, 64), (6949, 1536, 224, 4, 64), (77, 2048, 6208, 8, 128),
+                                          (6686, 4736, 176, 4, 128)])
+def test_row_blocks_of_the_streaming_kernel_fill_whole_rounds(M, K, N, bits, g):
+    """Row blocks of one product take equally long: 260 - 300 of them last two rounds on 256 compute units, so a shape with fewer,
+    wider blocks is chosen, all resident at once."""
+    m = re.search(r" mid-m rows=48 gp=(\d+) kw=(\d+) waves=(\d+)$", fq.gemm_describe(M, N, K, bits, g))
+    assert m and -(-(-(-N // 48)) // int(m.group(1))) * -(-M // 48) <= 256
+    assert fq.gemm_workspace_bytes(M, N, K, bits, g) == 0

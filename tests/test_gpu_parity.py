@@ -778,3 +778,17 @@ def test_gemm_small_row_blocks_above_256_rows(M, K, N, dtype, bits, g, shape):
     _say(f"M={M} K={K} N={N} {dtype} int{bits} g={g}: {desc}")
     assert shape in desc, desc
     _gemm_case(M, K, N, dtype, bits, g, seed=9700 + M)
+
+
+@pytest.mark.parametrize("M,K,N,dtype,bits,g,shape", [(257, 640, 144, "f16", 4, 32, "gp=1 kw=5"), (625, 1536, 208, "bf16", 3, 64, "gp=1 kw=6"),
+                                                      (2332, 2176, 288, "bf16", 8, 64, "gp=2 kw=6"), (2332, 2176, 288, "f16", 4, 128, "gp=2 kw=6"),
+                                                      (12241, 640, 144, "f16", 4, 128, "gp=3 kw=4"), (12288, 768, 80, "bf16", 4, 32, "gp=2 kw=6"),
+                                                      (12288, 1536, 208, "f16", 8, 64, "gp=5 kw=2")])
+def test_gemm_row_blocks_of_the_streaming_kernel_above_256_rows(M, K, N, dtype, bits, g, shape):
+    """Row blocks of 48 rows from 257 rows to the most that one launch takes (256 of them, the last of 1 row, lower or full);
+    block shapes chosen so that all blocks are resident at once."""
+    desc = _fq().gemm_describe(M, N, K, bits, g)
+    _say(f"gemm row blocks {dtype} int{bits} g={g} K={K} N={N} M={M}: {desc}")
+    assert f"mid-m rows=48 {shape}" in desc and _fq().gemm_workspace_bytes(M, N, K, bits, g) == 0
+    assert "mid-m" not in _fq().gemm_describe(12289, N, K, bits, g)
+    _gemm_case(M, K, N, dtype, bits, g, seed=8900 + M + K)
