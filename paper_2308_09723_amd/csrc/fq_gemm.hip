@@ -66,9 +66,8 @@ struct fq_mid_model {
     double work;         // microseconds of vector / matrix work per iteration of a full block (12 waves, a k-block of 48 columns each)
     double rec_bytes;    // codes and scales a wave loads per iteration
     int tile_bytes;      // activation tile of a k-worker
-    fq_mid_model(int mt, int64_t K, int bits, int g) {
-        const int kblk = fq_kblk(bits), sr = fq_scale_rows(bits, g);
-        KB = (int)(K / kblk);
+    fq_mid_model(int mt, int kblocks, int bits, int sr) : KB(kblocks) {
+        const int kblk = fq_kblk(bits);
         work = mt <= 2 ? (bits == 8 ? 0.85 : (bits == 3 ? 1.75 : 1.5)) : (bits == 8 ? 1.3 : (bits == 3 ? 2.6 : 2.4));
         work += (sr - 1) * (mt <= 2 ? 0.27 : 0.4);
         rec_bytes = MMA_NT * 64.0 * fq_rec_bytes(bits) + MMA_NT * 32.0 * sr;
@@ -81,13 +80,13 @@ struct fq_mid_model {
         if (kw > fit) kw = fit;
         return kw > KB ? KB : kw;
     }
-    // one iteration of a block: vector / matrix work, and memory at `rate` bytes per microsecond when `active` blocks are resident
-    double compute(int waves) const { return work * (double)((waves + 3) / 4) / 3.0; }
-    double memory(int gp, int kw, double active, double rate) const {
-        return active * (gp * kw * rec_bytes + 0.3 * kw * tile_bytes) / rate;
+    // one iteration of a block: vector / matrix work, and memory when `active` blocks are resident
+    double compute(int waves) const { return work * (1.0 / 3.0) * (double)((waves + 3) / 4); }
+    double memory(int gp, int kw, double active, double us_per_byte) const {
+        return active * (gp * kw * rec_bytes + 0.3 * kw * tile_bytes) * us_per_byte;
     }
     double iteration(int gp, int kw, double active) const {
-        const double t_work = compute(gp * kw), t_mem = memory(gp, kw, active, 7e6);
+        const double t_work = compute(gp * kw), t_mem = memory(gp, kw, active, 1.0 / 7e6);
         const double t_it = t_mem > t_work ? t_mem : t_work;
         return t_it > 1.4 ? t_it : 1.4;
     }
@@ -95,7 +94,7 @@ struct fq_mid_model {
 
 static double fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int ncu, fq_gemm_plan* p) {
     const int mt = M <= 32 ? 2 : 3;
-    const fq_mid_model model(mt, K, bits, g);
+    const fq_mid_model model(mt, (int)(K / fq_kblk(bits)), bits, fq_scale_rows(bits, g));
     const int ngroups = (int)((N / FQ_NTILE + MMA_NT - 1) / MMA_NT);
     double best = 1e30;
     for (int gp = 1; gp <= 12; ++gp) {
@@ -248,31 +247,39 @@ static const double* fq_tiled_costs(int bits, int g) {
 // time, the time its blocks hold the compute units in all, and the longest of them.  even: row blocks of one product, all as
 // long as each other, so that a launch of 280 blocks takes two whole rounds.  The shape is the best by that (140 such products
 // that it changes: 1.33x, 2332 x 288, K = 2176, 8-bit 25 -> 17 us); the time returned stays the one above, by which these products
-// take this kernel and no scratch, unless the tiled plan needs none either.
-static double fq_plan_grouped_mid(const int (&count)[3], int64_t N, int64_t K, int bits, int g, bool even, fq_small_shape* sh,
-                                  double* busy_us, double* block_us) {
+// take this kernel and no scratch, unless the tiled plan needs none either.  Where the blocks' work alone takes `limit` or
+// more, that time is returned and nothing is looked at.
+static double fq_plan_grouped_mid(const int (&count)[3], int64_t N, int64_t K, int bits, int g, bool even, double limit,
+                                  fq_small_shape* sh, double* busy_us, double* block_us) {
     static const double mid_f[2][3] = {{0.67, 1.13, 0.88}, {0.8, 0.96, 1.19}};      // (3- and 4-bit codes, 8-bit codes)
     const int ngroups = (int)((N / FQ_NTILE + MMA_NT - 1) / MMA_NT);
-    const double ncu = (double)fq_cu_count();
+    const int ncu_n = fq_cu_count();
+    const double ncu = (double)ncu_n, share = 1.0 / ncu;
     const int items = count[0] + count[1] + count[2];
-    const fq_mid_model model[3] = {fq_mid_model(1, K, bits, g), fq_mid_model(2, K, bits, g), fq_mid_model(3, K, bits, g)};
+    const int kblocks = (int)(K / fq_kblk(bits)), sr = fq_scale_rows(bits, g);
+    const fq_mid_model model[3] = {{1, kblocks, bits, sr}, {2, kblocks, bits, sr}, {3, kblocks, bits, sr}};
     const fq_mid_model& tallest = model[count[2] ? 2 : (count[1] ? 1 : 0)];
-    double best = 1e30, best_rank = 1e30;
+    double best = 1e30, best_rank = 1e30, least = 0.0;
+    for (int i = 0; i < 3; ++i) least += count[i] * mid_f[bits == 8][i] * model[i].work;
+    least *= share * (1.0 / 12.0) * ngroups * model[0].KB;
+    if (least >= limit) return least;
     for (int gp = 1; gp <= 12; ++gp) {
         const int kw = tallest.workers(gp);
-        const double per_item = (double)((ngroups + gp - 1) / gp);
-        const double active = per_item * items < ncu ? per_item * items : ncu;
+        if ((double)((tallest.KB + kw - 1) / kw) + 5.8 > best_rank) continue;      // (at least 1 us per iteration)
+        const int per_item = (ngroups + gp - 1) / gp;
+        const int64_t blocks = (int64_t)per_item * items;
+        const double active = blocks < ncu_n ? (double)blocks : ncu;
         double sum = 0.0, longest = 0.0;
         for (int i = 0; i < 3; ++i) {
             if (count[i] == 0) continue;
-            const double t_work = mid_f[bits == 8][i] * model[i].compute(gp * kw), t_mem = model[i].memory(gp, kw, active, 8.5e6);
+            const double t_work = mid_f[bits == 8][i] * model[i].compute(gp * kw), t_mem = model[i].memory(gp, kw, active, 1.0 / 8.5e6);
             const double t_it = t_work > t_mem ? t_work : t_mem;
             const double t = ((model[i].KB + kw - 1) / kw) * (t_it > 1.0 ? t_it : 1.0) + 5.8;
-            sum += t * per_item * count[i];
+            sum += t * ((double)per_item * count[i]);
             longest = t > longest ? t : longest;
         }
-        const double rounds = ceil(per_item * items / ncu) * longest;
-        double total = sum / ncu + 0.35 * longest;
+        const double rounds = (double)((blocks + ncu_n - 1) / ncu_n) * longest;
+        double total = sum * share + 0.35 * longest;
         total = total < rounds ? total : rounds;
         if (total < longest) total = longest;
         if (total < best) best = total;
@@ -297,16 +304,18 @@ constexpr int64_t FQ_ROW_BLOCKS_MOST_K = 6400;
 static double fq_small_us(int64_t M, int64_t N, int64_t K, int bits, int g, int ncu, int nt, int gp, int kw, int au, int gs) {
     const int kblk = fq_kblk(bits), sr = fq_scale_rows(bits, g), waves = gp * kw;
     const int ntiles = (int)(N / FQ_NTILE), KB = (int)(K / kblk);
-    const double blocks = (double)((ntiles + nt * gp - 1) / (nt * gp)) * gs;
-    const double slots = (double)ncu * (waves <= 6 ? 12 / waves : 1);
+    static const int resident[13] = {1, 12, 6, 4, 3, 2, 2, 1, 1, 1, 1, 1, 1};       // blocks of so many waves per compute unit
+    const int blocks_n = (ntiles + nt * gp - 1) / (nt * gp) * gs, slots_n = ncu * resident[waves];
+    const double blocks = (double)blocks_n;
+    const double slots = (double)slots_n;
     const double n_it = (double)((((KB + kw - 1) / kw) + gs - 1) / gs);
     const double bytes = waves * (nt * 64.0 * fq_rec_bytes(bits) + nt * 32.0 * sr) + (double)M * kw * kblk;
-    const double together = blocks <= ncu ? 1.0 : (blocks < slots ? blocks : slots) / ncu;
+    const double together = blocks <= ncu ? 1.0 : (blocks < slots ? blocks : slots) * (1.0 / ncu);
     const double work = 0.022 * waves * nt * ((bits == 8 ? 0.33 : 1.0) + 0.12 * sr) * together;
-    const double mem = bytes * (blocks < slots ? blocks : slots) / 9e6;
+    const double mem = bytes * (blocks < slots ? blocks : slots) * (1.0 / 9e6);
     const double t_it = (work > mem ? work : mem) + 0.3 + (au == 2 ? 0.3 : (au == 4 ? 2.7 : 0.0));
-    const double rounds = blocks / slots, full = ceil(rounds);
-    const double t = (3.9 + n_it * t_it) * (full > 1.0 ? 0.45 * full + 0.55 * rounds : 1.0);
+    double t = 3.9 + n_it * t_it;
+    if (blocks_n > slots_n) t *= 0.45 * (double)((blocks_n + slots_n - 1) / slots_n) + 0.55 * blocks / slots;
     return gs > 1 ? t + 3.6 + 2.0 * gs * (double)M * (double)N * 4.0 / 1.65e6 : t;
 }
 
@@ -390,7 +399,7 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
                 const int au = need <= 64 * gp ? 1 : (need <= 128 * gp ? 2 : 0);
                 int kw = SKINNY_VARIANTS[v].maxw / gp;
                 if (kw > KB) kw = KB;
-                if (au == 0 || kw < 1) continue;
+                if (au == 0 || kw < 1 || 3.9 + 0.3 * ((KB + kw - 1) / kw) > best_us) continue;
                 const double t = fq_small_us(M, N, K, bits, g, ncu, SKINNY_VARIANTS[v].nt, gp, kw, au, 1);
                 if (t < best_us - 1e-9) {
                     best_us = t;
@@ -545,8 +554,8 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
             //   601 .. 12288 rows    280   1.24x, 29 slower (7 of them than the 128-row blocks, 8 %)
             // (1408 x 1056, 324 rows, 8-bit 16.5 -> 9.4 us.)  The slower ones have K of 3000 and more beside few columns: the
             // tiled kernel's split of K wins there, but needs scratch that these products do not ask for.
-            int count[3] = {};
-            for (int32_t left = (int32_t)M, take = 0; left > 0; left -= take) {
+            int count[3] = {0, 0, M > 96 ? (int)(M - 49) / 48 : 0};       // (fq_mid_rows gives 48 while more than 96 are left)
+            for (int32_t left = (int32_t)M - 48 * count[2], take = 0; left > 0; left -= take) {
                 take = fq_mid_rows(left);
                 ++count[(take - 1) / 16];
             }
@@ -556,7 +565,7 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
             // ones, which lost by up to 1.4x where they took its place)
             const double rival = M > 256 && p.mt < 8 ? best128 : best;
             const double limit = 0.95 * (rival + 2.0);
-            bool pays = fq_plan_grouped_mid(count, N, K, bits, g, true, &sh, &busy, &longest) < limit;
+            bool pays = fq_plan_grouped_mid(count, N, K, bits, g, true, limit, &sh, &busy, &longest) < limit;
             if (pays && fq_partial_bytes(p, M, N) == 0 && !fq_via_f16(act_dtype, FQ_SCALE_F16, p, N)) {
                 const int blocks = ((ntiles + MMA_NT - 1) / MMA_NT + sh.gp - 1) / sh.gp * (count[0] + count[1] + count[2]);
                 pays = longest * ((blocks + ncu - 1) / ncu) < limit;
@@ -651,7 +660,7 @@ static double fq_grouped_us(const int32_t* offsets, int E, int64_t N, int64_t K,
     }
     if (count[FQ_TILE_MID] > 0) {
         double busy = 0.0, block = 0.0;
-        const double t = fq_plan_grouped_mid(mid_count, N, K, bits, g, false, &p->mid, &busy, &block);
+        const double t = fq_plan_grouped_mid(mid_count, N, K, bits, g, false, 1e30, &p->mid, &busy, &block);
         add(busy, block, t);
     }
     if (count[FQ_TILE_SMALL] > 0) {

@@ -47,6 +47,7 @@ inline bool fq_flexible(const fq_gemm_plan& p) { return p.kind == 1 && p.mt >= 5
 fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int act_dtype);
 // Rows of the next tile of the mid-M kernel when `left` are left: as few tiles as 48 rows allow, of nearly equal height.
 inline int32_t fq_mid_rows(int32_t left) {
+    if (left > 96) return 48;        // (three tiles and more of nearly equal height are 48 rows high)
     const int32_t n = (left + 47) / 48;
     const int32_t even = ((left + n - 1) / n + 15) / 16 * 16;
     return left < even ? left : even;

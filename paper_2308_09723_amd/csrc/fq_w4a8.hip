@@ -1179,8 +1179,10 @@ int w8_splits_by_fill(int64_t M, int64_t N, int64_t K) {
 // shapes (470 rows, 14848 x 15296: 86 MB instead of none).
 w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
     const int ncu = fq_cu_count();
+    const double share = 1.0 / ncu;
     const int ntiles = (int)(N / FQ_NTILE);
     const int KB = (int)(K / 128);
+    const int zr = g % 128 == 0 ? 1 : 2;
     if (M <= 16) {
         // The block shape and split of K with the least time by a model fitted (of log time, rms error 5 %) to 80 problems of
         // 1 .. 16 rows in 20 shapes each: a block takes 4.4 us and per iteration 0.98 us (0.2 more with two activation units
@@ -1200,16 +1202,19 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
             const int need = (int)M * W8S_KC;
             const int au = need <= 64 * gp ? 1 : (need <= 128 * gp ? 2 : 0);
             if (au == 0 || kw < 1) continue;
-            const int64_t blocks = (ngroups + gp - 1) / gp;
-            const int SB = (KB + kw - 1) / kw;
+            const int blocks = (ngroups + gp - 1) / gp, SB = (KB + kw - 1) / kw;
+            const double bytes = gp * kw * (3072.0 + 48.0 * zr) + 64.0 * (double)M * kw, per_it = au == 2 ? 1.18 : 0.98;
             for (int gs = 1; gs <= most && gs <= SB; ++gs) {
-                const double grid = (double)blocks * gs, full = ceil(grid / ncu);
+                const int grid = blocks * gs;
                 if (gs > 1 && grid > 330) break;
-                const double bytes = gp * kw * (3072.0 + 48.0 * (g % 128 == 0 ? 1 : 2)) + 64.0 * (double)M * kw;
-                const double mem = (grid < ncu ? grid : ncu) * bytes / 15.2e6;
-                double t = 4.4 + ((SB + gs - 1) / gs) * (mem + (au == 2 ? 1.18 : 0.98));
-                if (full > 1.0) t *= grid / ncu + 0.35 < full ? grid / ncu + 0.35 : full;
-                if (gs > 1) t += (t < 10.0 ? 3.1 : 2.1) + 2.0 * gs * (double)M * (double)N * 4.0 / 3.2e6;
+                const int n_it = (SB + gs - 1) / gs;
+                if (4.4 + n_it * per_it > best) continue;
+                double t = 4.4 + n_it * ((grid < ncu ? grid : ncu) * bytes * (1.0 / 15.2e6) + per_it);
+                if (grid > ncu) {
+                    const double full = (double)((grid + ncu - 1) / ncu), part = grid * share + 0.35;
+                    t *= part < full ? part : full;
+                }
+                if (gs > 1) t += (t < 10.0 ? 3.1 : 2.1) + 2.0 * gs * (double)M * (double)N * (4.0 / 3.2e6);
                 if (t < best - 1e-9) {
                     best = t;
                     p.gp = gp;
@@ -1234,13 +1239,15 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
     // Against the tiled kernel alone (32, 64 or 128 rows, K split until 192 tiles): 0.76 of the time on average inside
     // graphs, never more than 3 % slower; 12288 x 36864 us: M = 17 55 -> 40, M = 64 66 -> 46; 2816 x 5184, M = 95 22 -> 10.
     const int ngroups = (ntiles + W8M_NT - 1) / W8M_NT;
-    const int zr = g % 128 == 0 ? 1 : 2;
     const int most = w8_splits_by_fill(M, N, K);
     double best = 1e30;
-    auto launch_us = [&](double blocks, double block_us, int splits) {
-        const double r = blocks / ncu, full = ceil(r);
-        double t = (r <= 1.0 ? 1.0 : (r + 0.47 < full ? r + 0.47 : full)) * block_us;
-        if (splits > 1) t += 2.5 + 2.0 * splits * (double)M * (double)N * 4.0 / 5e6;
+    auto launch_us = [&](int64_t blocks, double block_us, int splits) {
+        double t = block_us;
+        if (blocks > ncu) {
+            const double full = (double)((blocks + ncu - 1) / ncu), part = blocks * share + 0.47;
+            t *= part < full ? part : full;
+        }
+        if (splits > 1) t += 2.5 + 2.0 * splits * (double)M * (double)N * (4.0 / 5e6);
         return t;
     };
     static const double mid_work[5] = {0.0, 0.0, 0.92, 1.09, 1.27};
@@ -1255,14 +1262,16 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
             kw = kw < KB ? kw : KB;
             const int nblocks_n = (ngroups + gp - 1) / gp;
             const int SB = (KB + kw - 1) / kw;
-            const double work = (mid_work[mt] + 0.37 * (zr - 1)) * (double)((gp * kw + 3) / 4) / 3.0;
+            const double work = (mid_work[mt] + 0.37 * (zr - 1)) * (1.0 / 3.0) * (double)((gp * kw + 3) / 4);
             for (int gs = 1; gs <= 4 && gs <= most && gs <= SB; gs *= 2) {
-                const double blocks = (double)nblocks_n * nblocks_m * gs;
+                const int64_t blocks = (int64_t)nblocks_n * nblocks_m * gs;
                 if (gs > 1 && blocks > 300) break;
-                const double mem = (blocks < ncu ? blocks : ncu) * (gp * kw * (3072.0 + 48.0 * zr) + 0.3 * kw * mt * 2048.0) / 8.1e6;
+                const int n_it = (SB + gs - 1) / gs;
+                if (6.7 + n_it * 0.94 > best) continue;
+                const double mem = (double)(blocks < ncu ? blocks : ncu) * (gp * kw * (3072.0 + 48.0 * zr) + 0.3 * kw * mt * 2048.0) * (1.0 / 8.1e6);
                 double t_it = work > mem ? work : mem;
                 if (t_it < 0.94) t_it = 0.94;
-                const double t = launch_us(blocks, 6.7 + ((SB + gs - 1) / gs) * t_it, gs);
+                const double t = launch_us(blocks, 6.7 + n_it * t_it, gs);
                 if (t < best - 1e-9) {
                     best = t;
                     p.mid = 1;
@@ -1286,7 +1295,7 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
             if (splits > KB || splits > most || (splits > 1 && tiles * splits > 600)) break;
             const int kbs = (KB + splits - 1) / splits;
             splits = (KB + kbs - 1) / kbs;
-            const double t = launch_us((double)tiles * splits, 6.5 + kbs * ((mt == 8 ? 1.18 : 0.80) + 0.03 * (zr - 1)), splits);
+            const double t = launch_us(tiles * splits, 6.5 + kbs * ((mt == 8 ? 1.18 : 0.80) + 0.03 * (zr - 1)), splits);
             if (t < best - 1e-9) {
                 best = t;
                 p.mid = 0;
