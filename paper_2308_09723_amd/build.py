@@ -53,18 +53,13 @@ NO_SPILL = [
     "fq_gemm_skinny_kernel<0, 4, 3, 2, 1, 12, 1, fq_no_items>",     # decode, fp16 int4 g >= 128: QKV / FC1 / FC2 / out-proj at M = 1
     "fq_gemm_skinny_kernel<0, 4, 1, 4, 1, 12, 1, fq_no_items>",     # out-proj at M = 8
     "fq_gemm_skinny_kernel<1, 4, 3, 2, 2, 12, 1, fq_small_items>",  # experts of at most 16 rows, bf16 int4 g = 64
-    "fq_gemm_mid_kernel<0, 4, 3, 2, 1, 12>",                # QKV / FC1 at M = 32, fp16
-    "fq_gemm_mid_kernel<1, 4, 3, 2, 1, 12>",                # the same, bf16
-    "fq_gemm_mid_kernel<0, 4, 3, 3, 1, 12>",                # M = 48, fp16
-    "fq_gemm_mid_items_kernel<0, 4, 3, 2, 12>",             # experts of 17 - 48 rows, fp16 int4 g = 64
-    "fq_gemm_mid_items_kernel<1, 4, 3, 2, 12>",             # the same, bf16
-    "fq_w4a8_mid_kernel<2, 1, 0>",                          # integer path, 17 - 32 rows
-    "fq_w4a8_mid_kernel<4, 1, 0>",                          # integer path, 49 - 64 rows
     "fq_gemm_mma_kernel<0, 4, 2, 3, 8, 1, false, 2, true, 1>",    # out-proj / FC2 at M = 32, fp16, post-scaled
     "fq_gemm_mma_kernel<0, 4, 7, 2, 8, 2, false, 2, false, 1>",   # 200 rows, fp16 int4 g = 64: 112 x 256
     "fq_gemm_mma_kernel<0, 4, 8, 3, 8, 1, false, 2, false, 1>",   # prefill, fp16
     "fq_gemm_mma_kernel<3, 4, 8, 3, 8, 1, false, 2, false, 1>",   # prefill, bf16 on the fp16 matrix path
 ]
+# Kernels of which no instantiation may: the streaming kernels of 17 rows and more, of row blocks and of grouped tiles.
+NO_SPILL_FAMILIES = ["fq_gemm_mid_kernel", "fq_gemm_mid_items_kernel", "fq_w4a8_mid_kernel"]
 
 
 def _run(cmd):
@@ -127,8 +122,9 @@ def _resource_report(rows, verbose):
         print(f"{len(table)} kernels compiled, {len(spilling)} use scratch memory (see _build/resources.txt):")
         for t in spilling:
             print(f"  {t[0]}: {t[4]} spilled VGPRs, {t[3]} B/lane of scratch, {t[1]} VGPRs, {t[5]} waves/SIMD")
-    bad = [t for t in spilling if t[0] in NO_SPILL]
-    missing = [k for k in NO_SPILL if filt and k not in {t[0] for t in table}]
+    bad = [t for t in spilling if t[0] in NO_SPILL or t[0].split("<")[0] in NO_SPILL_FAMILIES]
+    compiled = {t[0] for t in table} | {t[0].split("<")[0] for t in table}
+    missing = [k for k in NO_SPILL + NO_SPILL_FAMILIES if filt and k not in compiled]
     if bad:
         raise RuntimeError("register spills in kernels that must not spill: " + ", ".join(t[0] for t in bad))
     if missing:

@@ -900,7 +900,7 @@ __device__ __forceinline__ void mid_block(
 
     // unit of this lane's fragment row for k-step t (row tile 0): this one with 4 t folded in by an exclusive or (the
     // position inside the row is (4 t + j) ^ swz, and a row starts at a multiple of KC units)
-    const int a_rd0 = kw * TILE + ml * KC + (j ^ swz(ml));
+    int a_rd0 = kw * TILE + ml * KC + (j ^ swz(ml));
 
     f32x4 acc[MT][NT];
 #pragma unroll
@@ -1004,6 +1004,12 @@ __device__ __forceinline__ void mid_block(
             for (int d = 0; d < DEPTH; ++d) iterate(ring[d], it + d, true);
         }
         // drain: at most 2 * DEPTH - 1 iterations are left, the first min(DEPTH, left) already loaded
+        if constexpr (ACT != FQ_F16 && BITS == 4 && MT == 3 && SR == 1) {
+            // (the fragments' place is worked out once more: kept, it is the register that does not fit beside the loop's)
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
+            a_rd0 = kw * TILE + (ln & 15) * KC + ((ln >> 4) ^ swz(ln & 15));
+        }
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d)
             if (it + d < n_it) iterate(ring[d], it + d, it + d + DEPTH < n_it);
