@@ -678,7 +678,9 @@ static double fq_grouped_us(const int32_t* offsets, int E, int64_t N, int64_t K,
 
 // The cut with the least time by the model.  Against tiles of 128, 64 and 32 rows and the small-M kernel, each class on a
 // stream of its own, the 200 calls are 1.24x faster on average, and up to 3.3x on small matrices, where one launch takes the
-// place of four; 5 of them are more than 5 % slower (calls of 60 us and more: 9 % at worst).  A launch of 32-row tiles
+// place of four; 5 of them are more than 5 % slower (calls of 60 us and more: 9 % at worst).  Two sets of 200 others: experts
+// that all fit the small-M kernel 1.03x, 13 more than 3 % slower (12 % at worst), with taller ones 1.41x, 11 slower (8 %); a
+// different margin between the cuts makes as many calls slower as faster.  A launch of 32-row tiles
 // of the tiled kernel was the best choice in none of them.  Experts of at most 16 rows stay with the small-M kernel unless
 // the model gives that 15 % more, and with 8-bit codes always (up to 1.27x faster there).
 fq_grouped_plan fq_plan_grouped(const int32_t* offsets, int E, int64_t N, int64_t K, int bits, int g) {

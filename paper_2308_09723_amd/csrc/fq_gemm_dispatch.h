@@ -430,7 +430,8 @@ int launch_grouped_typed(const void* A, const int32_t* offsets, int E, const fq_
             for (int32_t r = offsets[e], take = 0; r < offsets[e + 1]; r += take) {
                 if (fq_next_tile(plan, offsets[e + 1] - r, &take) != cls || (height > 0 && (take + 15) / 16 * 16 != height)) continue;
                 small.row0[count] = r;
-                // (an expert of up to 48 rows, and what a 128- or 64-row tile leaves over, had lower tiles always)
+                // (an expert of up to 48 rows, and what 128- or 64-row tiles leave over, keep the operands, biased ones in
+                // bfloat16, that a product of as many rows has)
                 const bool exact = plan.cut == FQ_CUT_MID && offsets[e + 1] - offsets[e] > 48;
                 small.rows[count] = (uint8_t)(take | (exact ? FQ_ITEM_EXACT : 0));
                 small.expert[count] = (uint8_t)e;
