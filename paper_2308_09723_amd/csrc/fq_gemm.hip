@@ -454,7 +454,7 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
             if (tall && (N >= 8192 || M > 2048 || (bits == 8 && p128.waves == 8))) continue;
             // (a biased bfloat16 operand, as use_post and Dequant make it)
             const bool biased = bits != 8 && (fq_scale_rows(bits, g) == 1 || (mt == 2 && fq_scale_rows(bits, g) == 2));
-            if (tall && biased && (act_dtype != FQ_F16 || p128.tail_tiles > 0)) continue;
+            if (tall && biased && (act_dtype != FQ_F16 || p128.tail_tiles > 0 || p.splits != p128.splits)) continue;
             const int bm = mt * 16;
             const int64_t nbm = (M + bm - 1) / bm;
             const double u8 = mt == 8 ? cs[4] : (mt == 4 ? cs[2] : cs[0]);

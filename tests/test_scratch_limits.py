@@ -54,3 +54,15 @@ def test_integer_path_scratch_over_many_shapes():
         assert need <= _most_bytes(M, N, K), (M, K, N, g)
         split += need > 0
     assert split > 300
+
+
+def test_one_workspace_size_serves_every_type():
+    """fq_gemm_workspace_bytes is the largest need over activation types and scale formats, on narrow matrices too, where binary16
+    products alone take some block shapes."""
+    r = random.Random(7)
+    for _ in range(20000):
+        M, K, N = (int(math.exp(r.uniform(math.log(a), math.log(b)))) for a, b in ((49, 2400), (1, 64), (1, 511)))
+        K, N = 128 * K, 16 * N
+        bits, g = r.choice([3, 4, 8]), r.choice([32, 64, 128])
+        most = fq.gemm_workspace_bytes(M, N, K, bits, g)
+        assert all(fq.gemm_workspace_bytes_for(M, N, K, bits, g, a, s) <= most for a, s in ((0, 0), (1, 0), (1, 1))), (M, K, N, bits, g)
