@@ -2,6 +2,8 @@
 // that dispatch on activation type and code width.  The kernels themselves are instantiated
 // in fq_gemm_<type>_<bits>.hip.
 #include <hip/hip_runtime.h>
+#include <atomic>
+#include <chrono>
 #include <math.h>
 #include <mutex>
 #include <stdint.h>
@@ -43,6 +45,13 @@ int fq_cu_count() {
         return 256;
     }();
     return n;
+}
+
+// The calls of a process are numbered from a place of its own on, so that what another process left in memory carries no
+// tag of this one either.
+uint64_t fq_next_tag() {
+    static std::atomic<uint64_t> calls{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() * 0x9e3779b97f4a7c15ull >> 20};
+    return 0xffa5ull << 48 | (calls.fetch_add(1, std::memory_order_relaxed) & 0xffffffffffull) << 8;
 }
 
 // scale rows a layout k-block spans: 1, kblk / g, or one per 32-row step

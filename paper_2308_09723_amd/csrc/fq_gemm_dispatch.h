@@ -16,7 +16,7 @@ using namespace fqk;
 
 template <int ACT, int BITS, int NT, int DEPTH, int MAXW, int AU>
 int launch_skinny(const void* A, int64_t M, int64_t N, int64_t K, const void* codes, const void* scales, int g,
-                  void* C, float* partial, const fq_gemm_plan& plan, hipStream_t stream) {
+                  void* C, float* partial, const fq_gemm_plan& plan, uint64_t tag, hipStream_t stream) {
     const int kblk = fq_kblk(BITS);
     // scale rows per k-block: 1, KBLK / g, or one per 32-row step when g does not divide KBLK
     const int sr = (g % kblk) == 0 ? 1 : ((kblk % g) == 0 ? kblk / g : kblk / 32);
@@ -42,24 +42,24 @@ int launch_skinny(const void* A, int64_t M, int64_t N, int64_t K, const void* co
     hipLaunchKernelGGL(kern, dim3((unsigned)(bgroups * plan.splits)), dim3((unsigned)(plan.gp * plan.kw * 64)),
                        lds, stream, (const uint16_t*)A, (const u32x4*)codes, (const uint16_t*)scales,
                        (uint16_t*)C, partial, (int)M, (int)N, (int)K, g32, g32_recip, plan.gp, plan.kw,
-                       plan.splits, fq_no_items{});
+                       plan.splits, tag, fq_no_items{});
     return FQ_OK;
 }
 
 template <int ACT, int BITS, int NT, int DEPTH, int MAXW>
 int launch_skinny_au(const void* A, int64_t M, int64_t N, int64_t K, const void* codes, const void* scales,
-                     int g, void* C, float* partial, const fq_gemm_plan& plan, hipStream_t stream) {
+                     int g, void* C, float* partial, const fq_gemm_plan& plan, uint64_t tag, hipStream_t stream) {
     switch (plan.au) {
-        case 1: return launch_skinny<ACT, BITS, NT, DEPTH, MAXW, 1>(A, M, N, K, codes, scales, g, C, partial, plan, stream);
-        case 2: return launch_skinny<ACT, BITS, NT, DEPTH, MAXW, 2>(A, M, N, K, codes, scales, g, C, partial, plan, stream);
-        default: return launch_skinny<ACT, BITS, NT, DEPTH, MAXW, 4>(A, M, N, K, codes, scales, g, C, partial, plan, stream);
+        case 1: return launch_skinny<ACT, BITS, NT, DEPTH, MAXW, 1>(A, M, N, K, codes, scales, g, C, partial, plan, tag, stream);
+        case 2: return launch_skinny<ACT, BITS, NT, DEPTH, MAXW, 2>(A, M, N, K, codes, scales, g, C, partial, plan, tag, stream);
+        default: return launch_skinny<ACT, BITS, NT, DEPTH, MAXW, 4>(A, M, N, K, codes, scales, g, C, partial, plan, tag, stream);
     }
 }
 
 // Mid-M streaming kernel (plan.kind == 2)
 template <int ACT, int BITS, int NT, int MT, int MAXW>
 int launch_mid(const void* A, int64_t M, int64_t N, int64_t K, const void* codes, const void* scales, int g, void* C,
-               float* partial, const fq_gemm_plan& plan, hipStream_t stream) {
+               float* partial, const fq_gemm_plan& plan, uint64_t tag, hipStream_t stream) {
     constexpr int kblk = fq_kblk(BITS);
     constexpr int STEPS = kblk / FQ_KSTEP;
     const int sr = (g % kblk) == 0 ? 1 : ((kblk % g) == 0 ? kblk / g : STEPS);
@@ -80,7 +80,7 @@ int launch_mid(const void* A, int64_t M, int64_t N, int64_t K, const void* codes
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)(bgroups * plan.splits)), dim3((unsigned)(plan.gp * plan.kw * 64)), lds, stream,
                        (const uint16_t*)A, (const u32x4*)codes, (const uint16_t*)scales, (uint16_t*)C, partial, (int)M,
-                       (int)N, (int)K, g32, g32_recip, plan.gp, plan.kw, plan.splits);
+                       (int)N, (int)K, g32, g32_recip, plan.gp, plan.kw, plan.splits, tag);
     return FQ_OK;
 }
 
@@ -132,18 +132,23 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
                  int g, void* C, void* workspace, const fq_gemm_plan& plan, hipStream_t stream) {
     const int ntiles = (int)(N / FQ_NTILE);
     float* partial = (float*)workspace;
+    // The streaming kernels add a split of K themselves where a tile's partial sums are few enough for one block; not where
+    // the ticket in C would be misaligned.
+    const int tile_cols = plan.gp * FQ_NTILE * (plan.kind == 0 ? SKINNY_VARIANTS[plan.variant].nt : MMA_NT);
+    const bool sums = plan.kind != 1 && fq_sums_splits((int)M, tile_cols, plan.splits, C);
+    const uint64_t tag = sums ? fq_next_tag() : 0;
     if (plan.kind == 0) {
         int st;
         switch (plan.variant) {
-            case 0: st = launch_skinny_au<ACT, BITS, 3, 2, 12>(A, M, N, K, codes, scales, g, C, partial, plan, stream); break;
-            case 1: st = launch_skinny_au<ACT, BITS, 3, 3, 8>(A, M, N, K, codes, scales, g, C, partial, plan, stream); break;
-            case 2: st = launch_skinny_au<ACT, BITS, 1, 4, 12>(A, M, N, K, codes, scales, g, C, partial, plan, stream); break;
-            default: st = launch_skinny_au<ACT, BITS, 2, 3, 12>(A, M, N, K, codes, scales, g, C, partial, plan, stream); break;
+            case 0: st = launch_skinny_au<ACT, BITS, 3, 2, 12>(A, M, N, K, codes, scales, g, C, partial, plan, tag, stream); break;
+            case 1: st = launch_skinny_au<ACT, BITS, 3, 3, 8>(A, M, N, K, codes, scales, g, C, partial, plan, tag, stream); break;
+            case 2: st = launch_skinny_au<ACT, BITS, 1, 4, 12>(A, M, N, K, codes, scales, g, C, partial, plan, tag, stream); break;
+            default: st = launch_skinny_au<ACT, BITS, 2, 3, 12>(A, M, N, K, codes, scales, g, C, partial, plan, tag, stream); break;
         }
         if (st != FQ_OK) return st;
     } else if (plan.kind == 2) {
-        const int st = plan.mt == 2 ? launch_mid<ACT, BITS, MMA_NT, 2, 12>(A, M, N, K, codes, scales, g, C, partial, plan, stream)
-                                    : launch_mid<ACT, BITS, MMA_NT, 3, 12>(A, M, N, K, codes, scales, g, C, partial, plan, stream);
+        const int st = plan.mt == 2 ? launch_mid<ACT, BITS, MMA_NT, 2, 12>(A, M, N, K, codes, scales, g, C, partial, plan, tag, stream)
+                                    : launch_mid<ACT, BITS, MMA_NT, 3, 12>(A, M, N, K, codes, scales, g, C, partial, plan, tag, stream);
         if (st != FQ_OK) return st;
     } else if (plan.kind == 3) {
         // row blocks of the mid-M kernel: as few as 48 rows allow, of nearly equal height, all without a bias
@@ -296,7 +301,7 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
                            (const float*)partial, plan.tail_splits, (int)M, (int)N, nblocks_n, nblocks_m,
                            nblocks_n * nblocks_m - plan.tail_tiles, bm, bn_cols, (uint16_t*)C);
     }
-    if (plan.splits > 1) {
+    if (plan.splits > 1 && !sums) {
         const int64_t MN = M * N;
         dim3 grid((unsigned)((MN / 4 + 255) / 256));
         hipLaunchKernelGGL(fq_reduce_kernel<(ACT == FQ_F16 ? FQ_F16 : FQ_BF16)>, grid, dim3(256), 0, stream, (const float*)partial,
@@ -329,7 +334,7 @@ int launch_grouped_small(const void* A, const fq_small_items& items, int count, 
     const int64_t blocks = (int64_t)((ngroups + sh.gp - 1) / sh.gp) * count;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3((unsigned)(sh.gp * sh.kw * 64)), lds, stream, (const uint16_t*)A,
                        (const u32x4*)codes, (const uint16_t*)scales, (uint16_t*)C, (float*)nullptr, 0, (int)N, (int)K, g32,
-                       g32_recip, sh.gp, sh.kw, 1, items);
+                       g32_recip, sh.gp, sh.kw, 1, (uint64_t)0, items);
     return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_HIP;
 }
 

@@ -27,6 +27,7 @@
 
 #include "fq_internal.h"
 #include "fq_layout.h"
+#include "fq_split_sum.h"
 
 namespace fqk {
 
@@ -547,6 +548,16 @@ __device__ inline void recompute_not_finite(f32x4 (&acc)[NT], const uint16_t* A,
         for (int i = 0; i < 4; ++i) acc[nt][i] = acc[nt][i] * 0.0f == 0.0f ? acc[nt][i] : again[nt][i];
 }
 
+// the end of a block of gp groups of NT column tiles, the bx-th of its rows, where K is split over the grid
+template <int ACT, int NT>
+__device__ __forceinline__ void finish_splits(void* lds, const float* partial, int splits, uint16_t* C, int M, int N, int bx, int gp,
+                                              uint64_t tag) {
+    const int cols = gp * NT * FQ_NTILE;
+    finish_split_sums<f32x4>(lds, partial, (int64_t)M * N, splits, C, M, N, bx * cols, cols, tag, [&](int m, int n, const f32x4& v) {
+        *reinterpret_cast<u32x2*>(C + (int64_t)m * N + n) = pack4<ACT>(v);
+    });
+}
+
 // LDS row pitch of the activation buffer in 16-byte units: 16 rows + 1 pad, so that both the
 // fragment reads (16 lanes = 16 rows of one unit column) and the staging writes (consecutive
 // lanes = consecutive unit columns of one row) spread over the banks.
@@ -571,7 +582,7 @@ template <int ACT, int BITS, int NT, int DEPTH, int SR, int MAXW, int AU, typena
 __global__ __launch_bounds__(MAXW * 64) void fq_gemm_skinny_kernel(
     const uint16_t* __restrict__ A, const u32x4* __restrict__ codes, const uint16_t* __restrict__ scales,
     uint16_t* __restrict__ C, float* __restrict__ partial, int M, int N, int K, uint32_t g32,
-    uint32_t g32_recip, int gp, int kw_n, int grid_splits, ITEMS items) {
+    uint32_t g32_recip, int gp, int kw_n, int grid_splits, uint64_t tag, ITEMS items) {
     constexpr int KBLK = fq_kblk(BITS);
     constexpr int STEPS = KBLK / FQ_KSTEP;
     constexpr int KC = KBLK / 8;                    // 16-byte activation units per row and k-block
@@ -748,12 +759,13 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_skinny_kernel(
         if (grid_splits == 1) {
             *reinterpret_cast<u32x2*>(C + (int64_t)mq * N + n) = pack4<ACT>(v);
         } else {
-            *reinterpret_cast<f32x4*>(partial + ((int64_t)gsplit * M + mq) * N + n) = v;
+            store_partial(partial + ((int64_t)gsplit * M + mq) * N + n, v, tag != 0);
         }
     };
     if (kw_n == 1) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) store_quad(acc[nt], ng, nt, lane);
+        if constexpr (!ITEMS::grouped) finish_splits<ACT, NT>(lds, partial, grid_splits, C, M, N, bx, gp, tag);
         return;
     }
     f32x4* red = reinterpret_cast<f32x4*>(lds);
@@ -773,6 +785,7 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_skinny_kernel(
         }
         store_quad(v, bx * gp + gq, r >> 6, r & 63);
     }
+    if constexpr (!ITEMS::grouped) finish_splits<ACT, NT>(lds, partial, grid_splits, C, M, N, bx, gp, tag);
 }
 
 // ==========================================================================================
@@ -816,7 +829,7 @@ template <int ACT, int BITS, int NT, int MT, int DEPTH, int NBUF, int SR, bool E
 __device__ __forceinline__ void mid_block(
     u32x4* lds, const uint16_t* __restrict__ A, const u32x4* __restrict__ codes, const uint16_t* __restrict__ scales,
     uint16_t* __restrict__ C, float* __restrict__ partial, int M, int N, int K, uint32_t g32,
-    uint32_t g32_recip, int gp, int kw_n, int bx, int gsplit, int grid_splits) {
+    uint32_t g32_recip, int gp, int kw_n, int bx, int gsplit, int grid_splits, uint64_t tag) {
     constexpr int KBLK = fq_kblk(BITS);
     constexpr int STEPS = KBLK / FQ_KSTEP;
     constexpr int GSTEPS = STEPS / SR;              // k-steps per scale row
@@ -1055,7 +1068,7 @@ __device__ __forceinline__ void mid_block(
         if (grid_splits == 1) {
             *reinterpret_cast<u32x2*>(C + (int64_t)mq * N + n) = pack4<ACT>(v);
         } else {
-            *reinterpret_cast<f32x4*>(partial + ((int64_t)gsplit * M + mq) * N + n) = v;
+            store_partial(partial + ((int64_t)gsplit * M + mq) * N + n, v, tag != 0);
         }
     };
     if (kw_n == 1) {
@@ -1096,12 +1109,13 @@ template <int ACT, int BITS, int NT, int MT, int SR, int MAXW>
 __global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_kernel(
     const uint16_t* __restrict__ A, const u32x4* __restrict__ codes, const uint16_t* __restrict__ scales,
     uint16_t* __restrict__ C, float* __restrict__ partial, int M, int N, int K, uint32_t g32,
-    uint32_t g32_recip, int gp, int kw_n, int grid_splits) {
+    uint32_t g32_recip, int gp, int kw_n, int grid_splits, uint64_t tag) {
     extern __shared__ u32x4 lds[];
     const int ngroups = (N / FQ_NTILE + NT - 1) / NT;
     const int bgroups = (ngroups + gp - 1) / gp;      // blocks per grid split
     mid_block<ACT, BITS, NT, MT, mid_depth(MT), mid_bufs(MT), SR, mid_exact(ACT, BITS, MT, SR)>(lds, A, codes, scales, C, partial, M, N, K, g32, g32_recip, gp, kw_n,
-                                                                  blockIdx.x % bgroups, blockIdx.x / bgroups, grid_splits);
+                                                                  blockIdx.x % bgroups, blockIdx.x / bgroups, grid_splits, tag);
+    finish_splits<ACT, NT>(lds, partial, grid_splits, C, M, N, blockIdx.x % bgroups, gp, tag);
 }
 
 // Row tiles of up to 16, 32 or 48 rows, each with its own rows and weights, in one launch.  A launch per height would need
@@ -1129,7 +1143,7 @@ __global__ __launch_bounds__(MAXW * 64) void fq_gemm_mid_items_kernel(
     constexpr bool EX2 = mid_exact(ACT, BITS, 2, SR), EX3 = mid_exact(ACT, BITS, 3, SR);
 #define FQ_MID_ITEM(MT_, EXACT_)                                                                                          \
     mid_block<ACT, BITS, NT, MT_, mid_depth(MT_), mid_bufs(MT_), SR, EXACT_>(lds, A, codes, scales, C, nullptr, M, N, K, g32, \
-                                                                             g32_recip, gp, kw_n, bx, 0, 1)
+                                                                             g32_recip, gp, kw_n, bx, 0, 1, (uint64_t)0)
     if (!EX3 && exact && M > 32) FQ_MID_ITEM(3, true);
     else if (M > 32) FQ_MID_ITEM(3, EX3);
     else if (!EX2 && exact) FQ_MID_ITEM(2, true);

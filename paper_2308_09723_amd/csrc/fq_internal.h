@@ -26,6 +26,9 @@ double fq_mfma_probe_flops(int iterations, int int8);
 int fq_launch_mfma_rate_probe(const void* operands, void* sink, int iterations, int lds_reads, int int8,
                               hipStream_t stream);
 
+// A tag for the tickets of one call (fq_split_sum.h); never 0.
+uint64_t fq_next_tag();
+
 // product side
 struct fq_gemm_plan {
     int kind;      // 0 = skinny (M <= 16), 1 = tiled, 2 = mid-M streaming (17 <= M <= 48), 3 = its row blocks (M > 48)

@@ -644,6 +644,19 @@ __global__ __launch_bounds__(W8_WAVES * 64) void fq_gemm_w4a8_kernel(
 constexpr int W8S_PITCH = 17;      // LDS row pitch of the activation buffer in 16-byte units (16 rows + 1 pad)
 constexpr int W8S_KC = 8;          // 16-byte activation units per row and k-block
 
+// the end of a block of `cols` columns, the bx-th of its rows, where K is split over the grid (fq_split_sum.h; partial, alpha
+// and C at the block's row 0)
+template <int OUT>
+__device__ __forceinline__ void w8_finish_splits(void* lds, const int32_t* partial, int64_t stride, int splits, const float* alpha,
+                                                 const uint16_t* tstep, uint16_t* C, int rows, int N, int bx, int cols, uint64_t tag) {
+    finish_split_sums<v4i>(lds, partial, stride, splits, C, rows, N, bx * cols, cols, tag, [&](int m, int n, const v4i& v) {
+        float tn[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tn[i] = f16_bits_to_float(tstep[n + i]);
+        w8_store4<OUT>(C + (int64_t)m * N + n, v, alpha[m], tn);
+    });
+}
+
 template <int NT, int ZR, int AU>
 struct W8Stage {
     u32x4 wq[NT];
@@ -656,7 +669,7 @@ __global__ __launch_bounds__(MAXW * 64) void fq_w4a8_skinny_kernel(
     const int8_t* __restrict__ Aq, const float* __restrict__ alpha, const u32x4* __restrict__ codes,
     const uint8_t* __restrict__ z, const uint16_t* __restrict__ tstep, uint16_t* __restrict__ C,
     int32_t* __restrict__ partial, int M, int N, int K, uint32_t g32, uint32_t g32_recip, int gp, int kw_n,
-    int grid_splits) {
+    int grid_splits, uint64_t tag) {
     constexpr int KC = W8S_KC, PITCH = W8S_PITCH;
     typedef W8Stage<NT, ZR, AU> Stage;
     extern __shared__ u32x4 lds[];   // two activation buffers [kw_n * KC][PITCH]; later the reduction
@@ -823,12 +836,13 @@ __global__ __launch_bounds__(MAXW * 64) void fq_w4a8_skinny_kernel(
             for (int i = 0; i < 4; ++i) tn[i] = f16_bits_to_float(tstep[n + i]);
             w8_store4<OUT>(C + (int64_t)mq * N + n, v, alpha[mq], tn);
         } else {
-            *reinterpret_cast<v4i*>(partial + ((int64_t)gsplit * M + mq) * N + n) = v;
+            store_partial(partial + ((int64_t)gsplit * M + mq) * N + n, v, tag != 0);
         }
     };
     if (kw_n == 1) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) store_quad(acc[nt], ng, nt, lane);
+        w8_finish_splits<OUT>(lds, partial, (int64_t)M * N, grid_splits, alpha, tstep, C, M, N, bx, gp * NT * FQ_NTILE, tag);
         return;
     }
     v4i* red = reinterpret_cast<v4i*>(lds);
@@ -845,6 +859,7 @@ __global__ __launch_bounds__(MAXW * 64) void fq_w4a8_skinny_kernel(
         for (int w = 1; w < kw_n; ++w) v += src[w * NT * 64];
         store_quad(v, bx * gp + gq, r >> 6, r & 63);
     }
+    w8_finish_splits<OUT>(lds, partial, (int64_t)M * N, grid_splits, alpha, tstep, C, M, N, bx, gp * NT * FQ_NTILE, tag);
 }
 
 // ------------------------------------------------------------------------------------------------------
@@ -869,7 +884,7 @@ __global__ __launch_bounds__(W8M_MAXW * 64) void fq_w4a8_mid_kernel(
     const int8_t* __restrict__ Aq, const float* __restrict__ alpha, const u32x4* __restrict__ codes,
     const uint8_t* __restrict__ z, const uint16_t* __restrict__ tstep, uint16_t* __restrict__ C,
     int32_t* __restrict__ partial, int M, int N, int K, uint32_t g32, uint32_t g32_recip, int gp, int kw_n, int nblocks_m,
-    int grid_splits) {
+    int grid_splits, uint64_t tag) {
     constexpr int NT = W8M_NT, DEPTH = W8M_DEPTH;
     constexpr int TILE = 16 * MT * 8;               // 16-byte units of one k-worker's activation tile
     constexpr int NI = TILE / 64;                   // wave-level direct loads of such a tile
@@ -1053,7 +1068,7 @@ __global__ __launch_bounds__(W8M_MAXW * 64) void fq_w4a8_mid_kernel(
             for (int i = 0; i < 4; ++i) tn[i] = f16_bits_to_float(tstep[n + i]);
             w8_store4<OUT>(C + (int64_t)mq * N + n, v, alpha[mq], tn);
         } else {
-            *reinterpret_cast<v4i*>(partial + ((int64_t)gsplit * M + row0 + mq) * N + n) = v;
+            store_partial(partial + ((int64_t)gsplit * M + row0 + mq) * N + n, v, tag != 0);
         }
     };
     if (kw_n == 1) {
@@ -1061,6 +1076,8 @@ __global__ __launch_bounds__(W8M_MAXW * 64) void fq_w4a8_mid_kernel(
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) store_quad(acc[mt][nt], ng, mt, nt, lane);
+        w8_finish_splits<OUT>(lds, partial + (int64_t)row0 * N, (int64_t)M * N, grid_splits, alpha, tstep, C, rows, N, bx,
+                              gp * NT * FQ_NTILE, tag);
         return;
     }
     // the k-workers' sums of each column group, added by all threads of the block (one result quad each)
@@ -1081,6 +1098,8 @@ __global__ __launch_bounds__(W8M_MAXW * 64) void fq_w4a8_mid_kernel(
         const int tl = r >> 6;
         store_quad(v, bx * gp + gq, tl / NT, tl % NT, r & 63);
     }
+    w8_finish_splits<OUT>(lds, partial + (int64_t)row0 * N, (int64_t)M * N, grid_splits, alpha, tstep, C, rows, N, bx,
+                          gp * NT * FQ_NTILE, tag);
 }
 
 template <int OUT>
@@ -1342,7 +1361,7 @@ void w8_launch(const w8_plan& p, int g, const int8_t* Aq, const float* alpha, co
 
 template <int OUT, int ZR, int AU>
 int w8_launch_small(const w8_plan& p, int g, const int8_t* Aq, const float* alpha, const void* codes, const uint8_t* z,
-                    const void* tstep, void* C, int32_t* partial, int64_t M, int64_t N, int64_t K, hipStream_t stream) {
+                    const void* tstep, void* C, int32_t* partial, int64_t M, int64_t N, int64_t K, uint64_t tag, hipStream_t stream) {
     const size_t lds_act = (size_t)2 * p.kw * W8S_KC * W8S_PITCH * 16;
     const size_t lds_red = (size_t)p.gp * p.kw * W8S_NT * 64 * 16;
     const size_t lds = lds_act > lds_red ? lds_act : lds_red;       // at most 36 KiB
@@ -1351,13 +1370,13 @@ int w8_launch_small(const w8_plan& p, int g, const int8_t* Aq, const float* alph
     hipLaunchKernelGGL((fq_w4a8_skinny_kernel<W8S_NT, w8s_depth(ZR, AU), ZR, W8S_MAXW, AU, OUT>),
                        dim3((unsigned)(p.nblocks_n * p.splits)), dim3((unsigned)(p.gp * p.kw * 64)), lds, stream, Aq,
                        alpha, (const u32x4*)codes, z, (const uint16_t*)tstep, (uint16_t*)C, partial, (int)M, (int)N,
-                       (int)K, g32, g32_recip, p.gp, p.kw, p.splits);
+                       (int)K, g32, g32_recip, p.gp, p.kw, p.splits, tag);
     return FQ_OK;
 }
 
 template <int MT, int ZR, int OUT>
 int w8_launch_mid(const w8_plan& p, int g, const int8_t* Aq, const float* alpha, const void* codes, const uint8_t* z,
-                  const void* tstep, void* C, int32_t* partial, int64_t M, int64_t N, int64_t K, hipStream_t stream) {
+                  const void* tstep, void* C, int32_t* partial, int64_t M, int64_t N, int64_t K, uint64_t tag, hipStream_t stream) {
     const size_t lds = w8m_lds(MT, p.gp, p.kw);
     const uint32_t g32 = (uint32_t)(g / 32);
     const uint32_t g32_recip = (uint32_t)((((uint64_t)1 << 32) + g32 - 1) / g32);   // unused when g32 == 1
@@ -1369,7 +1388,7 @@ int w8_launch_mid(const w8_plan& p, int g, const int8_t* Aq, const float* alpha,
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)(p.nblocks_n * p.nblocks_m * p.splits)), dim3((unsigned)(p.gp * p.kw * 64)), lds,
                        stream, Aq, alpha, (const u32x4*)codes, z, (const uint16_t*)tstep, (uint16_t*)C, partial, (int)M, (int)N,
-                       (int)K, g32, g32_recip, p.gp, p.kw, p.nblocks_m, p.splits);
+                       (int)K, g32, g32_recip, p.gp, p.kw, p.nblocks_m, p.splits, tag);
     return FQ_OK;
 }
 
@@ -1377,12 +1396,15 @@ template <int OUT>
 int w8_gemm(const w8_plan& p, const int8_t* Aq, const float* alpha, int64_t M, int64_t N, int64_t K, const void* codes,
             const uint8_t* z, const void* tstep, int g, void* C, void* workspace, hipStream_t stream) {
     int32_t* partial = (int32_t*)workspace;
+    // the small-M and mid-M kernels add a split of K themselves where a tile's sums are few
+    const bool sums = (p.mid || p.small) && fq_sums_splits(M < p.mt * 16 ? (int)M : p.mt * 16, p.gp * W8M_NT * FQ_NTILE, p.splits, C);
+    const uint64_t tag = sums ? fq_next_tag() : 0;
     if (p.mid) {
         const bool zr1 = g % 128 == 0;
         int st;
 #define W8_MID(MT_)                                                                                                   \
-    st = zr1 ? w8_launch_mid<MT_, 1, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream)              \
-             : w8_launch_mid<MT_, 2, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream)
+    st = zr1 ? w8_launch_mid<MT_, 1, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, tag, stream)              \
+             : w8_launch_mid<MT_, 2, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, tag, stream)
         if (p.mt == 2) W8_MID(2);
         else if (p.mt == 3) W8_MID(3);
         else W8_MID(4);
@@ -1390,16 +1412,16 @@ int w8_gemm(const w8_plan& p, const int8_t* Aq, const float* alpha, int64_t M, i
         if (st != FQ_OK) return st;
     } else if (p.small) {
         const bool zr1 = g % 128 == 0;
-        if (zr1 && p.au == 1) w8_launch_small<OUT, 1, 1>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream);
-        else if (zr1) w8_launch_small<OUT, 1, 2>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream);
-        else if (p.au == 1) w8_launch_small<OUT, 2, 1>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream);
-        else w8_launch_small<OUT, 2, 2>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream);
+        if (zr1 && p.au == 1) w8_launch_small<OUT, 1, 1>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, tag, stream);
+        else if (zr1) w8_launch_small<OUT, 1, 2>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, tag, stream);
+        else if (p.au == 1) w8_launch_small<OUT, 2, 1>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, tag, stream);
+        else w8_launch_small<OUT, 2, 2>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, tag, stream);
     } else
     switch (p.mt) {
         case 4: w8_launch<4, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream); break;
         default: w8_launch<8, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream); break;
     }
-    if (p.splits > 1) {
+    if (p.splits > 1 && !sums) {
         const int64_t n4 = M * N / 4;
         hipLaunchKernelGGL(w8_finalize_kernel<OUT>, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, stream,
                            (const int32_t*)partial, p.splits, alpha, (const uint16_t*)tstep, M, N, (uint16_t*)C);

@@ -1,0 +1,109 @@
+"""A split of K over the grid that the product kernel sums itself (the block that takes the last ticket of a tile, counted
+in the output) gives the bits of the separate sum kernel, which outputs that are not 8-byte aligned still take -- whatever
+the output holds before the call, call after call, on two streams at once and replayed from a graph."""
+import pytest
+
+from gpu_util import torch_mod
+
+pytestmark = pytest.mark.gpu
+
+# (rows, K, N, bits, g, type): the smallest call; one and several column groups per block, with and without k-workers; a last
+# block with column tiles past the end; two and three row tiles with ragged rows
+SHAPES = [(4, 1024, 1024, 4, 128, "f16"), (1, 15744, 1248, 4, 128, "bf16"), (13, 6528, 3728, 4, 32, "f16"),
+          (16, 8192, 10000, 8, 128, "bf16"), (3, 2048, 16, 3, 64, "f16"), (21, 3200, 4400, 4, 64, "f16"),
+          (30, 7296, 2432, 8, 64, "f16"), (43, 7552, 1584, 4, 32, "bf16"), (48, 10240, 5264, 4, 128, "bf16")]
+
+
+def _case(M, K, N, bits, g, act, seed=1):
+    from paper_2308_09723_amd import fq
+    torch = torch_mod()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    W = (torch.randn((K, N), generator=gen, device="cuda") * 0.02).to(torch.float16)
+    codes, scales = fq.quantize(W, bits, g)
+    A = torch.randn((M, K), generator=gen, device="cuda").to(torch.float16 if act == "f16" else torch.bfloat16)
+    need = fq.gemm_workspace_bytes(M, N, K, bits, g)
+    assert need > 0, "the product does not split K"
+    return A, codes, scales, torch.empty(need, dtype=torch.uint8, device="cuda")
+
+
+def _outputs(M, N, dtype):
+    """An aligned output and one that starts two bytes past an aligned address."""
+    torch = torch_mod()
+    return torch.empty((M, N), dtype=dtype, device="cuda"), torch.empty(M * N + 4, dtype=dtype, device="cuda")[1:1 + M * N].view(M, N)
+
+
+@pytest.mark.parametrize("M,K,N,bits,g,act", SHAPES)
+def test_same_bits_as_the_separate_sum(M, K, N, bits, g, act):
+    from paper_2308_09723_amd import fq
+    torch = torch_mod()
+    A, codes, scales, ws = _case(M, K, N, bits, g, act)
+    C, apart = _outputs(M, N, A.dtype)
+    assert C.data_ptr() % 8 == 0 and apart.data_ptr() % 8 == 2
+    want = fq.gemm(A, codes, scales, bits, g, out=apart, workspace=ws).clone()
+    exact = A.double() @ (fq.unpack(codes, K, N, bits).double() * scales.double().repeat_interleave(g, 0))
+    assert float((want.double() - exact).norm() / exact.norm()) < (1.2e-3 if act == "f16" else 7e-3)
+    # zeros, the results themselves, NaNs, and words that look like tickets of other calls, full and begun
+    fills = [lambda: C.zero_(), lambda: None, lambda: C.fill_(float("nan")), lambda: C.view(torch.int16).fill_(-91)]
+    fills += [lambda n=n: C.view(torch.int64).fill_((-91 << 48) | n) for n in (0, 1, 7, 0x12345600)]
+    for i, fill in enumerate(fills * 3):
+        fill()
+        assert torch.equal(fq.gemm(A, codes, scales, bits, g, out=C, workspace=ws).view(torch.int16), want.view(torch.int16)), i
+
+
+def test_two_streams_at_once():
+    from paper_2308_09723_amd import fq
+    torch = torch_mod()
+    cases = [_case(4, 1024, 1024, 4, 128, "f16", 3) + (4, 128), _case(21, 3200, 4400, 4, 64, "f16", 4) + (4, 64)]
+    wants = [fq.gemm(A, c, s, b, g) for A, c, s, ws, b, g in cases]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in cases]
+    got = [[] for _ in cases]
+    for _ in range(20):
+        for i, (A, c, s, ws, b, g) in enumerate(cases):
+            with torch.cuda.stream(streams[i]):
+                got[i].append(fq.gemm(A, c, s, b, g, workspace=ws))
+    torch.cuda.synchronize()
+    for want, outs in zip(wants, got):
+        assert all(torch.equal(o, want) for o in outs)
+
+
+def test_replayed_with_the_tag_it_was_captured_with():
+    from paper_2308_09723_amd import fq
+    torch = torch_mod()
+    A, codes, scales, ws = _case(13, 6528, 3728, 4, 32, "f16")
+    C = torch.empty((13, 3728), dtype=A.dtype, device="cuda")
+    fq.gemm(A, codes, scales, 4, 32, out=C, workspace=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        fq.gemm(A, codes, scales, 4, 32, out=C, workspace=ws)
+    for rep in range(5):
+        A.mul_(1.5)
+        want = fq.gemm(A, codes, scales, 4, 32)        # eager work between the replays
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(C, want), rep
+
+
+@pytest.mark.parametrize("M,K,N,g,act", [(4, 4096, 1024, 128, "f16"), (1, 8448, 1024, 128, "bf16"), (16, 16256, 1808, 32, "f16"),
+                                         (13, 15744, 2048, 96, "bf16"), (43, 7040, 1472, 32, "bf16"), (52, 15744, 1552, 64, "f16"),
+                                         (130, 16384, 1040, 128, "bf16")])
+def test_integer_path_same_bits_as_the_separate_sum(M, K, N, g, act):
+    from paper_2308_09723_amd import fq
+    torch = torch_mod()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(2)
+    dtype = torch.float16 if act == "f16" else torch.bfloat16
+    codes, z, t = fq.quantize_w4a8((torch.randn((K, N), generator=gen, device="cuda") * 0.02).to(torch.float16), g)
+    Aq, alpha = fq.quantize_act_i8(torch.randn((M, K), generator=gen, device="cuda").to(dtype))
+    need = fq.gemm_w4a8_workspace_bytes(M, N, K, g)
+    assert need > 0, "the product does not split K"
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    C, apart = _outputs(M, N, dtype)
+    want = fq.gemm_w4a8(Aq, alpha, codes, z, t, g, dtype, out=apart, workspace=ws).clone()
+    for fill in (lambda: C.zero_(), lambda: None, lambda: C.fill_(float("nan")), lambda: C.view(torch.int64).fill_((-91 << 48) | 3)) * 4:
+        fill()
+        got = fq.gemm_w4a8(Aq, alpha, codes, z, t, g, dtype, out=C, workspace=ws)
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
