@@ -1,7 +1,8 @@
 """Builds libfq.so for gfx950 with hipcc (cross-compiles without a GPU).
 
 Every translation unit is compiled to an object file in parallel (the nine product-kernel
-instantiations dominate the build time), then linked into paper_2308_09723_amd/libfq.so.
+instantiations dominate the build time), then linked into paper_2308_09723_amd/libfq.so; beside them g++ compiles the native
+calls of fq.py into paper_2308_09723_amd/_fqcall.so.
 """
 from __future__ import annotations
 
@@ -14,6 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libfq.so")
+NATIVE_PATH = os.path.join(HERE, "_fqcall.so")      # the native calls of fq.py
 SOURCES = [
     "fq_api.hip",
     "fq_quantize.hip",
@@ -131,6 +133,20 @@ def _resource_report(rows, verbose):
         raise RuntimeError("NO_SPILL names kernels that were not compiled: " + ", ".join(missing))
 
 
+def _native_command():
+    """The command that compiles the native calls: host code only, against torch's headers (torch itself is not imported)."""
+    import importlib.util
+    import sysconfig
+
+    torch = importlib.util.find_spec("torch").submodule_search_locations[0]
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    include = [os.path.join(torch, "include"), os.path.join(torch, "include", "torch", "csrc", "api", "include"),
+               os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__", "-D_GLIBCXX_USE_CXX11_ABI=1"] +
+            [x for d in include for x in ("-isystem", d)] + [os.path.join(CSRC, "fq_binding.cpp"), "-L" + os.path.join(torch, "lib"),
+            "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", NATIVE_PATH])
+
+
 def build_lib(verbose: bool = True, jobs: int | None = None) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ_DIR, exist_ok=True)
@@ -149,8 +165,18 @@ def build_lib(verbose: bool = True, jobs: int | None = None) -> str:
             print(rest)
         return obj, _parse_resources(out)
 
+    def compile_native():
+        cmd = _native_command()
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        rc, out = _run(cmd)
+        if rc != 0:
+            raise RuntimeError("g++ failed on fq_binding.cpp:\n" + out)
+
     with ThreadPoolExecutor(max_workers=jobs) as pool:
+        native = pool.submit(compile_native)
         results = list(pool.map(compile_one, SOURCES))
+        native.result()
     objs = [r[0] for r in results]
     _resource_report([row for r in results for row in r[1]], verbose)
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB_PATH]

@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import array
 import ctypes
+import importlib.util
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -37,9 +38,9 @@ def load(build_if_missing: bool = True) -> ctypes.CDLL:
     global _lib
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
+    if not (os.path.exists(LIB_PATH) and os.path.exists(NATIVE_PATH)):
         if not build_if_missing:
-            raise FileNotFoundError(LIB_PATH)
+            raise FileNotFoundError(NATIVE_PATH if os.path.exists(LIB_PATH) else LIB_PATH)
         from . import build
 
         build.build_lib(verbose=False)
@@ -289,11 +290,15 @@ def gemm_w4a8_raw(Aq_ptr, alpha_ptr, M, N, K, codes_ptr, z_ptr, t_ptr, group_siz
 
 # ------------------------------------------------------------------ torch-tensor conveniences
 # (What a call spends here counts on small products: asking torch for its current stream as an object took 2.9 us of the
-# 9.1 us of a fq.gemm of one launch; the stream's address alone, and functions looked up once, leave 5.8.)
+# 9.1 us of a fq.gemm of one launch; the stream's address alone, and functions looked up once, leave 5.8, and the native calls
+# below 3.5.)
 def _torch():
     """torch, and the function that gives a device's current stream as an address, looked up on the first call."""
-    global _torch_mod, _raw_stream, _device
+    global _torch_mod, _raw_stream, _device, _native
     import torch
+
+    load()
+    _native = _load_native()
 
     _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     if _raw_stream is None:
@@ -304,6 +309,23 @@ def _torch():
 
 
 _torch_mod = _raw_stream = _device = None
+
+# The calls that a program makes over and over, in native code (csrc/fq_binding.cpp).  A function of it returns None where a
+# call is out of the ordinary; the Python below it then reports the error, or does without.
+NATIVE_PATH = os.path.join(_HERE, "_fqcall.so")
+_NATIVE_FUNCTIONS = ("fq_gemm_sf", "fq_gemm_workspace_bytes", "fq_gemm_grouped_sf", "fq_gemm_w4a8", "fq_gemm_w4a8_workspace_bytes",
+                     "fq_quantize_act_i8", "fq_quantize_sf", "fq_quantize_w4a8", "fq_codes_bytes", "fq_scales_bytes", "fq_zscale_bytes")
+_native = None
+
+
+def _load_native():
+    """The native calls, bound to the library that load() has loaded."""
+    spec = importlib.util.spec_from_file_location("_fqcall", NATIVE_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    lib = load()
+    module.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_FUNCTIONS))
+    return module
 
 
 def _stream():
@@ -341,6 +363,9 @@ def quantize(W, bits, group_size, scale_format=FQ_SCALE_F16):
     """W: cuda float16 [K, N] -> (codes uint8 [K*N*bits/8], scales [K/g, N] float16, or bfloat16 for
     scale_format=FQ_SCALE_BF16)."""
     torch = _torch_mod or _torch()
+    done = _native.quantize(W, bits, group_size, scale_format)
+    if done is not None:
+        return done
     assert W.is_cuda and W.dtype == torch.float16 and W.is_contiguous()
     K, N = W.shape
     g = K if group_size in (0, K) else group_size
@@ -389,6 +414,9 @@ def quant_error(W, codes, scales, bits, group_size):
 def gemm(A, codes, scales, bits, group_size, out=None, workspace=None):
     """A: cuda [M, K] float16/bfloat16 -> C [M, N] of the same dtype."""
     torch = _torch_mod or _torch()
+    done = _native.gemm(A, codes, scales, bits, group_size, out, workspace)
+    if done is not None:
+        return done
     assert A.is_cuda and A.is_contiguous()
     M, K = A.shape
     N = scales.shape[1]
@@ -412,6 +440,9 @@ def gemm(A, codes, scales, bits, group_size, out=None, workspace=None):
 def gemm_grouped(A, offsets, codes, scales, bits, group_size, N, out=None):
     """A: cuda [rows, K]; codes / scales: the experts' buffers back to back."""
     torch = _torch_mod or _torch()
+    done = _native.gemm_grouped(A, offsets, codes, scales, bits, group_size, N, out)
+    if done is not None:
+        return done
     rows, K = A.shape
     C = out if out is not None else torch.empty((rows, N), dtype=A.dtype, device=A.device)
     _check(gemm_grouped_sf_raw(A.data_ptr(), _act_code(A), offsets, N, K, codes.data_ptr(), scales.data_ptr(),
@@ -423,6 +454,9 @@ def gemm_grouped(A, offsets, codes, scales, bits, group_size, N, out=None):
 def quantize_w4a8(W, group_size):
     """W: cuda float16 [K, N] -> (codes uint8 [K*N/2], z uint8 [K/g, N], t float16 [N]) of the integer path."""
     torch = _torch_mod or _torch()
+    done = _native.quantize_w4a8(W, group_size)
+    if done is not None:
+        return done
     assert W.is_cuda and W.dtype == torch.float16 and W.is_contiguous()
     K, N = W.shape
     g = K if group_size in (0, K) else group_size
@@ -447,6 +481,9 @@ def unpack_w4a8(codes, K, N):
 def quantize_act_i8(A):
     """A: cuda [M, K] float16/bfloat16 -> (Aq int8 [M, K], alpha float32 [M])."""
     torch = _torch_mod or _torch()
+    done = _native.quantize_act_i8(A)
+    if done is not None:
+        return done
     assert A.is_cuda and A.is_contiguous()
     M, K = A.shape
     Aq = torch.empty((M, K), dtype=torch.int8, device=A.device)
@@ -459,6 +496,9 @@ def quantize_act_i8(A):
 def gemm_w4a8(Aq, alpha, codes, z, t, group_size, out_dtype, out=None, workspace=None):
     """C [M, N] (torch dtype out_dtype: float16 or bfloat16) = alpha * t * (Aq . (q * z))."""
     torch = _torch_mod or _torch()
+    done = _native.gemm_w4a8(Aq, alpha, codes, z, t, group_size, out_dtype, out, workspace)
+    if done is not None:
+        return done
     M, K = Aq.shape
     N = t.shape[0]
     C = out if out is not None else torch.empty((M, N), dtype=out_dtype, device=Aq.device)
