@@ -261,30 +261,32 @@ __global__ __launch_bounds__(256) void w8_act_quant_kernel(const uint16_t* __res
     for (int64_t k = units * 8 + threadIdx.x; k < K; k += 256) dst[k] = (int8_t)w8_act_code(act_to_float<ACT>(src[k]), al);
 }
 
-// Rows of whole 16-byte units at aligned addresses, short enough for the block's registers (8 units of 8 values per
+// Rows of whole 16-byte units at aligned addresses, short enough for the block's registers (UNITS units of 8 values per
 // thread): read once, eight values per load, kept in registers across the search for the largest one.
 // The quotient A / alpha must be the correctly rounded binary32 one (it is rounded a second time, to an integer): with
 // rs = 1 / alpha rounded to nearest, two steps x + fma(-x, alpha, A) * rs from x0 = A * rs give it (Markstein's theorem:
 // the second one starts within one unit in the last place), wherever residuals do not underflow and rs is finite; rows
 // with alpha outside 2^-90 .. 2^100 take the division.  Checked on the host against the division
 // (tests/encode_identity_check.c).  Then clamp, round by adding 1.5 * 2^23, keep the low byte.  Bound by memory:
-// 2048 x 12288 26 -> 16 us; eight rows 6.4 -> 4.9 us (latency: 1024 threads per row).
-constexpr int W8_ROW_UNITS = 8;
-template <int ACT, int THREADS>
+// 2048 x 12288 26 -> 16 us; eight rows 6.4 -> 4.9 us (latency: 1024 threads per row).  Threads that hold no more units than the
+// row needs (eight of them everywhere before: most loaded the last unit again), inside graphs, us: 8 x 12288 3.8 -> 3.1,
+// 512 x 4096 5.1 -> 3.0, 2048 x 1024 5.0 -> 3.5, 2048 x 12288 13.7 as before.
+constexpr int W8_ROW_UNITS = 8;      // the most units per thread
+template <int ACT, int THREADS, int UNITS>
 __global__ __launch_bounds__(THREADS) void w8_act_quant_row_kernel(const uint16_t* __restrict__ A, int units,
                                                                     int8_t* __restrict__ Aq, float* __restrict__ alpha) {
     __shared__ uint32_t red[THREADS / 64];
     const int64_t r = blockIdx.x;
     const u32x4* src = reinterpret_cast<const u32x4*>(A) + r * units;
-    u32x4 v[W8_ROW_UNITS];
+    u32x4 v[UNITS];
     u16x2_t m2 = {0, 0};
 #pragma unroll
-    for (int i = 0; i < W8_ROW_UNITS; ++i) {
+    for (int i = 0; i < UNITS; ++i) {
         const int u = threadIdx.x + i * THREADS;
         v[i] = src[u < units ? u : units - 1];           // (past the end: the last unit again, never stored)
     }
 #pragma unroll
-    for (int i = 0; i < W8_ROW_UNITS; ++i)
+    for (int i = 0; i < UNITS; ++i)
 #pragma unroll
         for (int d = 0; d < 4; ++d)                      // magnitudes of one format order like their bit patterns
             m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2_t, v[i][d] & 0x7fff7fffu));
@@ -311,7 +313,7 @@ __global__ __launch_bounds__(THREADS) void w8_act_quant_row_kernel(const uint16_
             return __float_as_uint(__builtin_amdgcn_fmed3f(x, -127.0f, 127.0f) + FQ_ENCODE_MAGIC);
         };
 #pragma unroll
-        for (int i = 0; i < W8_ROW_UNITS; ++i) {
+        for (int i = 0; i < UNITS; ++i) {
             const int u = threadIdx.x + i * THREADS;
             // (one unit after the other: all of them at once would take four times the registers)
             asm volatile("" : "+v"(v[i][0]), "+v"(v[i][1]), "+v"(v[i][2]), "+v"(v[i][3]));
@@ -334,13 +336,19 @@ void w8_launch_act_quant(const uint16_t* A, int64_t M, int64_t K, int8_t* Aq, fl
     const dim3 grid((unsigned)M);
     const bool wide = (K & 7) == 0 && ((uintptr_t)A & 15) == 0 && ((uintptr_t)Aq & 7) == 0;
     const int64_t units = K >> 3;
-    // few rows: as many threads per row as it has work for (one block per compute unit, latency counts); many rows:
-    // four waves per block, several blocks per compute unit
-    const bool narrow = units <= 256 * W8_ROW_UNITS && (M > 512 || units <= 256);
-    if (wide && narrow)
-        hipLaunchKernelGGL((w8_act_quant_row_kernel<ACT, 256>), grid, dim3(256), 0, stream, A, (int)units, Aq, alpha);
-    else if (wide && units <= 1024 * W8_ROW_UNITS)
-        hipLaunchKernelGGL((w8_act_quant_row_kernel<ACT, 1024>), grid, dim3(1024), 0, stream, A, (int)units, Aq, alpha);
+    // Few rows (one block per compute unit, latency counts): as many threads per row as it has units for, up to 1024, and
+    // no more units per thread than the row needs.  Many rows: four waves per block, several blocks per compute unit.
+#define W8_ROWS(THREADS_, UNITS_)                                                                                       \
+    hipLaunchKernelGGL((w8_act_quant_row_kernel<ACT, THREADS_, UNITS_>), grid, dim3(THREADS_), 0, stream, A, (int)units, Aq, alpha)
+    if (wide && units <= 256) W8_ROWS(256, 1);
+    else if (wide && M > 512 && units <= 256 * 2) W8_ROWS(256, 2);
+    else if (wide && M > 512 && units <= 256 * 4) W8_ROWS(256, 4);
+    else if (wide && M > 512 && units <= 256 * W8_ROW_UNITS) W8_ROWS(256, W8_ROW_UNITS);
+    else if (wide && units <= 512) W8_ROWS(512, 1);
+    else if (wide && units <= 1024) W8_ROWS(1024, 1);
+    else if (wide && units <= 1024 * 2) W8_ROWS(1024, 2);
+    else if (wide && units <= 1024 * W8_ROW_UNITS) W8_ROWS(1024, W8_ROW_UNITS);
+#undef W8_ROWS
     else
         hipLaunchKernelGGL(w8_act_quant_kernel<ACT>, grid, dim3(256), 0, stream, A, K, wide ? units : (int64_t)0, Aq, alpha);
 }

@@ -315,3 +315,13 @@ def test_wide_matrices_of_some_hundred_rows(M, K, N, g):
     C = from_dev_act(fq.gemm_w4a8(Aq, alpha, codes, z, t, g, torch_mod().bfloat16), "bf16")
     _, C_ref = oracle.gemm_ref_int(a_ref, alpha_ref, q_ref, z_ref, t_ref)
     _check_product(C, C_ref, "bf16", f"M={M} K={K} N={N} g={g}")
+
+
+@pytest.mark.parametrize("M", [3, 513])
+@pytest.mark.parametrize("K", [2048, 2056, 4096, 4104, 8192, 8200, 16384, 16392, 65536, 65544])
+def test_activation_quantiser_rows_at_the_edges_of_its_kernels(M, K):
+    """One to eight units of eight values per thread, 256 to 1024 threads per row, and rows beyond them."""
+    if M * K > 1 << 23:
+        M = 3
+    for dtype in ("f16", "bf16"):
+        _quantize_acts(workloads.activations(M, K, dtype, K + M), dtype)
