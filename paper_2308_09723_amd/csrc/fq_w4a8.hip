@@ -1255,8 +1255,11 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
         return p;
     }
     w8_plan p = {};
-    // More rows: the mid-M kernel (32, 48 or 64 rows per block, up to 700 rows) or the tiled one (64 or 128), whichever shape
-    // and split of K the model gives the least time.  The model was fitted (of log time, rms error 10 %) to 123 problems of
+    // More rows: the mid-M kernel (32, 48 or 64 rows per block) or the tiled one (64 or 128), whichever shape and split of K the
+    // model gives the least time; above 700 rows the mid-M kernel up to K = 10240 (and 12288 rows): narrow matrices make few
+    // tiles of 128 x 384 (823 rows of 1408 x 1552: 35).  240 products of 701 .. 2048 rows, the tiled kernel alone -> both:
+    // 1.10x on average, up to 1.9x (883 rows, 1664 x 1248 24 -> 13 us), none more than 3 % slower below that K, three of 15 above
+    // (10 % at worst); 100 of 2049 .. 12288 rows with up to 6400 columns 1.02x, none slower.  The model was fitted (of log time, rms error 10 %) to 123 problems of
     // 17 .. 2048 rows, K from 1152 to 16256, N from 1168 to 45856, in 35 shapes each:
     //   a block     mid-M: 6.7 us + iterations * the longest of 0.94 us, its vector and matrix work (0.92, 1.09 or 1.27 us for
     //               twelve waves, 0.37 more with two multiplier rows per k-block), its memory traffic at 8.1 TB/s;
@@ -1281,7 +1284,7 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
     static const double mid_work[5] = {0.0, 0.0, 0.92, 1.09, 1.27};
     static const int groups[6] = {1, 2, 3, 4, 6, 12};
     const int mt_low = M <= 32 ? 2 : 3, mt_high = M <= 32 ? 2 : (M <= 48 ? 3 : 4);
-    for (int mt = M > 48 && M <= 64 ? 4 : mt_low; M <= 700 && mt <= mt_high; ++mt) {
+    for (int mt = M > 48 && M <= 64 ? 4 : mt_low; (M <= 700 || (M <= 12288 && K <= 10240)) && mt <= mt_high; ++mt) {
         const int nblocks_m = (int)((M + mt * 16 - 1) / (mt * 16));
         const int fit = (int)(160 * 1024 / w8m_lds(mt, 1, 1));
         for (const int gp : groups) {

@@ -325,3 +325,18 @@ def test_activation_quantiser_rows_at_the_edges_of_its_kernels(M, K):
         M = 3
     for dtype in ("f16", "bf16"):
         _quantize_acts(workloads.activations(M, K, dtype, K + M), dtype)
+
+
+@pytest.mark.parametrize("M,K,N,g,split", [(701, 384, 400, 128, False), (833, 1152, 304, 32, False), (2049, 256, 144, 64, False),
+                                           (705, 10368, 272, 128, True), (801, 128, 12304, 128, False), (1030, 384, 9232, 32, False)])
+def test_more_than_700_rows_on_narrow_and_on_wide_matrices(M, K, N, g, split):
+    """Narrow matrices stay with the mid-M kernel's row blocks (the first three); K above 10240 and wide ones go to 128-row tiles,
+    with K split over the grid, an odd number of k-blocks and lower last row blocks."""
+    from paper_2308_09723_amd import fq
+    assert (fq.gemm_w4a8_workspace_bytes(M, N, K, g) > 0) == split
+    codes, z, t, q_ref, z_ref, t_ref = _quantize_weights(workloads.weights_gaussian(K, N, seed=M, outlier_prob=2e-3), g)
+    for dtype in ("f16", "bf16"):
+        Aq, alpha, a_ref, alpha_ref = _quantize_acts(workloads.activations(M, K, dtype, 3 + M), dtype)
+        C = fq.gemm_w4a8(Aq, alpha, codes, z, t, g, torch_mod().float16 if dtype == "f16" else torch_mod().bfloat16)
+        _, C_ref = oracle.gemm_ref_int(a_ref, alpha_ref, q_ref, z_ref, t_ref)
+        _check_product(from_dev_act(C, dtype), C_ref, dtype, f"M={M} K={K} N={N} g={g}")
