@@ -71,44 +71,70 @@ __global__ __launch_bounds__(256) void w8_fold_kernel(const uint16_t* __restrict
     amax[(int64_t)blockIdx.y * N + n] = m;
 }
 
-// Block = 32 columns x 8 slices of the groups (a column per thread left 48 blocks for a 12288-column matrix, each
-// thread walking every group twice: 60 us, now 9).
-__global__ __launch_bounds__(256) void w8_scales_kernel(const uint16_t* __restrict__ amax, int64_t N, int groups,
-                                                         uint8_t* __restrict__ z, uint16_t* __restrict__ tstep) {
-    __shared__ uint16_t red[8][32];
-    const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
-    const int64_t n = (int64_t)blockIdx.x * 32 + x;
+// Block = 2 LANES columns (two per thread) x SLICES slices of the groups, whose maxima stay in registers between the search
+// for the column's largest and the multipliers: 32 columns x 32 slices, or 64 x 8 for up to 32 groups.  Bound by latency and,
+// as few blocks as there are, by the tests of a multiplier.  With 32 columns x 8 slices per block, every group read twice and
+// a loop with a branch per test: traced, us: 12288 x 12288 g = 128 8.2 -> 5.1, 10240 x 6032 g = 64 10.9 -> 5.2; the whole
+// call at g = 32 1.17x on average over 20 matrices (5760 x 1312 23.8 -> 15.1).
+constexpr int W8_HELD = 8;          // groups per thread held in registers (further ones are read again)
+template <int LANES, int SLICES>
+__global__ __launch_bounds__(LANES * SLICES) void w8_scales_kernel(const uint16_t* __restrict__ amax, int64_t N, int groups,
+                                                                    uint8_t* __restrict__ z, uint16_t* __restrict__ tstep) {
+    __shared__ uint32_t red[SLICES][LANES + 1];
+    const int x = threadIdx.x % LANES, y = threadIdx.x / LANES;
+    const int64_t n = ((int64_t)blockIdx.x * LANES + x) * 2;                // N is a multiple of 16
     const bool ok = n < N;
-    uint16_t mcol = 0;
+    auto load = [&](int i) { return *reinterpret_cast<const uint32_t*>(amax + (int64_t)i * N + n); };
+    uint32_t held[W8_HELD];
+    u16x2_t m = {0, 0};
     if (ok) {
+#pragma unroll
+        for (int h = 0; h < W8_HELD; ++h) held[h] = y + SLICES * h < groups ? load(y + SLICES * h) : 0u;
+#pragma unroll
+        for (int h = 0; h < W8_HELD; ++h) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2_t, held[h]));
 #pragma unroll 4
-        for (int i = y; i < groups; i += 8) {
-            const uint16_t v = amax[(int64_t)i * N + n];
-            mcol = v > mcol ? v : mcol;
-        }
+        for (int i = y + SLICES * W8_HELD; i < groups; i += SLICES) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2_t, load(i)));
     }
-    red[y][x] = mcol;
+    red[y][x] = __builtin_bit_cast(uint32_t, m);
     __syncthreads();
     if (!ok) return;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) mcol = red[i][x] > mcol ? red[i][x] : mcol;
+#pragma unroll 8
+    for (int i = 0; i < SLICES; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2_t, red[i][x]));
     const float L = WLEVELS * (float)ZMAX;                                  // 240
-    const float two_m = 2.0f * f16_bits_to_float(mcol);
-    uint16_t tb = __half_as_ushort(__float2half_rn(__fdiv_rn(two_m, L)));   // nearest, then up if too small
-    if (__fmul_rn(L, f16_bits_to_float(tb)) < two_m) tb += 1;
-    if (y == 0) tstep[n] = tb;
-    const float t = f16_bits_to_float(tb);
-    const float r15t = t == 0.0f ? 0.0f : __fdiv_rn(1.0f, WLEVELS * t);
-#pragma unroll 4
-    for (int i = y; i < groups; i += 8) {
-        const float two_mi = 2.0f * f16_bits_to_float(amax[(int64_t)i * N + n]);
-        // an estimate of the quotient, then the exact tests on either side of it ((15 z) * t: exact)
-        int zi = (int)(two_mi * r15t);
-        zi = zi < 1 ? 1 : (zi > ZMAX ? ZMAX : zi);
-        while (zi > 1 && __fmul_rn(WLEVELS * (float)(zi - 1), t) >= two_mi) --zi;
-        while (zi < ZMAX && __fmul_rn(WLEVELS * (float)zi, t) < two_mi) ++zi;
-        z[(int64_t)i * N + n] = (uint8_t)zi;
+    float t[2], r15t[2];
+    uint32_t steps = 0;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const float two_m = 2.0f * f16_bits_to_float(m[c]);
+        uint16_t tb = __half_as_ushort(__float2half_rn(__fdiv_rn(two_m, L)));   // nearest, then up if too small
+        if (__fmul_rn(L, f16_bits_to_float(tb)) < two_m) tb += 1;
+        t[c] = f16_bits_to_float(tb);
+        r15t[c] = t[c] == 0.0f ? 0.0f : __fdiv_rn(1.0f, WLEVELS * t[c]);
+        steps |= (uint32_t)tb << (16 * c);
     }
+    if (y == 0) *reinterpret_cast<uint32_t*>(tstep + n) = steps;
+    auto store = [&](int i, uint32_t v) {
+        uint32_t out = 0;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const float two_mi = 2.0f * f16_bits_to_float((uint16_t)(v >> (16 * c)));
+            // the quotient two_mi / (15 t) cut to an integer is the multiplier, or one or two below it (the estimate's error
+            // is far below one); the tests are exact ((15 z) * t: exact)
+            int zi = (int)(two_mi * r15t[c]);
+            zi = zi < 1 ? 1 : (zi > ZMAX ? ZMAX : zi);
+            const bool one = __fmul_rn(WLEVELS * (float)zi, t[c]) < two_mi;
+            const bool two = one && __fmul_rn(WLEVELS * (float)(zi + 1), t[c]) < two_mi;
+            zi += (int)one + (int)two;
+            zi = zi > ZMAX ? ZMAX : zi;
+            out |= (uint32_t)zi << (8 * c);
+        }
+        *reinterpret_cast<uint16_t*>(z + (int64_t)i * N + n) = (uint16_t)out;
+    };
+#pragma unroll
+    for (int h = 0; h < W8_HELD; ++h)
+        if (y + SLICES * h < groups) store(y + SLICES * h, held[h]);
+#pragma unroll 1
+    for (int i = y + SLICES * W8_HELD; i < groups; i += SLICES) store(i, load(i));
 }
 
 // row of the k-block that element e of dword d of lane group j holds
@@ -1474,8 +1500,12 @@ int fq_quantize_w4a8(const void* W_f16, int64_t K, int64_t N, int group_size, vo
         hipLaunchKernelGGL(w8_fold_kernel, dim3((unsigned)((N + 255) / 256), (unsigned)groups), dim3(256), 0, s,
                            (const uint16_t*)fine, N, g / f, amax);
     }
-    hipLaunchKernelGGL(w8_scales_kernel, dim3((unsigned)((N + 31) / 32)), dim3(256), 0, s, (const uint16_t*)amax, N,
-                       groups, zscale, (uint16_t*)tstep_f16);
+    if (groups <= 32)
+        hipLaunchKernelGGL((w8_scales_kernel<32, 8>), dim3((unsigned)((N + 63) / 64)), dim3(256), 0, s, (const uint16_t*)amax, N,
+                           groups, zscale, (uint16_t*)tstep_f16);
+    else
+        hipLaunchKernelGGL((w8_scales_kernel<16, 32>), dim3((unsigned)((N + 31) / 32)), dim3(512), 0, s, (const uint16_t*)amax, N,
+                           groups, zscale, (uint16_t*)tstep_f16);
     hipLaunchKernelGGL(w8_encode_kernel, dim3((unsigned)((N + 127) / 128), (unsigned)(K / 128)), dim3(256), 0, s,
                        (const uint16_t*)W_f16, N, g, (const uint8_t*)zscale, (const uint16_t*)tstep_f16, (uint32_t*)codes);
     return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_HIP;

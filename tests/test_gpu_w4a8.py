@@ -340,3 +340,15 @@ def test_more_than_700_rows_on_narrow_and_on_wide_matrices(M, K, N, g, split):
         C = fq.gemm_w4a8(Aq, alpha, codes, z, t, g, torch_mod().float16 if dtype == "f16" else torch_mod().bfloat16)
         _, C_ref = oracle.gemm_ref_int(a_ref, alpha_ref, q_ref, z_ref, t_ref)
         _check_product(from_dev_act(C, dtype), C_ref, dtype, f"M={M} K={K} N={N} g={g}")
+
+
+@pytest.mark.parametrize("K,N,g", [(128, 16, 128), (1024, 48, 32), (1152, 80, 32), (4096, 32, 128), (8192, 16, 32), (8320, 16, 32),
+                                   (10240, 48, 32), (33 * 384, 16, 384)])
+def test_weight_quantiser_numbers_of_groups(K, N, g):
+    """1 to 320 groups per column: both block shapes of the multiplier kernel (32 and 33 groups), groups held in registers and
+    read again (256, 257), last columns past the matrix."""
+    W = workloads.weights_gaussian(K, N, seed=K + N, outlier_prob=2e-3)
+    W[: K // 2, 1] = 0
+    W[:, 2] = 0
+    W[g:, 3] = (W[g:, 3].astype(np.float32) * 2.0 ** -6).astype(np.float16)     # multipliers at their lowest
+    _quantize_weights(W, g)
