@@ -792,3 +792,14 @@ def test_gemm_row_blocks_of_the_streaming_kernel_above_256_rows(M, K, N, dtype, 
     assert f"mid-m rows=48 {shape}" in desc and _fq().gemm_workspace_bytes(M, N, K, bits, g) == 0
     assert "mid-m" not in _fq().gemm_describe(12289, N, K, bits, g)
     _gemm_case(M, K, N, dtype, bits, g, seed=8900 + M + K)
+
+
+@pytest.mark.parametrize("K,N,g", [(2048, 48, 32), (384, 48, 96), (640, 48, 160), (4480, 16, 224), (896, 16, 448), (3200, 272, 800),
+                                   (128 * 33, 16, 128 * 33), (31 * 128, 32, 31 * 32), (160 * 256, 144, 160)])
+def test_quantizer_group_abs_max_row_remainders(K, N, g):
+    """The abs-max of groups whose rows do not fill the last round of loads: 2 to 14 rows per thread and one more or less, few blocks
+    (eight rows in flight) and 256 or more (four), groups of whole 128-row blocks; the largest value in a group's last row."""
+    W = workloads.weights_gaussian(K, N, seed=g, outlier_prob=2e-3)
+    W[g - 1 :: g, 3] = np.float16(-9.0)
+    W[g - 1 :: g, 5] = np.float16(7.0)
+    assert_quantizer_parity(W, 4, g)
