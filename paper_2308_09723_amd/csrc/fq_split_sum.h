@@ -25,13 +25,13 @@ namespace fqk {
 constexpr int FQ_MOST_FUSED_SPLITS = 8;      // partial sums that a lane of the last block has in flight
 
 // Whether a block adds the splits of its tile (rows x cols, partial sums of 32 bits): not where the word in C would not be
-// aligned, nor above 96 KiB of partial sums per tile, which one block reads in 5 us and more where the sum kernel's blocks
+// aligned, nor above 80 KiB of partial sums per tile, which one block reads in 5 us and more where the sum kernel's blocks
 // share them.  Timed inside graphs, where a launch costs the host nothing, 100 products of 1 - 48 rows: 192 B - 24 KiB
-// 1.10x on average (5248 x 1920, 9 rows 9.4 -> 8.0 us), 24 - 96 KiB 1.04x (none more than 2 % slower), above 0.92x
+// 1.10x on average (5248 x 1920, 9 rows 9.4 -> 8.0 us), 24 - 80 KiB 1.04x (none more than 2 % slower), above 0.92 - 1.02x
 // (3968 x 4240, 36 rows, 162 KiB 13.2 -> 15.5; 8192 x 28672, 16 rows, 180 KiB 43.5 -> 44.9).  A call on its own also saves
 // the launch: 1024 x 1024, 4 rows 10.1 -> 6.5 us.
 inline bool fq_sums_splits(int rows, int cols, int splits, const void* C) {
-    return splits > 1 && splits <= FQ_MOST_FUSED_SPLITS && ((uintptr_t)C & 7) == 0 && (int64_t)rows * cols * 4 * splits <= 96 * 1024;
+    return splits > 1 && splits <= FQ_MOST_FUSED_SPLITS && ((uintptr_t)C & 7) == 0 && (int64_t)rows * cols * 4 * splits <= 80 * 1024;
 }
 
 // Bits of the 64-bit word: 0xffa5 | 40 bits that count the calls of the process | 8 bits that count blocks.
