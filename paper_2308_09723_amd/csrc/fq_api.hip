@@ -357,7 +357,8 @@ int fq_gemm_describe(int64_t M, int64_t N, int64_t K, int bits, int group_size, 
     if (n < 0 || (size_t)n >= buf_bytes) return FQ_OK;
     const fq_gemm_plan f = fq_plan_gemm(M, N, K, bits, g, FQ_F16);
     if (streams)
-        snprintf(buf + n, buf_bytes - n, " mid-m rows=%d gp=%d kw=%d waves=%d", 16 * p.mt, p.gp, p.kw, p.waves);
+        snprintf(buf + n, buf_bytes - n, "%s mid-m rows=%d gp=%d kw=%d waves=%d", p.nt == 1 ? " cols=16" : "", 16 * p.mt, p.gp, p.kw,
+                 p.waves);
     else if (low || fq_flexible(p))
         snprintf(buf + n, buf_bytes - n, " rows=%d cols=%d", 16 * p.mt, p.waves * p.nt * FQ_NTILE);
     else if (below_class(f) || fq_flexible(f))

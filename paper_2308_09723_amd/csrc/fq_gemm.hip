@@ -122,6 +122,7 @@ static double fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int 
                 best = t;
                 p->kind = 2;
                 p->mt = mt;
+                p->nt = MMA_NT;
                 p->gp = gp;
                 p->kw = kw;
                 p->waves = gp * kw;
@@ -130,6 +131,57 @@ static double fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int 
         }
     }
     return best;
+}
+
+// Waves of 16 columns instead of 48 (nt = 1), without a split of K, in place of the plan above: 48 columns leave half the chip
+// idle on matrices of less than 12288 of them, 16 fill it in one round of blocks.  Both are weighed by a model
+// of either width, fitted together (of log time, rms error 9 %) to 360 problems of 17 .. 48 rows, 1024 .. 17600 columns, in 30
+// shapes each: a block takes its start and end, and per iteration a latency, its waves' vector and matrix work, and memory
+// traffic, which add up.  The narrow waves have to win by 7 %, by 20 % where they replace a split (the model ranks those
+// worse; scratch only shrinks).  Of those problems 157 change, 1.20x faster on average, one more than 3 % slower (3.4 %);
+// 2176 x 2336, 28 rows, g = 32 11.3 -> 7.7 us.  From 12000 columns on 9 of 34 became slower.
+static double fq_mid_us(int nt, int mt, int KB, int ngroups, int64_t M, int64_t N, int bits, int sr, int gp, int kw, int splits, int ncu) {
+    static const double c[2][9] = {      // work of 32 and 48 rows, 8- and 3-bit codes' share of it, a further scale row; us
+        {0.331, 0.566, 0.542, 1.007, 0.050, 0.364, 4.89, 3.27, 0.50},      // per iteration, per block, more for a second one
+        {0.927, 1.325, 0.615, 1.069, 0.253, 0.342, 6.46, 10.0, 0.39}};     // beside it, ragged end
+    const double* x = c[nt == 1 ? 0 : 1];
+    const int waves = gp * kw, blocks = (ngroups + gp - 1) / gp * splits, SB = (KB + kw - 1) / kw, n_it = (SB + splits - 1) / splits;
+    const int tile = mt * 16 * fq_kblk(bits) * 2, act = (mt == 3 ? 2 : 3) * kw * tile, red = waves * nt * mt * 1024;
+    int resident = 160 * 1024 / (act > red ? act : red);
+    resident = resident < 24 / waves ? resident : 24 / waves;
+    const int slots = ncu * (resident > 1 ? resident : 1);
+    const double share = (double)blocks / ncu, together = share < 1.0 ? 1.0 : (share < (double)slots / ncu ? share : (double)slots / ncu);
+    const double work = x[mt == 2 ? 0 : 1] * (bits == 8 ? x[2] : (bits == 3 ? x[3] : 1.0)) + x[4] * (sr - 1);
+    const double bytes = waves * (nt * 64.0 * fq_rec_bytes(bits) + nt * 32.0 * sr);
+    double t = x[6] + x[7] * (together - 1.0) +
+               n_it * (x[5] + work * ((waves + 3) / 4) * together * (1.0 / 3.0) + (blocks < slots ? blocks : slots) * bytes * (1.0 / 16e6));
+    if (blocks > slots) {
+        const double full = (double)((blocks + slots - 1) / slots), part = (double)blocks / slots + x[8];
+        t *= part < full ? part : full;
+    }
+    return splits > 1 ? t + 1.9 + 2.0 * splits * (double)M * (double)N * (4.0 / 5.6e6) : t;
+}
+
+static void fq_plan_mid_narrow(int64_t M, int64_t N, int64_t K, int bits, int g, int ncu, fq_gemm_plan* p) {
+    if (N > 12000) return;
+    const int mt = p->mt, KB = (int)(K / fq_kblk(bits)), sr = fq_scale_rows(bits, g), ntiles = (int)(N / FQ_NTILE);
+    const fq_mid_model model(mt, KB, bits, sr);
+    double best = (p->splits > 1 ? 0.80 : 0.93) *
+                  fq_mid_us(MMA_NT, mt, KB, (ntiles + MMA_NT - 1) / MMA_NT, M, N, bits, sr, p->gp, p->kw, p->splits, ncu);
+    static const int groups[6] = {1, 2, 3, 4, 6, 12};
+    for (const int gp : groups) {
+        const int kw = model.workers(gp);
+        if ((ntiles + gp - 1) / gp > ncu) continue;      // (a second round: 8-bit codes on 8400 columns 0.74 - 0.93)
+        const double t = fq_mid_us(1, mt, KB, ntiles, M, N, bits, sr, gp, kw, 1, ncu);
+        if (t < best) {
+            best = t;
+            p->nt = 1;
+            p->gp = gp;
+            p->kw = kw;
+            p->waves = gp * kw;
+            p->splits = 1;
+        }
+    }
 }
 
 // The streaming kernel or the tiled one (plan t, t_tiled by its model) for 17 .. 48 rows.  Measured in turn on 23
@@ -550,7 +602,10 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
         if (M <= 48) {
             fq_gemm_plan mid = {};
             const double t_mid = fq_plan_mid(M, N, K, bits, g, ncu, &mid);
-            if (fq_mid_pays(t_mid, p, best, M, N, bits, g)) return mid;
+            if (fq_mid_pays(t_mid, p, best, M, N, bits, g)) {
+                fq_plan_mid_narrow(M, N, K, bits, g, ncu, &mid);
+                return mid;
+            }
         }
         best = fq_plan_flexible(M, N, K, bits, g, act_dtype, ncu, best, &p);
         if (M > 48 && K <= FQ_ROW_BLOCKS_MOST_K && (M <= 256 || (N < 8192 && M <= 48 * 256))) {

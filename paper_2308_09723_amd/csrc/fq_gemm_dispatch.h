@@ -134,7 +134,7 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
     float* partial = (float*)workspace;
     // The streaming kernels add a split of K themselves where a tile's partial sums are few enough for one block; not where
     // the ticket in C would be misaligned.
-    const int tile_cols = plan.gp * FQ_NTILE * (plan.kind == 0 ? SKINNY_VARIANTS[plan.variant].nt : MMA_NT);
+    const int tile_cols = plan.gp * FQ_NTILE * (plan.kind == 0 ? SKINNY_VARIANTS[plan.variant].nt : plan.nt);
     const bool sums = plan.kind != 1 && fq_sums_splits((int)M, tile_cols, plan.splits, C);
     const uint64_t tag = sums ? fq_next_tag() : 0;
     if (plan.kind == 0) {
@@ -147,8 +147,13 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
         }
         if (st != FQ_OK) return st;
     } else if (plan.kind == 2) {
-        const int st = plan.mt == 2 ? launch_mid<ACT, BITS, MMA_NT, 2, 12>(A, M, N, K, codes, scales, g, C, partial, plan, tag, stream)
-                                    : launch_mid<ACT, BITS, MMA_NT, 3, 12>(A, M, N, K, codes, scales, g, C, partial, plan, tag, stream);
+        int st;
+#define FQ_MID_LAUNCH(NT_, MT_) st = launch_mid<ACT, BITS, NT_, MT_, 12>(A, M, N, K, codes, scales, g, C, partial, plan, tag, stream)
+        if (plan.nt == 1 && plan.mt == 2) FQ_MID_LAUNCH(1, 2);
+        else if (plan.nt == 1) FQ_MID_LAUNCH(1, 3);
+        else if (plan.mt == 2) FQ_MID_LAUNCH(MMA_NT, 2);
+        else FQ_MID_LAUNCH(MMA_NT, 3);
+#undef FQ_MID_LAUNCH
         if (st != FQ_OK) return st;
     } else if (plan.kind == 3) {
         // row blocks of the mid-M kernel: as few as 48 rows allow, of nearly equal height, all without a bias

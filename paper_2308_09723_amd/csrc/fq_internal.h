@@ -33,7 +33,7 @@ uint64_t fq_next_tag();
 struct fq_gemm_plan {
     int kind;      // 0 = skinny (M <= 16), 1 = tiled, 2 = mid-M streaming (17 <= M <= 48), 3 = its row blocks (M > 48)
     int mt;        // row tiles of 16 per block (tiled and mid-M kernel)
-    int nt;        // tiled kernel: column tiles of 16 per wave (3, or 2 in the flexible shapes)
+    int nt;        // column tiles of 16 per wave: tiled kernel 3, or 2 in the flexible shapes; mid-M kernel 3 or 1
     int waves;     // waves per block
     int variant;   // small-M kernel: which compiled variant (NT, ring depth, register class)
     int gp, kw;    // small-M and mid-M kernel: column groups x k-workers per block

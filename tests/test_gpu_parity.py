@@ -803,3 +803,17 @@ def test_quantizer_group_abs_max_row_remainders(K, N, g):
     W[g - 1 :: g, 3] = np.float16(-9.0)
     W[g - 1 :: g, 5] = np.float16(7.0)
     assert_quantizer_parity(W, 4, g)
+
+
+@pytest.mark.parametrize("M,K,N,bits,g,dtype,narrow", [
+    (17, 1024, 1040, 4, 128, "f16", True), (32, 1280, 4032, 4, 0, "bf16", True), (33, 1920, 5504, 4, 32, "bf16", True),
+    (48, 1408, 2768, 8, 32, "f16", True), (30, 1152, 336, 3, 64, "bf16", True), (20, 128, 16, 4, 128, "bf16", True),
+    (24, 640, 8208, 4, 64, "f16", True), (41, 2048, 528, 8, 0, "bf16", True), (18, 1536, 3088, 4, 96, "bf16", True),
+    (17, 640, 12304, 4, 64, "bf16", False), (48, 384, 12320, 3, 128, "f16", False), (33, 1536, 8480, 8, 64, "bf16", False),
+    (40, 512, 12304, 4, 32, "f16", False), (21, 5120, 4400, 4, 64, "f16", False), (48, 10240, 2064, 8, 128, "bf16", False)])
+def test_gemm_mid_rows_16_and_48_columns_per_wave(M, K, N, bits, g, dtype, narrow):
+    """17 .. 48 rows: waves of 16 columns on matrices that they spread over more of the chip, of 48 on wide ones and where K is
+    split over the grid (the last two), each with a last block that is not full and every number of scale rows per k-block."""
+    desc = _fq().gemm_describe(M, N, K, bits, g)
+    assert "mid-m" in desc and ("cols=16" in desc) == narrow, desc
+    _gemm_case(M, K, N, dtype, bits, g, seed=M + K + N)
