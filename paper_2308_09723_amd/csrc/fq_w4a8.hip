@@ -905,26 +905,26 @@ __global__ __launch_bounds__(MAXW * 64) void fq_w4a8_skinny_kernel(
 // is split, too), and blocks of 48 GP columns cut a small output finer.  12288 x 36864, g = 128, tiled kernel ->
 // this one, us: M = 17 55 -> 40 (5.9 TB/s of weights), M = 32 55 -> 41, M = 64 66 -> 46; 8192 x 8192, M = 128 30 -> 24.
 // ------------------------------------------------------------------------------------------------------
-constexpr int W8M_NT = 3, W8M_DEPTH = 3, W8M_MAXW = 12;
+constexpr int W8M_DEPTH = 3, W8M_MAXW = 12;
 
-template <int ZR>
+template <int NT, int ZR>
 struct W8MStage {
-    u32x4 wq[W8M_NT];
-    uint32_t zq[ZR][W8M_NT];
+    u32x4 wq[NT];
+    uint32_t zq[ZR][NT];
 };
 
-template <int MT, int ZR, int OUT>
+template <int NT, int MT, int ZR, int OUT>
 __global__ __launch_bounds__(W8M_MAXW * 64) void fq_w4a8_mid_kernel(
     const int8_t* __restrict__ Aq, const float* __restrict__ alpha, const u32x4* __restrict__ codes,
     const uint8_t* __restrict__ z, const uint16_t* __restrict__ tstep, uint16_t* __restrict__ C,
     int32_t* __restrict__ partial, int M, int N, int K, uint32_t g32, uint32_t g32_recip, int gp, int kw_n, int nblocks_m,
     int grid_splits, uint64_t tag) {
-    constexpr int NT = W8M_NT, DEPTH = W8M_DEPTH;
+    constexpr int DEPTH = W8M_DEPTH;
     constexpr int TILE = 16 * MT * 8;               // 16-byte units of one k-worker's activation tile
     constexpr int NI = TILE / 64;                   // wave-level direct loads of such a tile
     constexpr int NW = NT + ZR * NT;                // vector loads of one stage
     static_assert((DEPTH - 1) * NW < 64, "wait counter range");
-    typedef W8MStage<ZR> Stage;
+    typedef W8MStage<NT, ZR> Stage;
     extern __shared__ u32x4 lds[];   // three activation buffers [kw_n][TILE]; later the reduction
 
     const int tid = threadIdx.x;
@@ -1156,15 +1156,16 @@ struct w8_plan {
     int mt, splits, kb_per_split, nblocks_n, nblocks_m;
     int small, gp, kw, au;      // small-M kernel (M <= 16): column groups x k-workers per block, activation units per lane
     int mid;                    // mid-M kernel (gp, kw as above, mt row tiles per block)
+    int nt;                     // column tiles per wave of either: 3 or 1
 };
 
-constexpr int W8S_NT = 3, W8S_MAXW = 12;   // the small-M kernel that is compiled in
+constexpr int W8S_NT = 3, W8S_MAXW = 12;   // the small-M kernel (and NT = 1)
 // ring depth: three stages where the registers allow it without spills (one multiplier row per k-block and one
 // activation unit per lane: 164 registers; measured 4 - 6 % faster than two on the OPT-175B shapes), else two
 constexpr int w8s_depth(int zr, int au) { return zr == 1 && au == 1 ? 3 : 2; }
 
-constexpr size_t w8m_lds(int mt, int gp, int kw) {
-    const size_t act = (size_t)3 * kw * mt * 16 * 8 * 16, red = (size_t)gp * kw * mt * W8M_NT * 64 * 16;
+constexpr size_t w8m_lds(int nt, int mt, int gp, int kw) {
+    const size_t act = (size_t)3 * kw * mt * 16 * 8 * 16, red = (size_t)gp * kw * mt * nt * 64 * 16;
     return act > red ? act : red;
 }
 
@@ -1178,6 +1179,7 @@ w8_plan w8_plan_small_by_fill(int64_t M, int64_t N, int64_t K) {
     const int ngroups = (int)((N / FQ_NTILE + W8S_NT - 1) / W8S_NT);
     p.small = 1;
     p.mt = 1;
+    p.nt = W8S_NT;
     p.nblocks_m = 1;
     double best = -1.0;
     for (int gp = 1; gp <= W8S_MAXW; ++gp) {
@@ -1226,11 +1228,79 @@ int w8_splits_by_fill(int64_t M, int64_t N, int64_t K) {
     return (KB + kbs - 1) / kbs;
 }
 
+// Waves of 16 columns instead of 48 (p.nt = 1), without a split of K, in place of a plan of the small-M or mid-M kernel: on narrow
+// matrices 48 columns leave half the chip idle, 16 fill it in one round of blocks.  Both widths are weighed by models of their
+// own (not the plan's: fitted together, of log time, rms error 6 % up to 16 rows and 10 % above, to 150 problems each of 1024 ..
+// 16000 columns in 20 shapes): a block takes its start and end, and per iteration a latency, its waves' vector and matrix work
+// and memory traffic, which add up.  The narrow waves have to win by 7 % (15 % in place of a split) up to 16 rows; above, by
+// 10 % (15 % above 64 rows), up to 8192 columns (8704 columns, 30 rows 6.8 -> 7.4 us) and not in place of a split (the models rank
+// those worse).  Scratch only shrinks.  Those problems: 1.08x on average up to 16 rows (65 change, one 3 % slower), 1.06x above.
+double w8_width_us(const w8_plan& p, int64_t M, int64_t N, int KB, int zr, int ncu) {
+    // work per iteration of twelve waves, more per row tile beyond two, for a second row of multipliers, for a second
+    // activation unit; latency; a block beside it, a second one on the compute unit; ragged end
+    static const double c[4][8] = {{0.476, 0.0, 0.109, 0.361, 0.026, 4.12, 1.18, 0.0}, {1.025, 0.0, 0.142, 0.236, 0.001, 4.58, 10.0, 0.21},
+                                   {0.028, 0.081, 0.170, 0.0, 0.392, 5.58, 2.53, 0.41}, {0.482, 0.146, 0.272, 0.0, 0.321, 7.37, 9.14, 0.56}};
+    const double* x = c[2 * p.mid + (p.nt == 1 ? 0 : 1)];
+    const int waves = p.gp * p.kw, SB = (KB + p.kw - 1) / p.kw, n_it = (SB + p.splits - 1) / p.splits;
+    const size_t act = (size_t)2 * p.kw * W8S_KC * W8S_PITCH * 16, red = (size_t)waves * p.nt * 1024;
+    const size_t lds = p.mid ? w8m_lds(p.nt, p.mt, p.gp, p.kw) : (act > red ? act : red);
+    int resident = (int)(160 * 1024 / lds);
+    resident = resident < 24 / waves ? resident : 24 / waves;
+    const double slots = (double)ncu * (resident > 1 ? resident : 1), blocks = (double)p.nblocks_n * p.nblocks_m * p.splits;
+    const double at_once = blocks < slots ? blocks : slots, together = at_once > ncu ? at_once / ncu : 1.0;
+    const double work = x[0] + (p.mid ? x[1] * (p.mt - 2) : x[3] * (p.au - 1)) + x[2] * (zr - 1);
+    const double bytes = waves * p.nt * (1024.0 + 16.0 * zr) + (p.mid ? 0.0 : (double)M * p.kw * 128.0);
+    double t = x[5] + x[6] * (together - 1.0) +
+               n_it * (x[4] + work * ((waves + 3) / 4) * together * (1.0 / 3.0) + at_once * bytes * (p.mid ? 1.0 / 18.6e6 : 1.0 / 27e6));
+    if (blocks > slots) {
+        const double full = ceil(blocks / slots), part = blocks / slots + x[7];
+        t *= part < full ? part : full;
+    }
+    if (p.splits > 1) t += (p.mid ? 1.9 : 1.4) + 2.0 * p.splits * (double)M * (double)N * (p.mid ? 4.0 / 7e6 : 4.0 / 1.62e6);
+    return t;
+}
+
+w8_plan w8_narrow(const w8_plan& wide, int64_t M, int64_t N, int64_t K, int g) {
+    if (wide.mid ? N > 8192 || wide.splits > 1 : !wide.small) return wide;
+    const int ncu = fq_cu_count(), KB = (int)(K / 128), zr = g % 128 == 0 ? 1 : 2, ntiles = (int)(N / FQ_NTILE);
+    const double margin = wide.mid ? (M > 64 ? 0.85 : 0.90) : (wide.splits > 1 ? 0.85 : 0.93);
+    double best = margin * w8_width_us(wide, M, N, KB, zr, ncu);
+    w8_plan chosen = wide;
+    static const int groups[6] = {1, 2, 3, 4, 6, 12}, tiles[2] = {3, 4};
+    for (int m = 0; m < 2; ++m) {
+        w8_plan p = wide;
+        p.nt = 1;
+        p.splits = 1;
+        if (M > 64) {                                   // 48 and 64 rows per block
+            p.mt = tiles[m];
+            p.nblocks_m = (int)((M + p.mt * 16 - 1) / (p.mt * 16));
+        } else if (m > 0) {
+            break;
+        }
+        const int fit = p.mid ? (int)(160 * 1024 / w8m_lds(1, p.mt, 1, 1)) : 12;
+        for (const int gp : groups) {
+            const int need = (int)M * W8S_KC;
+            p.gp = gp;
+            p.kw = 12 / gp < fit ? 12 / gp : fit;
+            if (p.kw > KB) p.kw = KB;
+            p.au = p.mid ? 0 : (need <= 64 * gp ? 1 : (need <= 128 * gp ? 2 : 0));
+            p.nblocks_n = (ntiles + gp - 1) / gp;
+            if ((!p.mid && p.au == 0) || (int64_t)p.nblocks_n * p.nblocks_m > ncu) continue;
+            const double t = w8_width_us(p, M, N, KB, zr, ncu);
+            if (t < best) {
+                best = t;
+                chosen = p;
+            }
+        }
+    }
+    return chosen;
+}
+
 // The plan with the least time by the models below.  None splits K into more slabs than filling the chip alone would take
 // (the two functions above): fq_gemm_w4a8_workspace_bytes named those slabs before there were models, and a call for which
 // a workspace of that size, or none, was enough must not be refused.  Without that limit the models ask for more in 0.4 % of
 // shapes (470 rows, 14848 x 15296: 86 MB instead of none).
-w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
+w8_plan w8_plan_wide(int64_t M, int64_t N, int64_t K, int g) {
     const int ncu = fq_cu_count();
     const double share = 1.0 / ncu;
     const int ntiles = (int)(N / FQ_NTILE);
@@ -1295,7 +1365,7 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
     // Against the tiled kernel alone (32, 64 or 128 rows, K split until 192 tiles): 0.76 of the time on average inside
     // graphs, never more than 3 % slower; 204 others, called one after the other: 1.38x faster on average, 10 more than 3 % slower
     // (14 % at worst: K of 10000 and more, or fewer splits than the former rule's); 12288 x 36864 us: M = 17 55 -> 40, M = 64 66 -> 46; 2816 x 5184, M = 95 22 -> 10.
-    const int ngroups = (ntiles + W8M_NT - 1) / W8M_NT;
+    const int ngroups = (ntiles + 2) / 3;
     const int most = w8_splits_by_fill(M, N, K);
     double best = 1e30;
     auto launch_us = [&](int64_t blocks, double block_us, int splits) {
@@ -1312,7 +1382,7 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
     const int mt_low = M <= 32 ? 2 : 3, mt_high = M <= 32 ? 2 : (M <= 48 ? 3 : 4);
     for (int mt = M > 48 && M <= 64 ? 4 : mt_low; (M <= 700 || (M <= 12288 && K <= 10240)) && mt <= mt_high; ++mt) {
         const int nblocks_m = (int)((M + mt * 16 - 1) / (mt * 16));
-        const int fit = (int)(160 * 1024 / w8m_lds(mt, 1, 1));
+        const int fit = (int)(160 * 1024 / w8m_lds(3, mt, 1, 1));
         for (const int gp : groups) {
             int kw = W8M_MAXW / gp;
             kw = kw < fit ? kw : fit;
@@ -1332,6 +1402,7 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
                 if (t < best - 1e-9) {
                     best = t;
                     p.mid = 1;
+                    p.nt = 3;
                     p.mt = mt;
                     p.gp = gp;
                     p.kw = kw;
@@ -1367,6 +1438,12 @@ w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
     return p;
 }
 
+// (Up to 16 rows matrices of up to 64 column tiles keep their plan: callers and tests take those to need scratch.)
+w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
+    const w8_plan p = w8_plan_wide(M, N, K, g);
+    return M <= 16 && 4 * (N / FQ_NTILE) <= fq_cu_count() ? p : w8_narrow(p, M, N, K, g);
+}
+
 size_t w8_partial_bytes(const w8_plan& p, int64_t M, int64_t N) {
     return p.splits > 1 ? (size_t)p.splits * (size_t)M * (size_t)N * sizeof(int32_t) : 0;
 }
@@ -1396,28 +1473,28 @@ void w8_launch(const w8_plan& p, int g, const int8_t* Aq, const float* alpha, co
 #undef W8_GO
 }
 
-template <int OUT, int ZR, int AU>
+template <int OUT, int NT, int ZR, int AU>
 int w8_launch_small(const w8_plan& p, int g, const int8_t* Aq, const float* alpha, const void* codes, const uint8_t* z,
                     const void* tstep, void* C, int32_t* partial, int64_t M, int64_t N, int64_t K, uint64_t tag, hipStream_t stream) {
     const size_t lds_act = (size_t)2 * p.kw * W8S_KC * W8S_PITCH * 16;
-    const size_t lds_red = (size_t)p.gp * p.kw * W8S_NT * 64 * 16;
+    const size_t lds_red = (size_t)p.gp * p.kw * NT * 64 * 16;
     const size_t lds = lds_act > lds_red ? lds_act : lds_red;       // at most 36 KiB
     const uint32_t g32 = (uint32_t)(g / 32);
     const uint32_t g32_recip = (uint32_t)((((uint64_t)1 << 32) + g32 - 1) / g32);   // unused when g32 == 1
-    hipLaunchKernelGGL((fq_w4a8_skinny_kernel<W8S_NT, w8s_depth(ZR, AU), ZR, W8S_MAXW, AU, OUT>),
+    hipLaunchKernelGGL((fq_w4a8_skinny_kernel<NT, w8s_depth(ZR, AU), ZR, W8S_MAXW, AU, OUT>),
                        dim3((unsigned)(p.nblocks_n * p.splits)), dim3((unsigned)(p.gp * p.kw * 64)), lds, stream, Aq,
                        alpha, (const u32x4*)codes, z, (const uint16_t*)tstep, (uint16_t*)C, partial, (int)M, (int)N,
                        (int)K, g32, g32_recip, p.gp, p.kw, p.splits, tag);
     return FQ_OK;
 }
 
-template <int MT, int ZR, int OUT>
+template <int NT, int MT, int ZR, int OUT>
 int w8_launch_mid(const w8_plan& p, int g, const int8_t* Aq, const float* alpha, const void* codes, const uint8_t* z,
                   const void* tstep, void* C, int32_t* partial, int64_t M, int64_t N, int64_t K, uint64_t tag, hipStream_t stream) {
-    const size_t lds = w8m_lds(MT, p.gp, p.kw);
+    const size_t lds = w8m_lds(NT, MT, p.gp, p.kw);
     const uint32_t g32 = (uint32_t)(g / 32);
     const uint32_t g32_recip = (uint32_t)((((uint64_t)1 << 32) + g32 - 1) / g32);   // unused when g32 == 1
-    auto kern = fq_w4a8_mid_kernel<MT, ZR, OUT>;
+    auto kern = fq_w4a8_mid_kernel<NT, MT, ZR, OUT>;
     if (lds > 160 * 1024 || p.gp * p.kw > W8M_MAXW) return FQ_ERR_UNSUPPORTED;
     if (lds > 65536) {
         static std::atomic<uint64_t> raised;
@@ -1434,25 +1511,40 @@ int w8_gemm(const w8_plan& p, const int8_t* Aq, const float* alpha, int64_t M, i
             const uint8_t* z, const void* tstep, int g, void* C, void* workspace, hipStream_t stream) {
     int32_t* partial = (int32_t*)workspace;
     // the small-M and mid-M kernels add a split of K themselves where a tile's sums are few
-    const bool sums = (p.mid || p.small) && fq_sums_splits(M < p.mt * 16 ? (int)M : p.mt * 16, p.gp * W8M_NT * FQ_NTILE, p.splits, C);
+    const bool sums = (p.mid || p.small) && fq_sums_splits(M < p.mt * 16 ? (int)M : p.mt * 16, p.gp * p.nt * FQ_NTILE, p.splits, C);
     const uint64_t tag = sums ? fq_next_tag() : 0;
     if (p.mid) {
         const bool zr1 = g % 128 == 0;
         int st;
-#define W8_MID(MT_)                                                                                                   \
-    st = zr1 ? w8_launch_mid<MT_, 1, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, tag, stream)              \
-             : w8_launch_mid<MT_, 2, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, tag, stream)
-        if (p.mt == 2) W8_MID(2);
-        else if (p.mt == 3) W8_MID(3);
-        else W8_MID(4);
+#define W8_MID(NT_, MT_)                                                                                              \
+    st = zr1 ? w8_launch_mid<NT_, MT_, 1, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, tag, stream)    \
+             : w8_launch_mid<NT_, MT_, 2, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, tag, stream)
+        if (p.nt == 1) {
+            if (p.mt == 2) W8_MID(1, 2);
+            else if (p.mt == 3) W8_MID(1, 3);
+            else W8_MID(1, 4);
+        } else {
+            if (p.mt == 2) W8_MID(3, 2);
+            else if (p.mt == 3) W8_MID(3, 3);
+            else W8_MID(3, 4);
+        }
 #undef W8_MID
         if (st != FQ_OK) return st;
     } else if (p.small) {
         const bool zr1 = g % 128 == 0;
-        if (zr1 && p.au == 1) w8_launch_small<OUT, 1, 1>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, tag, stream);
-        else if (zr1) w8_launch_small<OUT, 1, 2>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, tag, stream);
-        else if (p.au == 1) w8_launch_small<OUT, 2, 1>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, tag, stream);
-        else w8_launch_small<OUT, 2, 2>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, tag, stream);
+#define W8_SMALL(NT_, ZR_, AU_) w8_launch_small<OUT, NT_, ZR_, AU_>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, tag, stream)
+        if (p.nt == 1) {
+            if (zr1 && p.au == 1) W8_SMALL(1, 1, 1);
+            else if (zr1) W8_SMALL(1, 1, 2);
+            else if (p.au == 1) W8_SMALL(1, 2, 1);
+            else W8_SMALL(1, 2, 2);
+        } else {
+            if (zr1 && p.au == 1) W8_SMALL(W8S_NT, 1, 1);
+            else if (zr1) W8_SMALL(W8S_NT, 1, 2);
+            else if (p.au == 1) W8_SMALL(W8S_NT, 2, 1);
+            else W8_SMALL(W8S_NT, 2, 2);
+        }
+#undef W8_SMALL
     } else
     switch (p.mt) {
         case 4: w8_launch<4, OUT>(p, g, Aq, alpha, codes, z, tstep, C, partial, M, N, K, stream); break;

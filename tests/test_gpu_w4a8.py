@@ -352,3 +352,22 @@ def test_weight_quantiser_numbers_of_groups(K, N, g):
     W[:, 2] = 0
     W[g:, 3] = (W[g:, 3].astype(np.float32) * 2.0 ** -6).astype(np.float16)     # multipliers at their lowest
     _quantize_weights(W, g)
+
+
+@pytest.mark.parametrize("M,K,N,g", [(1, 1152, 1040, 128), (16, 1024, 1552, 32), (9, 2304, 2064, 96), (5, 128, 4112, 128), (3, 384, 8208, 64),
+                                     (17, 1024, 1040, 128), (33, 1152, 1552, 32), (48, 384, 4112, 64), (64, 640, 2064, 128),
+                                     (20, 128, 16, 32), (100, 1152, 528, 64), (129, 256, 272, 128)])
+def test_waves_of_16_columns(M, K, N, g):
+    """The integer path's streaming kernels with 16 columns per wave, which narrow matrices take: no scratch, last blocks that are
+    not full, one to four row tiles and several row blocks, both numbers of multiplier rows, fewer k-blocks than k-workers."""
+    from paper_2308_09723_amd import fq
+    torch = torch_mod()
+    assert fq.gemm_w4a8_workspace_bytes(M, N, K, g) == 0
+    codes, z, t, q_ref, z_ref, t_ref = _quantize_weights(workloads.weights_gaussian(K, N, seed=500 + M, outlier_prob=2e-3), g)
+    for dtype in ("f16", "bf16"):
+        Aq, alpha, a_ref, alpha_ref = _quantize_acts(workloads.activations(M, K, dtype, 510 + M), dtype)
+        out = torch.full((M + 1, N), 7.0, dtype=torch.float16 if dtype == "f16" else torch.bfloat16, device="cuda")
+        fq.gemm_w4a8(Aq, alpha, codes, z, t, g, out.dtype, out=out[:M])
+        _, C_ref = oracle.gemm_ref_int(a_ref, alpha_ref, q_ref, z_ref, t_ref)
+        _check_product(from_dev_act(out[:M], dtype), C_ref, dtype, f"M={M} K={K} N={N} g={g}")
+        assert bool((out[M] == 7.0).all())
