@@ -140,12 +140,13 @@ static double fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int 
 // traffic, which add up.  The narrow waves have to win by 7 %, by 20 % where they replace a split (the model ranks those
 // worse; scratch only shrinks).  Of those problems 157 change, 1.20x faster on average, one more than 3 % slower (3.4 %);
 // 2176 x 2336, 28 rows, g = 32 11.3 -> 7.7 us.  From 12000 columns on 9 of 34 became slower.
-static double fq_mid_us(int nt, int mt, int KB, int ngroups, int64_t M, int64_t N, int bits, int sr, int gp, int kw, int splits, int ncu) {
+static double fq_mid_us(int nt, int mt, int KB, int ngroups, int row_blocks, int64_t M, int64_t N, int bits, int sr, int gp, int kw,
+                        int splits, int ncu) {
     static const double c[2][9] = {      // work of 32 and 48 rows, 8- and 3-bit codes' share of it, a further scale row; us
         {0.331, 0.566, 0.542, 1.007, 0.050, 0.364, 4.89, 3.27, 0.50},      // per iteration, per block, more for a second one
         {0.927, 1.325, 0.615, 1.069, 0.253, 0.342, 6.46, 10.0, 0.39}};     // beside it, ragged end
     const double* x = c[nt == 1 ? 0 : 1];
-    const int waves = gp * kw, blocks = (ngroups + gp - 1) / gp * splits, SB = (KB + kw - 1) / kw, n_it = (SB + splits - 1) / splits;
+    const int waves = gp * kw, blocks = (ngroups + gp - 1) / gp * row_blocks * splits, SB = (KB + kw - 1) / kw, n_it = (SB + splits - 1) / splits;
     const int tile = mt * 16 * fq_kblk(bits) * 2, act = (mt == 3 ? 2 : 3) * kw * tile, red = waves * nt * mt * 1024;
     int resident = 160 * 1024 / (act > red ? act : red);
     resident = resident < 24 / waves ? resident : 24 / waves;
@@ -167,12 +168,12 @@ static void fq_plan_mid_narrow(int64_t M, int64_t N, int64_t K, int bits, int g,
     const int mt = p->mt, KB = (int)(K / fq_kblk(bits)), sr = fq_scale_rows(bits, g), ntiles = (int)(N / FQ_NTILE);
     const fq_mid_model model(mt, KB, bits, sr);
     double best = (p->splits > 1 ? 0.80 : 0.93) *
-                  fq_mid_us(MMA_NT, mt, KB, (ntiles + MMA_NT - 1) / MMA_NT, M, N, bits, sr, p->gp, p->kw, p->splits, ncu);
+                  fq_mid_us(MMA_NT, mt, KB, (ntiles + MMA_NT - 1) / MMA_NT, 1, M, N, bits, sr, p->gp, p->kw, p->splits, ncu);
     static const int groups[6] = {1, 2, 3, 4, 6, 12};
     for (const int gp : groups) {
         const int kw = model.workers(gp);
         if ((ntiles + gp - 1) / gp > ncu) continue;      // (a second round: 8-bit codes on 8400 columns 0.74 - 0.93)
-        const double t = fq_mid_us(1, mt, KB, ntiles, M, N, bits, sr, gp, kw, 1, ncu);
+        const double t = fq_mid_us(1, mt, KB, ntiles, 1, M, N, bits, sr, gp, kw, 1, ncu);
         if (t < best) {
             best = t;
             p->nt = 1;
@@ -180,6 +181,40 @@ static void fq_plan_mid_narrow(int64_t M, int64_t N, int64_t K, int bits, int g,
             p->kw = kw;
             p->waves = gp * kw;
             p->splits = 1;
+        }
+    }
+}
+
+// Row blocks of the mid-M kernel (kind 3) with 16 columns per wave, for 49 .. 256 rows on less than 8192 columns: in one round of
+// blocks, without a split, where the model above puts them below the present plan's time (best, by its own model).  A few dozen
+// blocks of the other shapes leave most of the chip idle there, or pay for a split's second launch.  Chosen by margin: 150 products
+// of 49 .. 400 rows (in graphs, against the plans without it) gave 1.015x, 1.035x, 1.053x at 0.8, 0.9, 1.0 of that time,
+// none slower; 1.065x at 1.1, but three slower (0.86x at worst).  150 products of 49 .. 256 rows twice, each side timed first
+// once: 1.10x on average both times; of those it changes by more than 3 %, 126 have K up to 6400 and became 1.25x as fast on average,
+// none slower (1152 x 560, 133 rows 12.1 -> 6.6 us; 2304 x 3280, 159 rows 13.2 -> 10.9).  Longer K keeps its plan: 2 of 12
+// became slower there (9472 x 272, 204 rows 20.2 -> 24.2 us).  Scratch only shrinks.  Above 256 rows and from 8192
+// columns on the plan depends on the activations' type (binary16 alone takes some shapes), so a change for one type could leave
+// another with more scratch than the one size that serves all.
+static void fq_plan_rows_narrow(int64_t M, int64_t N, int64_t K, int bits, int g, int ncu, double best, fq_gemm_plan* p) {
+    const int row_blocks = (int)((M + 47) / 48), ntiles = (int)(N / FQ_NTILE);
+    const int mt = fq_mid_rows((int32_t)M) > 32 ? 3 : 2, KB = (int)(K / fq_kblk(bits)), sr = fq_scale_rows(bits, g);
+    const fq_mid_model model(mt, KB, bits, sr);
+    static const int groups[6] = {1, 2, 3, 4, 6, 12};
+    for (const int gp : groups) {
+        const int kw = model.workers(gp);
+        if ((ntiles + gp - 1) / gp * row_blocks > ncu) continue;
+        const double t = fq_mid_us(1, mt, KB, ntiles, row_blocks, M, N, bits, sr, gp, kw, 1, ncu);
+        if (t < best) {
+            best = t;
+            *p = fq_gemm_plan{};
+            p->kind = 3;
+            p->mt = 3;
+            p->nt = 1;
+            p->gp = gp;
+            p->kw = kw;
+            p->waves = gp * kw;
+            p->splits = 1;
+            p->tail_splits = 1;
         }
     }
 }
@@ -629,7 +664,8 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
             // ones, which lost by up to 1.4x where they took its place)
             const double rival = M > 256 && p.mt < 8 ? best128 : best;
             const double limit = 0.95 * (rival + 2.0);
-            bool pays = fq_plan_grouped_mid(count, N, K, bits, g, true, limit, &sh, &busy, &longest) < limit;
+            const double rows_us = fq_plan_grouped_mid(count, N, K, bits, g, true, limit, &sh, &busy, &longest);
+            bool pays = rows_us < limit;
             if (pays && fq_partial_bytes(p, M, N) == 0 && !fq_via_f16(act_dtype, FQ_SCALE_F16, p, N)) {
                 const int blocks = ((ntiles + MMA_NT - 1) / MMA_NT + sh.gp - 1) / sh.gp * (count[0] + count[1] + count[2]);
                 pays = longest * ((blocks + ncu - 1) / ncu) < limit;
@@ -644,8 +680,10 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
                 p.waves = sh.gp * sh.kw;
                 p.splits = 1;
                 p.tail_splits = 1;
+                best = rows_us;
             }
         }
+        if (M > 48 && M <= 256 && N < 8192 && K <= FQ_ROW_BLOCKS_MOST_K) fq_plan_rows_narrow(M, N, K, bits, g, ncu, best, &p);
     }
     return p;
 }

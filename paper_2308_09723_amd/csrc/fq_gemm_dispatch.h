@@ -85,10 +85,10 @@ int launch_mid(const void* A, int64_t M, int64_t N, int64_t K, const void* codes
 }
 
 // Tiles of up to 48 rows of a grouped product: the mid-M kernel, no split of K over the grid.
-template <int ACT, int BITS>
+template <int ACT, int BITS, int NT>
 int launch_mid_items(const void* A, const fq_small_items& items, int count, int rows_max, const fq_small_shape& sh, int64_t N,
                      int64_t K, const void* codes, const void* scales, int g, void* C, hipStream_t stream) {
-    constexpr int NT = MMA_NT, MAXW = 12;
+    constexpr int MAXW = 12;
     constexpr int kblk = fq_kblk(BITS);
     constexpr int STEPS = kblk / FQ_KSTEP;
     const int sr = (g % kblk) == 0 ? 1 : ((kblk % g) == 0 ? kblk / g : STEPS);
@@ -167,7 +167,8 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
             items.expert[count] = 0;
             ++count;
         }
-        const int st = launch_mid_items<ACT, BITS>(A, items, count, 48, {plan.gp, plan.kw}, N, K, codes, scales, g, C, stream);
+        const int st = plan.nt == 1 ? launch_mid_items<ACT, BITS, 1>(A, items, count, 48, {plan.gp, plan.kw}, N, K, codes, scales, g, C, stream)
+                                    : launch_mid_items<ACT, BITS, MMA_NT>(A, items, count, 48, {plan.gp, plan.kw}, N, K, codes, scales, g, C, stream);
         if (st != FQ_OK) return st;
     } else {
         // rows of K per k-block of this block shape (two layout blocks at a time for 8-bit codes in the
@@ -430,7 +431,7 @@ int launch_grouped_typed(const void* A, const int32_t* offsets, int E, const fq_
         const int n = count, most = rows_max;
         count = rows_max = 0;
         if (n == 0) return FQ_OK;
-        if (mid) return launch_mid_items<ACT, BITS>(A, small, n, most, plan.mid, N, K, codes, scales, g, C, streams[FQ_TILE_MID]);
+        if (mid) return launch_mid_items<ACT, BITS, MMA_NT>(A, small, n, most, plan.mid, N, K, codes, scales, g, C, streams[FQ_TILE_MID]);
         return launch_grouped_small<ACT, BITS>(A, small, n, most, N, K, codes, scales, g, C, streams[FQ_TILE_SMALL]);
     };
     // the tallest tiles of the mid-M kernel first, those of the small-M kernel last

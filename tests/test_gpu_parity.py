@@ -817,3 +817,17 @@ def test_gemm_mid_rows_16_and_48_columns_per_wave(M, K, N, bits, g, dtype, narro
     desc = _fq().gemm_describe(M, N, K, bits, g)
     assert "mid-m" in desc and ("cols=16" in desc) == narrow, desc
     _gemm_case(M, K, N, dtype, bits, g, seed=M + K + N)
+
+
+@pytest.mark.parametrize("M,K,N,bits,g,dtype,narrow", [
+    (49, 1152, 1104, 4, 64, "bf16", True), (96, 1408, 816, 3, 128, "f16", True), (97, 1536, 3952, 4, 32, "f16", True),
+    (143, 1664, 976, 8, 128, "bf16", True), (145, 2304, 3280, 4, 128, "f16", True), (197, 3840, 2832, 4, 0, "bf16", True),
+    (256, 1152, 1552, 4, 96, "f16", True), (66, 896, 16, 4, 32, "bf16", True),
+    (257, 1152, 1552, 4, 96, "bf16", False), (133, 1152, 8192, 4, 64, "f16", False),
+    (89, 6912, 288, 8, 64, "f16", False)])
+def test_gemm_row_blocks_of_16_columns_per_wave(M, K, N, bits, g, dtype, narrow):
+    """49 .. 256 rows on less than 8192 columns: row blocks of 48 and fewer rows with waves of 16 columns, a last row block and a
+    last column block that are not full, and the first sizes beyond the range."""
+    desc = _fq().gemm_describe(M, N, K, bits, g)
+    assert ("cols=16" in desc) == narrow, desc
+    _gemm_case(M, K, N, dtype, bits, g, seed=M + K + N)
