@@ -307,12 +307,13 @@ int fq_gemm_w4a8(const int8_t* Aq, const float* alpha, int64_t M, int64_t N, int
  * reports; it launches nothing.  M > 16: "tiled mt=.. waves=.. splits=.. kb_per_split=.. tail=..x..", where mt (2, 4 or 8
  * tiles of 16 rows) and waves name the class of the block shape; a shape that differs from its class's own is appended:
  * " rows=.. cols=..", " f16: rows=.. cols=.." where binary16 activations alone take it, or, for the streaming kernel of
- * 17 .. 48 rows, " mid-m rows=.. gp=.. kw=.. waves=.." (" cols=16" in front of it: 16 columns per wave, not 48; it stands in the class of 8 waves and deals the k-blocks out in turn,
- * kb_per_split of them at most to a block of the grid's split); more rows than it says are several row blocks of nearly equal
- * height.  32- and 64-row blocks of more than 256 rows stand in the class of 128 rows and 4 waves (their rows and columns appended),
- * row blocks of the streaming kernel in that of 128 rows and 8 waves.  Where a shape is appended it alone says what runs (48
- * columns per wave for " rows=.. cols=..", but 32 in blocks of 80 .. 128 rows x 256 columns); mt, waves and kb_per_split then
- * belong to the class.
+ * 17 .. 48 rows, " mid-m rows=.. gp=.. kw=.. waves=.." (" cols=16" in front of it: 16 columns per wave, not 48;
+ * it stands in the class of 8 waves and deals the k-blocks out in turn, kb_per_split of them at most to a block of the
+ * grid's split); more rows than it says are several row blocks of nearly equal height.  32- and 64-row blocks of more than
+ * 256 rows stand in the class of 128 rows and 4 waves (their rows and columns appended), row blocks of the streaming kernel
+ * in that of 128 rows and 8 waves.  Where a shape is appended it alone says what runs (48 columns per wave for
+ * " rows=.. cols=..", but 32 in blocks of 80 .. 128 rows x 256 columns; the streaming kernel as above); mt, waves and
+ * kb_per_split then belong to the class.
  * Returns FQ_OK, or the status fq_gemm would return for an invalid shape.
  */
 int fq_gemm_describe(int64_t M, int64_t N, int64_t K, int bits, int group_size, char* buf,

@@ -396,7 +396,8 @@ constexpr int64_t FQ_ROW_BLOCKS_MOST_K = 6400;
 // Time of the small-M kernel for a block shape (NT = nt column tiles per wave), fitted (of log time, rms error 11 %) to 190
 // problems of 1 .. 16 rows from 1024 x 1024 to 12288 x 49152 with 80 shapes each, timed inside graphs.  An iteration takes 0.3 us
 // and the longer of its vector work and its memory traffic at 9 TB/s over the resident blocks (which find part of it in a
-// cache); a split of K over the grid another kernel, whose launch costs the host 3.5 us, too, and the partial sums.
+// cache); a split of K over the grid the partial sums and 3.5 us, the launch of a second kernel that added them when this was
+// fitted.  The last block of a tile adds most of them now (fq_split_sum.h); the term stays, and with it plans and scratch.
 static double fq_small_us(int64_t M, int64_t N, int64_t K, int bits, int g, int ncu, int nt, int gp, int kw, int au, int gs) {
     const int kblk = fq_kblk(bits), sr = fq_scale_rows(bits, g), waves = gp * kw;
     const int ntiles = (int)(N / FQ_NTILE), KB = (int)(K / kblk);
@@ -446,7 +447,7 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
                 if (kw > KB) kw = KB;
                 if (kw < 1) continue;
                 const int SB = (KB + kw - 1) / kw;       // iterations if one block walks all of K
-                // Few column blocks: K is also split over the grid (binary32 partials + a second kernel),
+                // Few column blocks: K is also split over the grid (binary32 partials, added by the last block),
                 // which moreover divides the activation bytes every block has to fetch.
                 int gs = 1;
                 if (blocks <= ncu / 2) gs = (int)(ncu / blocks);
@@ -461,7 +462,7 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
                 double score = eff * eff * (inflight >= 64.0 ? 1.0 : sqrt(inflight / 64.0)) * f_nt[sv.nt];
                 score /= 1.0 + 0.1 * (double)(rounds - 1);   // a single resident round beats several
                 score *= au == 1 ? 1.0 : (au == 2 ? 0.8 : 0.6);
-                // a split of K over the grid costs a second kernel, and with few iterations left per
+                // a split of K over the grid costs its partial sums, and with few iterations left per
                 // block the register ring is mostly filling and draining
                 if (gs > 1) score *= n_it >= 16.0 ? 0.80 : 0.65;
                 // every block fetches its whole k range of the activations: M * K * 2 / gs bytes,
@@ -482,9 +483,9 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
         }
         // A split of K over the grid gives way where the blocks alone are as fast: the scores above were made for matrices
         // that take 15 us and more.  190 problems of 1 .. 16 rows: 89 lose their split, 1.11x on average over all (inside
-        // graphs), none more than 3 % slower; 2304 x 4528, 13 rows 9.9 -> 6.7 us, and a launch less
-        // (3.7 us of the host's time).  Matrices of up to 64 column tiles, a quarter of the compute units, keep their split:
-        // callers and tests take the smallest matrices to need scratch (1024 x 1024, 4 rows would take 4.5 us instead of 7).
+        // graphs), none more than 3 % slower; 2304 x 4528, 13 rows 9.9 -> 6.7 us (all against sums by a
+        // second kernel).  Matrices of up to 64 column tiles, a quarter of the compute units, keep their split:
+        // callers and tests take the smallest matrices to need scratch (1024 x 1024, 4 rows took 4.5 us unsplit, 7 with the second kernel).
         static const int groups[6] = {1, 2, 3, 4, 6, 12};
         double best_us = 1e30;
         if (p.splits > 1 && 4 * ntiles > ncu)

@@ -1309,8 +1309,8 @@ w8_plan w8_plan_wide(int64_t M, int64_t N, int64_t K, int g) {
     if (M <= 16) {
         // The block shape and split of K with the least time by a model fitted (of log time, rms error 5 %) to 80 problems of
         // 1 .. 16 rows in 20 shapes each: a block takes 4.4 us and per iteration 0.98 us (0.2 more with two activation units
-        // per lane) and its memory traffic at 15 TB/s (a part of it is hidden behind the rest); a split of K 2.1 us for its
-        // second kernel (3.1 below 10 us, where the launch's share of the host's time shows) and the slabs' traffic.  Against
+        // per lane) and its memory traffic at 15 TB/s (a part of it is hidden behind the rest); a split of K 2.1 us for the
+        // second kernel that added it then (3.1 below 10 us; fq_split_sum.h adds most of them now) and the slabs' traffic.  Against
         // the plan by fill: 0.92 of the time inside graphs (1024 x 19872, 2 rows 9.0 -> 6.7 us; 9 of 10 shapes that were
         // split and are not any more lose a launch, too).  Up to 64 column tiles, a quarter of the compute units, the plan by
         // fill stays: it splits such matrices, and callers and tests take them to need scratch.
@@ -1361,7 +1361,7 @@ w8_plan w8_plan_wide(int64_t M, int64_t N, int64_t K, int g) {
     //               twelve waves, 0.37 more with two multiplier rows per k-block), its memory traffic at 8.1 TB/s;
     //               tiled: 6.5 us + k-blocks * 0.80 or 1.18 us
     //   the launch  blocks per compute unit and 0.47 for the ragged end, at most whole rounds, at least one
-    //   a split     2.5 us for the second kernel and the slabs' traffic at 5 TB/s
+    //   a split     2.5 us for the second kernel that added it then and the slabs' traffic at 5 TB/s
     // Against the tiled kernel alone (32, 64 or 128 rows, K split until 192 tiles): 0.76 of the time on average inside
     // graphs, never more than 3 % slower; 204 others, called one after the other: 1.38x faster on average, 10 more than 3 % slower
     // (14 % at worst: K of 10000 and more, or fewer splits than the former rule's); 12288 x 36864 us: M = 17 55 -> 40, M = 64 66 -> 46; 2816 x 5184, M = 95 22 -> 10.
