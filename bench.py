@@ -262,8 +262,8 @@ def main():
             # kernel plans than the ones this run used
             "traffic": traffic,
             "traffic_source": traffic_note,
-            "kernel": "fq_gemm_skinny_kernel (8 products per step, plus fq_reduce_kernel for the one that splits K "
-                      "over the grid; algorithmic bytes of the step / mean HIP-event duration of its back-to-back "
+            "kernel": "fq_gemm_skinny_kernel (8 products per step, the one that splits K over the grid adds its "
+                      "partial sums itself; algorithmic bytes of the step / mean HIP-event duration of its back-to-back "
                       "launches)",
             "algorithmic_bytes_per_step": algo_bytes,
             "kernel_us_per_step": round(kernel_us, 2),
