@@ -3,6 +3,7 @@
 #define FQ_INTERNAL_H_
 
 #include <hip/hip_runtime.h>
+#include <initializer_list>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -28,6 +29,16 @@ int fq_launch_mfma_rate_probe(const void* operands, void* sink, int iterations, 
 
 // A tag for the tickets of one call (fq_split_sum.h); never 0.
 uint64_t fq_next_tag();
+// Whether `bytes` bytes from C on share memory with one of the buffers that a call reads.
+struct fq_span {
+    const void* p;
+    size_t bytes;
+};
+inline bool fq_overlaps(const void* C, size_t bytes, std::initializer_list<fq_span> read) {
+    for (const fq_span& r : read)
+        if ((uintptr_t)C < (uintptr_t)r.p + r.bytes && (uintptr_t)r.p < (uintptr_t)C + bytes) return true;
+    return false;
+}
 
 // product side
 struct fq_gemm_plan {

@@ -62,3 +62,19 @@ def assert_gemm_close(C, C_ref, dtype, what=""):
     err = np.max(np.abs(C - C_ref))
     assert err <= TOL[dtype] * scale, f"{what}: max err {err:.4g} > {TOL[dtype]} * {scale:.4g}"
     return err / scale if scale > 0 else 0.0
+
+
+def kernels_of(call):
+    """The number of kernels that `call` enqueues: the nodes of a capture of it, which is never run.  (Call it once before:
+    the first launch of some shapes is not capturable.)"""
+    import ctypes
+
+    torch = torch_mod()
+    with open("/proc/self/maps") as maps:
+        path = next(line.split()[-1] for line in maps if "libamdhip64" in line)
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    n = ctypes.c_size_t()
+    assert ctypes.CDLL(path).hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value

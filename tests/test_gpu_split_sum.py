@@ -3,7 +3,7 @@ in the output) gives the bits of the separate sum kernel, which outputs that are
 the output holds before the call, call after call, on two streams at once and replayed from a graph."""
 import pytest
 
-from gpu_util import torch_mod
+from gpu_util import kernels_of, torch_mod
 
 pytestmark = pytest.mark.gpu
 
@@ -107,3 +107,41 @@ def test_integer_path_same_bits_as_the_separate_sum(M, K, N, g, act):
         fill()
         got = fq.gemm_w4a8(Aq, alpha, codes, z, t, g, dtype, out=C, workspace=ws)
         assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
+def test_a_product_over_its_own_activations_sums_in_a_second_kernel():
+    """C on memory that the product reads: tickets there would change what other blocks still read, so the separate kernel adds
+    the partial sums once everything is read, and the result is that of an output of its own."""
+    from paper_2308_09723_amd import fq
+    torch = torch_mod()
+    A, codes, scales, ws = _case(4, 1024, 1024, 4, 128, "f16")
+    def product(a, c):
+        return fq.gemm(a, codes, scales, 4, 128, out=c, workspace=ws)
+
+    C = torch.empty_like(A)
+    want = product(A, C).clone()
+    rows = torch.cat([A, A])                 # the output begins in the middle of the activations
+    assert kernels_of(lambda: product(A, C)) == 1
+    assert kernels_of(lambda: product(A, A)) == kernels_of(lambda: product(rows[:4], rows[2:6])) == 2
+    product(rows[:4], rows[2:6])
+    assert torch.equal(rows[2:6], want) and torch.equal(rows[:2], A[:2]) and torch.equal(rows[6:], A[2:])
+    product(A, A)
+    assert torch.equal(A, want)
+
+
+def test_integer_path_over_its_own_activations_sums_in_a_second_kernel():
+    from paper_2308_09723_amd import fq
+    torch = torch_mod()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    codes, z, t = fq.quantize_w4a8((torch.randn((4096, 1024), generator=gen, device="cuda") * 0.02).to(torch.float16), 128)
+    Aq, alpha = fq.quantize_act_i8(torch.randn((4, 4096), generator=gen, device="cuda").to(torch.float16))
+    ws = torch.empty(fq.gemm_w4a8_workspace_bytes(4, 1024, 4096, 128), dtype=torch.uint8, device="cuda")
+    C, over = torch.empty((4, 1024), dtype=torch.float16, device="cuda"), Aq.view(torch.float16).view(-1)[:4096].view(4, 1024)
+
+    def product(c):
+        return fq.gemm_w4a8(Aq, alpha, codes, z, t, 128, torch.float16, out=c, workspace=ws)
+
+    want = product(C).clone()
+    assert kernels_of(lambda: product(C)) == 1 and kernels_of(lambda: product(over)) == 2
+    assert torch.equal(product(over), want)
