@@ -171,7 +171,10 @@ int fq_quant_error_sf(const void* W_f16, int64_t K, int64_t N, int bits, int gro
  *   A           in   [M, K] row-major, act_dtype
  *   codes       in   packed codes written by fq_quantize for the same (K, N, bits)
  *   scales_f16  in   [K/g, N] binary16
- *   C           out  [M, N] row-major, act_dtype
+ *   C           out  [M, N] row-major, act_dtype.  Working storage until the call has ended (a product that
+ *                    splits K counts its blocks in it): calls that may run at the same time need outputs of
+ *                    their own, also where they would write the same results, and C must not overlap an
+ *                    input or the workspace.
  *   workspace        device scratch, >= fq_gemm_workspace_bytes(M, N, K, bits, group_size)
  *                    bytes (may be NULL when that is 0)
  * M = 0 is a valid no-op.  Deterministic: the same inputs give the same bits.
@@ -289,7 +292,8 @@ int fq_quantize_act_i8(const void* A, int act_dtype, int64_t M, int64_t K, int8_
  * fq_gemm_w4a8 -- the product of the integer path.
  *   Aq, alpha            in   as written by fq_quantize_act_i8
  *   codes, zscale, tstep in   as written by fq_quantize_w4a8 for the same (K, N, group_size)
- *   C                    out  [M, N] row-major, out_dtype (FQ_F16 or FQ_BF16)
+ *   C                    out  [M, N] row-major, out_dtype (FQ_F16 or FQ_BF16); working storage until the call has ended,
+ *                             as fq_gemm's
  *   workspace                 device scratch, >= fq_gemm_w4a8_workspace_bytes(M, N, K, group_size) bytes (int32 sums
  *                             of products whose K range is split over several blocks; may be NULL when that is 0)
  * Asynchronous on `stream`, no allocation, deterministic.

@@ -54,6 +54,19 @@ uint64_t fq_next_tag() {
     return 0xffa5ull << 48 | (calls.fetch_add(1, std::memory_order_relaxed) & 0xffffffffffull) << 8;
 }
 
+// Atomics of agent scope count among the compute units of one device, in that device's own memory.  C in pinned host memory, in
+// managed memory or on another GPU is only ever stored to, as is memory that the runtime cannot place (asked in 60 ns each).
+bool fq_counts_tickets(const void* C, hipStream_t stream) {
+    if (hipPeekAtLastError() != hipSuccess) return false;      // (an earlier error is not this call's to clear)
+    hipPointerAttribute_t at = {};
+    hipDevice_t dev = -1;
+    if (hipPointerGetAttributes(&at, C) != hipSuccess || hipStreamGetDevice(stream, &dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == (int)dev && !at.isManaged && at.allocationFlags == 0;
+}
+
 // scale rows a layout k-block spans: 1, kblk / g, or one per 32-row step
 static int fq_scale_rows(int bits, int g) {
     const int kblk = fq_kblk(bits);

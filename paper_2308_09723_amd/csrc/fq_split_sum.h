@@ -10,7 +10,13 @@
 // (the scratch of a product is exactly its partial sums): a block counts in a word that carries the call's tag, and tags
 // the word first where it does not.  A tag is used by one call only (fq_next_tag) and is gone when the call ends, since
 // the results take its place, so that a captured call may be replayed with the tag that it was captured with.  Its upper
-// 16 bits are a NaN in either 16-bit type, 0xffa5, that no conversion to those types makes.
+// 16 bits are a NaN in either 16-bit type, 0xffa5; results could hold that one too (a NaN's payload may pass through a
+// conversion), but not with the call's 40 bits beside it.
+//
+// So C must be the call's own while it runs: a second call that counted in the same words at the same time would replace the
+// tag, and neither would find its last block.  (A word elsewhere would have to be the library's: the scratch that callers hand
+// over holds the partial sums and nothing else.)  Where C lies on an input, or is not the device's own memory, the separate sum
+// kernel adds, as it does for outputs that are not aligned.
 //
 // Memory: partial sums and tickets are read and written with accesses of agent scope, which pass by the L2 caches (one
 // per XCD, not coherent with each other within a kernel); a block's ticket is taken after its stores have completed.

@@ -145,3 +145,32 @@ def test_integer_path_over_its_own_activations_sums_in_a_second_kernel():
     want = product(C).clone()
     assert kernels_of(lambda: product(C)) == 1 and kernels_of(lambda: product(over)) == 2
     assert torch.equal(product(over), want)
+
+
+def test_outputs_in_host_memory_are_summed_by_a_second_kernel():
+    """Tickets are counted with atomics of the device: C in pinned host memory is only stored to."""
+    from paper_2308_09723_amd import fq
+    torch = torch_mod()
+    A, codes, scales, ws = _case(4, 1024, 1024, 4, 128, "f16")
+    C, host = torch.empty_like(A), torch.zeros((4, 1024), dtype=torch.float16, pin_memory=True)
+
+    def product(c):
+        return fq.gemm(A, codes, scales, 4, 128, out=c, workspace=ws)
+
+    want = product(C)
+    assert kernels_of(lambda: product(C)) == 1 and kernels_of(lambda: product(host)) == 2
+    product(host)
+    torch.cuda.synchronize()
+    assert torch.equal(host, want.cpu())
+    codes, z, t = fq.quantize_w4a8((torch.randn((4096, 1024), device="cuda") * 0.02).to(torch.float16), 128)
+    Aq, alpha = fq.quantize_act_i8(torch.randn((4, 4096), device="cuda").to(torch.float16))
+    ws = torch.empty(fq.gemm_w4a8_workspace_bytes(4, 1024, 4096, 128), dtype=torch.uint8, device="cuda")
+
+    def integer(c):
+        return fq.gemm_w4a8(Aq, alpha, codes, z, t, 128, torch.float16, out=c, workspace=ws)
+
+    want = integer(C)
+    assert kernels_of(lambda: integer(C)) == 1 and kernels_of(lambda: integer(host)) == 2
+    integer(host)
+    torch.cuda.synchronize()
+    assert torch.equal(host, want.cpu())
