@@ -6,8 +6,10 @@
 // -> 5.6.
 //
 // Every function returns None, having launched nothing, where anything is out of the ordinary: objects that are not plain
-// CUDA tensors, torch function modes, other types than the listed ones, a status that is not FQ_OK.  fq.py then takes its own
-// way, which reports the error or does what it always did.  Only arguments are looked at; nothing is kept between calls.
+// CUDA tensors, torch function modes, other types than the listed ones, arguments or a workspace that the library refuses.  fq.py
+// then takes its own way, which reports the error or does what it always did.  An error of the runtime (FQ_ERR_HIP) may follow
+// launches that were enqueued, so it is raised here and the call is not made again.  Only arguments are looked at; nothing is
+// kept between calls.
 #include <Python.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>
@@ -40,7 +42,12 @@ struct {
     decltype(&fq_zscale_bytes) zscale_bytes;
 } lib;
 
+PyObject* fq_error;       // fq.FqError
+
 struct not_plain {};      // thrown: the Python way
+struct runtime_error {    // thrown: FqError(FQ_ERR_HIP, where)
+    const char* where;
+};
 
 const at::Tensor& tensor(PyObject* o) {
     if (!THPVariable_CheckExact(o)) throw not_plain();
@@ -79,13 +86,14 @@ void arguments(Py_ssize_t got, Py_ssize_t want) {
     if (got != want || at::impl::torch_function_mode_enabled()) throw not_plain();
 }
 
-// runs `f` (a call of the library) without the interpreter's lock
+// runs `f` (a call of the library's function `where`) without the interpreter's lock
 template <typename F>
-void call(F f) {
+void call(const char* where, F f) {
     int status;
     Py_BEGIN_ALLOW_THREADS
     status = f();
     Py_END_ALLOW_THREADS
+    if (status == FQ_ERR_HIP) throw runtime_error{where};
     if (status != FQ_OK) throw not_plain();
 }
 
@@ -114,6 +122,11 @@ template <typename F>
 PyObject* guarded(F f) {
     try {
         return f();
+    } catch (const runtime_error& e) {
+        PyObject* raised = PyObject_CallFunction(fq_error, "is", (int)FQ_ERR_HIP, e.where);
+        if (raised) PyErr_SetObject(fq_error, raised);
+        Py_XDECREF(raised);
+        return nullptr;
     } catch (...) {
         PyErr_Clear();
         Py_RETURN_NONE;
@@ -133,7 +146,7 @@ PyObject* gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
         size_t size = 0;
         void* ws = scratch(a[6], A, [&] { return lib.gemm_workspace_bytes(M, N, K, bits, g); }, &size, &own);
         void *Cp = C.data_ptr(), *s = stream();
-        call([&] { return lib.gemm_sf(Ap, act, M, N, K, cp, sp, format, bits, g, Cp, ws, size, s); });
+        call("fq_gemm_sf", [&] { return lib.gemm_sf(Ap, act, M, N, K, cp, sp, format, bits, g, Cp, ws, size, s); });
         return result(a[5], std::move(C));
     });
 }
@@ -153,7 +166,7 @@ PyObject* gemm_grouped(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const void *Ap = A.data_ptr(), *cp = codes.data_ptr(), *sp = scales.data_ptr();
         at::Tensor C = a[7] != Py_None ? tensor(a[7]) : empty({A.size(0), N}, A.scalar_type(), A);
         void *Cp = C.data_ptr(), *s = stream();
-        call([&] {
+        call("fq_gemm_grouped_sf", [&] {
             return lib.gemm_grouped_sf(Ap, act, offsets, (int)count - 1, N, K, cp, sp, format, bits, g, Cp, nullptr, 0, s);
         });
         return result(a[7], std::move(C));
@@ -173,7 +186,7 @@ PyObject* quantize_act_i8(PyObject*, PyObject* const* a, Py_ssize_t n) {
         int8_t* qp = (int8_t*)Aq.data_ptr();
         float* alp = (float*)alpha.data_ptr();
         void* s = stream();
-        call([&] { return lib.quantize_act_i8(Ap, act, M, K, qp, alp, s); });
+        call("fq_quantize_act_i8", [&] { return lib.quantize_act_i8(Ap, act, M, K, qp, alp, s); });
         return Py_BuildValue("(NN)", THPVariable_Wrap(std::move(Aq)), THPVariable_Wrap(std::move(alpha)));
     });
 }
@@ -194,7 +207,7 @@ PyObject* gemm_w4a8(PyObject*, PyObject* const* a, Py_ssize_t n) {
         size_t size = 0;
         void* ws = scratch(a[8], Aq, [&] { return lib.gemm_w4a8_workspace_bytes(M, N, K, g); }, &size, &own);
         void *Cp = C.data_ptr(), *s = stream();
-        call([&] { return lib.gemm_w4a8(qp, alp, M, N, K, cp, zp, tp, g, Cp, type, ws, size, s); });
+        call("fq_gemm_w4a8", [&] { return lib.gemm_w4a8(qp, alp, M, N, K, cp, zp, tp, g, Cp, type, ws, size, s); });
         return result(a[7], std::move(C));
     });
 }
@@ -213,7 +226,7 @@ PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
         at::Tensor codes = empty({(int64_t)cb}, at::kByte, W);
         at::Tensor scales = empty({g == 0 ? 1 : K / g, N}, format == FQ_SCALE_BF16 ? at::kBFloat16 : at::kHalf, W);
         void *cp = codes.data_ptr(), *sp = scales.data_ptr(), *s = stream();
-        call([&] { return lib.quantize_sf(Wp, K, N, bits, g, format, cp, sp, s); });
+        call("fq_quantize_sf", [&] { return lib.quantize_sf(Wp, K, N, bits, g, format, cp, sp, s); });
         return Py_BuildValue("(NN)", THPVariable_Wrap(std::move(codes)), THPVariable_Wrap(std::move(scales)));
     });
 }
@@ -232,27 +245,29 @@ PyObject* quantize_w4a8(PyObject*, PyObject* const* a, Py_ssize_t n) {
                    t = empty({N}, at::kHalf, W);
         void *cp = codes.data_ptr(), *tp = t.data_ptr(), *s = stream();
         uint8_t* zp = (uint8_t*)z.data_ptr();
-        call([&] { return lib.quantize_w4a8(Wp, K, N, g, cp, zp, tp, s); });
+        call("fq_quantize_w4a8", [&] { return lib.quantize_w4a8(Wp, K, N, g, cp, zp, tp, s); });
         return Py_BuildValue("(NNN)", THPVariable_Wrap(std::move(codes)), THPVariable_Wrap(std::move(z)), THPVariable_Wrap(std::move(t)));
     });
 }
 
-// bind(addresses of the functions of `lib`, in its order)
+// bind(FqError, addresses of the functions of `lib`, in its order)
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
     constexpr Py_ssize_t count = sizeof(lib) / sizeof(void*);
-    if (n != count) {
+    if (n != 1 + count) {
         PyErr_SetString(PyExc_TypeError, "bind: wrong number of functions");
         return nullptr;
     }
     void* p[count];
-    for (Py_ssize_t i = 0; i < n; ++i) {
-        p[i] = PyLong_AsVoidPtr(a[i]);
+    for (Py_ssize_t i = 0; i < count; ++i) {
+        p[i] = PyLong_AsVoidPtr(a[1 + i]);
         if (!p[i]) {
             if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "bind: no address");
             return nullptr;
         }
     }
     memcpy(&lib, p, sizeof(lib));
+    Py_INCREF(a[0]);
+    Py_XSETREF(fq_error, a[0]);
     Py_RETURN_NONE;
 }
 

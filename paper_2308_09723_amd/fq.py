@@ -311,7 +311,8 @@ def _torch():
 _torch_mod = _raw_stream = _device = None
 
 # The calls that a program makes over and over, in native code (csrc/fq_binding.cpp).  A function of it returns None where a
-# call is out of the ordinary; the Python below it then reports the error, or does without.
+# call is out of the ordinary; the Python below it then reports the error, or does without.  (Errors of the HIP runtime, which
+# may come after launches, it raises itself.)
 NATIVE_PATH = os.path.join(_HERE, "_fqcall.so")
 _NATIVE_FUNCTIONS = ("fq_gemm_sf", "fq_gemm_workspace_bytes", "fq_gemm_grouped_sf", "fq_gemm_w4a8", "fq_gemm_w4a8_workspace_bytes",
                      "fq_quantize_act_i8", "fq_quantize_sf", "fq_quantize_w4a8", "fq_codes_bytes", "fq_scales_bytes", "fq_zscale_bytes")
@@ -324,7 +325,7 @@ def _load_native():
     module = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(module)
     lib = load()
-    module.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_FUNCTIONS))
+    module.bind(FqError, *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_FUNCTIONS))
     return module
 
 

@@ -1,5 +1,7 @@
 """The native calls of the torch layer (csrc/fq_binding.cpp) against the Python they stand in for: the same outputs, and None --
 the Python way, with its errors -- wherever a call is out of the ordinary."""
+import ctypes
+
 import pytest
 
 from paper_2308_09723_amd import fq
@@ -103,3 +105,42 @@ def test_same_outputs_and_errors_as_the_python_way(monkeypatch):
         Aq, alpha = fq.quantize_act_i8(x)
     s.synchronize()
     assert torch.equal(Aq, fq.quantize_act_i8(x)[0])
+
+
+@pytest.mark.gpu
+def test_an_error_of_the_runtime_is_raised_and_the_call_not_made_again(monkeypatch):
+    """FQ_ERR_HIP can follow launches that were enqueued.  The library's functions are stubs here, which launch nothing."""
+    import torch
+    native = _native()
+    W = (torch.randn((1024, 1040), device="cuda") * 0.02).to(torch.float16)
+    A = torch.randn((7, 1024), device="cuda").to(torch.float16)
+    codes, scales = fq.quantize(W, 4, 128)
+    c8, z, t = fq.quantize_w4a8(W, 128)
+    Aq, alpha = fq.quantize_act_i8(A)
+    calls, real = [], fq.load()
+
+    class Library:
+        def __getattr__(self, name):
+            if name not in stubs:
+                return getattr(real, name)
+            return stubs[name]
+
+    names = [n for n in fq._NATIVE_FUNCTIONS if not n.endswith("_bytes")]
+    stubs = {n: ctypes.CFUNCTYPE(ctypes.c_int)(lambda n=n: (calls.append(n), fq.FQ_ERR_HIP)[1]) for n in names}
+    monkeypatch.setattr(fq, "load", lambda *args: Library())
+    try:
+        monkeypatch.setattr(fq, "_native", fq._load_native())
+        for name, call in (("fq_gemm_sf", lambda: fq.gemm(A, codes, scales, 4, 128)),
+                           ("fq_gemm_grouped_sf", lambda: fq.gemm_grouped(A, [0, 7], codes, scales, 4, 128, 1040)),
+                           ("fq_gemm_w4a8", lambda: fq.gemm_w4a8(Aq, alpha, c8, z, t, 128, torch.float16)),
+                           ("fq_quantize_act_i8", lambda: fq.quantize_act_i8(A)), ("fq_quantize_sf", lambda: fq.quantize(W, 4, 128)),
+                           ("fq_quantize_w4a8", lambda: fq.quantize_w4a8(W, 128))):
+            with pytest.raises(fq.FqError) as e:
+                call()
+            assert (e.value.status, str(e.value)) == (fq.FQ_ERR_HIP, f"{name}: FQ_ERR_HIP")
+            assert calls == [name]
+            calls.clear()
+    finally:
+        monkeypatch.undo()
+        fq._load_native()                # the library's own functions again
+    assert fq._native is native and torch.equal(fq.quantize_act_i8(A)[0], Aq)
