@@ -2,13 +2,15 @@
 
 Every translation unit is compiled to an object file in parallel (the nine product-kernel
 instantiations dominate the build time), then linked into paper_2308_09723_amd/libfq.so; beside them g++ compiles the native
-calls of fq.py into paper_2308_09723_amd/_fqcall.so.
+calls of fq.py into paper_2308_09723_amd/_fqcall.so.  The library needs neither these nor torch: without them fq.py issues
+its calls from Python.
 """
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -134,17 +136,38 @@ def _resource_report(rows, verbose):
 
 
 def _native_command():
-    """The command that compiles the native calls: host code only, against torch's headers (torch itself is not imported)."""
+    """The command that compiles the native calls: host code only, against torch's headers (torch itself is not imported).
+    None without torch."""
     import importlib.util
     import sysconfig
 
-    torch = importlib.util.find_spec("torch").submodule_search_locations[0]
+    spec = importlib.util.find_spec("torch")
+    if spec is None:
+        return None
+    torch = spec.submodule_search_locations[0]
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     include = [os.path.join(torch, "include"), os.path.join(torch, "include", "torch", "csrc", "api", "include"),
                os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
     return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__", "-D_GLIBCXX_USE_CXX11_ABI=1"] +
             [x for d in include for x in ("-isystem", d)] + [os.path.join(CSRC, "fq_binding.cpp"), "-L" + os.path.join(torch, "lib"),
             "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", NATIVE_PATH])
+
+
+def build_native(verbose: bool = True) -> str | None:
+    """Compiles the native calls; None, with a warning and no earlier build left in their place, where that is not possible."""
+    cmd = _native_command()
+    if verbose and cmd:
+        print(" ".join(cmd), flush=True)
+    try:
+        rc, out = _run(cmd) if cmd else (1, "torch is not installed")
+    except OSError as e:
+        rc, out = 1, str(e)
+    if rc == 0:
+        return NATIVE_PATH
+    if os.path.exists(NATIVE_PATH):
+        os.remove(NATIVE_PATH)
+    warnings.warn("the native calls of fq.py were not built: " + out, RuntimeWarning, stacklevel=2)
+    return None
 
 
 def build_lib(verbose: bool = True, jobs: int | None = None) -> str:
@@ -165,16 +188,8 @@ def build_lib(verbose: bool = True, jobs: int | None = None) -> str:
             print(rest)
         return obj, _parse_resources(out)
 
-    def compile_native():
-        cmd = _native_command()
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        rc, out = _run(cmd)
-        if rc != 0:
-            raise RuntimeError("g++ failed on fq_binding.cpp:\n" + out)
-
     with ThreadPoolExecutor(max_workers=jobs) as pool:
-        native = pool.submit(compile_native)
+        native = pool.submit(build_native, verbose)
         results = list(pool.map(compile_one, SOURCES))
         native.result()
     objs = [r[0] for r in results]

@@ -10,6 +10,7 @@ import array
 import ctypes
 import importlib.util
 import os
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libfq.so")
@@ -38,9 +39,9 @@ def load(build_if_missing: bool = True) -> ctypes.CDLL:
     global _lib
     if _lib is not None:
         return _lib
-    if not (os.path.exists(LIB_PATH) and os.path.exists(NATIVE_PATH)):
+    if not os.path.exists(LIB_PATH):
         if not build_if_missing:
-            raise FileNotFoundError(NATIVE_PATH if os.path.exists(LIB_PATH) else LIB_PATH)
+            raise FileNotFoundError(LIB_PATH)
         from . import build
 
         build.build_lib(verbose=False)
@@ -319,13 +320,24 @@ _NATIVE_FUNCTIONS = ("fq_gemm_sf", "fq_gemm_workspace_bytes", "fq_gemm_grouped_s
 _native = None
 
 
+class _NoNative:
+    """In place of the native calls where they are not built or do not fit this torch: every call goes the Python way."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _load_native():
     """The native calls, bound to the library that load() has loaded."""
-    spec = importlib.util.spec_from_file_location("_fqcall", NATIVE_PATH)
-    module = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(module)
-    lib = load()
-    module.bind(FqError, *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_FUNCTIONS))
+    try:
+        spec = importlib.util.spec_from_file_location("_fqcall", NATIVE_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        lib = load()
+        module.bind(FqError, *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_FUNCTIONS))
+    except (ImportError, OSError, TypeError) as e:      # not there, another torch's or Python's, another build's
+        warnings.warn(f"calls are issued from Python, which takes about twice as long: {e}", RuntimeWarning, stacklevel=2)
+        return _NoNative()
     return module
 
 

@@ -35,6 +35,53 @@ def test_host_tensors_and_wrong_arguments_go_the_python_way():
             call()
 
 
+@pytest.mark.parametrize("fault", ["no torch", "no compiler", "compile error"])
+def test_the_library_builds_without_the_native_calls(monkeypatch, tmp_path, fault):
+    """libfq.so is linked where the native calls cannot be compiled, and no earlier build of them stays beside it."""
+    import importlib.util
+
+    from paper_2308_09723_amd import build
+
+    commands, find_spec = [], importlib.util.find_spec
+
+    def run(cmd):
+        commands.append(cmd)
+        if cmd[0] != "g++":
+            return 0, ""
+        if fault == "no compiler":
+            raise FileNotFoundError("g++")
+        return 1, "error"
+
+    monkeypatch.setattr(build, "_run", run)
+    monkeypatch.setattr(build, "_resource_report", lambda rows, verbose: None)
+    for name, value in (("OBJ_DIR", "obj"), ("LIB_PATH", "libfq.so"), ("NATIVE_PATH", "_fqcall.so")):
+        monkeypatch.setattr(build, name, str(tmp_path / value))
+    if fault == "no torch":
+        monkeypatch.setattr(importlib.util, "find_spec", lambda name, *a: None if name == "torch" else find_spec(name, *a))
+    (tmp_path / "_fqcall.so").write_bytes(b"an earlier build")
+    with pytest.warns(RuntimeWarning, match="not built"):
+        assert build.build_lib(verbose=False) == str(tmp_path / "libfq.so")
+    assert "-shared" in commands[-1] and commands[-1][-1] == str(tmp_path / "libfq.so")
+    assert not (tmp_path / "_fqcall.so").exists()
+
+
+@pytest.mark.parametrize("there", ["missing", "not a library"])
+def test_without_the_native_calls_everything_goes_the_python_way(monkeypatch, tmp_path, there):
+    path = tmp_path / "_fqcall.so"
+    if there == "not a library":
+        path.write_bytes(b"something else")
+    import torch
+    for name, value in (("NATIVE_PATH", str(path)), ("_lib", None), ("_native", None), ("_torch_mod", None)):
+        monkeypatch.setattr(fq, name, value)
+    assert fq.load(build_if_missing=False) is not None       # the C interface needs libfq.so alone
+    A = torch.zeros((4, 128), dtype=torch.float16)
+    with pytest.warns(RuntimeWarning, match="issued from Python"):
+        fq._torch()
+    assert fq._native.gemm(A, A, A, 4, 128, None, None) is None and fq._native.quantize_act_i8(A) is None
+    with pytest.raises(AssertionError):                      # (host tensors: the Python way's own check)
+        fq.quantize_act_i8(A)
+
+
 @pytest.mark.gpu
 def test_same_outputs_and_errors_as_the_python_way(monkeypatch):
     import torch
