@@ -41,6 +41,9 @@ def test_same_bits_as_the_separate_sum(M, K, N, bits, g, act):
     C, apart = _outputs(M, N, A.dtype)
     assert C.data_ptr() % 8 == 0 and apart.data_ptr() % 8 == 2
     want = fq.gemm(A, codes, scales, bits, g, out=apart, workspace=ws).clone()
+    fq.gemm(A, codes, scales, bits, g, out=C, workspace=ws)
+    assert kernels_of(lambda: fq.gemm(A, codes, scales, bits, g, out=C, workspace=ws)) == 1
+    assert kernels_of(lambda: fq.gemm(A, codes, scales, bits, g, out=apart, workspace=ws)) == 2
     exact = A.double() @ (fq.unpack(codes, K, N, bits).double() * scales.double().repeat_interleave(g, 0))
     assert float((want.double() - exact).norm() / exact.norm()) < (1.2e-3 if act == "f16" else 7e-3)
     # zeros, the results themselves, NaNs, and words that look like tickets of other calls, full and begun
@@ -103,10 +106,50 @@ def test_integer_path_same_bits_as_the_separate_sum(M, K, N, g, act):
     ws = torch.empty(need, dtype=torch.uint8, device="cuda")
     C, apart = _outputs(M, N, dtype)
     want = fq.gemm_w4a8(Aq, alpha, codes, z, t, g, dtype, out=apart, workspace=ws).clone()
+    fq.gemm_w4a8(Aq, alpha, codes, z, t, g, dtype, out=C, workspace=ws)
+    assert kernels_of(lambda: fq.gemm_w4a8(Aq, alpha, codes, z, t, g, dtype, out=C, workspace=ws)) == 1
+    assert kernels_of(lambda: fq.gemm_w4a8(Aq, alpha, codes, z, t, g, dtype, out=apart, workspace=ws)) == 2
     for fill in (lambda: C.zero_(), lambda: None, lambda: C.fill_(float("nan")), lambda: C.view(torch.int64).fill_((-91 << 48) | 3)) * 4:
         fill()
         got = fq.gemm_w4a8(Aq, alpha, codes, z, t, g, dtype, out=C, workspace=ws)
         assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    alpha[0], alpha[M // 2] = float("nan"), float("inf")         # (row 0 holds the tickets)
+    want = fq.gemm_w4a8(Aq, alpha, codes, z, t, g, dtype, out=apart, workspace=ws).clone()
+    for _ in range(3):
+        got = fq.gemm_w4a8(Aq, alpha, codes, z, t, g, dtype, out=C, workspace=ws)
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16)) and not torch.isfinite(got[0]).any()
+
+
+@pytest.mark.parametrize("M,K,N,bits,g,kernels", [(30, 4864, 1824, 4, 32, 1), (28, 5120, 2048, 4, 128, 1), (36, 4480, 2576, 4, 64, 2),
+                                                  (32, 5248, 1776, 3, 32, 2), (16, 8192, 28672, 8, 128, 2)])
+def test_tiles_of_more_than_80_KiB_of_partial_sums_are_summed_by_a_second_kernel(M, K, N, bits, g, kernels):
+    """78.8, 73.5, 81, 84 and 180 KiB per tile: the kernel that runs, and the results of either."""
+    from paper_2308_09723_amd import fq
+    torch = torch_mod()
+    A, codes, scales, ws = _case(M, K, N, bits, g, "f16")
+    C, apart = _outputs(M, N, A.dtype)
+    want = fq.gemm(A, codes, scales, bits, g, out=apart, workspace=ws)
+    assert torch.equal(fq.gemm(A, codes, scales, bits, g, out=C, workspace=ws), want)
+    assert kernels_of(lambda: fq.gemm(A, codes, scales, bits, g, out=C, workspace=ws)) == kernels
+
+
+@pytest.mark.parametrize("M,K,N,bits,g,act", [SHAPES[0], SHAPES[1], SHAPES[4], SHAPES[5], SHAPES[7]])
+def test_results_that_are_not_finite_have_the_bits_of_the_separate_sum(M, K, N, bits, g, act):
+    """Infinities and NaNs in row 0, whose first results hold the tickets, among them the NaN that a ticket's upper bits are."""
+    from paper_2308_09723_amd import fq
+    torch = torch_mod()
+    A, codes, scales, ws = _case(M, K, N, bits, g, act)
+    C, apart = _outputs(M, N, A.dtype)
+    A[M - 1, K // 2] = float("inf")
+    for first in (float("inf"), float("-inf"), float("nan"), -91):
+        if first == -91:
+            A.view(torch.int16)[0, 5] = first
+        else:
+            A[0, 5] = first
+        want = fq.gemm(A, codes, scales, bits, g, out=apart, workspace=ws).clone()
+        for _ in range(3):
+            got = fq.gemm(A, codes, scales, bits, g, out=C, workspace=ws)
+            assert torch.equal(got.view(torch.int16), want.view(torch.int16)) and not torch.isfinite(got[0]).all()
 
 
 def test_a_product_over_its_own_activations_sums_in_a_second_kernel():
