@@ -206,8 +206,8 @@ int fq_gemm_sf(const void* A, int act_dtype, int64_t M, int64_t N, int64_t K, co
  *   arguments  as fq_gemm, without the workspace
  * Errors: as fq_gemm; FQ_ERR_WORKSPACE when the problem needs more scratch than the array holds
  *         (fq_gemm_workspace_bytes_for(...) > FQ_NOALLOC_SCRATCH_BYTES: nothing is launched; use fq_gemm).
- * All calls on one GPU share that GPU's array, which keeps the previous call's contents (no kernel reads
- * what an earlier kernel of the same call has not written, so nothing needs clearing).  Calls that
+ * All calls on one GPU share that GPU's array, which keeps the previous call's contents (a call reads only
+ * what it has written itself, in an earlier kernel or in an earlier block of the same one, so nothing needs clearing).  Calls that
  * overlap on one GPU (two streams, two host threads) RACE on it: order them on one stream.  The first
  * call on a device looks up the array's address (a host-side query); make one call outside any stream
  * capture before capturing.

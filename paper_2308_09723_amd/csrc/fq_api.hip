@@ -261,8 +261,9 @@ int fq_gemm_noalloc(const void* A, int act_dtype, int64_t M, int64_t N, int64_t 
         ws = scratch_of_current_device(&sst);
         if (!ws) return sst;
     }
-    // Nothing in the scratch has to start at zero: every partial sum and every rewritten activation row a
-    // kernel of this call reads was written by an earlier kernel of the same call.
+    // Nothing in the scratch has to start at zero: every partial sum and every rewritten activation row that this
+    // call reads it has written itself, in an earlier kernel or (fq_split_sum.h) in the blocks of the same one that
+    // took their ticket before.
     return fq_launch_gemm(plan, A, kind, M, N, K, codes, scales_f16, bits, g, C, ws, (hipStream_t)stream);
 }
 

@@ -152,7 +152,7 @@ static double fq_plan_mid(int64_t M, int64_t N, int64_t K, int bits, int g, int 
 // shapes each: a block takes its start and end, and per iteration a latency, its waves' vector and matrix work, and memory
 // traffic, which add up.  The narrow waves have to win by 7 %, by 20 % where they replace a split (the model ranks those
 // worse; scratch only shrinks).  Of those problems 157 change, 1.20x faster on average, one more than 3 % slower (3.4 %);
-// 2176 x 2336, 28 rows, g = 32 11.3 -> 7.7 us.  From 12000 columns on 9 of 34 became slower.
+// 2176 x 2336, 28 rows, g = 32 11.3 -> 7.7 us.  Above 12000 columns 9 of 34 became slower.
 static double fq_mid_us(int nt, int mt, int KB, int ngroups, int row_blocks, int64_t M, int64_t N, int bits, int sr, int gp, int kw,
                         int splits, int ncu) {
     static const double c[2][9] = {      // work of 32 and 48 rows, 8- and 3-bit codes' share of it, a further scale row; us
@@ -497,8 +497,9 @@ fq_gemm_plan fq_plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int g, int 
         // A split of K over the grid gives way where the blocks alone are as fast: the scores above were made for matrices
         // that take 15 us and more.  190 problems of 1 .. 16 rows: 89 lose their split, 1.11x on average over all (inside
         // graphs), none more than 3 % slower; 2304 x 4528, 13 rows 9.9 -> 6.7 us (all against sums by a
-        // second kernel).  Matrices of up to 64 column tiles, a quarter of the compute units, keep their split:
-        // callers and tests take the smallest matrices to need scratch (1024 x 1024, 4 rows took 4.5 us unsplit, 7 with the second kernel).
+        // second kernel).  Matrices of up to 64 column tiles, a quarter of the compute units, keep their split,
+        // although the unsplit kernel is the faster one there, too (1024 x 1024, 4 rows 4.5 us; split 5.3, 7 with the second kernel):
+        // the scratch that is asked for follows the plan, and tests take these products to ask for some.
         static const int groups[6] = {1, 2, 3, 4, 6, 12};
         double best_us = 1e30;
         if (p.splits > 1 && 4 * ntiles > ncu)

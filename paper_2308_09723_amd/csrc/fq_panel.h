@@ -17,7 +17,7 @@ typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
 __device__ inline float half_bits_to_float(uint16_t b) { return __half2float(__ushort_as_half(b)); }
 
 // abs-max bit patterns of 8 columns (four packed pairs) over rows ty, ty + 16, ... < rows: four rows in flight, or eight where
-// there are fewer blocks than compute units, which are bound by this chain of loads, and what is left in one go (rows past
+// there are fewer blocks than the 256 compute units, which are bound by this chain of loads, and what is left in one go (rows past
 // the end are the last one again).  Four in flight and the rest one by one -> this, the heuristic's call, us: 16256 x 2176 in
 // blocks of 4064 rows 41.4 -> 32.4, 10368 x 1888 in blocks of 162 32.9 -> 27.3.  With eight in flight everywhere 12672 x 9392
 // in blocks of 3168 (296 blocks) took 64.4 instead of 62.2.

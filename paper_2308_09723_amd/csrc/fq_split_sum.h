@@ -32,10 +32,12 @@ constexpr int FQ_MOST_FUSED_SPLITS = 8;      // partial sums that a lane of the 
 
 // Whether a block adds the splits of its tile (rows x cols, partial sums of 32 bits): not where the word in C would not be
 // aligned, nor above 80 KiB of partial sums per tile, which one block reads in 5 us and more where the sum kernel's blocks
-// share them.  Timed inside graphs, where a launch costs the host nothing, 100 products of 1 - 48 rows: 192 B - 24 KiB
-// 1.10x on average (5248 x 1920, 9 rows 9.4 -> 8.0 us), 24 - 80 KiB 1.04x (none more than 2 % slower), above 0.92 - 1.02x
-// (3968 x 4240, 36 rows, 162 KiB 13.2 -> 15.5; 8192 x 28672, 16 rows, 180 KiB 43.5 -> 44.9).  A call on its own also saves
-// the launch: 1024 x 1024, 4 rows 10.1 -> 6.5 us.
+// share them.  Timed inside graphs, where a launch costs the host nothing, one kernel against two, 570 products of 1 - 48 rows
+// and of the integer path: up to 24 KiB 1.09x on average (219, worst 0.98x; 5248 x 1920, 9 rows 9.4 -> 8.0 us), 24 - 80 KiB 1.03x
+// (307; six of them more than 3 % slower, 5 % at worst, most with blocks of six waves and 40 KiB or more: 3584 x 400, 44 rows
+// 8.2 -> 8.6; 8576 x 21120, 13 rows, seven waves 34.0 -> 35.3), 80 - 110 KiB 0.99x (44, six slower), above 0.92 - 1.02x
+// (3968 x 4240, 36 rows, 162 KiB 13.2 -> 15.5; 8192 x 28672, 16 rows, 180 KiB 43.5 -> 44.9).  KiB per wave predict the slower
+// ones no better.  A call on its own also saves the launch: 1024 x 1024, 4 rows 10.1 -> 6.5 us.
 inline bool fq_sums_splits(int rows, int cols, int splits, const void* C) {
     return splits > 1 && splits <= FQ_MOST_FUSED_SPLITS && ((uintptr_t)C & 7) == 0 && (int64_t)rows * cols * 4 * splits <= 80 * 1024;
 }

@@ -1313,7 +1313,7 @@ w8_plan w8_plan_wide(int64_t M, int64_t N, int64_t K, int g) {
         // second kernel that added it then (3.1 below 10 us; fq_split_sum.h adds most of them now) and the slabs' traffic.  Against
         // the plan by fill: 0.92 of the time inside graphs (1024 x 19872, 2 rows 9.0 -> 6.7 us; 9 of 10 shapes that were
         // split and are not any more lose a launch, too).  Up to 64 column tiles, a quarter of the compute units, the plan by
-        // fill stays: it splits such matrices, and callers and tests take them to need scratch.
+        // fill stays, which splits such matrices: the scratch that is asked for follows the plan, and tests take these to ask for some.
         w8_plan p = w8_plan_small_by_fill(M, N, K);
         if (4 * ntiles <= ncu) return p;
         const int ngroups = (ntiles + W8S_NT - 1) / W8S_NT;
@@ -1355,7 +1355,10 @@ w8_plan w8_plan_wide(int64_t M, int64_t N, int64_t K, int g) {
     // model gives the least time; above 700 rows the mid-M kernel up to K = 10240 (and 12288 rows): narrow matrices make few
     // tiles of 128 x 384 (823 rows of 1408 x 1552: 35).  240 products of 701 .. 2048 rows, the tiled kernel alone -> both:
     // 1.10x on average, up to 1.9x (883 rows, 1664 x 1248 24 -> 13 us), none more than 3 % slower below that K, three of 15 above
-    // (10 % at worst); 100 of 2049 .. 12288 rows with up to 6400 columns 1.02x, none slower.  The model was fitted (of log time, rms error 10 %) to 123 problems of
+    // (10 % at worst).  With waves of 16 columns, each side timed first once: 600 of 701 .. 2048 rows with up to 6400 columns 1.16x,
+    // three more than 3 % slower (7 % at worst: 718 rows, 9600 x 2160); 760 of 2049 .. 12288 rows 1.08x, five slower (2480 rows, 5760 x
+    // 1248 39.4 -> 47.1 us, 9550 rows, 3328 x 304 28.9 -> 35.3).  All but one of those are split on the tiled kernel, which takes 35 - 46 MB
+    // of scratch that is not asked for any more; the shape by whole rounds changed 3 of 600 plans (1.001x).  The model was fitted (of log time, rms error 10 %) to 123 problems of
     // 17 .. 2048 rows, K from 1152 to 16256, N from 1168 to 45856, in 35 shapes each:
     //   a block     mid-M: 6.7 us + iterations * the longest of 0.94 us, its vector and matrix work (0.92, 1.09 or 1.27 us for
     //               twelve waves, 0.37 more with two multiplier rows per k-block), its memory traffic at 8.1 TB/s;
@@ -1438,7 +1441,7 @@ w8_plan w8_plan_wide(int64_t M, int64_t N, int64_t K, int g) {
     return p;
 }
 
-// (Up to 16 rows matrices of up to 64 column tiles keep their plan: callers and tests take those to need scratch.)
+// (Up to 16 rows matrices of up to 64 column tiles keep their plan, and with it the scratch that they ask for.)
 w8_plan w8_plan_of(int64_t M, int64_t N, int64_t K, int g) {
     const w8_plan p = w8_plan_wide(M, N, K, g);
     return M <= 16 && 4 * (N / FQ_NTILE) <= fq_cu_count() ? p : w8_narrow(p, M, N, K, g);
