@@ -55,16 +55,19 @@ uint64_t fq_next_tag() {
 }
 
 // Atomics of agent scope count among the compute units of one device, in that device's own memory.  C in pinned host memory, in
-// managed memory or on another GPU is only ever stored to, as is memory that the runtime cannot place (asked in 60 ns each).
-bool fq_counts_tickets(const void* C, hipStream_t stream) {
+// managed memory or on another GPU is only ever stored to, as is memory that the runtime cannot place (asked in 60 ns each), and
+// partial sums there are read by a later kernel only.
+bool fq_counts_tickets(const void* C, const void* partial, hipStream_t stream) {
     if (hipPeekAtLastError() != hipSuccess) return false;      // (an earlier error is not this call's to clear)
-    hipPointerAttribute_t at = {};
     hipDevice_t dev = -1;
-    if (hipPointerGetAttributes(&at, C) != hipSuccess || hipStreamGetDevice(stream, &dev) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
+    bool plain = hipStreamGetDevice(stream, &dev) == hipSuccess;
+    for (const void* p : {C, partial}) {
+        hipPointerAttribute_t at = {};
+        plain = plain && hipPointerGetAttributes(&at, p) == hipSuccess && at.type == hipMemoryTypeDevice && at.device == (int)dev &&
+                !at.isManaged && at.allocationFlags == 0;
     }
-    return at.type == hipMemoryTypeDevice && at.device == (int)dev && !at.isManaged && at.allocationFlags == 0;
+    if (!plain) (void)hipGetLastError();
+    return plain;
 }
 
 // scale rows a layout k-block spans: 1, kblk / g, or one per 32-row step

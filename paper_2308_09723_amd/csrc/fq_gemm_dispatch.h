@@ -134,12 +134,13 @@ int launch_typed(const void* A, int64_t M, int64_t N, int64_t K, const void* cod
     float* partial = (float*)workspace;
     // The streaming kernels add a split of K themselves where a tile's partial sums are few enough for one block; not where
     // the ticket in C would be misaligned, nor where C lies on what other blocks still read (a product written over its own
-    // activations: the separate sum writes once everything is read), nor where C is not the device's own memory.
+    // activations: the separate sum writes once everything is read), nor where C or the scratch is not the
+    // device's own memory.
     const int tile_cols = plan.gp * FQ_NTILE * (plan.kind == 0 ? SKINNY_VARIANTS[plan.variant].nt : plan.nt);
     const bool sums = plan.kind != 1 && fq_sums_splits((int)M, tile_cols, plan.splits, C) &&
                       !fq_overlaps(C, (size_t)(M * N * 2), {{A, (size_t)(M * K * 2)}, {codes, (size_t)(K * N * BITS / 8)},
                                    {scales, (size_t)(K / g * N * 2)}, {partial, fq_partial_bytes(plan, M, N)}}) &&
-                      fq_counts_tickets(C, stream);
+                      fq_counts_tickets(C, partial, stream);
     const uint64_t tag = sums ? fq_next_tag() : 0;
     if (plan.kind == 0) {
         int st;

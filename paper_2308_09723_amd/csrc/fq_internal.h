@@ -29,8 +29,9 @@ int fq_launch_mfma_rate_probe(const void* operands, void* sink, int iterations, 
 
 // A tag for the tickets of one call (fq_split_sum.h); never 0.
 uint64_t fq_next_tag();
-// Whether C is memory that tickets can be counted in: allocated on the stream's device, in no special way.
-bool fq_counts_tickets(const void* C, hipStream_t stream);
+// Whether C is memory that tickets can be counted in and the blocks of one kernel can hand each other partial sums through
+// `partial`: both allocated on the stream's device, in no special way.
+bool fq_counts_tickets(const void* C, const void* partial, hipStream_t stream);
 // Whether `bytes` bytes from C on share memory with one of the buffers that a call reads.
 struct fq_span {
     const void* p;

@@ -15,7 +15,7 @@
 //
 // So C must be the call's own while it runs: a second call that counted in the same words at the same time would replace the
 // tag, and neither would find its last block.  (A word elsewhere would have to be the library's: the scratch that callers hand
-// over holds the partial sums and nothing else.)  Where C lies on an input, or is not the device's own memory, the separate sum
+// over holds the partial sums and nothing else.)  Where C lies on an input, or C or the scratch is not the device's own memory, the separate sum
 // kernel adds, as it does for outputs that are not aligned.
 //
 // Memory: partial sums and tickets are read and written with accesses of agent scope, which pass by the L2 caches (one

@@ -1513,12 +1513,12 @@ template <int OUT>
 int w8_gemm(const w8_plan& p, const int8_t* Aq, const float* alpha, int64_t M, int64_t N, int64_t K, const void* codes,
             const uint8_t* z, const void* tstep, int g, void* C, void* workspace, hipStream_t stream) {
     int32_t* partial = (int32_t*)workspace;
-    // the small-M and mid-M kernels add a split of K themselves where a tile's sums are few and C is the device's own
-    // memory and lies on nothing that is read
+    // the small-M and mid-M kernels add a split of K themselves where a tile's sums are few, C and the scratch are
+    // the device's own memory and C lies on nothing that is read
     const bool sums = (p.mid || p.small) && fq_sums_splits(M < p.mt * 16 ? (int)M : p.mt * 16, p.gp * p.nt * FQ_NTILE, p.splits, C) &&
                       !fq_overlaps(C, (size_t)(M * N * 2), {{Aq, (size_t)(M * K)}, {alpha, (size_t)M * 4}, {codes, (size_t)(K * N / 2)},
                                    {z, (size_t)(K / g * N)}, {tstep, (size_t)N * 2}, {partial, w8_partial_bytes(p, M, N)}}) &&
-                      fq_counts_tickets(C, stream);
+                      fq_counts_tickets(C, partial, stream);
     const uint64_t tag = sums ? fq_next_tag() : 0;
     if (p.mid) {
         const bool zr1 = g % 128 == 0;

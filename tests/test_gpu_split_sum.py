@@ -190,21 +190,24 @@ def test_integer_path_over_its_own_activations_sums_in_a_second_kernel():
     assert torch.equal(product(over), want)
 
 
-def test_outputs_in_host_memory_are_summed_by_a_second_kernel():
-    """Tickets are counted with atomics of the device: C in pinned host memory is only stored to."""
+def test_outputs_and_scratch_in_host_memory_are_summed_by_a_second_kernel():
+    """Tickets are counted with atomics of the device: C in pinned host memory is only stored to, and partial sums there are read
+    by a later kernel."""
     from paper_2308_09723_amd import fq
     torch = torch_mod()
     A, codes, scales, ws = _case(4, 1024, 1024, 4, 128, "f16")
     C, host = torch.empty_like(A), torch.zeros((4, 1024), dtype=torch.float16, pin_memory=True)
 
-    def product(c):
-        return fq.gemm(A, codes, scales, 4, 128, out=c, workspace=ws)
+    def product(c, scratch=ws):
+        return fq.gemm(A, codes, scales, 4, 128, out=c, workspace=scratch)
 
-    want = product(C)
-    assert kernels_of(lambda: product(C)) == 1 and kernels_of(lambda: product(host)) == 2
+    want = product(C).clone()
+    host_ws = torch.zeros(ws.numel(), dtype=torch.uint8, pin_memory=True)
+    assert kernels_of(lambda: product(C)) == 1 and kernels_of(lambda: product(host)) == kernels_of(lambda: product(C, host_ws)) == 2
     product(host)
+    product(C.zero_(), host_ws)
     torch.cuda.synchronize()
-    assert torch.equal(host, want.cpu())
+    assert torch.equal(host, want.cpu()) and torch.equal(C, want)
     codes, z, t = fq.quantize_w4a8((torch.randn((4096, 1024), device="cuda") * 0.02).to(torch.float16), 128)
     Aq, alpha = fq.quantize_act_i8(torch.randn((4, 4096), device="cuda").to(torch.float16))
     ws = torch.empty(fq.gemm_w4a8_workspace_bytes(4, 1024, 4096, 128), dtype=torch.uint8, device="cuda")
@@ -212,8 +215,23 @@ def test_outputs_in_host_memory_are_summed_by_a_second_kernel():
     def integer(c):
         return fq.gemm_w4a8(Aq, alpha, codes, z, t, 128, torch.float16, out=c, workspace=ws)
 
-    want = integer(C)
+    want = integer(C).clone()
     assert kernels_of(lambda: integer(C)) == 1 and kernels_of(lambda: integer(host)) == 2
     integer(host)
     torch.cuda.synchronize()
     assert torch.equal(host, want.cpu())
+
+
+def test_the_librarys_own_scratch_is_plain_memory():
+    """fq_gemm_noalloc adds its splits in one kernel, too."""
+    from paper_2308_09723_amd import fq
+    torch = torch_mod()
+    A, codes, scales, ws = _case(4, 1024, 1024, 4, 128, "f16")
+    C = torch.empty_like(A)
+
+    def noalloc():
+        assert fq.gemm_noalloc_raw(A.data_ptr(), fq.FQ_F16, 4, 1024, 1024, codes.data_ptr(), scales.data_ptr(), 4, 128, C.data_ptr(),
+                                   torch.cuda.current_stream().cuda_stream) == fq.FQ_OK
+
+    noalloc()
+    assert torch.equal(C, fq.gemm(A, codes, scales, 4, 128, workspace=ws)) and kernels_of(noalloc) == 1
